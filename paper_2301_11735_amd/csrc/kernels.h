@@ -208,7 +208,7 @@ hipError_t launch_observables(uint8_t *scratch, const void *state, int L, int en
 // per lattice holding the codes (one byte per site), the map's mark bitmap,
 // its pair list and the full threshold table in LDS.
 constexpr int kMapMaxL = 256;
-constexpr int kMapThreads = 512;
+constexpr int kMapThreads = 1024;  // 16 waves: up to 16 maps are built side by side, as LDS allows (14 at L = 128)
 struct MapArgs {
     int count;
     uint8_t *scratch[kMaxBatch];

@@ -3,11 +3,11 @@
 //
 // One block per lattice (up to 256 lattices per launch, L <= 256).  Per map:
 //   1. the block clears a bitmap of marked sites;
-//   2. wave 0 builds the map with the paper's sequential algorithm -- draw a
-//      site until an unmarked one comes up, mark it; the same for the
-//      partner; record the pair; mark the neighbours of both -- its 64 lanes
-//      computing the next 256 site draws at once and the wave taking them in
-//      draw order;
+//   2. one wave a map builds it with the paper's sequential algorithm -- draw
+//      a site until an unmarked one comes up, mark it; the same for the
+//      partner; record the pair; mark the neighbours of both -- taking 64
+//      draws at a time (build_map); the block's waves build the next maps of
+//      the launch side by side;
 //   3. all threads apply one coupled-pair Metropolis step (section 3.1) to the
 //      map's pairs in parallel.  No two pairs of a map interact, so this equals
 //      applying them one after another; a pair's own sites may be neighbours,
@@ -33,114 +33,224 @@ constexpr uint32_t kSetQm1 = 0xDC73u;    // (3,0) (3,1) (0,3) (1,3)
 
 __device__ __forceinline__ int sigma_of(uint32_t c) { return (c & 2u) ? 0 : 1 - 2 * (int)(c & 1u); }
 
-__device__ __forceinline__ void site_neighbours(int L, uint32_t s, uint32_t (&nb)[4])
+// Sites s < 2^16 and sides L <= 256: y = s / L from magic = ceil(2^32 / L)
+// (the rounding error s (magic L - 2^32) stays below 2^24).
+__device__ __forceinline__ void site_neighbours(int L, uint32_t magic, uint32_t s, uint32_t (&nb)[4])
 {
-    const uint32_t y = s / (uint32_t)L, x = s - y * (uint32_t)L;
-    const uint32_t row = y * (uint32_t)L;
+    const uint32_t y = __umulhi(s, magic), row = y * (uint32_t)L, x = s - row;
     nb[0] = row + (x + 1 == (uint32_t)L ? 0 : x + 1);
     nb[1] = row + (x == 0 ? (uint32_t)L - 1 : x - 1);
     nb[2] = (y + 1 == (uint32_t)L ? 0 : row + (uint32_t)L) + x;
     nb[3] = (y == 0 ? (uint32_t)L * ((uint32_t)L - 1) : row - (uint32_t)L) + x;
 }
 
-// Map m into pairs[] (a | b << 16), by the calling wave (several waves of a
-// block build different maps at once, each in its own bitmap).  Per round the
-// 64 lanes compute the next 256 site draws, their neighbours and whether each
-// was already marked when the round began (one ballot per draw slot); then the
-// wave walks the draws in draw order with uniform control flow: a draw marked
-// at the start of the round is rejected without touching LDS, any other is
-// checked against the live bitmap (a broadcast LDS read, which the in-order LDS
-// queue orders after the marks already issued).  Marks are LDS atomic ors.
+__device__ __forceinline__ uint32_t marked(const uint32_t *bitmap, uint32_t s)
+{
+    return (((const volatile uint32_t *)bitmap)[s >> 5] >> (s & 31u)) & 1u;
+}
+__device__ __forceinline__ uint32_t mark(uint32_t *bitmap, uint32_t s)
+{
+    return (atomicOr(&bitmap[s >> 5], 1u << (s & 31u)) >> (s & 31u)) & 1u;  // was it marked?
+}
+__device__ __forceinline__ void unmark(uint32_t *bitmap, uint32_t s) { atomicAnd(&bitmap[s >> 5], ~(1u << (s & 31u))); }
+
+__device__ __forceinline__ uint32_t rank_in(uint64_t mask)  // set bits of the mask below this lane
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+// Map m into pairs[] (a in the low half, b in the high half), by the calling
+// wave (several waves of a block build different maps at once, each in its
+// own bitmap).  The paper's walk over the draws is sequential, but its
+// outcome only depends on the order where two draws interact: a draw is
+// taken unless its site is marked, and taking it marks it and (once its pair
+// is whole) its neighbours.  So the wave takes the next 64 draws at once:
+//   1. lanes whose site is unmarked are candidates; each marks its site
+//      tentatively and then looks whether a neighbour's mark is new, or its
+//      own was set by another lane (one of two equal sites sees that);
+//   2. with f the first lane that saw one, no two candidates before f
+//      interact, and every one of them is what the walk takes; f itself too
+//      unless its site was double (its neighbours then are all later lanes),
+//      and always if it is the first candidate;
+//   3. tentative marks past that prefix are withdrawn, the accepted sites
+//      get their place in the pair list by their rank, the neighbours of
+//      whole pairs are marked, and the next window starts after the prefix.
+// A site carried over from the window before counts as one before f for every
+// candidate but the first, which is its partner.  A mark never goes away once its draw is accepted, so a draw rejected
+// against the marks before the window is rejected in the walk as well.  A
+// pair without its second site at the end of a prefix carries over (its
+// neighbours are still unmarked, as in the walk).
+//
+// The build is bound by the chain of dependent LDS operations of a window
+// (about five) and by the windows cut short by interacting draws, not by
+// bandwidth; a walk one draw at a time took a chain of LDS round trips per
+// candidate.  A call on 256 lattices of L = 128, 10 maps each: 2098 -> 254 us.
+//
+// NN (nearest-neighbour partners): a draw on an unmarked site takes the
+// next draw as its direction.  Runs of unmarked draws are independent (the
+// draw before a run is marked: rejected, or the direction of the run before),
+// so the first sites are the draws of each run at even distance from its
+// start: runs that start on an even lane are the bits of U that the carry of
+// U + (their starts) clears.  A dropped pair (marked partner) still marks its
+// first site tentatively, since whether that draw is a first site at all
+// depends on the pairs before it.
 template <bool NN>
-__device__ void build_map(uint32_t *bitmap, uint32_t *pairs, int L, uint32_t N, uint32_t n_pairs, uint32_t m_lo,
-                          uint32_t m_hi, uint32_t key0, uint32_t key1)
+__device__ void build_map(uint32_t *bitmap, uint32_t *pairs, int L, uint32_t magic, uint32_t N, uint32_t n_pairs,
+                          uint32_t m_lo, uint32_t m_hi, uint32_t key0, uint32_t key1)
 {
     const uint32_t lane = threadIdx.x & 63u;
-    uint32_t k = 0, count = 0, need_b = 0, a_site = 0;
-    uint32_t an[4] = {0u, 0u, 0u, 0u};  // neighbours of the pending first site
+    const uint64_t self = 1ull << lane;
+    uint16_t *half = (uint16_t *)pairs;  // half[2 i] = a, half[2 i + 1] = b of pair i
+    uint32_t k = 0, count = 0, pend = 0, pend_site = 0;
+    uint32_t base = 0;  // lane l holds draws base + 4 l .. + 3
+    u32x4 w = philox4x32_10(m_lo, kDomMap, lane, m_hi, key0, key1);
     while (count < n_pairs) {
-        // draws k .. k+255: draw d is word d mod 4 of Philox call d / 4, held by lane d / 4
-        const u32x4 w = philox4x32_10(m_lo, kDomMap, (k >> 2) + lane, m_hi, key0, key1);
-        const uint32_t raw[4] = {w.x, w.y, w.z, w.w};
-        const uint32_t c[4] = {mulhi_u32(w.x, N), mulhi_u32(w.y, N), mulhi_u32(w.z, N), mulhi_u32(w.w, N)};
-        uint32_t nbv[4][4];
-        uint64_t pre[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            site_neighbours(L, c[q], nbv[q]);
-            pre[q] = __ballot((bitmap[c[q] >> 5] >> (c[q] & 31u)) & 1u);
+        if (k - base > 192u) {  // the window's 64 draws are not all held
+            base = k & ~3u;
+            w = philox4x32_10(m_lo, kDomMap, (base >> 2) + lane, m_hi, key0, key1);
         }
-        for (int l = 0; l < 64 && count < n_pairs; ++l) {
+        const uint32_t d = k - base + lane;  // < 256
+        const int from = (int)(d >> 2);
+        const uint32_t r0 = __shfl(w.x, from, 64), r1 = __shfl(w.y, from, 64), r2 = __shfl(w.z, from, 64),
+                       r3 = __shfl(w.w, from, 64);
+        const uint32_t raw = d & 2u ? (d & 1u ? r3 : r2) : (d & 1u ? r1 : r0);
+        const uint32_t a = mulhi_u32(raw, N);
+        uint32_t an[4], was[4];
+        site_neighbours(L, magic, a, an);
+        const uint32_t was_a = marked(bitmap, a);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if (count >= n_pairs) continue;
-                if (NN && need_b) {
-                    // nearest-neighbour partner: this draw picks neighbour raw >> 30 of a
-                    need_b = 0;
-                    const uint32_t d = (uint32_t)__builtin_amdgcn_readlane((int)raw[q], l) >> 30;
-                    const uint32_t b = d == 0 ? an[0] : d == 1 ? an[1] : d == 2 ? an[2] : an[3];
-                    const uint32_t bw = (uint32_t)__builtin_amdgcn_readfirstlane((int)bitmap[b >> 5]);
-                    if (bw & (1u << (b & 31u))) continue;  // drop the pair, start over
-                    uint32_t bn[4];
-                    site_neighbours(L, b, bn);
-                    if (lane == 0) {
-                        pairs[count] = a_site | (b << 16);
-                        atomicOr(&bitmap[a_site >> 5], 1u << (a_site & 31u));
-                        atomicOr(&bitmap[b >> 5], 1u << (b & 31u));
+        for (int e = 0; e < 4; ++e) was[e] = marked(bitmap, an[e]);
+        if constexpr (!NN) {
+            const bool cand = !was_a;
+            const uint64_t C = __ballot(cand);
+            if (C == 0) {
+                k += 64u;
+                continue;
+            }
+            uint32_t dup = 0, hit = 0;
+            if (cand) dup = mark(bitmap, a);
+            __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            atomicOr(&bitmap[an[e] >> 5], 1u << (an[e] & 31u));
-                            atomicOr(&bitmap[bn[e] >> 5], 1u << (bn[e] & 31u));
-                        }
-                    }
-                    ++count;
-                    continue;
-                }
-                if ((pre[q] >> l) & 1u) continue;
-                const uint32_t site = (uint32_t)__builtin_amdgcn_readlane((int)c[q], l);
-                const uint32_t word = (uint32_t)__builtin_amdgcn_readfirstlane((int)bitmap[site >> 5]);
-                if (word & (1u << (site & 31u))) continue;
-                if (NN) {
-                    // first site of a nearest-neighbour pair: marked only once the pair is kept
-                    a_site = site;
+            for (int e = 0; e < 4; ++e) {
+                hit |= marked(bitmap, an[e]) & ~was[e];
+                // the first candidate makes the carried pair whole
+                if (pend && an[e] == pend_site && (C & (self - 1ull))) dup = 1u;
+            }
+            const uint64_t F = __ballot(cand && (dup | hit));
+            uint64_t acc = C;
+            uint32_t taken = 64u;
+            if (F) {
+                const uint32_t f = (uint32_t)__builtin_ctzll(F);
+                const uint64_t D = __ballot(cand && dup);  // f interacts with a site before it
+                const bool with_f = f == (uint32_t)__builtin_ctzll(C) || !((D >> f) & 1u);
+                acc = C & ((1ull << f) - 1ull);
+                if (with_f) acc |= 1ull << f;
+                taken = with_f ? f + 1u : f;
+            }
+            const uint32_t left = 2u * (n_pairs - count) - pend;  // sites the map still takes
+            const uint32_t rank = rank_in(acc);
+            acc = __ballot((acc & self) && rank < left);
+            const bool mine = acc & self;
+            if (F || acc != C) {
+                __builtin_amdgcn_wave_barrier();
+                if (cand && !mine) unmark(bitmap, a);
+                __builtin_amdgcn_wave_barrier();
+                if (mine) mark(bitmap, a);  // a withdrawn double shared its bit
+            }
+            const uint32_t sites = (uint32_t)__popcll(acc) + pend, whole = sites >> 1;
+            const uint32_t r = rank + pend;
+            if (mine) {
+                half[2u * count + r] = (uint16_t)a;
+                if ((r >> 1) < whole) {
 #pragma unroll
-                    for (int d = 0; d < 4; ++d) an[d] = (uint32_t)__builtin_amdgcn_readlane((int)nbv[q][d], l);
-                    need_b = 1;
-                    continue;
-                }
-                if (lane == 0) atomicOr(&bitmap[site >> 5], 1u << (site & 31u));
-                if (!need_b) {
-                    a_site = site;
-#pragma unroll
-                    for (int d = 0; d < 4; ++d) an[d] = (uint32_t)__builtin_amdgcn_readlane((int)nbv[q][d], l);
-                    need_b = 1;
-                } else {
-                    if (lane == 0) {
-                        pairs[count] = a_site | (site << 16);
-#pragma unroll
-                        for (int d = 0; d < 4; ++d) atomicOr(&bitmap[an[d] >> 5], 1u << (an[d] & 31u));
-                    }
-#pragma unroll
-                    for (int d = 0; d < 4; ++d) {
-                        const uint32_t t = (uint32_t)__builtin_amdgcn_readlane((int)nbv[q][d], l);
-                        if (lane == 0) atomicOr(&bitmap[t >> 5], 1u << (t & 31u));
-                    }
-                    ++count;
-                    need_b = 0;
+                    for (int e = 0; e < 4; ++e) mark(bitmap, an[e]);
                 }
             }
+            if (pend && whole > 0 && lane < 4u) {  // the carried first site's neighbours
+                uint32_t pn[4];
+                site_neighbours(L, magic, pend_site, pn);
+                mark(bitmap, lane == 0 ? pn[0] : lane == 1 ? pn[1] : lane == 2 ? pn[2] : pn[3]);
+            }
+            if (sites & 1u) {
+                // the last accepted site waits for its partner (none accepted: the carried one still does)
+                if (acc) pend_site = (uint32_t)__builtin_amdgcn_readlane((int)a, 63 - (int)__builtin_clzll(acc));
+                pend = 1u;
+            } else {
+                pend = 0u;
+            }
+            count += whole;
+            k += taken;
+        } else {
+            const uint64_t kEven = 0x5555555555555555ull;
+            const uint64_t U = __ballot(!was_a);
+            const uint64_t even_starts = U & ~(U << 1) & kEven;
+            const uint64_t even_runs = U & ~(U + even_starts);
+            uint64_t C = (even_runs & kEven) | (U & ~even_runs & ~kEven);
+            uint32_t taken = (C >> 63) ? 63u : 64u;  // a first site on the last lane waits for the next window
+            C &= ~(1ull << 63);
+            if (C == 0) {
+                k += taken;
+                continue;
+            }
+            const uint32_t dir = __shfl_down(raw, 1, 64) >> 30;
+            const uint32_t b = dir == 0 ? an[0] : dir == 1 ? an[1] : dir == 2 ? an[2] : an[3];
+            const uint32_t was_b = dir == 0 ? was[0] : dir == 1 ? was[1] : dir == 2 ? was[2] : was[3];
+            uint32_t bn[4], wasb[4];
+            site_neighbours(L, magic, b, bn);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) wasb[e] = marked(bitmap, bn[e]);
+            const bool cand = C & self, keep = cand && !was_b;
+            uint32_t dup = 0, hit = 0;
+            if (cand) dup = mark(bitmap, a);
+            if (keep) dup |= mark(bitmap, b);
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (!(keep && an[e] == b)) hit |= marked(bitmap, an[e]) & ~was[e];
+                if (keep && bn[e] != a) hit |= marked(bitmap, bn[e]) & ~wasb[e];
+            }
+            const uint64_t F = __ballot(cand && (dup | hit));
+            uint64_t acc = C;
+            if (F) {
+                const uint32_t f = (uint32_t)__builtin_ctzll(F);
+                const uint64_t D = __ballot(cand && dup);
+                const bool with_f = f == (uint32_t)__builtin_ctzll(C) || !((D >> f) & 1u);
+                acc = C & ((1ull << f) - 1ull);
+                if (with_f) acc |= 1ull << f;
+                taken = with_f ? f + 2u : f;
+            }
+            acc = __ballot((acc & self) && keep);
+            const uint32_t rank = rank_in(acc);
+            acc = __ballot((acc & self) && rank < n_pairs - count);
+            const bool mine = acc & self;
+            __builtin_amdgcn_wave_barrier();
+            if (cand && !mine) {
+                unmark(bitmap, a);
+                if (keep) unmark(bitmap, b);
+            }
+            __builtin_amdgcn_wave_barrier();
+            if (mine) {
+                pairs[count + rank] = a | (b << 16);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {  // a and b are among each other's neighbours
+                    mark(bitmap, an[e]);
+                    mark(bitmap, bn[e]);
+                }
+            }
+            count += (uint32_t)__popcll(acc);
+            k += taken;
         }
-        k += 256u;
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
 // Sums of S and sigma over the neighbours of s other than `other`; adj = 1 if
 // `other` is one of them.
-__device__ __forceinline__ void side_sum(const uint8_t *codes, int L, uint32_t s, uint32_t other, int &sS, int &sG,
-                                         int &adj)
+__device__ __forceinline__ void side_sum(const uint8_t *codes, int L, uint32_t magic, uint32_t s, uint32_t other,
+                                         int &sS, int &sG, int &adj)
 {
     uint32_t nb[4];
-    site_neighbours(L, s, nb);
+    site_neighbours(L, magic, s, nb);
     sS = 0;
     sG = 0;
 #pragma unroll
@@ -156,8 +266,8 @@ __device__ __forceinline__ void side_sum(const uint8_t *codes, int L, uint32_t s
 }
 
 // One coupled-pair Metropolis step on sites (a, b), a and b possibly adjacent.
-__device__ __forceinline__ void map_pair_step(uint8_t *codes, const uint32_t *thr, int L, uint32_t a, uint32_t b,
-                                              uint32_t uc, uint32_t ua, int (&tr)[3])
+__device__ __forceinline__ void map_pair_step(uint8_t *codes, const uint32_t *thr, int L, uint32_t magic,
+                                              uint32_t a, uint32_t b, uint32_t uc, uint32_t ua, int (&tr)[3])
 {
     const uint32_t ca = codes[a], cb = codes[b];
     const int Sa = charge_of(ca), Sb = charge_of(cb), q = Sa + Sb;
@@ -167,8 +277,8 @@ __device__ __forceinline__ void map_pair_step(uint8_t *codes, const uint32_t *th
     const uint32_t cfg = ((q == 1 ? kSetQp1 : q == 0 ? kSetQ0 : kSetQm1) >> (4u * j)) & 15u;
     const uint32_t na = cfg & 3u, nb = cfg >> 2;
     int sSa, sGa, sSb, sGb, adj = 0;
-    side_sum(codes, L, a, b, sSa, sGa, adj);
-    side_sum(codes, L, b, a, sSb, sGb, adj);
+    side_sum(codes, L, magic, a, b, sSa, sGa, adj);
+    side_sum(codes, L, magic, b, a, sSb, sGb, adj);
     const int Ga = sigma_of(ca), Gb = sigma_of(cb);
     const int Sna = charge_of(na), Snb = charge_of(nb), Gna = sigma_of(na), Gnb = sigma_of(nb);
     const int nD = Sna * Sna - Sa * Sa + Snb * Snb - Sb * Sb;
@@ -193,7 +303,8 @@ __global__ void __launch_bounds__(kMapThreads) k_map_steps(MapArgs args)
     const uint32_t N = (uint32_t)L * (uint32_t)L;
     const uint32_t per = args.nn ? 20u : 10u;
     const uint32_t n_pairs = N / per < 1u ? 1u : N / per;
-    const uint32_t G = (uint32_t)args.builders;            // maps built at once, one per wave
+    const uint32_t G = (uint32_t)args.builders;             // maps built at once, one per wave
+    const uint32_t magic = 0xFFFFFFFFu / (uint32_t)L + 1u;  // ceil(2^32 / L)
     const uint32_t bwords = (N + 31u) / 32u;
     uint32_t *thr = smem;                                   // kTabSize
     uint8_t *codes = (uint8_t *)(smem + kTabSize);          // N bytes
@@ -228,11 +339,11 @@ __global__ void __launch_bounds__(kMapThreads) k_map_steps(MapArgs args)
         if (wave < group) {
             const uint64_t m = first + m0 + wave;
             if (args.nn)
-                build_map<true>(bitmaps + wave * bwords, pairs + wave * n_pairs, L, N, n_pairs, (uint32_t)m,
-                                (uint32_t)(m >> 32), d.key0, d.key1);
+                build_map<true>(bitmaps + wave * bwords, pairs + wave * n_pairs, L, magic, N, n_pairs,
+                                (uint32_t)m, (uint32_t)(m >> 32), d.key0, d.key1);
             else
-                build_map<false>(bitmaps + wave * bwords, pairs + wave * n_pairs, L, N, n_pairs, (uint32_t)m,
-                                 (uint32_t)(m >> 32), d.key0, d.key1);
+                build_map<false>(bitmaps + wave * bwords, pairs + wave * n_pairs, L, magic, N, n_pairs,
+                                 (uint32_t)m, (uint32_t)(m >> 32), d.key0, d.key1);
         }
         __syncthreads();
         // ...then apply them in map order
@@ -244,10 +355,10 @@ __global__ void __launch_bounds__(kMapThreads) k_map_steps(MapArgs args)
             for (uint32_t c = threadIdx.x; 2u * c < n_pairs; c += blockDim.x) {
                 const u32x4 w = philox4x32_10(m_lo, kDomMapStep, c, m_hi, d.key0, d.key1);
                 const uint32_t p0 = mp[2u * c];
-                map_pair_step(codes, thr, L, p0 & 0xFFFFu, p0 >> 16, w.x, w.y, tr);
+                map_pair_step(codes, thr, L, magic, p0 & 0xFFFFu, p0 >> 16, w.x, w.y, tr);
                 if (2u * c + 1u < n_pairs) {
                     const uint32_t p1 = mp[2u * c + 1u];
-                    map_pair_step(codes, thr, L, p1 & 0xFFFFu, p1 >> 16, w.z, w.w, tr);
+                    map_pair_step(codes, thr, L, magic, p1 & 0xFFFFu, p1 >> 16, w.z, w.w, tr);
                 }
             }
             __syncthreads();
@@ -275,14 +386,14 @@ __global__ void __launch_bounds__(kMapThreads) k_map_steps(MapArgs args)
 
 hipError_t launch_map_steps(const MapArgs &a, int max_L, hipStream_t s)
 {
-    // as many concurrent builders (at most one per wave) as LDS allows
+    // as many concurrent builders (at most one per wave) as LDS allows, shared
+    // evenly over the rounds that the maps then take (10 maps with room for
+    // 14 builders are one round, 20 two rounds of 10)
     MapArgs b = a;
-    b.builders = 1;
-    for (int g = kMapThreads / 64; g > 1; g /= 2)
-        if (map_lds_bytes(max_L, g) <= kMapLdsMax) {
-            b.builders = g;
-            break;
-        }
+    int most = kMapThreads / 64;
+    while (most > 1 && map_lds_bytes(max_L, most) > kMapLdsMax) --most;
+    const uint32_t rounds = (a.n_maps + (uint32_t)most - 1u) / (uint32_t)most;
+    b.builders = (int32_t)((a.n_maps + rounds - 1u) / rounds);
     hipLaunchKernelGGL(k_map_steps, dim3((unsigned)b.count), dim3(kMapThreads), map_lds_bytes(max_L, b.builders), s,
                        b);
     return hipGetLastError();

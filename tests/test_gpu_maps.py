@@ -147,3 +147,18 @@ def test_neighbour_pairs_lose_the_low_temperature_fluctuations():
     assert abs(c - ex["C"]) < 4 * c_err + 0.05 * ex["C"], (c, c_err, ex["C"])
     c_nn = res[lat.MAP_NEIGHBOUR][2]
     assert c_nn < 0.25 * ex["C"], (c_nn, ex["C"])
+
+
+@pytest.mark.parametrize("partner", [lat.MAP_ANY, lat.MAP_NEIGHBOUR], ids=["any", "neighbour"])
+@pytest.mark.parametrize("L", [4, 12, 16, 20, 24, 48, 64, 256])
+def test_map_windows_match_the_sequential_walk(L, partner):
+    """Maps whose draws interact often (few sites for 64 draws at once), whose
+    last window ends inside a pair, and rounds of unequal numbers of builders."""
+    spec = SMALL.with_(L=L, n=0.0, seed=900 + L, T=1.1, encoding=0)
+    n = 33 if L < 256 else 7
+    _say(f"case map windows L={L} partner={partner} maps={n}")
+    g, o = _make(spec), _oracle(spec)
+    g.map_steps((1 << 32) - 5, n, partner)  # the map index crosses a 32-bit word
+    _oracle_maps(spec, o, (1 << 32) - 5, n, nn=partner == lat.MAP_NEIGHBOUR)
+    _assert_same(g, o, f"after {n} maps")
+    g.destroy()
