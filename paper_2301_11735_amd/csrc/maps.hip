@@ -67,24 +67,23 @@ __device__ __forceinline__ uint32_t rank_in(uint64_t mask)  // set bits of the m
 // is whole) its neighbours.  So the wave takes the next 64 draws at once:
 //   1. lanes whose site is unmarked are candidates; each marks its site
 //      tentatively and then looks whether a neighbour's mark is new, or its
-//      own was set by another lane (one of two equal sites sees that);
-//   2. with f the first lane that saw one, no two candidates before f
-//      interact, and every one of them is what the walk takes; f itself too
-//      unless its site was double (its neighbours then are all later lanes),
-//      and always if it is the first candidate;
-//   3. tentative marks past that prefix are withdrawn, the accepted sites
-//      get their place in the pair list by their rank, the neighbours of
-//      whole pairs are marked, and the next window starts after the prefix.
-// A site carried over from the window before counts as one before f for every
-// candidate but the first, which is its partner.  A mark never goes away once its draw is accepted, so a draw rejected
+//      own was set by another lane (one of two equal sites sees that, and
+//      the other is found by comparison);
+//   2. a candidate that saw nothing is what the walk takes, whatever the
+//      others do; those that did are decided in order, by comparing their
+//      site with all lanes: one is rejected if an accepted lane before it has
+//      the same site, or is next to it and belongs to a pair that is whole by
+//      then (a site carried over from the window before likewise);
+//   3. the marks of rejected candidates are withdrawn, the accepted sites get
+//      their place in the pair list by their rank, and the neighbours of
+//      whole pairs are marked.
+// A mark never goes away once its draw is accepted, so a draw rejected
 // against the marks before the window is rejected in the walk as well.  A
-// pair without its second site at the end of a prefix carries over (its
-// neighbours are still unmarked, as in the walk).
+// pair without its second site at the end of a window carries over.
 //
 // The build is bound by the chain of dependent LDS operations of a window
-// (about five) and by the windows cut short by interacting draws, not by
-// bandwidth; a walk one draw at a time took a chain of LDS round trips per
-// candidate.  A call on 256 lattices of L = 128, 10 maps each: 2098 -> 254 us.
+// (about five) and by the draws decided in order, not by bandwidth; a walk one draw at a time took a chain of LDS round trips per
+// candidate.  A call on 256 lattices of L = 128, 10 maps each: 2098 -> 231 us.
 //
 // NN (nearest-neighbour partners): a draw on an unmarked site takes the
 // next draw as its direction.  Runs of unmarked draws are independent (the
@@ -93,7 +92,10 @@ __device__ __forceinline__ uint32_t rank_in(uint64_t mask)  // set bits of the m
 // start: runs that start on an even lane are the bits of U that the carry of
 // U + (their starts) clears.  A dropped pair (marked partner) still marks its
 // first site tentatively, since whether that draw is a first site at all
-// depends on the pairs before it.
+// depends on the pairs before it.  An interaction moves the first sites after
+// it, so here a window ends before the first lane f that saw one (after f if
+// its own sites were not double: its neighbours then are all later lanes, and
+// always if it is the first), and the next one starts there.
 template <bool NN>
 __device__ void build_map(uint32_t *bitmap, uint32_t *pairs, int L, uint32_t magic, uint32_t N, uint32_t n_pairs,
                           uint32_t m_lo, uint32_t m_hi, uint32_t key0, uint32_t key1)
@@ -127,25 +129,31 @@ __device__ void build_map(uint32_t *bitmap, uint32_t *pairs, int L, uint32_t mag
                 k += 64u;
                 continue;
             }
-            uint32_t dup = 0, hit = 0;
+            uint32_t dup = 0, hit = 0, carried = 0;
             if (cand) dup = mark(bitmap, a);
             __builtin_amdgcn_wave_barrier();
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 hit |= marked(bitmap, an[e]) & ~was[e];
-                // the first candidate makes the carried pair whole
-                if (pend && an[e] == pend_site && (C & (self - 1ull))) dup = 1u;
+                carried |= pend && an[e] == pend_site;
             }
-            const uint64_t F = __ballot(cand && (dup | hit));
-            uint64_t acc = C;
-            uint32_t taken = 64u;
-            if (F) {
-                const uint32_t f = (uint32_t)__builtin_ctzll(F);
-                const uint64_t D = __ballot(cand && dup);  // f interacts with a site before it
-                const bool with_f = f == (uint32_t)__builtin_ctzll(C) || !((D >> f) & 1u);
-                acc = C & ((1ull << f) - 1ull);
-                if (with_f) acc |= 1ull << f;
-                taken = with_f ? f + 1u : f;
+            // candidates that interact with another one or with the carried site
+            uint64_t F = __ballot(cand && (dup | hit | carried));
+            for (uint64_t D = __ballot(cand && dup); D; D &= D - 1ull)
+                F |= __ballot(cand && a == (uint32_t)__builtin_amdgcn_readlane((int)a, (int)__builtin_ctzll(D)));
+            const uint64_t P = __ballot(carried);
+            uint64_t acc = C & ~F;
+            for (uint64_t rest = F; rest; rest &= rest - 1ull) {
+                const int j = (int)__builtin_ctzll(rest);
+                const uint32_t t = (uint32_t)__builtin_amdgcn_readlane((int)a, j);
+                const uint64_t before = acc & ((1ull << j) - 1ull);  // all decided
+                // a first site that waits for its partner has not marked its neighbours
+                const bool waiting = ((uint32_t)__popcll(before) + pend) & 1u;
+                const uint64_t last = waiting && before ? 1ull << (63 - (int)__builtin_clzll(before)) : 0ull;
+                const uint64_t same = __ballot(a == t);
+                const uint64_t next_to = __ballot(an[0] == t || an[1] == t || an[2] == t || an[3] == t);
+                const bool taken_before = (before & (same | (next_to & ~last))) != 0 || (before && ((P >> j) & 1u));
+                if (!taken_before) acc |= 1ull << j;
             }
             const uint32_t left = 2u * (n_pairs - count) - pend;  // sites the map still takes
             const uint32_t rank = rank_in(acc);
@@ -179,7 +187,7 @@ __device__ void build_map(uint32_t *bitmap, uint32_t *pairs, int L, uint32_t mag
                 pend = 0u;
             }
             count += whole;
-            k += taken;
+            k += 64u;
         } else {
             const uint64_t kEven = 0x5555555555555555ull;
             const uint64_t U = __ballot(!was_a);
@@ -394,7 +402,9 @@ hipError_t launch_map_steps(const MapArgs &a, int max_L, hipStream_t s)
     while (most > 1 && map_lds_bytes(max_L, most) > kMapLdsMax) --most;
     const uint32_t rounds = (a.n_maps + (uint32_t)most - 1u) / (uint32_t)most;
     b.builders = (int32_t)((a.n_maps + rounds - 1u) / rounds);
-    hipLaunchKernelGGL(k_map_steps, dim3((unsigned)b.count), dim3(kMapThreads), map_lds_bytes(max_L, b.builders), s,
+    // half the waves where neither the builders nor the pairs of a map need more
+    const uint32_t threads = b.builders <= 8 && max_L <= 100 ? kMapThreads / 2 : kMapThreads;
+    hipLaunchKernelGGL(k_map_steps, dim3((unsigned)b.count), dim3(threads), map_lds_bytes(max_L, b.builders), s,
                        b);
     return hipGetLastError();
 }
