@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "device_common.h"
 #include "word_task.h"
@@ -78,6 +79,428 @@ __device__ __forceinline__ void unstage_lattice(const uint32_t *lat, const LatDe
     }
 }
 
+// This thread's share of a lattice's tracker slots (phase kernels) and, for
+// thread 0, its tracker base (single-block kernels).
+__device__ __forceinline__ void tracker_partial(const uint8_t *scr, long long (&t3)[3])
+{
+    const long long *slots = (const long long *)(scr + kScrSlots);
+    for (int i = threadIdx.x; i < kMaxSlots; i += blockDim.x) {
+        t3[0] += slots[3 * i];
+        t3[1] += slots[3 * i + 1];
+        t3[2] += slots[3 * i + 2];
+    }
+    if (threadIdx.x == 0) {
+        const long long *base = (const long long *)(scr + kScrTrackBase);
+        t3[0] += base[0];
+        t3[1] += base[1];
+        t3[2] += base[2];
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Per-site form, one byte per site in LDS (row-major), for lattices of any
+// side up to kSiteMaxL.  A site's byte is (1 + S) | (1 + sigma) << 4, so that
+// the bytes of four neighbours add up to both neighbour sums at once (at
+// most 8 a nibble), a site is read with one byte load, and new codes are
+// written with plain byte stores (its pair's lane is the only one that reads
+// or writes them in the phase).
+//
+// What bounds these sizes is the chain of a phase (byte loads, two dependent
+// table gathers, the store, the block barrier), not the work: L = 32 has 128
+// pairs a phase on one compute unit.  So the pairs of a phase are spread over
+// as many threads as help (one pair a thread up to kSiteOnePair pairs, else the
+// two pairs of a Philox call), a thread with one task makes the next phase's
+// draws while its own loads are in flight, the choice slot of a draw does
+// not depend on the state, and a launch holds a whole series of observation
+// intervals with the observables taken from LDS in between.
+//
+// Measured against the two-bit form, whose neighbours are ten shifted word
+// reads and whose codes are merged with LDS atomics: L = 32, 1000 sweeps with
+// observables every 10 as one series 6197 -> 1696 us; 224 lattices of L = 16,
+// 200 intervals of one sweep in a graph 3611 -> 816 us; 40 lattices of L = 100,
+// 50 sweeps 521 -> 247 us; 12 of L = 300, 20 sweeps 1295 -> 726 us.
+
+constexpr uint32_t kSiteHash = 0x2B298945u;  // (byte_a | byte_b << 8) -> 4 distinct top bits for the 16 states
+constexpr uint32_t site_byte(int code) { return code == 0 ? 0x21u : code == 1 ? 0x01u : code == 2 ? 0x12u : 0x10u; }
+constexpr uint32_t kSiteBytes = site_byte(0) | site_byte(1) << 8 | site_byte(2) << 16 | site_byte(3) << 24;
+
+constexpr TransSlots make_site_slots()
+{
+    TransSlots t{};
+    for (int st = 0; st < 16; ++st)
+        for (int slot = 0; slot < 12; ++slot) {
+            uint32_t coef = 0, C = 0;
+            int a1 = 0, b1 = 0;
+            trans_slot(st, slot, coef, C, a1, b1);
+            const uint32_t x = site_byte(st & 3) | site_byte(st >> 2) << 8;
+            const uint32_t at = 2u * (16u * ((x * kSiteHash) >> 28) + (uint32_t)slot);
+            t.v[at] = coef;
+            t.v[at + 1] = C | (site_byte(a1) | site_byte(b1) << 8) << 16;
+        }
+    return t;
+}
+constexpr bool site_hash_distinct()
+{
+    uint32_t seen = 0;
+    for (int st = 0; st < 16; ++st) {
+        const uint32_t x = site_byte(st & 3) | site_byte(st >> 2) << 8, h = (x * kSiteHash) >> 28;
+        if ((seen >> h) & 1u) return false;
+        seen |= 1u << h;
+    }
+    return true;
+}
+static_assert(site_hash_distinct(), "the 16 pair states get 16 table rows");
+__device__ const TransSlots kSiteSlots = make_site_slots();
+
+// Pairs a phase up to which a thread takes one pair: two waves a SIMD, whose
+// repeated draws still fit into the chain of a phase.
+constexpr uint32_t kSiteOnePair = 512;
+constexpr uint32_t kSchedSweeps = 16;   // sweeps whose schedule words are made at once
+
+// Four codes (one a byte) to four site bytes, and back.
+__device__ __forceinline__ uint32_t site_from_codes(uint32_t c) { return __builtin_amdgcn_perm(0u, kSiteBytes, c); }
+__device__ __forceinline__ uint32_t codes_from_site(uint32_t e)
+{
+    const uint32_t one = 0x01010101u;
+    return ((e >> 3) & (one << 1)) | (~((e >> 5) | (e >> 1)) & one);  // charged; sigma = -1 or S = -1
+}
+
+__device__ __forceinline__ void stage_sites(uint32_t *lat, const LatDesc &d)
+{
+    const uint32_t L = (uint32_t)d.L, N = L * L;
+    if (d.enc == 0) {
+        if (((uintptr_t)d.state & 3u) == 0) {
+            const uint32_t *src = (const uint32_t *)d.state;
+            for (uint32_t i = threadIdx.x; i < N / 4u; i += blockDim.x) lat[i] = site_from_codes(src[i] & 0x03030303u);
+        } else {
+            const uint8_t *src = (const uint8_t *)d.state;
+            for (uint32_t i = threadIdx.x; i < N; i += blockDim.x)
+                ((uint8_t *)lat)[i] = (uint8_t)(kSiteBytes >> (8u * (src[i] & 3u)));
+        }
+    } else {
+        // word (c, Y, j) of the class layout: sites x = 4 (16 j + t) + (c & 3) of row 2 Y + (c >> 2)
+        const uint32_t *src = (const uint32_t *)d.state;
+        const uint32_t W = L >> 6, csz = (L >> 1) * W;
+        for (uint32_t i = threadIdx.x; i < 8u * csz; i += blockDim.x) {
+            const uint32_t c = i / csz, rem = i - c * csz, Y = rem / W, j = rem - Y * W, w = src[i];
+            uint8_t *row = (uint8_t *)lat + (2u * Y + (c >> 2)) * L + 64u * j + (c & 3u);
+#pragma unroll
+            for (uint32_t t = 0; t < 16u; ++t) row[4u * t] = (uint8_t)(kSiteBytes >> (8u * ((w >> (2u * t)) & 3u)));
+        }
+    }
+}
+
+__device__ __forceinline__ void unstage_sites(const uint32_t *lat, const LatDesc &d)
+{
+    const uint32_t L = (uint32_t)d.L, N = L * L;
+    if (d.enc == 0) {
+        if (((uintptr_t)d.state & 3u) == 0) {
+            uint32_t *dst = (uint32_t *)d.state;
+            for (uint32_t i = threadIdx.x; i < N / 4u; i += blockDim.x) dst[i] = codes_from_site(lat[i]);
+        } else {
+            uint8_t *dst = (uint8_t *)d.state;
+            for (uint32_t i = threadIdx.x; i < N; i += blockDim.x)
+                dst[i] = (uint8_t)codes_from_site(((const uint8_t *)lat)[i]) & 3u;
+        }
+    } else {
+        uint32_t *dst = (uint32_t *)d.state;
+        const uint32_t W = L >> 6, csz = (L >> 1) * W;
+        for (uint32_t i = threadIdx.x; i < 8u * csz; i += blockDim.x) {
+            const uint32_t c = i / csz, rem = i - c * csz, Y = rem / W, j = rem - Y * W;
+            const uint32_t *row = lat + ((2u * Y + (c >> 2)) * L + 64u * j) / 4u;
+            uint32_t w = 0;
+#pragma unroll
+            for (uint32_t t = 0; t < 16u; ++t)
+                w |= ((codes_from_site(row[t]) >> (8u * (c & 3u))) & 3u) << (2u * t);
+            dst[i] = w;
+        }
+    }
+}
+
+// Byte offsets of a pair's first site in phase 0 (phase p: p more) and its
+// surroundings: rows above and below, the left neighbour in phase 0, the
+// right one in phase 3.
+struct SitePos {
+    uint32_t x4, row, a, u, d, l, r;
+};
+__device__ __forceinline__ SitePos site_pos(uint32_t pi, uint32_t L, uint32_t Lq, uint32_t N, uint32_t magicLq)
+{
+    const uint32_t Y = Lq == 1u ? pi : __umulhi(pi, magicLq), X = pi - Y * Lq;
+    SitePos s;
+    s.x4 = 4u * X;
+    s.row = 2u * Y * L;
+    s.a = s.row + s.x4;
+    s.u = (Y == 0 ? N : s.row) - L + s.x4;
+    s.d = s.a + L;  // y is even: never the last row
+    s.l = X == 0 ? s.row + L - 1u : s.a - 1u;
+    s.r = X + 1u == Lq ? s.row : s.a + 4u;
+    return s;
+}
+
+struct SiteDraw {
+    uint32_t slot8, ua;
+};
+template <int PP>
+__device__ __forceinline__ void site_draws(uint64_t s, uint32_t p, uint32_t task, uint32_t key0, uint32_t key1,
+                                           SiteDraw (&o)[PP])
+{
+    const u32x4 w = philox4x32_10((uint32_t)s, p, PP == 2 ? task : task >> 1, (uint32_t)(s >> 32), key0, key1);
+    const bool odd = PP == 1 && (task & 1u);
+    o[0] = SiteDraw{slot8_of(odd ? w.z : w.x), min(odd ? w.w : w.y, 0xFFFFFFFEu)};
+    if constexpr (PP == 2) o[1] = SiteDraw{slot8_of(w.z), min(w.w, 0xFFFFFFFEu)};
+}
+
+// Byte offsets of a pair's second site in phase P with displacement (Dx, Dy),
+// DyL = Dy L, and of its neighbours.  x mod n for x < 2 n is min(x, x - n) in
+// unsigned arithmetic.
+struct SiteB {
+    uint32_t b, l, r, d;
+};
+template <int P>
+__device__ __forceinline__ SiteB site_b(const SitePos &s, uint32_t L, uint32_t N, uint32_t Dx, uint32_t DyL)
+{
+    uint32_t xb = s.x4 + P + Dx;
+    xb = min(xb, xb - L);
+    uint32_t rb = s.row + DyL;
+    rb = min(rb, rb - N);
+    uint32_t rd = rb + L;  // y_b is odd: never the first row
+    rd = min(rd, rd - N);
+    return SiteB{rb + xb, rb + min(xb - 1u, xb - 1u + L), rb + min(xb + 1u, xb + 1u - L), rd + xb};
+}
+
+// One coupled-pair step in phase P on the sites s and q.
+template <int P>
+__device__ __forceinline__ void site_step(uint8_t *lat, const SitePos &s, const SiteB &q, uint32_t L,
+                                          const SiteDraw &dr, const uint8_t *s_tab, const uint8_t *s_trans,
+                                          uint32_t &packed)
+{
+    const uint32_t ea = lat[s.a + P], eb = lat[q.b];
+    const uint32_t na = (uint32_t)lat[P > 0 ? s.a + P - 1 : s.l] + lat[P < 3 ? s.a + P + 1 : s.r] + lat[s.u + P] +
+                        lat[s.d + P];
+    const uint32_t nb = (uint32_t)lat[q.l] + lat[q.r] + lat[q.b - L] + lat[q.d];
+    const uint32_t t = na | nb << 8, x = ea | eb << 8;
+    const uint32_t bpack = (t & 0x0F0Fu) | (t & 0xF0F0u) << 12;
+    const uint2 tr = *(const uint2 *)(s_trans + ((((x * kSiteHash) >> 21) & 0x780u) | dr.slot8));
+    const uint32_t idx = (uint32_t)__builtin_amdgcn_sdot4((int)tr.x, (int)bpack, (int)tr.y, false);
+    const uint2 e = *(const uint2 *)(s_tab + (uint32_t)(uint16_t)(idx << 3));
+    const bool acc = dr.ua < e.x;
+    packed += acc ? e.y : 0u;
+    const uint32_t nw = acc ? tr.y >> 16 : x;
+    lat[s.a + P] = (uint8_t)nw;
+    lat[q.b] = (uint8_t)(nw >> 8);
+}
+
+// Displacements of a sweep's four phases from its schedule words (uniform).
+struct SiteSchedule {
+    uint32_t Dx[4], DyL[4];
+};
+__device__ __forceinline__ SiteSchedule site_schedule(const uint32_t *Wd, uint32_t L)
+{
+    uint32_t w[9];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) w[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)Wd[i]);
+    const uint32_t r = 1u + (((w[0] >> 8) * 3u) >> 24);
+    SiteSchedule o;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        o.Dx[p] = r + 4u * mulhi_u32(w[1 + 2 * p], L >> 2);
+        o.DyL[p] = (1u + 2u * mulhi_u32(w[2 + 2 * p], L >> 1)) * L;
+    }
+    return o;
+}
+// Schedule words of up to kSchedSweeps sweeps from s on, one Philox call a thread.
+__device__ __forceinline__ void make_schedules(uint32_t *sched, uint64_t s, uint32_t sweeps, const LatDesc &d)
+{
+    const uint32_t t = threadIdx.x;
+    if (t >= 3u * min(kSchedSweeps, sweeps)) return;
+    const uint64_t q = s + t / 3u;
+    const u32x4 w = philox4x32_10((uint32_t)q, kDomSchedule, t % 3u, (uint32_t)(q >> 32), d.key0, d.key1);
+    sched[4u * t] = w.x;
+    sched[4u * t + 1u] = w.y;
+    sched[4u * t + 2u] = w.z;
+    sched[4u * t + 3u] = w.w;
+}
+
+// `intervals` times `every` sweeps of the lattice in LDS from sweep first on,
+// each interval followed by observe(k).  PP pairs a task; One: every thread
+// has at most one task, whose draws and second sites of the next phase are
+// made while the current phase's loads are in flight.
+template <int PP, bool One, typename F>
+__device__ __forceinline__ void site_sweeps(uint8_t *lat, uint32_t *sched, const LatDesc &d, uint64_t first,
+                                            uint32_t intervals, uint32_t every, const uint8_t *s_tab,
+                                            const uint8_t *s_trans, int (&tr)[3], F observe)
+{
+    const uint32_t L = (uint32_t)d.L, Lq = L >> 2, N = L * L;
+    const uint32_t magicLq = Lq == 1u ? 0u : 0xFFFFFFFFu / Lq + 1u;
+    const uint32_t tasks = N / (8u * PP), n = intervals * every;
+    const bool mine = threadIdx.x < tasks;
+    make_schedules(sched, first, n, d);
+    __syncthreads();
+    SiteSchedule sc = site_schedule(sched, L);
+    SitePos pos[PP];
+    SiteDraw dr[PP];
+    SiteB q[PP];
+    if (One) {
+        site_draws<PP>(first, 0u, threadIdx.x, d.key0, d.key1, dr);
+#pragma unroll
+        for (int h = 0; h < PP; ++h) {
+            pos[h] = site_pos(mine ? threadIdx.x * PP + (uint32_t)h : 0u, L, Lq, N, magicLq);
+            q[h] = site_b<0>(pos[h], L, N, sc.Dx[0], sc.DyL[0]);
+        }
+    }
+    uint32_t left = every, k = 0;  // sweeps left of interval k
+    for (uint32_t i = 0; i < n; ++i) {
+        const uint64_t s = first + i;
+        SiteSchedule next = sc;
+        uint32_t packed = 0u;  // One: at most 8 accepted moves a sweep
+        auto phase = [&](auto pc) {
+            constexpr int P = decltype(pc)::value;
+            constexpr int P1 = (P + 1) & 3;
+            // the words of the next kSchedSweeps sweeps, into the half of the
+            // buffer that was last read a sweep or more ago
+            const uint32_t j = i + 1u;
+            if (P == 0 && j % kSchedSweeps == 0 && j < n)
+                make_schedules(sched + 12u * (j % (2u * kSchedSweeps)), s + 1, n - j, d);
+            if (P == 3) next = site_schedule(sched + 12u * (j % (2u * kSchedSweeps)), L);
+            if (One) {
+                if (mine) {
+                    SiteDraw nd[PP];
+                    site_draws<PP>(P < 3 ? s : s + 1, P1, threadIdx.x, d.key0, d.key1, nd);
+#pragma unroll
+                    for (int h = 0; h < PP; ++h) {
+                        site_step<P>(lat, pos[h], q[h], L, dr[h], s_tab, s_trans, packed);
+                        dr[h] = nd[h];
+                        q[h] = site_b<P1>(pos[h], L, N, P < 3 ? sc.Dx[P1] : next.Dx[0], P < 3 ? sc.DyL[P1] : next.DyL[0]);
+                    }
+                }
+            } else {
+                for (uint32_t t = threadIdx.x; t < tasks; t += blockDim.x) {
+                    site_draws<PP>(s, P, t, d.key0, d.key1, dr);
+                    packed = 0u;
+#pragma unroll
+                    for (int h = 0; h < PP; ++h) {
+                        const SitePos at = site_pos(t * PP + (uint32_t)h, L, Lq, N, magicLq);
+                        site_step<P>(lat, at, site_b<P>(at, L, N, sc.Dx[P], sc.DyL[P]), L, dr[h], s_tab, s_trans,
+                                     packed);
+                    }
+                    unpack_tracker(packed, tr);
+                }
+            }
+            __syncthreads();
+        };
+        phase(std::integral_constant<int, 0>{});
+        phase(std::integral_constant<int, 1>{});
+        phase(std::integral_constant<int, 2>{});
+        phase(std::integral_constant<int, 3>{});
+        sc = next;
+        if (One) unpack_tracker(packed, tr);
+        if (--left == 0) {
+            observe(k);
+            ++k;
+            left = every;
+        }
+    }
+}
+
+// This thread's share of the seven observable sums, four sites at a time:
+// with u = 1 + S and g = 1 + sigma as bytes, sum S S' over the 2N bonds is
+// sum u u' - 4 sum u + 2N (every site is in four bonds), sum S^2 is
+// sum u^2 - 2 sum u + N, and the offsets cancel in the staggered sums.
+__device__ __forceinline__ void site_observables(const uint32_t *lat, uint32_t L, int (&v)[7])
+{
+    const uint32_t Lq = L >> 2, n = L * Lq, m4 = 0x0F0F0F0Fu, ones = 0x01010101u;
+    uint32_t su = 0, sg = 0, suu = 0, bu = 0, bg = 0, cnt = 0;
+    int stu = 0, stg = 0;
+    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
+        const uint32_t y = i / Lq, X = i - y * Lq;
+        const uint32_t w = lat[i], w1 = lat[X + 1u == Lq ? i + 1u - Lq : i + 1u], wd = lat[y + 1u == L ? X : i + Lq];
+        const uint32_t wr = __builtin_amdgcn_alignbit(w1, w, 8u);
+        const uint32_t u = w & m4, g = (w >> 4) & m4;
+        const int sign = (int)((y & 1u) ? 0x01FF01FFu : 0xFF01FF01u);
+        su = __builtin_amdgcn_udot4(u, ones, su, false);
+        sg = __builtin_amdgcn_udot4(g, ones, sg, false);
+        suu = __builtin_amdgcn_udot4(u, u, suu, false);
+        bu = __builtin_amdgcn_udot4(u, wr & m4, bu, false);
+        bu = __builtin_amdgcn_udot4(u, wd & m4, bu, false);
+        bg = __builtin_amdgcn_udot4(g, (wr >> 4) & m4, bg, false);
+        bg = __builtin_amdgcn_udot4(g, (wd >> 4) & m4, bg, false);
+        stg = __builtin_amdgcn_sdot4((int)g, sign, stg, false);
+        stu = __builtin_amdgcn_sdot4((int)u, sign, stu, false);
+        cnt += 4u;
+    }
+    v[0] = (int)su - (int)cnt;
+    v[1] = (int)suu - 2 * (int)su + (int)cnt;
+    v[2] = (int)bu - 4 * (int)su + 2 * (int)cnt;
+    v[3] = (int)bg - 4 * (int)sg + 2 * (int)cnt;
+    v[4] = (int)sg - (int)cnt;
+    v[5] = stg;
+    v[6] = stu;
+}
+
+__global__ void __launch_bounds__(1024) k_sweep_site(BatchArgs args)
+{
+    __shared__ __align__(16) uint2 s_tab[kDevTabEntries + 1];
+    __shared__ __align__(16) uint32_t s_trans[2 * 256];
+    __shared__ uint32_t sched[2 * 12 * kSchedSweeps];
+    __shared__ int part[16][10];
+    __shared__ long long base[3];
+    extern __shared__ uint32_t lat[];
+    uint8_t *scr = args.scratch[blockIdx.x];
+    const LatDesc d = *(const LatDesc *)(scr + kScrDesc);
+    {
+        const uint2 *g_tab = (const uint2 *)(scr + kScrDevTab);
+        for (int i = threadIdx.x; i < kDevTabEntries; i += blockDim.x) s_tab[i] = g_tab[i];
+        for (int i = threadIdx.x; i < 2 * 256; i += blockDim.x) s_trans[i] = kSiteSlots.v[i];
+    }
+    stage_sites(lat, d);
+    if (args.obs_out) {
+        // the tracker total before this launch
+        long long t3[3] = {0, 0, 0};
+        tracker_partial(scr, t3);
+        block_reduce_store<3>(t3, base);
+    }
+    __syncthreads();
+
+    const uint32_t L = (uint32_t)d.L, N = L * L, my_sweeps = args.sweeps[blockIdx.x];
+    const uint32_t intervals = args.obs_out ? args.intervals : 1u;
+    const bool single = N / 8u <= min(blockDim.x, kSiteOnePair), one = N / 16u <= blockDim.x;
+    const uint8_t *tab = (const uint8_t *)s_tab, *trans = (const uint8_t *)s_trans;
+    int tr[3] = {0, 0, 0};
+    // no other wave writes the lattice or `part` before the next block barrier
+    // of the sweeps, and there are four of those between two intervals
+    auto observe = [&](uint32_t k) {
+        if (!args.obs_out) return;
+        int v[10] = {tr[0], tr[1], tr[2]};
+        int o[7];
+        site_observables(lat, L, o);
+#pragma unroll
+        for (int q = 0; q < 7; ++q) v[3 + q] = o[q];
+        wave_partials<10, int>(v, part);
+        __syncthreads();
+        unsigned long long *rec =
+            args.obs_out + (size_t)args.obs_stride * k + (size_t)args.obs_words * blockIdx.x;
+        if (threadIdx.x < 10) {
+            long long sum = threadIdx.x < 3 ? base[threadIdx.x] : 0ll;
+            for (uint32_t w = 0; w < blockDim.x >> 6; ++w) sum += (long long)part[w][threadIdx.x];
+            rec[threadIdx.x] = (unsigned long long)sum;
+        }
+        if (args.obs_words > 10 && threadIdx.x == 0) rec[10] = d.next_sweep + (uint64_t)my_sweeps * (k + 1u);
+    };
+    if (my_sweeps > 0) {
+        uint8_t *bytes = (uint8_t *)lat;
+        if (single)
+            site_sweeps<1, true>(bytes, sched, d, d.next_sweep, intervals, my_sweeps, tab, trans, tr, observe);
+        else if (one)
+            site_sweeps<2, true>(bytes, sched, d, d.next_sweep, intervals, my_sweeps, tab, trans, tr, observe);
+        else
+            site_sweeps<2, false>(bytes, sched, d, d.next_sweep, intervals, my_sweeps, tab, trans, tr, observe);
+    }
+    unstage_sites(lat, d);
+    if (threadIdx.x == 0) ((LatDesc *)(scr + kScrDesc))->next_sweep = d.next_sweep + (uint64_t)my_sweeps * intervals;
+    block_reduce_add<3>(tr, (unsigned long long *)(scr + kScrTrackBase));
+}
+
+// Two bits per site, any side: where the per-site form's bytes do not fit.
 __global__ void __launch_bounds__(1024) k_sweep_lds(BatchArgs args)
 {
     __shared__ uint2 s_tab[kDevTabEntries];
@@ -229,24 +652,6 @@ __device__ __forceinline__ void obs_sums_2bit(const uint32_t *st, int L, long lo
     for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) obs_word_2bit(st, L, i, v);
 }
 
-// This thread's share of a lattice's tracker slots (phase kernels) and, for
-// thread 0, its tracker base (single-block kernels).
-__device__ __forceinline__ void tracker_partial(const uint8_t *scr, long long (&t3)[3])
-{
-    const long long *slots = (const long long *)(scr + kScrSlots);
-    for (int i = threadIdx.x; i < kMaxSlots; i += blockDim.x) {
-        t3[0] += slots[3 * i];
-        t3[1] += slots[3 * i + 1];
-        t3[2] += slots[3 * i + 2];
-    }
-    if (threadIdx.x == 0) {
-        const long long *base = (const long long *)(scr + kScrTrackBase);
-        t3[0] += base[0];
-        t3[1] += base[1];
-        t3[2] += base[2];
-    }
-}
-
 // MaxThreads = 512 serves blocks of up to 512 threads (measured faster: the
 // compiler schedules for fewer waves per SIMD), 1024 the largest blocks.
 template <int MaxThreads>
@@ -299,12 +704,13 @@ __global__ void __launch_bounds__(MaxThreads) k_sweep_lds_w(BatchArgs args)
             // the interval's observables from the LDS copy, and the tracker
             // total as k_obs_batch would read it after this launch: the
             // slots, the base before this launch and this launch's own moves
-            unsigned long long *o = args.obs_out + 10 * (size_t)blockIdx.x;
+            unsigned long long *o = args.obs_out + (size_t)args.obs_words * blockIdx.x;
             long long t3[3] = {tr[0], tr[1], tr[2]};
             tracker_partial(scr, t3);
             long long v[7] = {0, 0, 0, 0, 0, 0, 0};
             obs_sums_2bit(lat, d.L, v);
             if (threadIdx.x < 10) o[threadIdx.x] = 0ull;
+            if (args.obs_words > 10 && threadIdx.x == 0) o[10] = d.next_sweep + my_sweeps;
             __syncthreads();
             block_reduce_add<7>(v, o + 3);
             block_reduce_add<3>(t3, o);
@@ -347,8 +753,9 @@ __global__ void __launch_bounds__(256) k_obs_batch(BatchArgs args, unsigned long
     } else {
         obs_sums_2bit((const uint32_t *)d.state, L, v);
     }
-    unsigned long long *o = out + 10 * (size_t)blockIdx.x;
+    unsigned long long *o = out + (size_t)(args.obs_words > 10 ? 11 : 10) * blockIdx.x;
     if (threadIdx.x < 10) o[threadIdx.x] = 0ull;
+    if (args.obs_words > 10 && threadIdx.x == 0) o[10] = d.next_sweep;
     __syncthreads();
     block_reduce_add<7>(v, o + 3);
     long long t3[3] = {0, 0, 0};
@@ -364,6 +771,9 @@ hipError_t init_kernel_attributes()
     const int bytes = (int)(lds_state_words(kLdsMaxL) * 4u);
     hipError_t e = hipFuncSetAttribute((const void *)k_sweep_lds, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (e == hipSuccess)
+        e = hipFuncSetAttribute((const void *)k_sweep_site, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                kSiteMaxL * kSiteMaxL);
+    if (e == hipSuccess)
         e = hipFuncSetAttribute((const void *)k_sweep_lds_w<512>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (e == hipSuccess)
         e = hipFuncSetAttribute((const void *)k_sweep_lds_w<1024>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
@@ -372,13 +782,19 @@ hipError_t init_kernel_attributes()
 
 hipError_t launch_sweep_lds(const BatchArgs &a, int max_L, int threads, bool word, hipStream_t s)
 {
-    // default block: per-site form, one thread per Philox call (two pairs);
-    // word form, two threads per a-word (at least 256)
+    // default block: word form, two threads per a-word (at least 256);
+    // per-site form, one thread per pair up to kSiteOnePair pairs, else one
+    // per Philox call (two pairs); two-bit form above it, the same
     const uint32_t sq = (uint32_t)max_L * (uint32_t)max_L;
-    const uint32_t units = word ? std::max(256u, sq / 64u) : sq / 16u;
+    const bool site = launch_fuses_intervals(max_L, word);
+    const uint32_t units = word ? std::max(256u, sq / 64u) : site && sq / 8u <= kSiteOnePair ? sq / 8u : sq / 16u;
     uint32_t block = units < 1024u ? ((units + 63u) / 64u) * 64u : 1024u;
     if (threads > 0) block = (uint32_t)std::min(1024, std::max(64, threads / 64 * 64));
     if (block < 64u) block = 64u;
+    if (site) {
+        hipLaunchKernelGGL(k_sweep_site, dim3((unsigned)a.count), dim3(block), (size_t)sq, s, a);
+        return hipGetLastError();
+    }
     const size_t lds = lds_state_words(max_L) * 4u;
     // a.obs_out: the 512-thread word form writes the observables itself;
     // the other forms are followed by the observables launch

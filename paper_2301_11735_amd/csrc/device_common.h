@@ -112,6 +112,44 @@ __device__ __forceinline__ uint32_t pair_step(uint32_t st, uint32_t bpack, uint3
     return pair_step_k2(st, (kKq2 >> (2u * st)) & 3u, bpack, uc, ua, s_trans, s_tab, packed);
 }
 
+// Transition table of section 3.1's coupled-pair move with 12 choice slots a
+// state, so that the slot depends on the draw alone: slot floor(12 u) holds
+// configuration floor(12 u) / 2 = floor(6 u) where k_q = 6, floor(12 u) / 3 =
+// floor(4 u) where k_q = 4, and the null move where the pair is frozen.
+// Entry 16 x + slot of state x is {coef, C | codes << 16}: coef and C as in
+// the host's transition table (dot4(coef, sums) + C is the device-table
+// index, at most 932, so a dot4 that accumulates onto the whole word leaves the
+// high half alone).
+struct TransSlots {
+    uint32_t v[2 * 256];
+};
+constexpr uint32_t trans_i8(int v) { return (uint32_t)(uint8_t)(int8_t)v; }
+constexpr void trans_slot(int st, int slot, uint32_t &coef, uint32_t &C, int &a1, int &b1)
+{
+    constexpr int S[4] = {0, 0, 1, -1}, G[4] = {1, -1, 0, 0};
+    constexpr int plus[4] = {2 | 0 << 2, 2 | 1 << 2, 0 | 2 << 2, 1 | 2 << 2};
+    constexpr int zero[6] = {2 | 3 << 2, 3 | 2 << 2, 0 | 0 << 2, 1 | 1 << 2, 0 | 1 << 2, 1 | 0 << 2};
+    constexpr int minus[4] = {3 | 0 << 2, 3 | 1 << 2, 0 | 3 << 2, 1 | 3 << 2};
+    const int ca = st & 3, cb = st >> 2, q = S[ca] + S[cb];
+    const int to = q == 0 ? zero[slot / 2] : q == 1 ? plus[slot / 3] : q == -1 ? minus[slot / 3] : st;
+    a1 = to & 3;
+    b1 = to >> 2;
+    const int dSa = S[a1] - S[ca], dSb = S[b1] - S[cb], dGa = G[a1] - G[ca], dGb = G[b1] - G[cb];
+    const int nD = S[a1] * S[a1] + S[b1] * S[b1] - S[ca] * S[ca] - S[cb] * S[cb];
+    if (dSa == 2 || dSa == -2) {  // charge swap: V line
+        coef = trans_i8(dSa) | trans_i8(dSb) << 8;
+        C = (uint32_t)(kDevVLine + 16);
+    } else if (dGa == 2 || dGa == -2 || dGb == 2 || dGb == -2) {  // spin change: J line
+        coef = trans_i8(dGa) << 16 | trans_i8(dGb) << 24;
+        C = (uint32_t)(kDevJLine + 16 - 4 * (dGa + dGb));
+    } else {
+        coef = trans_i8(17 * dSa) | trans_i8(17 * dSb) << 8 | trans_i8(dGa) << 16 | trans_i8(dGb) << 24;
+        C = (uint32_t)((nD / 2 + 1) * kDevSlice + 8 * 17 + 8 - 4 * (dGa + dGb));
+    }
+}
+// Byte offset 8 floor(12 (uc >> 8) / 2^24) of the draw's slot.
+__device__ __forceinline__ uint32_t slot8_of(uint32_t uc) { return __umulhi(uc & ~255u, 96u) & 0x78u; }
+
 // Per-thread tracker: counts and biased sums of the accepted triples.
 __device__ __forceinline__ void unpack_tracker(uint32_t packed, int (&tr)[3])
 {

@@ -90,23 +90,24 @@ int lattice_batch_graph_create(lattice *const *hs, int32_t count, uint32_t sweep
         if (e == hipSuccess) {
             std::vector<lattice *> small, big;
             for (lattice *h : g->hs) (h->path == kPathLds ? small : big).push_back(h);
-            for (uint32_t k = 0; k < intervals && rc == LAT_OK; ++k) {
+            if (big.empty()) {
+                // an interval's sweeps and observables are one launch in the
+                // word form, and many intervals are one in the per-site form
+                const ObsTarget obs{(unsigned long long *)d_out, intervals, 10u, 10u * (uint32_t)count};
+                rc = enqueue_lds_sweeps(g->hs.data(), count, nullptr, sweeps, cs, /*tune=*/false, &obs);
+            }
+            for (uint32_t k = 0; k < intervals && rc == LAT_OK && !big.empty(); ++k) {
                 unsigned long long *slot = (unsigned long long *)d_out + 10 * (size_t)count * k;
-                if (big.empty()) {
-                    // the sweeps and the interval's observables, in one launch for the word form
-                    rc = enqueue_lds_sweeps(g->hs.data(), count, nullptr, sweeps, cs, /*tune=*/false, slot);
-                } else {
-                    // the multi-block word path computes its schedules on the
-                    // device, so its launch series replays like the on-chip
-                    // one; one launch per phase, since a graph's kernel node
-                    // does not guarantee the co-residency that the persistent
-                    // form's device-wide barrier needs
-                    rc = enqueue_lds_sweeps(small.data(), (int32_t)small.size(), nullptr, sweeps, cs, false);
-                    if (rc == LAT_OK)
-                        rc = enqueue_offchip_sweeps(big.data(), (int32_t)big.size(), nullptr, sweeps, cs,
-                                                    /*convert=*/true, /*persistent=*/false);
-                    if (rc == LAT_OK) rc = enqueue_observables_batch(g->hs.data(), count, slot, cs);
-                }
+                // the multi-block word path computes its schedules on the
+                // device, so its launch series replays like the on-chip one;
+                // one launch per phase, since a graph's kernel node does not
+                // guarantee the co-residency that the persistent form's
+                // device-wide barrier needs
+                rc = enqueue_lds_sweeps(small.data(), (int32_t)small.size(), nullptr, sweeps, cs, false);
+                if (rc == LAT_OK)
+                    rc = enqueue_offchip_sweeps(big.data(), (int32_t)big.size(), nullptr, sweeps, cs,
+                                                /*convert=*/true, /*persistent=*/false);
+                if (rc == LAT_OK) rc = enqueue_observables_batch(g->hs.data(), count, slot, cs);
             }
             const hipError_t e2 = hipStreamEndCapture(cs, &g->graph);
             if (rc == LAT_OK && e2 != hipSuccess) e = e2;

@@ -71,12 +71,18 @@ int guarded(const char *what, F &&body) noexcept
 }
 // Advance lattices resident in LDS; lattice i by sweeps[i] (null: `uniform`).
 // tune = false: no autotuning launches (the tuned or default block size),
-// as needed under stream capture.  obs_dev non-null: then also write the
-// lattices' observables into obs_dev (10 int64 each, as
-// enqueue_observables_batch), from LDS at the end of the 512-thread
-// word-form launch or by a separate launch after the other forms.
+// as needed under stream capture.  obs non-null: `intervals` times over, each
+// time followed by the lattices' observables in obs->dev (obs->words int64 a
+// lattice as enqueue_observables_batch, obs->stride int64 from one interval to
+// the next), written from LDS by the sweep launch where its form does that.
+struct ObsTarget {
+    unsigned long long *dev;
+    uint32_t intervals;
+    uint32_t words;   // 10, or 11 with the next sweep index appended (series records)
+    uint32_t stride;
+};
 int enqueue_lds_sweeps(lattice *const *hs, int32_t count, const uint32_t *sweeps, uint32_t uniform,
-                       hipStream_t stream, bool tune = true, unsigned long long *obs_dev = nullptr);
+                       hipStream_t stream, bool tune = true, const ObsTarget *obs = nullptr);
 // One batched observables launch per 256 lattices into dev (10 int64 each).
 int enqueue_observables_batch(lattice *const *hs, int32_t count, unsigned long long *dev, hipStream_t stream);
 // Lattices on the off-chip paths (words, phase): lattice i by sweeps[i]

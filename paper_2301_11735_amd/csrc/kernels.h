@@ -86,17 +86,31 @@ struct LatDesc {
 constexpr int kLdsMaxL = 512;
 inline size_t lds_state_words(int L) { return (size_t)8 * (L / 2) * ((L / 4 + 15) / 16); }
 
-// One launch of the batched kernel: block b advances lattice b by sweeps[b].
+// The per-site form (k_sweep_site) keeps one byte per site in LDS: sides up to
+// 384, whose 144 KiB leave room for its tables; above, k_sweep_lds keeps two
+// bits per site.
+constexpr int kSiteMaxL = 384;
+
+// One launch of the batched kernel: block b advances lattice b by sweeps[b],
+// `intervals` times over in the per-site form (1 in the others).
 constexpr int kMaxBatch = 256;
 struct BatchArgs {
     int count;
     uint8_t *scratch[kMaxBatch];
     uint32_t sweeps[kMaxBatch];
-    // non-null: after the sweeps, lattice b's observables and tracker total
-    // go to obs_out[10b ..] in k_obs_batch's layout (written by the sweep
-    // kernel itself in its 512-thread word form, else by k_obs_batch)
+    // non-null: after the sweeps of interval k, lattice b's observables and
+    // tracker total go to obs_out[obs_stride k + obs_words b ..] in
+    // k_obs_batch's layout (written by the sweep kernel itself in the per-site
+    // form and the 512-thread word form, else by k_obs_batch); obs_words = 11
+    // appends the lattice's next sweep index (a series record), else 10
     unsigned long long *obs_out;
+    uint32_t intervals, obs_words, obs_stride;
 };
+// Sweeps of one launch of the per-site form over several intervals: bounds
+// how long a launch runs (about half a second at L = 384).
+constexpr uint32_t kFusedSweeps = 16384;
+// Whether one launch may hold several observation intervals.
+inline bool launch_fuses_intervals(int max_L, bool word) { return !word && max_L <= kSiteMaxL; }
 
 // One phase of one sweep: phase p, displacement D = (r + 4m, 1 + 2k).
 struct PhaseArgs {

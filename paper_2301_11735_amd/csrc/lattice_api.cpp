@@ -790,7 +790,7 @@ int enqueue_observables_batch(lattice *const *hs, int32_t count, unsigned long l
 
 // Batched path: lattices resident in LDS, up to kMaxBatch per launch.
 int enqueue_lds_sweeps(lattice *const *hs, int32_t count, const uint32_t *sweeps, uint32_t uniform,
-                       hipStream_t stream, bool tune, unsigned long long *obs_dev)
+                       hipStream_t stream, bool tune, const ObsTarget *obs)
 {
     // LATTICE_LDS_SITE=1 keeps every batch on the per-site form (tests compare the two)
     const char *env = std::getenv("LATTICE_LDS_SITE");
@@ -808,19 +808,30 @@ int enqueue_lds_sweeps(lattice *const *hs, int32_t count, const uint32_t *sweeps
             updates += (double)hs[b + i]->N * a.sweeps[i];
             word = word && hs[b + i]->L % 64 == 0;
         }
-        hipEvent_t t0 = nullptr, t1 = nullptr;
-        int slot = -1;
-        const int threads = tune ? batch_threads_for(max_L, a.count, word, stream, &t0, &t1, &slot)
-                                 : batch_threads_tuned(max_L, a.count, word);
-        a.obs_out = obs_dev ? obs_dev + 10 * (size_t)b : nullptr;
-        if (t0) (void)hipEventRecord(t0, stream);
-        hipError_t e = launch_sweep_lds(a, max_L, threads, word, stream);
-        if (e != hipSuccess) return hip_fail(e, "batched kernel launch");
-        if (t1) {
-            (void)hipEventRecord(t1, stream);
-            batch_threads_done(slot, updates);
+        const uint32_t intervals = obs ? obs->intervals : 1u;
+        // per-site form: its block size follows from the largest side, and one
+        // launch holds as many intervals as kFusedSweeps sweeps allow
+        const bool fused = launch_fuses_intervals(max_L, word);
+        const uint32_t most = *std::max_element(a.sweeps, a.sweeps + a.count);
+        const uint32_t per_launch = fused ? std::max(1u, kFusedSweeps / std::max(1u, most)) : 1u;
+        a.obs_words = obs ? obs->words : 10u;
+        a.obs_stride = obs ? obs->stride : 0u;
+        for (uint32_t k = 0; k < intervals; k += per_launch) {
+            a.intervals = std::min(per_launch, intervals - k);
+            a.obs_out = obs ? obs->dev + (size_t)obs->stride * k + (size_t)obs->words * (size_t)b : nullptr;
+            hipEvent_t t0 = nullptr, t1 = nullptr;
+            int slot = -1;
+            const int threads = tune && !fused ? batch_threads_for(max_L, a.count, word, stream, &t0, &t1, &slot)
+                                               : batch_threads_tuned(max_L, a.count, word);
+            if (t0) (void)hipEventRecord(t0, stream);
+            hipError_t e = launch_sweep_lds(a, max_L, threads, word, stream);
+            if (e != hipSuccess) return hip_fail(e, "batched kernel launch");
+            if (t1) {
+                (void)hipEventRecord(t1, stream);
+                batch_threads_done(slot, updates);
+            }
+            for (int i = 0; i < a.count; ++i) hs[b + i]->done += (uint64_t)a.sweeps[i] * a.intervals;
         }
-        for (int i = 0; i < a.count; ++i) hs[b + i]->done += a.sweeps[i];
     }
     return LAT_OK;
 }
@@ -1114,9 +1125,14 @@ int lattice_sweep_series(lattice *h, uint32_t intervals, uint32_t every, void *d
         bool ran = false;
         const int rc0 = enqueue_words_persistent(one, 1, nullptr, intervals, every, (long long *)d_series, st, &ran);
         if (rc0) return rc0;
+        if (h->path == kPathLds) {
+            const ObsTarget obs{(unsigned long long *)d_series, intervals, kSeriesRecord / 8, kSeriesRecord / 8};
+            const int rc = enqueue_lds_sweeps(one, 1, nullptr, every, st, /*tune=*/false, &obs);
+            if (rc) return rc;
+            ran = true;
+        }
         for (uint32_t k = 0; k < intervals && !ran; ++k) {
-            const int rc = h->path == kPathLds ? enqueue_lds_sweeps(one, 1, nullptr, every, st, /*tune=*/false)
-                                               : enqueue_offchip_sweeps(one, 1, nullptr, every, st, /*convert=*/false);
+            const int rc = enqueue_offchip_sweeps(one, 1, nullptr, every, st, /*convert=*/false);
             if (rc) return rc;
             long long *rec = (long long *)((uint8_t *)d_series + kSeriesRecord * (size_t)k);
             const hipError_t e = launch_observables(h->d_scratch, h->packed ? (const void *)work : h->d_state, h->L,
