@@ -122,7 +122,7 @@ __device__ __forceinline__ void tracker_partial(const uint8_t *scr, long long (&
 
 constexpr uint32_t kSiteHash = 0x2B298945u;  // (byte_a | byte_b << 8) -> 4 distinct top bits for the 16 states
 constexpr uint32_t site_byte(int code) { return code == 0 ? 0x21u : code == 1 ? 0x01u : code == 2 ? 0x12u : 0x10u; }
-constexpr uint32_t kSiteBytes = site_byte(0) | site_byte(1) << 8 | site_byte(2) << 16 | site_byte(3) << 24;
+static_assert((site_byte(0) | site_byte(1) << 8 | site_byte(2) << 16 | site_byte(3) << 24) == kSiteBytes, "site bytes");
 
 constexpr TransSlots make_site_slots()
 {
@@ -157,8 +157,7 @@ __device__ const TransSlots kSiteSlots = make_site_slots();
 constexpr uint32_t kSiteOnePair = 512;
 constexpr uint32_t kSchedSweeps = 16;   // sweeps whose schedule words are made at once
 
-// Four codes (one a byte) to four site bytes, and back.
-__device__ __forceinline__ uint32_t site_from_codes(uint32_t c) { return __builtin_amdgcn_perm(0u, kSiteBytes, c); }
+// Four site bytes to four codes (one a byte).
 __device__ __forceinline__ uint32_t codes_from_site(uint32_t e)
 {
     const uint32_t one = 0x01010101u;
@@ -402,39 +401,17 @@ __device__ __forceinline__ void site_sweeps(uint8_t *lat, uint32_t *sched, const
     }
 }
 
-// This thread's share of the seven observable sums, four sites at a time:
-// with u = 1 + S and g = 1 + sigma as bytes, sum S S' over the 2N bonds is
-// sum u u' - 4 sum u + 2N (every site is in four bonds), sum S^2 is
-// sum u^2 - 2 sum u + N, and the offsets cancel in the staggered sums.
+// This thread's share of the seven observable sums.
 __device__ __forceinline__ void site_observables(const uint32_t *lat, uint32_t L, int (&v)[7])
 {
-    const uint32_t Lq = L >> 2, n = L * Lq, m4 = 0x0F0F0F0Fu, ones = 0x01010101u;
-    uint32_t su = 0, sg = 0, suu = 0, bu = 0, bg = 0, cnt = 0;
-    int stu = 0, stg = 0;
+    const uint32_t Lq = L >> 2, n = L * Lq;
+    SiteSums sums;
     for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
-        const uint32_t y = i / Lq, X = i - y * Lq;
-        const uint32_t w = lat[i], w1 = lat[X + 1u == Lq ? i + 1u - Lq : i + 1u], wd = lat[y + 1u == L ? X : i + Lq];
-        const uint32_t wr = __builtin_amdgcn_alignbit(w1, w, 8u);
-        const uint32_t u = w & m4, g = (w >> 4) & m4;
-        const int sign = (int)((y & 1u) ? 0x01FF01FFu : 0xFF01FF01u);
-        su = __builtin_amdgcn_udot4(u, ones, su, false);
-        sg = __builtin_amdgcn_udot4(g, ones, sg, false);
-        suu = __builtin_amdgcn_udot4(u, u, suu, false);
-        bu = __builtin_amdgcn_udot4(u, wr & m4, bu, false);
-        bu = __builtin_amdgcn_udot4(u, wd & m4, bu, false);
-        bg = __builtin_amdgcn_udot4(g, (wr >> 4) & m4, bg, false);
-        bg = __builtin_amdgcn_udot4(g, (wd >> 4) & m4, bg, false);
-        stg = __builtin_amdgcn_sdot4((int)g, sign, stg, false);
-        stu = __builtin_amdgcn_sdot4((int)u, sign, stu, false);
-        cnt += 4u;
+        const uint32_t y = i / Lq, X = i - y * Lq, w = lat[i];
+        const uint32_t w1 = lat[X + 1u == Lq ? i + 1u - Lq : i + 1u];
+        sums.add(w, __builtin_amdgcn_alignbit(w1, w, 8u), lat[y + 1u == L ? X : i + Lq], y);
     }
-    v[0] = (int)su - (int)cnt;
-    v[1] = (int)suu - 2 * (int)su + (int)cnt;
-    v[2] = (int)bu - 4 * (int)su + 2 * (int)cnt;
-    v[3] = (int)bg - 4 * (int)sg + 2 * (int)cnt;
-    v[4] = (int)sg - (int)cnt;
-    v[5] = stg;
-    v[6] = stu;
+    sums.get(v);
 }
 
 __global__ void __launch_bounds__(1024) k_sweep_site(BatchArgs args)
@@ -735,21 +712,15 @@ __global__ void __launch_bounds__(256) k_obs_batch(BatchArgs args, unsigned long
     const int L = d.L;
     long long v[7] = {0, 0, 0, 0, 0, 0, 0};
     if (d.enc == 0) {
-        const int8_t *st = (const int8_t *)d.state;
-        for (uint32_t i = threadIdx.x; i < (uint32_t)L * L; i += blockDim.x) {
-            const int y = (int)(i / L), x = (int)(i - (uint32_t)y * L);
-            const uint32_t c = (uint32_t)st[i];
-            const uint32_t cr = (uint32_t)st[(size_t)y * L + (x + 1 == L ? 0 : x + 1)];
-            const uint32_t cd = (uint32_t)st[(size_t)(y + 1 == L ? 0 : y + 1) * L + x];
-            const int S = charge_of(c), G = spin_of(c), sg = ((x + y) & 1) ? -1 : 1;
-            v[0] += S;
-            v[1] += S * S;
-            v[2] += S * (charge_of(cr) + charge_of(cd));
-            v[3] += G * (spin_of(cr) + spin_of(cd));
-            v[4] += G;
-            v[5] += sg * G;
-            v[6] += sg * S;
-        }
+        const uint8_t *st = (const uint8_t *)d.state;
+        SiteSums sums;
+        if (L % 16 == 0 && ((uintptr_t)st & 15u) == 0)
+            for (uint32_t t = threadIdx.x; t < (uint32_t)L * L / 16u; t += blockDim.x)
+                obs_group_int8<4>(st, (uint32_t)L, t, sums);
+        else
+            for (uint32_t t = threadIdx.x; t < (uint32_t)L * L / 4u; t += blockDim.x)
+                obs_group_int8<1>(st, (uint32_t)L, t, sums);
+        sums.get(v);
     } else {
         obs_sums_2bit((const uint32_t *)d.state, L, v);
     }

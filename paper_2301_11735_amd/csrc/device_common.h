@@ -399,6 +399,85 @@ __device__ __forceinline__ uint32_t gather_byte(uint32_t r0, uint32_t r1, uint32
 __device__ __forceinline__ int spin_of(uint32_t c) { return (c & 2u) ? 0 : 1 - 2 * (int)(c & 1u); }
 __device__ __forceinline__ int charge_of(uint32_t c) { return (c & 2u) ? 1 - 2 * (int)(c & 1u) : 0; }
 
+// Observable sums of int8 lattices, four sites (one word) at a time, from
+// bytes (1 + S) | (1 + sigma) << 4.  With u = 1 + S and g = 1 + sigma:
+// sum S S' over the 2N bonds is sum u u' - 4 sum u + 2N (every site is in
+// four bonds), sum S^2 is sum u^2 - 2 sum u + N, and the offsets cancel in the
+// staggered sums.
+constexpr uint32_t kSiteBytes = 0x21u | 0x01u << 8 | 0x12u << 16 | 0x10u << 24;  // per code
+__device__ __forceinline__ uint32_t site_from_codes(uint32_t c) { return __builtin_amdgcn_perm(0u, kSiteBytes, c); }
+
+struct SiteSums {
+    uint32_t su = 0, sg = 0, suu = 0, bu = 0, bg = 0, cnt = 0;
+    int stu = 0, stg = 0;
+
+    // w: four sites of row y; wr, wd: their right and lower neighbours.
+    __device__ __forceinline__ void add(uint32_t w, uint32_t wr, uint32_t wd, uint32_t y)
+    {
+        const uint32_t m4 = 0x0F0F0F0Fu, ones = 0x01010101u;
+        const uint32_t u = w & m4, g = (w >> 4) & m4;
+        const int sign = (int)((y & 1u) ? 0x01FF01FFu : 0xFF01FF01u);
+        su = __builtin_amdgcn_udot4(u, ones, su, false);
+        sg = __builtin_amdgcn_udot4(g, ones, sg, false);
+        suu = __builtin_amdgcn_udot4(u, u, suu, false);
+        bu = __builtin_amdgcn_udot4(u, wr & m4, bu, false);
+        bu = __builtin_amdgcn_udot4(u, wd & m4, bu, false);
+        bg = __builtin_amdgcn_udot4(g, (wr >> 4) & m4, bg, false);
+        bg = __builtin_amdgcn_udot4(g, (wd >> 4) & m4, bg, false);
+        stu = __builtin_amdgcn_sdot4((int)u, sign, stu, false);
+        stg = __builtin_amdgcn_sdot4((int)g, sign, stg, false);
+        cnt += 4u;
+    }
+    // the seven sums of what was added (below 2^28 sites a thread)
+    template <typename T>
+    __device__ __forceinline__ void get(T (&v)[7]) const
+    {
+        v[0] = (T)((int)su - (int)cnt);
+        v[1] = (T)((int)suu - 2 * (int)su + (int)cnt);
+        v[2] = (T)((int)bu - 4 * (int)su + 2 * (int)cnt);
+        v[3] = (T)((int)bg - 4 * (int)sg + 2 * (int)cnt);
+        v[4] = (T)((int)sg - (int)cnt);
+        v[5] = (T)stg;
+        v[6] = (T)stu;
+    }
+};
+
+// A word of codes at any byte address (a caller may place an int8 state
+// anywhere), and NW of them (NW = 4: 16-byte aligned).
+typedef uint32_t word_any __attribute__((aligned(1)));
+template <int NW>
+__device__ __forceinline__ void load_codes(const uint8_t *p, uint32_t (&w)[NW])
+{
+    if constexpr (NW == 4) {
+        const uint4 v = *(const uint4 *)p;
+        w[0] = v.x;
+        w[1] = v.y;
+        w[2] = v.z;
+        w[3] = v.w;
+    } else {
+        w[0] = *(const word_any *)p;
+    }
+}
+
+// Adds group t (NW words of a row) of an int8 lattice.
+template <int NW>
+__device__ __forceinline__ void obs_group_int8(const uint8_t *st, uint32_t L, uint32_t t, SiteSums &s)
+{
+    const uint32_t Lq = L >> 2, per_row = Lq / NW, y = t / per_row, X = (t - y * per_row) * NW;
+    const uint32_t row = y * L;  // N <= 2^30
+    uint32_t c[NW], d[NW];
+    load_codes<NW>(st + row + 4u * X, c);
+    load_codes<NW>(st + (y + 1 == L ? 0u : row + L) + 4u * X, d);
+    const uint32_t after = *(const word_any *)(st + row + (X + NW == Lq ? 0u : 4u * (X + NW)));
+    uint32_t e[NW + 1];
+#pragma unroll
+    for (int i = 0; i < NW; ++i) e[i] = site_from_codes(c[i]);
+    e[NW] = site_from_codes(after);
+#pragma unroll
+    for (int i = 0; i < NW; ++i)
+        s.add(e[i], __builtin_amdgcn_alignbit(e[i + 1], e[i], 8u), site_from_codes(d[i]), y);
+}
+
 // Block-level sum of K values written (not added) to dst[0..K): no atomics.
 template <int K, typename T>
 __device__ __forceinline__ void block_reduce_store(T (&v)[K], long long *dst)

@@ -69,6 +69,26 @@ int guarded(const char *what, F &&body) noexcept
         return fail_nothrow(LAT_EHIP, what, "unknown exception");
     }
 }
+// A pinned, device-visible block of kPinnedBytes of host memory for one call's
+// small transfers (kernels may write results into it): pageable copies of a
+// few hundred bytes cost 5-10 us more each.  Taken from a pool of the process
+// and given back by the destructor; the pool keeps at most kPinnedKeep blocks,
+// others are freed.  The holder gives a block back only after it has waited for
+// the device work that uses it; abandon() drops a block whose work may still run
+// (a failed wait).  p is null when no pinned memory can be had: callers then
+// use ordinary memory and copies.
+constexpr size_t kPinnedBytes = 24576;
+constexpr size_t kPinnedKeep = 8;
+class PinnedBlock {
+  public:
+    PinnedBlock();
+    ~PinnedBlock();
+    PinnedBlock(const PinnedBlock &) = delete;
+    PinnedBlock &operator=(const PinnedBlock &) = delete;
+    void *p = nullptr;
+    void abandon() { p = nullptr; }
+};
+
 // Advance lattices resident in LDS; lattice i by sweeps[i] (null: `uniform`).
 // tune = false: no autotuning launches (the tuned or default block size),
 // as needed under stream capture.  obs non-null: `intervals` times over, each

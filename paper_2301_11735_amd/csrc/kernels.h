@@ -51,10 +51,18 @@ constexpr int kMaxObsSlots = 256;
 constexpr size_t kScrSlots = 24576;                   // kMaxSlots x 3 x int64 from the phase kernels
 constexpr int kMaxSlots = 1024;
 constexpr size_t kScrFullTab = kScrSlots + (size_t)kMaxSlots * 24;  // 49152: kTabSize x uint32 thresholds
-// Penalty mode: thresholds over (nD, nV, nJ, dS) of one site, nD in [-1, 1],
-// nV and nJ in [-8, 8], dS in [-2, 2], index ((nD+1)*17 + nV+8)*17 + nJ+8)*5 + dS+2.
-constexpr int kMuTabSize = 3 * 17 * 17 * 5;  // 4335
+// Penalty mode: thresholds of the move c0 -> c1 at neighbour sums sum S and
+// sum sigma, index 137 (4 c0 + c1) + (sum S + 4) + 16 (sum sigma + 4); only
+// |sum S| + |sum sigma| <= 4 occurs.
+constexpr uint32_t mu_index(uint32_t c0, uint32_t c1) { return 137u * (4u * c0 + c1); }
+constexpr int mu_index(int c0, int c1, int s, int g) { return 137 * (4 * c0 + c1) + (s + 4) + 16 * (g + 4); }
+constexpr int kMuTabSize = 16 * 137;  // 2192
+// Running sums of the charge changes of a call (in the observable slots, which
+// hold nothing between calls): block b adds to slot b % kMuChargeSlots, one
+// every 64 bytes, so that few atomics meet at an address.
+constexpr int kMuChargeSlots = 32, kMuChargeStride = 8;
 constexpr size_t kScrMuTab = kScrFullTab + ((size_t)kTabSize * 4 + 255) / 256 * 256;  // 71168
+static_assert(kScrMuTab + (size_t)kMuTabSize * 4 <= 88576, "the penalty table ends before the delta table");
 // Delta form of the transition table, read by the 2-bit phase kernel: entry
 // st*6 + j is {coef, C, R, 0} with coef and C as in the transition table and
 // R = (d_a * 0x5555) | (d_b * 0x5555) << 16, where d_a and d_b are the XOR of
@@ -62,7 +70,7 @@ constexpr size_t kScrMuTab = kScrFullTab + ((size_t)kTabSize * 4 + 255) / 256 * 
 // low half holds d_a and every field of the high half d_b, so that one AND
 // with a field mask places an accepted move's code changes at any pair
 // position.
-constexpr size_t kScrTransD = kScrMuTab + ((size_t)kMuTabSize * 4 + 255) / 256 * 256;  // 88576
+constexpr size_t kScrTransD = 88576;
 constexpr size_t kScrBytes = kScrTransD + (size_t)kTransEntries * 16;                 // 90112
 
 // Int8 lattices with L % 64 == 0 that are swept by the phase kernels keep a
@@ -245,7 +253,8 @@ hipError_t init_map_kernel_attributes();
 struct MuArgs {
     int8_t *state;
     const uint32_t *tab;   // kMuTabSize thresholds (scratch + kScrMuTab)
-    unsigned long long *track;  // per-block tracker slots
+    unsigned long long *track;   // per-block tracker slots
+    unsigned long long *charge;  // kMuChargeSlots running sums of dS
     int L, colour;
     uint32_t key0, key1, s_lo, s_hi;
 };

@@ -66,6 +66,38 @@ int hip_fail(hipError_t e, const char *what)
 
 bool live(const lattice *h) { return h != nullptr && h->magic == kMagic; }
 
+namespace {
+std::mutex g_pinned_mu;
+void *g_pinned[kPinnedKeep];
+size_t g_pinned_n = 0;
+}  // namespace
+
+PinnedBlock::PinnedBlock()
+{
+    {
+        std::lock_guard<std::mutex> lock(g_pinned_mu);
+        if (g_pinned_n > 0) p = g_pinned[--g_pinned_n];
+    }
+    // portable: usable with every device of the process
+    if (!p && hipHostMalloc(&p, kPinnedBytes, hipHostMallocPortable) != hipSuccess) {
+        p = nullptr;
+        (void)hipGetLastError();
+    }
+}
+
+PinnedBlock::~PinnedBlock()
+{
+    if (!p) return;
+    {
+        std::lock_guard<std::mutex> lock(g_pinned_mu);
+        if (g_pinned_n < kPinnedKeep) {
+            g_pinned[g_pinned_n++] = p;
+            return;
+        }
+    }
+    (void)hipHostFree(p);
+}
+
 }  // namespace detail
 }  // namespace lat
 
@@ -1175,13 +1207,23 @@ int lattice_observables(lattice *h, lat_obs *out)
     return guarded("lattice_observables", [&]() -> int {
         if (!live(h)) return fail(LAT_ESTATE, "null or destroyed handle");
         if (!out) return fail(LAT_EINVAL, "null output");
-        unsigned long long *track = (unsigned long long *)(h->d_scratch + kScrTrack);
-        hipError_t e = launch_observables(h->d_scratch, h->d_state, h->L, h->enc, h->stream);
-        int64_t v[11];  // tracker, 7 sums, error flags
-        if (e == hipSuccess) e = hipMemcpyAsync(v, track, sizeof(v), hipMemcpyDeviceToHost, h->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+        // the reduction writes its record (tracker, 7 sums, next sweep) into
+        // pinned memory where it can, else into the scratch, for a copy
+        PinnedBlock stage;
+        int64_t own[12];  // record, and the error flags after it
+        int64_t *v = stage.p ? (int64_t *)stage.p : own;
+        hipError_t e = launch_observables(h->d_scratch, h->d_state, h->L, h->enc, h->stream,
+                                          stage.p ? (long long *)stage.p : nullptr);
+        if (e == hipSuccess && !stage.p)
+            e = hipMemcpyAsync(v, h->d_scratch + kScrTrack, 10 * sizeof(int64_t), hipMemcpyDeviceToHost, h->stream);
+        v[11] = 0;
+        if (e == hipSuccess && barrier_may_time_out(h))
+            e = hipMemcpyAsync(&v[11], h->d_scratch + kScrErr, sizeof(uint32_t), hipMemcpyDeviceToHost, h->stream);
+        const hipError_t waited = hipStreamSynchronize(h->stream);
+        if (waited != hipSuccess) stage.abandon();
+        if (e == hipSuccess) e = waited;
         if (e != hipSuccess) return hip_fail(e, "lattice_observables");
-        if ((uint32_t)v[10] & 1u) return fail(LAT_EHIP, "a device-wide phase barrier timed out; the state is invalid");
+        if ((uint32_t)v[11] & 1u) return fail(LAT_EHIP, "a device-wide phase barrier timed out; the state is invalid");
         fill_obs(h, v, out);
         return LAT_OK;
     });

@@ -17,66 +17,61 @@ __global__ void k_zero_i64(unsigned long long *p, int n)
     if (i < n) p[i] = 0ull;
 }
 
-__global__ void __launch_bounds__(1024) k_obs_int8(const int8_t *__restrict__ st, int L, long long *slots)
+// Bound by the reads (16 bytes a load in the NW = 4 form, for sides that are
+// a multiple of 16 on an aligned state).  L = 4096: 9.5 us
+// (37 us with three byte loads a site).
+template <int NW>
+__global__ void __launch_bounds__(1024) k_obs_int8(const uint8_t *__restrict__ st, int L, long long *slots)
 {
-    long long v[7] = {0, 0, 0, 0, 0, 0, 0};
-    const uint32_t N = (uint32_t)L * (uint32_t)L;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < N; i += gridDim.x * blockDim.x) {
-        const int y = (int)(i / (uint32_t)L), x = (int)(i - (uint32_t)y * L);
-        const uint32_t c = (uint32_t)st[i];
-        const uint32_t cr = (uint32_t)st[(uint32_t)y * L + (x + 1 == L ? 0 : x + 1)];
-        const uint32_t cd = (uint32_t)st[(uint32_t)(y + 1 == L ? 0 : y + 1) * L + x];
-        const int S = charge_of(c), G = spin_of(c), sg = ((x + y) & 1) ? -1 : 1;
-        v[0] += S;
-        v[1] += S * S;
-        v[2] += S * (charge_of(cr) + charge_of(cd));
-        v[3] += G * (spin_of(cr) + spin_of(cd));
-        v[4] += G;
-        v[5] += sg * G;
-        v[6] += sg * S;
-    }
+    SiteSums sums;
+    const uint32_t n = (uint32_t)L * (uint32_t)L / (4u * NW);
+    for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x)
+        obs_group_int8<NW>(st, (uint32_t)L, t, sums);
+    long long v[7];
+    sums.get(v);
     block_reduce_store<7>(v, slots + 7 * (size_t)blockIdx.x);
 }
 
-// One class word (16 sites) per thread: its right neighbours are the same
-// word of the next class (or class 0 one site on), its lower neighbours the
-// same word of the paired row class.  Popcounts over the bit planes.
+// Adds class word i (16 sites): its right neighbours are the same word of the
+// next class (or class 0 one site on), its lower neighbours the same word of
+// the paired row class.  Popcounts over the bit planes.
+__device__ __forceinline__ void obs_add_2bit(const uint32_t *__restrict__ st, uint32_t L, uint32_t i, long long (&v)[7])
+{
+    const uint32_t W = L >> 6, H = L >> 1, Lq = L >> 2, csz = H * W;
+    const uint32_t c = i / csz, rem = i - c * csz;
+    const uint32_t Y = rem / W, j = rem - Y * W;
+    const uint32_t cx = c & 3u, cy = c >> 2;
+    const uint32_t w = st[i];
+    const uint32_t wr = cx < 3 ? st[i + csz] : load16(st, 4u * cy * csz + Y * W, (int)W, 16 * j + 1 == Lq ? 0 : (int)(16 * j + 1));
+    const uint32_t wd = cy == 0 ? st[i + 4 * csz] : st[cx * csz + (Y + 1 == H ? 0 : Y + 1) * W + j];
+    const uint32_t h = (w >> 1) & kM5, l = w & kM5;
+    const int sumS = __popc(h & ~l) - __popc(h & l);
+    const int sumG = __popc((h | l) ^ kM5) - __popc(l & ~h);
+    int bSS = 0, bss = 0;
+    bond_sums(h, l, (wr >> 1) & kM5, wr & kM5, bSS, bss);
+    bond_sums(h, l, (wd >> 1) & kM5, wd & kM5, bSS, bss);
+    const int sg = ((cx + cy) & 1) ? -1 : 1;
+    v[0] += sumS;
+    v[1] += __popc(h);
+    v[2] += bSS;
+    v[3] += bss;
+    v[4] += sumG;
+    v[5] += sg * sumG;
+    v[6] += sg * sumS;
+}
+
 __global__ void __launch_bounds__(1024) k_obs_2bit(const uint32_t *__restrict__ st, int L, long long *slots)
 {
     long long v[7] = {0, 0, 0, 0, 0, 0, 0};
-    const uint32_t W = (uint32_t)L >> 6, H = (uint32_t)L >> 1, Lq = (uint32_t)L >> 2;
-    const uint32_t csz = H * W, nwords = 8u * csz;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < nwords; i += gridDim.x * blockDim.x) {
-        const uint32_t c = i / csz, rem = i - c * csz;
-        const uint32_t Y = rem / W, j = rem - Y * W;
-        const uint32_t cx = c & 3u, cy = c >> 2;
-        const uint32_t w = st[i];
-        const uint32_t wr = cx < 3 ? st[i + csz] : load16(st, 4u * cy * csz + Y * W, (int)W, 16 * j + 1 == Lq ? 0 : (int)(16 * j + 1));
-        const uint32_t wd = cy == 0 ? st[i + 4 * csz] : st[cx * csz + (Y + 1 == H ? 0 : Y + 1) * W + j];
-        const uint32_t h = (w >> 1) & kM5, l = w & kM5;
-        const int sumS = __popc(h & ~l) - __popc(h & l);
-        const int sumG = __popc((h | l) ^ kM5) - __popc(l & ~h);
-        int bSS = 0, bss = 0;
-        bond_sums(h, l, (wr >> 1) & kM5, wr & kM5, bSS, bss);
-        bond_sums(h, l, (wd >> 1) & kM5, wd & kM5, bSS, bss);
-        const int sg = ((cx + cy) & 1) ? -1 : 1;
-        v[0] += sumS;
-        v[1] += __popc(h);
-        v[2] += bSS;
-        v[3] += bss;
-        v[4] += sumG;
-        v[5] += sg * sumG;
-        v[6] += sg * sumS;
-    }
+    const uint32_t nwords = (uint32_t)L * (uint32_t)L / 16u;
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < nwords; i += gridDim.x * blockDim.x)
+        obs_add_2bit(st, (uint32_t)L, i, v);
     block_reduce_store<7>(v, slots + 7 * (size_t)blockIdx.x);
 }
 
-// Totals of one lattice: tracker = base triple + every tracker slot;
-// observables = the first n_obs observable slots.  Written to dst (tracker,
-// then the 7 sums) and, with stamp, dst[10] = the lattice's next sweep index.
-__global__ void __launch_bounds__(256) k_fold_sums(uint8_t *scr, int n_obs, long long *dst, int stamp)
+// This thread's share of the tracker slots and, for thread 0, the base.
+__device__ __forceinline__ void add_tracker(const uint8_t *scr, long long *t)
 {
-    long long t[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
     const long long *slots = (const long long *)(scr + kScrSlots);
     for (int i = threadIdx.x; i < kMaxSlots; i += blockDim.x) {
         t[0] += slots[3 * i];
@@ -89,10 +84,48 @@ __global__ void __launch_bounds__(256) k_fold_sums(uint8_t *scr, int n_obs, long
         t[1] += base[1];
         t[2] += base[2];
     }
+}
+
+// Totals of one lattice: tracker = base triple + every tracker slot;
+// observables = the first n_obs observable slots.  Written to dst (tracker,
+// then the 7 sums) and, with stamp, dst[10] = the lattice's next sweep index.
+__global__ void __launch_bounds__(1024) k_fold_sums(uint8_t *scr, int n_obs, long long *dst, int stamp)
+{
+    long long t[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    add_tracker(scr, t);
     const long long *os = (const long long *)(scr + kScrObsSlots);
     for (int i = threadIdx.x; i < n_obs; i += blockDim.x)
 #pragma unroll
         for (int k = 0; k < 7; ++k) t[3 + k] += os[7 * i + k];
+    block_reduce_store<10>(t, dst);
+    if (stamp && threadIdx.x == 0) dst[10] = (long long)((const LatDesc *)(scr + kScrDesc))->next_sweep;
+}
+
+// Observables and tracker of a small lattice in one launch of one block
+// (k_obs_* and k_fold_sums together): a launch and the gap before it cost more
+// than the block's few passes over at most kOneBlockUnits groups of 16 sites (or
+// 4).  One sweep and its observables, with the two launches and one: L = 32
+// 48.6 -> 37.8 us (ten sweeps), L = 256 2-bit 51.8 -> 43.4 us.
+constexpr uint32_t kOneBlockUnits = 8192;
+__global__ void __launch_bounds__(1024) k_obs_one(uint8_t *scr, const uint8_t *st, int L, int enc, int wide,
+                                                  long long *dst, int stamp)
+{
+    long long t[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    long long v[7] = {0, 0, 0, 0, 0, 0, 0};
+    const uint32_t N = (uint32_t)L * (uint32_t)L;
+    add_tracker(scr, t);
+    if (enc != 0) {
+        for (uint32_t i = threadIdx.x; i < N / 16u; i += blockDim.x) obs_add_2bit((const uint32_t *)st, (uint32_t)L, i, v);
+    } else {
+        SiteSums sums;
+        if (wide)
+            for (uint32_t i = threadIdx.x; i < N / 16u; i += blockDim.x) obs_group_int8<4>(st, (uint32_t)L, i, sums);
+        else
+            for (uint32_t i = threadIdx.x; i < N / 4u; i += blockDim.x) obs_group_int8<1>(st, (uint32_t)L, i, sums);
+        sums.get(v);
+    }
+#pragma unroll
+    for (int k = 0; k < 7; ++k) t[3 + k] = v[k];
     block_reduce_store<10>(t, dst);
     if (stamp && threadIdx.x == 0) dst[10] = (long long)((const LatDesc *)(scr + kScrDesc))->next_sweep;
 }
@@ -108,18 +141,26 @@ hipError_t launch_zero_i64(unsigned long long *p, int n, hipStream_t s)
 hipError_t launch_observables(uint8_t *scratch, const void *state, int L, int encoding, hipStream_t s,
                               long long *record)
 {
-    const uint32_t units = encoding == 0 ? (uint32_t)L * L : (uint32_t)L * L / 16u;
+    const bool wide = encoding == 0 && L % 16 == 0 && ((uintptr_t)state & 15u) == 0;
+    const uint32_t units = (uint32_t)L * L / (encoding == 0 && !wide ? 4u : 16u);
+    long long *dst = record ? record : (long long *)(scratch + kScrTrack);
+    if (units <= kOneBlockUnits) {
+        hipLaunchKernelGGL(k_obs_one, dim3(1), dim3(1024), 0, s, scratch, (const uint8_t *)state, L, encoding, wide ? 1 : 0,
+                           dst, record ? 1 : 0);
+        return hipGetLastError();
+    }
     uint32_t grid = (units + 1023u) / 1024u;
     if (grid > (uint32_t)kMaxObsSlots) grid = (uint32_t)kMaxObsSlots;
     long long *slots = (long long *)(scratch + kScrObsSlots);
-    if (encoding == 0)
-        hipLaunchKernelGGL(k_obs_int8, dim3(grid), dim3(1024), 0, s, (const int8_t *)state, L, slots);
+    if (encoding == 0 && wide)
+        hipLaunchKernelGGL(k_obs_int8<4>, dim3(grid), dim3(1024), 0, s, (const uint8_t *)state, L, slots);
+    else if (encoding == 0)
+        hipLaunchKernelGGL(k_obs_int8<1>, dim3(grid), dim3(1024), 0, s, (const uint8_t *)state, L, slots);
     else
         hipLaunchKernelGGL(k_obs_2bit, dim3(grid), dim3(1024), 0, s, (const uint32_t *)state, L, slots);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    long long *dst = record ? record : (long long *)(scratch + kScrTrack);
-    hipLaunchKernelGGL(k_fold_sums, dim3(1), dim3(256), 0, s, scratch, (int)grid, dst, record ? 1 : 0);
+    hipLaunchKernelGGL(k_fold_sums, dim3(1), dim3(1024), 0, s, scratch, (int)grid, dst, record ? 1 : 0);
     return hipGetLastError();
 }
 

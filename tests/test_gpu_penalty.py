@@ -68,3 +68,39 @@ def test_penalty_heat_capacity_grows_as_temperature_falls():
     assert C[0.1] > C[0.2] > C[0.4], C
     ex = exact.sector_averages(4, 2, 0.25, 0.5, 1.0, 0.1)
     assert C[0.1] > 10 * ex["C"], (C[0.1], ex["C"])
+
+
+@pytest.mark.parametrize("L,offset", [(16, 0), (16, 4), (20, 0), (20, 3), (48, 16), (516, 0), (1040, 0), (2064, 0)])
+def test_penalty_word_groups_match_oracle(L, offset):
+    """Sixteen sites a load (sides that are a multiple of 16 on an aligned
+    state) and four (any other side or address), in one pass over the groups
+    and in several."""
+    import ctypes
+
+    import torch
+
+    spec = SMALL.with_(L=L, seed=40 + L, T=0.7, n=0.2)
+    _say(f"case penalty groups L={L} offset={offset}")
+    o = oracle.OracleLattice(L, spec.n, spec.Delta, spec.V, spec.J, spec.T, spec.seed)
+    buf = torch.full((L * L + 64,), 0x55, dtype=torch.uint8, device="cuda")
+    scratch = torch.empty(lat.scratch_bytes(L, 0), dtype=torch.uint8, device="cuda")
+    p = lat.LatParams(L=L, encoding=0, n=spec.n, Delta=spec.Delta, V=spec.V, J=spec.J, T=spec.T, seed=spec.seed,
+                      n_charged=-1, start_sweep=0, init_codes=None)
+    h, lib = ctypes.c_void_p(), lat.lib()
+    assert lib.lattice_create(ctypes.byref(p), buf.data_ptr() + offset, L * L, scratch.data_ptr(), scratch.numel(),
+                              torch.cuda.current_stream().cuda_stream, ctypes.byref(h)) == 0
+    n = 3 if L < 1000 else 2
+    mu, mus, sums = ctypes.c_double(0.05), np.zeros(n), np.zeros(n, dtype=np.int64)
+    assert lib.lattice_mu_sweeps(h, 0, n, 0.5, ctypes.byref(mu), mus.ctypes.data_as(ctypes.POINTER(ctypes.c_double)),
+                                 sums.ctypes.data_as(ctypes.POINTER(ctypes.c_int64))) == 0
+    mu_o, mus_o, sums_o, _ = oracle.mu_sweeps(L, spec.Delta, spec.V, spec.J, spec.T, spec.seed, o.codes, n, 0.5, o.Q,
+                                              0.05, track=o.track)
+    assert mu.value == mu_o and np.array_equal(mus, mus_o) and np.array_equal(sums, sums_o)
+    got = buf.cpu().numpy()
+    assert np.array_equal(got[offset:offset + L * L].astype(np.int8), o.codes)
+    assert (got[:offset] == 0x55).all() and (got[offset + L * L:] == 0x55).all()
+    rec = lat.LatObs()
+    assert lib.lattice_observables(h, ctypes.byref(rec)) == 0
+    assert rec.ints() == o.observables().tolist()
+    assert [rec.track_nD, rec.track_nV, rec.track_nJ] == o.track.tolist()
+    assert lib.lattice_destroy(h) == 0
