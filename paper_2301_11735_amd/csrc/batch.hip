@@ -552,7 +552,7 @@ __global__ void __launch_bounds__(1024) k_sweep_lds(BatchArgs args)
 
 template <int Q, bool Barrier>
 __device__ __forceinline__ void word_sweeps(uint32_t *lat, uint32_t *sched, const LatDesc &d, uint32_t my_sweeps,
-                                            const uint2 *s_tab, const uint4 *s_transd, int (&tr)[3])
+                                            const uint2 *s_tab, const uint8_t *s_slots, int (&tr)[3])
 {
     WordPhase f;
     f.W = d.L >> 6;
@@ -573,8 +573,8 @@ __device__ __forceinline__ void word_sweeps(uint32_t *lat, uint32_t *sched, cons
         const int q = (int)(threadIdx.x & (uint32_t)(Q - 1));
 #pragma unroll
         for (int i = 0; i < kTaskCalls<Q>; ++i)
-            pre[i] = philox4x32_10((uint32_t)d.next_sweep, 0u, c0 + (uint32_t)call_of_task<Q>(q, i),
-                                   (uint32_t)(d.next_sweep >> 32), d.key0, d.key1);
+            pre[i] = pair_draws(philox4x32_10((uint32_t)d.next_sweep, 0u, c0 + (uint32_t)call_of_task<Q>(q, i),
+                                              (uint32_t)(d.next_sweep >> 32), d.key0, d.key1));
     }
     for (uint32_t i = 0; i < my_sweeps; ++i) {
         const uint64_t s = d.next_sweep + i;
@@ -610,11 +610,11 @@ __device__ __forceinline__ void word_sweeps(uint32_t *lat, uint32_t *sched, cons
             }
             if (pipe) {
                 if (threadIdx.x < tasks)
-                    word_task<Q, Barrier, kDrawPipe>(lat, f, threadIdx.x, s_tab, s_transd, tr, pre,
+                    word_task<Q, Barrier, kDrawPipe>(lat, f, threadIdx.x, s_tab, s_slots, tr, pre,
                                                      p < 3 ? s : s + 1, p < 3 ? p + 1 : 0);
             } else {
                 for (uint32_t t = threadIdx.x; t < tasks; t += blockDim.x)
-                    word_task<Q, Barrier>(lat, f, t, s_tab, s_transd, tr);
+                    word_task<Q, Barrier>(lat, f, t, s_tab, s_slots, tr);
             }
             __syncthreads();
         }
@@ -636,7 +636,7 @@ __global__ void __launch_bounds__(MaxThreads) k_sweep_lds_w(BatchArgs args)
 {
     constexpr bool kBarrier = MaxThreads > 512;
     __shared__ uint2 s_tab[kDevTabEntries];
-    __shared__ uint4 s_transd[kTransEntries];
+    __shared__ __align__(16) uint2 slots[kSlotEntries];
     __shared__ uint32_t sched[24];
     extern __shared__ uint32_t lat[];
     uint8_t *scr = args.scratch[blockIdx.x];
@@ -659,11 +659,12 @@ __global__ void __launch_bounds__(MaxThreads) k_sweep_lds_w(BatchArgs args)
     stage_lattice(lat, d, g);
     {
         const uint2 *g_tab = (const uint2 *)(scr + kScrDevTab);
-        const uint4 *g_transd = (const uint4 *)(scr + kScrTransD);
+        const uint2 *g_slots = (const uint2 *)kWordSlots.v;
         for (int i = threadIdx.x; i < kDevTabEntries; i += blockDim.x) s_tab[i] = g_tab[i];
-        for (int i = threadIdx.x; i < kTransEntries; i += blockDim.x) s_transd[i] = g_transd[i];
+        for (int i = threadIdx.x; i < kSlotEntries; i += blockDim.x) slots[i] = g_slots[i];
         __syncthreads();
     }
+    const uint8_t *s_slots = (const uint8_t *)slots;
 
     // threads per a-word: the largest Q <= 8 with Q * (a-words) <= block size
     const uint32_t words = g.csz;
@@ -671,10 +672,10 @@ __global__ void __launch_bounds__(MaxThreads) k_sweep_lds_w(BatchArgs args)
     while (Q < 8 && words * (uint32_t)(2 * Q) <= blockDim.x) Q *= 2;
     int tr[3] = {0, 0, 0};
     switch (Q) {
-    case 1: word_sweeps<1, kBarrier>(lat, sched, d, my_sweeps, s_tab, s_transd, tr); break;
-    case 2: word_sweeps<2, kBarrier>(lat, sched, d, my_sweeps, s_tab, s_transd, tr); break;
-    case 4: word_sweeps<4, kBarrier>(lat, sched, d, my_sweeps, s_tab, s_transd, tr); break;
-    default: word_sweeps<8, kBarrier>(lat, sched, d, my_sweeps, s_tab, s_transd, tr); break;
+    case 1: word_sweeps<1, kBarrier>(lat, sched, d, my_sweeps, s_tab, s_slots, tr); break;
+    case 2: word_sweeps<2, kBarrier>(lat, sched, d, my_sweeps, s_tab, s_slots, tr); break;
+    case 4: word_sweeps<4, kBarrier>(lat, sched, d, my_sweeps, s_tab, s_slots, tr); break;
+    default: word_sweeps<8, kBarrier>(lat, sched, d, my_sweeps, s_tab, s_slots, tr); break;
     }
     if constexpr (MaxThreads <= 512) {
         if (args.obs_out) {

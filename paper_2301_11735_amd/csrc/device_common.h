@@ -36,18 +36,6 @@ constexpr uint32_t make_kq2()
 }
 constexpr uint32_t kKq2 = make_kq2();
 
-// k_q/2 of the 16 pairs of an aligned (a-word, b-word) couple, 2 bits per
-// pair at the pairs' own bit positions: a pair is frozen when both sites are
-// charges of one sign, has k_q = 4 when exactly one site is charged, and
-// k_q = 6 otherwise.
-__device__ __forceinline__ uint32_t word_kq2(uint32_t A, uint32_t B)
-{
-    const uint32_t ha = (A >> 1) & kM5, la = A & kM5, hb = (B >> 1) & kM5, lb = B & kM5;
-    const uint32_t frozen = ha & hb & ~(la ^ lb);
-    const uint32_t one = ha ^ hb;
-    return (~(one | frozen) & kM5) | ((~frozen & kM5) << 1);
-}
-
 // Pair states of 8 pairs: nibble u of the result is code_a | code_b << 2 of
 // pair 8*half + u, for the aligned (a-word, b-word) couple (A, B).  One byte
 // permute gathers (A byte, B byte) pairs, then two swap stages interleave
@@ -86,23 +74,6 @@ __device__ __forceinline__ uint32_t pair_step_k2(uint32_t st, uint32_t kq2, uint
     const bool acc = min(ua, 0xFFFFFFFEu) < e.x;
     packed += acc ? e.y : 0u;
     return acc ? (tr.y >> 16) : st;
-}
-
-// The same step with the delta form of the transition table: an accepted
-// move ORs its code changes into dacc at the fields that `fields` selects
-// (the pair's 2-bit field in the low half for site a and in the high half for
-// site b); the caller XORs the accumulated changes into the codes.
-__device__ __forceinline__ void pair_step_delta(uint32_t st, uint32_t kq2, uint32_t bpack, uint32_t uc, uint32_t ua,
-                                                const uint4 *__restrict__ s_transd, const uint2 *__restrict__ s_tab,
-                                                uint32_t fields, uint32_t &packed, uint32_t &dacc)
-{
-    const uint32_t j = ((uc >> 8) * kq2) >> 23;
-    const uint4 tr = s_transd[st * 6u + j];
-    const int idx = __builtin_amdgcn_sdot4((int)tr.x, (int)bpack, (int)tr.y, false);
-    const uint2 e = s_tab[idx];
-    const bool acc = min(ua, 0xFFFFFFFEu) < e.x;
-    packed += acc ? e.y : 0u;
-    dacc |= tr.z & (acc ? fields : 0u);
 }
 
 __device__ __forceinline__ uint32_t pair_step(uint32_t st, uint32_t bpack, uint32_t uc, uint32_t ua,
@@ -149,6 +120,54 @@ constexpr void trans_slot(int st, int slot, uint32_t &coef, uint32_t &C, int &a1
 }
 // Byte offset 8 floor(12 (uc >> 8) / 2^24) of the draw's slot.
 __device__ __forceinline__ uint32_t slot8_of(uint32_t uc) { return __umulhi(uc & ~255u, 96u) & 0x78u; }
+
+// Word form: x = code_a | code_b << 2, and in the place of the codes the code
+// changes d_a * 0x55 | d_b * 0x5500 (d: the XOR of new and old code): each
+// 2-bit field of the high half's low byte holds site a's change and of its high
+// byte site b's, so that one AND with a field mask places them at any of four
+// pair positions.  8 bytes an entry, one ds_read_b64 a pair: the 16-byte
+// entries that hold eight positions took twice the LDS cycles.
+constexpr TransSlots make_word_slots()
+{
+    TransSlots t{};
+    for (int st = 0; st < 16; ++st)
+        for (int slot = 0; slot < 12; ++slot) {
+            uint32_t coef = 0, C = 0;
+            int a1 = 0, b1 = 0;
+            trans_slot(st, slot, coef, C, a1, b1);
+            const uint32_t at = 2u * (16u * (uint32_t)st + (uint32_t)slot);
+            t.v[at] = coef;
+            t.v[at + 1] = C | ((uint32_t)(a1 ^ (st & 3)) * 0x55u | (uint32_t)(b1 ^ (st >> 2)) * 0x5500u) << 16;
+        }
+    return t;
+}
+__device__ const TransSlots kWordSlots = make_word_slots();
+constexpr int kSlotEntries = 256;
+
+// A Philox call as the two pairs' {slot offset, acceptance draw}: the draw is
+// compared as min(u, 2^32 - 2) < threshold, so that the reserved "always"
+// threshold 2^32 - 1 accepts every draw.
+__device__ __forceinline__ u32x4 pair_draws(const u32x4 &w)
+{
+    return u32x4{slot8_of(w.x), min(w.y, 0xFFFFFFFEu), slot8_of(w.z), min(w.w, 0xFFFFFFFEu)};
+}
+
+// One coupled-pair Metropolis step (section 3.1) from the byte offset of its
+// transition entry, the packed neighbour sums (sumS_a+4, sumS_b+4, sumsig_a+4,
+// sumsig_b+4) and the acceptance draw.  An accepted move adds its packed triple to `packed`
+// and ORs its code changes into dacc at `fields` (0x03030000 << 2 (t mod 4) for
+// pair t of its word: bytes 2 and 3 collect the changes of the a-sites and the
+// b-sites of four pairs).
+__device__ __forceinline__ void pair_step_slot(uint32_t entry, uint32_t bpack, uint32_t ua, const uint8_t *s_slots,
+                                               const uint2 *s_tab, uint32_t fields, uint32_t &packed, uint32_t &dacc)
+{
+    const uint2 tr = *(const uint2 *)(s_slots + entry);
+    const uint32_t idx = (uint32_t)__builtin_amdgcn_sdot4((int)tr.x, (int)bpack, (int)tr.y, false);
+    const uint2 e = *(const uint2 *)((const uint8_t *)s_tab + (uint32_t)(uint16_t)(idx << 3));
+    const bool acc = ua < e.x;
+    packed += acc ? e.y : 0u;
+    dacc |= tr.y & (acc ? fields : 0u);
+}
 
 // Per-thread tracker: counts and biased sums of the accepted triples.
 __device__ __forceinline__ void unpack_tracker(uint32_t packed, int (&tr)[3])

@@ -97,20 +97,20 @@ struct PairWords {
 };
 
 // LDS tables of the 2-bit phase kernels, in 8-byte units: the device
-// threshold table, one pad entry, the delta transition table (16-byte
-// aligned), and two spare entries that absorb the writes of threads past the
-// end during staging.  Staging moves 16 bytes (two units) at a time.
-constexpr int kLdsTransD = kDevTabEntries + 1;                // 934: 16-byte aligned
-constexpr int kLdsTabUnits = kLdsTransD + 2 * kTransEntries;  // 1126
-constexpr int kLdsTabPairs = kLdsTabUnits / 2;                // 563
-static_assert((kLdsTransD * 8) % 16 == 0 && kLdsTabUnits % 2 == 0, "delta table alignment");
-static_assert(kScrTrans >= (size_t)kLdsTransD * 8, "the last device-table pair reads scratch, not past it");
+// threshold table, one pad entry, the transition slots (16-byte aligned), and
+// two spare entries that absorb the writes of threads past the end during
+// staging.  Staging moves 16 bytes (two units) at a time.
+constexpr int kLdsSlots = kDevTabEntries + 1;             // 934: 16-byte aligned
+constexpr int kLdsTabUnits = kLdsSlots + kSlotEntries;    // 1190
+constexpr int kLdsTabPairs = kLdsTabUnits / 2;            // 595
+static_assert((kLdsSlots * 8) % 16 == 0 && kLdsTabUnits % 2 == 0, "slot table alignment");
+static_assert(kScrTrans >= (size_t)kLdsSlots * 8, "the last device-table pair reads scratch, not past it");
 
 // Units 2i and 2i+1 of the LDS tables from the lattice's scratch.  The pair
 // holding the pad unit reads the scratch bytes after the device table.
 __device__ __forceinline__ uint4 table_pair(const PhaseArgs &a, int i)
 {
-    return 2 * i < kLdsTransD ? *(const uint4 *)(a.dev_tab + 2 * i) : a.trans_d[i - kLdsTransD / 2];
+    return 2 * i < kLdsSlots ? *(const uint4 *)(a.dev_tab + 2 * i) : ((const uint4 *)kWordSlots.v)[i - kLdsSlots / 2];
 }
 
 // One phase of the 2-bit lattice by this block: row groups blockIdx.x,
@@ -125,7 +125,7 @@ __device__ __forceinline__ void phase_2bit(const PhaseArgs &a, int rows_per_bloc
                                            int (&tr)[3])
 {
     const uint2 *s_tab = s_tabs;
-    const uint4 *s_transd = (const uint4 *)(s_tabs + kLdsTransD);
+    const uint8_t *s_slots = (const uint8_t *)(s_tabs + kLdsSlots);
     const int L = a.L, W = L >> 6, H = L >> 1, Lq = L >> 2;
     const int rr = W == 1 ? (int)threadIdx.x : (int)__umulhi(threadIdx.x, a.magicW), j = (int)threadIdx.x - rr * W;
     const int n_groups = H >> __builtin_ctz((unsigned)rows_per_block);  // a power of two
@@ -198,8 +198,7 @@ __device__ __forceinline__ void phase_2bit(const PhaseArgs &a, int rows_per_bloc
         // high nibbles; g = 1, 3: odd sites).  Philox call c serves t = 2c and
         // 2c+1, so calls 0,2,4,6 need planes 0 and 1, calls 1,3,5,7 planes 2
         // and 3; handling them in that order keeps 8 packed words live.
-        uint32_t dlo = 0u, dhi = 0u, packed = 0u;  // code changes of pairs 0-7 and 8-15
-        const uint32_t kq2w = word_kq2(cw.A0, B0);
+        uint32_t dacc[4] = {0u, 0u, 0u, 0u}, packed = 0u;  // code changes of pairs 4k .. 4k+3
         const uint32_t st8[2] = {pair_states8(cw.A0, B0, 0), pair_states8(cw.A0, B0, 1)};
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
@@ -212,20 +211,23 @@ __device__ __forceinline__ void phase_2bit(const PhaseArgs &a, int rows_per_bloc
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const int c = 2 * k + half;
-                const u32x4 w = call_of(gg, c);
+                const u32x4 w = pair_draws(call_of(gg, c));
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
-                    const int t = 2 * c + h;
-                    const uint32_t s0 = (st8[t >> 3] >> (4 * (t & 7))) & 15u;
-                    const uint32_t fields = 0x00030003u << (2 * (t & 7));
-                    pair_step_delta(s0, (kq2w >> (2 * t)) & 3u, h ? go[k] : ge[k], h ? w.z : w.x, h ? w.w : w.y,
-                                    s_transd, s_tab, fields, packed, t < 8 ? dlo : dhi);
+                    const int t = 2 * c + h, at = 4 * (t & 7);
+                    const uint32_t s7 = at >= 7 ? st8[t >> 3] >> (at >= 7 ? at - 7 : 0) : st8[t >> 3] << (at < 7 ? 7 - at : 0);
+                    pair_step_slot((s7 & 0x780u) | (h ? w.z : w.x), h ? go[k] : ge[k], h ? w.w : w.y, s_slots, s_tab,
+                                   0x03030000u << (2 * (t & 3)), packed, dacc[k]);
                 }
             }
         }
         unpack_tracker(packed, tr);
-        const uint32_t Anew = cw.A0 ^ __builtin_amdgcn_perm(dhi, dlo, 0x05040100u);
-        const uint32_t Bnew = B0 ^ __builtin_amdgcn_perm(dhi, dlo, 0x07060302u);
+        const uint32_t Anew = cw.A0 ^ __builtin_amdgcn_perm(__builtin_amdgcn_perm(dacc[3], dacc[2], 0x0C0C0602u),
+                                                            __builtin_amdgcn_perm(dacc[1], dacc[0], 0x0C0C0602u),
+                                                            0x05040100u);
+        const uint32_t Bnew = B0 ^ __builtin_amdgcn_perm(__builtin_amdgcn_perm(dacc[3], dacc[2], 0x0C0C0703u),
+                                                         __builtin_amdgcn_perm(dacc[1], dacc[0], 0x0C0C0703u),
+                                                         0x05040100u);
         word_put(st, oA0 + (uint32_t)Y * W + j, Anew);
         uint32_t *x = xch + bb * blockDim.x;
         x[threadIdx.x] = Bnew;

@@ -241,7 +241,7 @@ __device__ __forceinline__ uint32_t task_call0(const WordPhase &f, uint32_t task
 constexpr int kDrawInPlace = 0, kDrawPipe = 1, kDrawGiven = 2;
 template <int Q, bool Barrier, int Pipe = kDrawInPlace, bool Combine = false, bool Coh = false, bool Obs = false>
 __device__ __forceinline__ void word_task(uint32_t *lat, const WordPhase &f, uint32_t task, const uint2 *s_tab,
-                                          const uint4 *s_transd, int (&tr)[3], u32x4 *pre = nullptr,
+                                          const uint8_t *s_slots, int (&tr)[3], u32x4 *pre = nullptr,
                                           uint64_t ns = 0, int np = 0, int *dv = nullptr)
 {
     static_assert(!Obs || Combine, "the observable moves are taken where a word's changes are combined");
@@ -309,27 +309,27 @@ __device__ __forceinline__ void word_task(uint32_t *lat, const WordPhase &f, uin
     }
 
     const uint32_t call0 = (uint32_t)Y * (uint32_t)(Lq >> 1) + 8u * (uint32_t)j;
-    // code changes of pairs 0-7 (dlo) and 8-15 (dhi): site a's in the low
-    // half, site b's in the high half
-    uint32_t dlo = 0u, dhi = 0u, packed = 0u;
-    const uint32_t kq2w = word_kq2(A0, B0);
+    // code changes of pairs 4g .. 4g+3 in dacc[g]: a-sites in byte 2, b-sites
+    // in byte 3 (Q = 4: groups q/2 and q/2 + 2 in dacc[0] and [1]; Q = 8:
+    // group q/2 in dacc[0])
+    uint32_t dacc[Q <= 2 ? 4 : 8 / Q] = {}, packed = 0u;
     u32x4 nxt[kTaskCalls<Q>];
     if constexpr (Pipe == kDrawPipe) {
 #pragma unroll
         for (int i = 0; i < kTaskCalls<Q>; ++i)
-            nxt[i] = philox4x32_10((uint32_t)ns, (uint32_t)np, call0 + (uint32_t)call_of_task<Q>(q, i),
-                                   (uint32_t)(ns >> 32), f.key0, f.key1);
+            nxt[i] = pair_draws(philox4x32_10((uint32_t)ns, (uint32_t)np, call0 + (uint32_t)call_of_task<Q>(q, i),
+                                              (uint32_t)(ns >> 32), f.key0, f.key1));
     }
-    auto do_call = [&](int i, int c, uint32_t be, uint32_t bo, uint32_t &dacc) {
-        const u32x4 w =
-            Pipe != kDrawInPlace ? pre[i]
-                                 : philox4x32_10(f.s_lo, (uint32_t)f.p, call0 + (uint32_t)c, f.s_hi, f.key0, f.key1);
+    auto do_call = [&](int i, int c, uint32_t be, uint32_t bo, uint32_t &d) {
+        const u32x4 w = Pipe != kDrawInPlace ? pre[i]
+                                             : pair_draws(philox4x32_10(f.s_lo, (uint32_t)f.p, call0 + (uint32_t)c, f.s_hi,
+                                                                        f.key0, f.key1));
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int t = 2 * c + h;
-            const uint32_t s0 = ((A0 >> (2 * t)) & 3u) | (((B0 >> (2 * t)) & 3u) << 2);
-            pair_step_delta(s0, (kq2w >> (2 * t)) & 3u, h ? bo : be, h ? w.z : w.x, h ? w.w : w.y, s_transd, s_tab,
-                            0x00030003u << (2 * (t & 7)), packed, dacc);
+            const uint32_t entry =
+                (((A0 >> (2 * t)) & 3u) << 7) | (((B0 >> (2 * t)) & 3u) << 9) | (h ? w.z : w.x);
+            pair_step_slot(entry, h ? bo : be, h ? w.w : w.y, s_slots, s_tab, 0x03030000u << (2 * (t & 3)), packed, d);
         }
     };
     if constexpr (Q <= 2) {
@@ -345,10 +345,7 @@ __device__ __forceinline__ void word_task(uint32_t *lat, const WordPhase &f, uin
 #pragma unroll
             for (int kk = 0; kk < 4; ++kk) {  // pairs 4kk .. 4kk+3
                 const int slot = Q == 1 ? 4 * hh + kk : kk;
-                if (kk < 2)
-                    do_call(slot, 2 * kk + half, ge[kk], go[kk], dlo);
-                else
-                    do_call(slot, 2 * kk + half, ge[kk], go[kk], dhi);
+                do_call(slot, 2 * kk + half, ge[kk], go[kk], dacc[kk]);
                 if (Barrier) __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -358,21 +355,26 @@ __device__ __forceinline__ void word_task(uint32_t *lat, const WordPhase &f, uin
         const uint32_t rEG0 = (sa.EG >> sh) & kM0F, rEG1 = (sb.EG >> sh) & kM0F;
         const uint32_t rOS0 = (sa.OS >> sh) & kM0F, rOS1 = (sb.OS >> sh) & kM0F;
         const uint32_t rOG0 = (sa.OG >> sh) & kM0F, rOG1 = (sb.OG >> sh) & kM0F;
-        uint32_t dx = 0u;  // Q = 8: pairs 4kk .. 4kk+3 of the one call, kk = q >> 1
 #pragma unroll
-        for (int i = 0; i < 8 / Q; ++i) {  // Q = 4: i = 0 covers pairs 0-7, i = 1 pairs 8-15
+        for (int i = 0; i < 8 / Q; ++i) {  // pairs of group kk
             const uint32_t kk = (uint32_t)(q >> 1) + 2u * (uint32_t)i;
             const uint32_t sel = kk | ((4u + kk) << 8) | 0x0C0C0000u;
             do_call(i, 2 * (int)kk + half, gather_byte(rES0, rES1, rEG0, rEG1, sel),
-                    gather_byte(rOS0, rOS1, rOG0, rOG1, sel), Q == 8 ? dx : (i == 0 ? dlo : dhi));
-        }
-        if (Q == 8) {
-            dlo = (q >> 1) < 2 ? dx : 0u;
-            dhi = (q >> 1) < 2 ? 0u : dx;
+                    gather_byte(rOS0, rOS1, rOG0, rOG1, sel), dacc[i]);
         }
     }
-    const uint32_t dA = __builtin_amdgcn_perm(dhi, dlo, 0x05040100u);
-    const uint32_t dB = __builtin_amdgcn_perm(dhi, dlo, 0x07060302u);
+    // the changes as words: 2-bit fields of the 16 a-sites and of the b-sites
+    uint32_t dA, dB;
+    if constexpr (Q <= 2) {
+        dA = __builtin_amdgcn_perm(__builtin_amdgcn_perm(dacc[3], dacc[2], 0x0C0C0602u),
+                                   __builtin_amdgcn_perm(dacc[1], dacc[0], 0x0C0C0602u), 0x05040100u);
+        dB = __builtin_amdgcn_perm(__builtin_amdgcn_perm(dacc[3], dacc[2], 0x0C0C0703u),
+                                   __builtin_amdgcn_perm(dacc[1], dacc[0], 0x0C0C0703u), 0x05040100u);
+    } else {
+        const uint32_t last = Q == 4 ? dacc[8 / Q - 1] : 0u;
+        dA = __builtin_amdgcn_perm(last, dacc[0], 0x0C060C02u) << (8 * (q >> 1));
+        dB = __builtin_amdgcn_perm(last, dacc[0], 0x0C070C03u) << (8 * (q >> 1));
+    }
     if constexpr (Pipe == kDrawPipe) {
 #pragma unroll
         for (int i = 0; i < kTaskCalls<Q>; ++i) pre[i] = nxt[i];

@@ -26,7 +26,7 @@ template <int Q>
 __global__ void __launch_bounds__(kWordsPhaseMaxThreads) k_phase_words(WordsArgs a)
 {
     __shared__ uint2 s_tab[kDevTabEntries];
-    __shared__ uint4 s_transd[kTransEntries];
+    __shared__ __align__(16) uint2 s_slots[kSlotEntries];
     // the lattice of this block (uniform; at most kWordsBatch lattices)
     int li = 0;
     while (li + 1 < a.count && blockIdx.x >= a.first_block[li + 1]) ++li;
@@ -36,9 +36,9 @@ __global__ void __launch_bounds__(kWordsPhaseMaxThreads) k_phase_words(WordsArgs
     uint32_t *st = d.enc == 1 ? (uint32_t *)d.state : (uint32_t *)(scr + kScrWork);
     {
         const uint2 *g_tab = (const uint2 *)(scr + kScrDevTab);
-        const uint4 *g_transd = (const uint4 *)(scr + kScrTransD);
         for (int i = threadIdx.x; i < kDevTabEntries; i += blockDim.x) s_tab[i] = g_tab[i];
-        for (int i = threadIdx.x; i < kTransEntries; i += blockDim.x) s_transd[i] = g_transd[i];
+        const uint2 *g_slots = (const uint2 *)kWordSlots.v;
+        for (int i = threadIdx.x; i < kSlotEntries; i += blockDim.x) s_slots[i] = g_slots[i];
     }
     const uint64_t s = d.next_sweep + a.iter;
     int r, mm[4], kk[4];
@@ -52,7 +52,7 @@ __global__ void __launch_bounds__(kWordsPhaseMaxThreads) k_phase_words(WordsArgs
     const uint32_t task = b * blockDim.x + threadIdx.x;
     int tr[3] = {0, 0, 0};
     // tasks = Q * csz is a multiple of Q, so a word's lanes are all in or all out
-    if (task < (uint32_t)Q * csz) word_task<Q, false, kDrawInPlace, true>(st, f, task, s_tab, s_transd, tr);
+    if (task < (uint32_t)Q * csz) word_task<Q, false, kDrawInPlace, true>(st, f, task, s_tab, (const uint8_t *)s_slots, tr);
     block_reduce_add<3>(tr, (unsigned long long *)(scr + kScrSlots) + 3 * (size_t)b);
 }
 
@@ -100,7 +100,7 @@ template <int Q, bool Obs>
 __global__ void __launch_bounds__(kWordsThreads) k_words_series(WordsSeriesArgs a)
 {
     __shared__ uint2 s_tab[kDevTabEntries];
-    __shared__ uint4 s_transd[kTransEntries];
+    __shared__ __align__(16) uint2 s_slots[kSlotEntries];
     int li = 0;  // this block's lattice (uniform)
     while (li + 1 < a.count && blockIdx.x >= a.first_block[li + 1]) ++li;
     uint8_t *scr = a.scratch[li];
@@ -108,9 +108,9 @@ __global__ void __launch_bounds__(kWordsThreads) k_words_series(WordsSeriesArgs 
     uint32_t *st = d.enc == 1 ? (uint32_t *)d.state : (uint32_t *)(scr + kScrWork);
     {
         const uint2 *g_tab = (const uint2 *)(scr + kScrDevTab);
-        const uint4 *g_transd = (const uint4 *)(scr + kScrTransD);
         for (int i = threadIdx.x; i < kDevTabEntries; i += blockDim.x) s_tab[i] = g_tab[i];
-        for (int i = threadIdx.x; i < kTransEntries; i += blockDim.x) s_transd[i] = g_transd[i];
+        const uint2 *g_slots = (const uint2 *)kWordSlots.v;
+        for (int i = threadIdx.x; i < kSlotEntries; i += blockDim.x) s_slots[i] = g_slots[i];
     }
     __syncthreads();
     unsigned *counter = (unsigned *)(a.scratch[0] + kScrBarrier), *err = (unsigned *)(scr + kScrErr);
@@ -129,8 +129,8 @@ __global__ void __launch_bounds__(kWordsThreads) k_words_series(WordsSeriesArgs 
     auto draws = [&](uint64_t s, int p) {
 #pragma unroll
         for (int i = 0; i < kTaskCalls<Q>; ++i)
-            pre[i] = philox4x32_10((uint32_t)s, (uint32_t)p, c0 + (uint32_t)call_of_task<Q>(q, i), (uint32_t)(s >> 32),
-                                   d.key0, d.key1);
+            pre[i] = pair_draws(philox4x32_10((uint32_t)s, (uint32_t)p, c0 + (uint32_t)call_of_task<Q>(q, i),
+                                              (uint32_t)(s >> 32), d.key0, d.key1));
     };
     int r, mm[4], kk[4];
     device_schedule(d.L, d.key0, d.key1, d.next_sweep, r, mm, kk);
@@ -153,12 +153,12 @@ __global__ void __launch_bounds__(kWordsThreads) k_words_series(WordsSeriesArgs 
                     word_phase_setup(f, d.L, d.key0, d.key1, s, p, r, mm, kk);
                     if (one) {
                         if (mine)
-                            word_task<Q, false, kDrawGiven, true, true, Obs>(st, f, first, s_tab, s_transd, tr, pre, 0,
+                            word_task<Q, false, kDrawGiven, true, true, Obs>(st, f, first, s_tab, (const uint8_t *)s_slots, tr, pre, 0,
                                                                              0, dv);
                     } else {
                         // stride is a multiple of Q: a word's lanes are all in or all out
                         for (uint32_t t = first; t < n_tasks; t += stride)
-                            word_task<Q, false, kDrawInPlace, true, true, Obs>(st, f, t, s_tab, s_transd, tr, nullptr,
+                            word_task<Q, false, kDrawInPlace, true, true, Obs>(st, f, t, s_tab, (const uint8_t *)s_slots, tr, nullptr,
                                                                                0, 0, dv);
                     }
                 }
