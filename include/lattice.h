@@ -117,16 +117,18 @@ int lattice_create(const lat_params *p, void *d_state, size_t state_bytes, void 
 /* Advance by `sweeps` sweeps (section 3.1 update, section 3.2 parallel form):
  * each sweep is four phases of N/8 non-interacting coupled pairs, so every
  * site is updated once per sweep.  Asynchronous on the handle's stream.
- * Lattices with L % 64 == 0 and 256 < L <= 1024 advance in one cooperative
+ * Lattices with L % 64 == 0 and 256 < L <= 2048 advance in one cooperative
  * launch per call, whose blocks must all be resident at once, with a
  * device-wide barrier after every phase: kernels of other streams running
  * at the same time can delay it, and a barrier that waits longer than about
- * 0.2 s (LATTICE_BARRIER_TICKS: another bound, in 10 ns ticks of the device
- * clock) marks the state invalid, which the next read (lattice_observables,
- * lattice_observables_batch, lattice_series_read) reports as LAT_EHIP.
- * LATTICE_WORDS_PERSISTENT=0 in the environment at the call selects one
- * launch per phase instead; set it for calls captured into a HIP graph,
- * whose kernel nodes do not guarantee that all blocks are resident at once.
+ * 0.2 s, or 10 s at the start of the launch, where its last blocks may wait for
+ * such kernels (LATTICE_BARRIER_TICKS: another bound than 0.2 s, in 10 ns
+ * ticks of the device clock) marks the state invalid, which the next read
+ * (lattice_observables, lattice_observables_batch, lattice_series_read)
+ * reports as LAT_EHIP.  LATTICE_WORDS_PERSISTENT=0 in the environment at the
+ * call selects one launch per phase instead; calls captured into a HIP graph
+ * take that form by themselves, since a graph's kernel nodes do not guarantee
+ * that all blocks are resident at once.
  * Errors: LAT_ESTATE, LAT_EHIP. */
 int lattice_sweep(lattice *h, uint32_t sweeps);
 
@@ -165,8 +167,8 @@ int lattice_read_state(lattice *h, int8_t *host_codes);
  * L % 64 == 0, L <= 512 otherwise) advance together in one launch per 256 of
  * them, each resident in on-chip memory for all the sweeps; those with
  * L % 64 == 0 up to 2048 advance together on the multi-block word kernel (one
- * cooperative launch per 64 of them up to L = 1024, as lattice_sweep, else
- * one launch per phase); larger ones one after another.  The caller orders hip_stream
+ * cooperative launch per 64 of them, as lattice_sweep); larger ones one after
+ * another.  The caller orders hip_stream
  * after any pending work of the lattices' own streams.  A lattice may appear
  * only once.  Errors: LAT_EINVAL, LAT_ESTATE, LAT_EHIP. */
 int lattice_sweep_batch(lattice *const *hs, int32_t count, uint32_t sweeps, void *hip_stream);

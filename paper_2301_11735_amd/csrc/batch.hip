@@ -45,10 +45,10 @@ __device__ __forceinline__ void stage_lattice(uint32_t *lat, const LatDesc &d, c
     const int L = g.L, Lq = g.Lq;
     const uint32_t nwords = 8u * g.csz;
     if (d.enc == 1) {
-        const uint32_t *src = (const uint32_t *)d.state;  // same layout, Wp = L/64
+        const LAT_GLOBAL uint32_t *src = (const LAT_GLOBAL uint32_t *)d.state;  // same layout, Wp = L/64
         for (uint32_t i = threadIdx.x; i < nwords; i += blockDim.x) lat[i] = src[i];
     } else {
-        const int8_t *src = (const int8_t *)d.state;
+        const LAT_GLOBAL int8_t *src = (const LAT_GLOBAL int8_t *)d.state;
         for (uint32_t i = threadIdx.x; i < nwords; i += blockDim.x) {
             const int c = (int)(i / g.csz);
             const uint32_t rem = i - (uint32_t)c * g.csz;
@@ -68,10 +68,10 @@ __device__ __forceinline__ void unstage_lattice(const uint32_t *lat, const LatDe
 {
     const int L = g.L;
     if (d.enc == 1) {
-        uint32_t *dst = (uint32_t *)d.state;
+        LAT_GLOBAL uint32_t *dst = (LAT_GLOBAL uint32_t *)d.state;
         for (uint32_t i = threadIdx.x; i < 8u * g.csz; i += blockDim.x) dst[i] = lat[i];
     } else {
-        int8_t *dst = (int8_t *)d.state;
+        LAT_GLOBAL int8_t *dst = (LAT_GLOBAL int8_t *)d.state;
         for (uint32_t i = threadIdx.x; i < (uint32_t)L * L; i += blockDim.x) {
             const int y = (int)(i / L), x = (int)(i - (uint32_t)y * L);
             dst[i] = (int8_t)lds_code(lat, g, 4 * (y & 1) + (x & 3), y >> 1, x >> 2);
@@ -169,16 +169,16 @@ __device__ __forceinline__ void stage_sites(uint32_t *lat, const LatDesc &d)
     const uint32_t L = (uint32_t)d.L, N = L * L;
     if (d.enc == 0) {
         if (((uintptr_t)d.state & 3u) == 0) {
-            const uint32_t *src = (const uint32_t *)d.state;
+            const LAT_GLOBAL uint32_t *src = (const LAT_GLOBAL uint32_t *)d.state;
             for (uint32_t i = threadIdx.x; i < N / 4u; i += blockDim.x) lat[i] = site_from_codes(src[i] & 0x03030303u);
         } else {
-            const uint8_t *src = (const uint8_t *)d.state;
+            const LAT_GLOBAL uint8_t *src = (const LAT_GLOBAL uint8_t *)d.state;
             for (uint32_t i = threadIdx.x; i < N; i += blockDim.x)
                 ((uint8_t *)lat)[i] = (uint8_t)(kSiteBytes >> (8u * (src[i] & 3u)));
         }
     } else {
         // word (c, Y, j) of the class layout: sites x = 4 (16 j + t) + (c & 3) of row 2 Y + (c >> 2)
-        const uint32_t *src = (const uint32_t *)d.state;
+        const LAT_GLOBAL uint32_t *src = (const LAT_GLOBAL uint32_t *)d.state;
         const uint32_t W = L >> 6, csz = (L >> 1) * W;
         for (uint32_t i = threadIdx.x; i < 8u * csz; i += blockDim.x) {
             const uint32_t c = i / csz, rem = i - c * csz, Y = rem / W, j = rem - Y * W, w = src[i];
@@ -194,15 +194,15 @@ __device__ __forceinline__ void unstage_sites(const uint32_t *lat, const LatDesc
     const uint32_t L = (uint32_t)d.L, N = L * L;
     if (d.enc == 0) {
         if (((uintptr_t)d.state & 3u) == 0) {
-            uint32_t *dst = (uint32_t *)d.state;
+            LAT_GLOBAL uint32_t *dst = (LAT_GLOBAL uint32_t *)d.state;
             for (uint32_t i = threadIdx.x; i < N / 4u; i += blockDim.x) dst[i] = codes_from_site(lat[i]);
         } else {
-            uint8_t *dst = (uint8_t *)d.state;
+            LAT_GLOBAL uint8_t *dst = (LAT_GLOBAL uint8_t *)d.state;
             for (uint32_t i = threadIdx.x; i < N; i += blockDim.x)
                 dst[i] = (uint8_t)codes_from_site(((const uint8_t *)lat)[i]) & 3u;
         }
     } else {
-        uint32_t *dst = (uint32_t *)d.state;
+        LAT_GLOBAL uint32_t *dst = (LAT_GLOBAL uint32_t *)d.state;
         const uint32_t W = L >> 6, csz = (L >> 1) * W;
         for (uint32_t i = threadIdx.x; i < 8u * csz; i += blockDim.x) {
             const uint32_t c = i / csz, rem = i - c * csz, Y = rem / W, j = rem - Y * W;

@@ -311,6 +311,11 @@ __device__ __forceinline__ void grid_barrier(unsigned *counter, unsigned target,
     __syncthreads();
 }
 
+// Global memory, said in the type: a pointer that was read from memory (a
+// descriptor's state) gets flat accesses otherwise, with 64-bit addresses in
+// vector registers and LDS counters to wait for.
+#define LAT_GLOBAL __attribute__((address_space(1)))
+
 // Word i of an array below 4 GiB (every lattice state is): a 32-bit byte
 // offset from the base, so that a uniform base stays in scalar registers and
 // no 64-bit address is formed per access.

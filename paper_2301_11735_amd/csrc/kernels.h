@@ -150,6 +150,7 @@ constexpr long long kBarrierTimeoutTicks = 20000000;
 // skipped.  Block b of a lattice adds its tracker sums to tracker slot b.
 constexpr int kWordsBatch = 64;
 constexpr int kWordsThreads = 256;
+constexpr int kWordsSeriesMaxThreads = 512;  // of the persistent form with at least 4 lanes per a-word
 struct WordsArgs {
     int count;
     int p;
@@ -173,16 +174,15 @@ hipError_t launch_phase_words(const WordsArgs &a, int Q, int threads, hipStream_
 // desc->next_sweep += sweeps[i] for every lattice of the series.
 hipError_t launch_advance_words(const WordsArgs &a, hipStream_t s);
 // Persistent multi-block form: up to kWordsBatch lattices (blocks
-// first_block[i] .. first_block[i+1]-1 update lattice i) for intervals x
-// every sweeps in one cooperative launch, a device-wide barrier after every
-// phase; lattice i runs its first sweeps[i] of them.  With records (one
-// lattice, kSeriesRecord bytes each, as launch_observables writes them) the
-// observables and tracker after every interval.  The barrier counter (in
-// the first lattice's scratch) is cleared and the records initialised by
-// kernels enqueued first.
+// first_block[i] .. first_block[i+1]-1 update lattice i) for sweeps[i] sweeps
+// each in one cooperative launch, a device-wide barrier of a lattice's blocks
+// after every phase.  With records (one lattice, intervals x every sweeps,
+// kSeriesRecord bytes each, as launch_observables writes them) the observables
+// and tracker after every interval.  The barrier words (in each lattice's
+// scratch) are cleared and the records initialised by kernels enqueued first.
 struct WordsSeriesArgs {
     int count;
-    int threads;              // block size: a multiple of 64 up to kWordsThreads
+    int threads;              // block size: a multiple of 64 up to kWordsThreads (Q >= 4: kWordsSeriesMaxThreads)
     long long barrier_ticks;  // bound of each device-wide barrier wait (device wall-clock ticks)
     uint32_t intervals, every;
     long long *records;  // null: no observables

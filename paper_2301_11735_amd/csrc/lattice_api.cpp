@@ -471,7 +471,7 @@ int enqueue_words_sweeps(lattice *const *hs, int32_t count, const uint32_t *swee
 
 }  // namespace
 
-constexpr int kWordsPersistentMaxL = 1024;
+constexpr int kWordsPersistentMaxL = 2048;
 
 namespace {
 
@@ -504,16 +504,53 @@ long long words_barrier_ticks()
     return kBarrierTimeoutTicks;
 }
 
-// Block size of the persistent word kernel: 256 threads unless
-// LATTICE_WORDS_SERIES_BLOCK asks for another multiple of 64 up to 256
-// (smaller blocks spread a lattice over more compute units).
-int words_series_threads()
+// Lanes per a-word and block size of the persistent word kernel for the n
+// lattices of a launch.  A phase is a chain of latencies, which more lanes
+// shorten (8 lanes: two pairs each) as long as a lattice's blocks still meet on
+// one counter, which is faster up to 64 of them; so for one lattice as many
+// lanes as 64 blocks of 256 threads hold, but at least 2.  Above L = 1024 the
+// blocks meet in two levels anyway, and 4 lanes in blocks of 512 threads
+// measured best.  us a sweep, plain / with observables, for 2 lanes, 4 lanes, 4 in
+// blocks of 512, 8 lanes: L = 512 12.8/14.4, 10.6/12.1, 12.3/13.9, 9.6/12.0;
+// L = 1024 12.3/14.7, 13.3/16.3, 12.4/14.9, 12.2/15.0; L = 2048 15.8/19.2,
+// 16.2/19.5, 14.2/18.3, 20.3/25.2.  Several lattices take fewer lanes until
+// a block a compute unit holds them all, since more lanes load more words in
+// all: 8 of L = 512 with 8 / 4 / 2 lanes 11.7 / 10.7 / 13.1 us, 48 of them
+// with 8 / 1 33.6 / 21.8, 4 of L = 2048 with 4 / 1 45.6 / 24.3.
+// LATTICE_WORDS_LANES (1, 2, 4 or 8) and LATTICE_WORDS_SERIES_BLOCK (a multiple
+// of 64 up to the largest for the lanes) override.
+struct WordsShape {
+    int Q, threads;
+};
+WordsShape words_series_shape(lattice *const *hs, int32_t n)
 {
+    auto blocks = [&](const WordsShape &w) {
+        uint32_t sum = 0;
+        for (int32_t i = 0; i < n; ++i) sum += words_blocks(hs[i]->L, w.Q, w.threads);
+        return sum;
+    };
+    int max_L = 0;
+    for (int32_t i = 0; i < n; ++i) max_L = std::max(max_L, hs[i]->L);
+    WordsShape w{8, kWordsThreads};
+    if (max_L > 1024)
+        w = {4, kWordsSeriesMaxThreads};
+    else
+        while (w.Q > 2 && words_blocks(max_L, w.Q) > 64u) w.Q /= 2;
+    while (n > 1 && w.Q > 1 && blocks(w) > 256u) {
+        w.Q /= 2;
+        if (w.Q < 4) w.threads = kWordsThreads;
+    }
+    if (const char *v = std::getenv("LATTICE_WORDS_LANES")) {
+        const int want = std::atoi(v);
+        if (want == 1 || want == 2 || want == 4 || want == 8) w.Q = want;
+    }
+    const int most = w.Q >= 4 ? kWordsSeriesMaxThreads : kWordsThreads;
+    w.threads = std::min(w.threads, most);
     if (const char *v = std::getenv("LATTICE_WORDS_SERIES_BLOCK")) {
         const int want = std::atoi(v);
-        if (want >= 64 && want <= kWordsThreads && want % 64 == 0) return want;
+        if (want >= 64 && want <= most && want % 64 == 0) w.threads = want;
     }
-    return kWordsThreads;
+    return w;
 }
 
 }  // namespace
@@ -528,33 +565,18 @@ int enqueue_words_persistent(lattice *const *hs, int32_t count, const uint32_t *
         if (hs[i]->path != kPathWords) return LAT_OK;
         max_L = std::max(max_L, hs[i]->L);
     }
-    // default: on up to L = 1024, where it measured faster than one launch
-    // per phase (13.2 against 21.9 us a sweep at L = 512, 23.0 against
-    // 24.7 us at L = 1024); above, its device-coherent loads, which no
-    // compute unit's cache serves, cost more than the launches they save
-    // (43 against 28 us at L = 2048).  A series with observables every sweep
-    // takes its records from the tracked moves in this form (no pass over
-    // the lattice, no extra barrier): 25.6 us a sweep at L = 1024, against
-    // 34.6 us with launches per phase and a reduction launch per interval.
+    // default: on for every lattice of this path, against one launch per phase
+    // (us a sweep, plain / with observables after every sweep): L = 512
+    // 9.6 / 12.0 against 21.7 / 34.4, L = 1024 12.3 / 14.7 against 22.0 /
+    // 34.8, L = 2048 14.2 / 18.3 against 23.6 / 36.5.
     // LATTICE_WORDS_PERSISTENT=0|1 overrides.
     const char *v = std::getenv("LATTICE_WORDS_PERSISTENT");
     if (v ? std::atoi(v) == 0 : max_L > kWordsPersistentMaxL) return LAT_OK;
     if (records && count != 1) return fail(LAT_EINVAL, "an observation series holds one lattice");
-    // lanes per a-word: 8 up to L = 512 and 2 above.  This form's
-    // device-coherent loads set its pace, and fewer lanes per word load fewer
-    // words in all: at L = 1024 a sweep with its observables took 26.9, 29.6
-    // and 35.5 us with 2, 4 and 8 lanes (at L = 512, 17-19 us with any of
-    // them); at L = 2048, 43 and 78 us with 2 and 4.  LATTICE_WORDS_LANES
-    // (1, 2, 4 or 8) overrides.  Blocks of 256 threads: 128 and 64 measured
-    // slower at L = 512 and 1024 (more blocks meet at every barrier).
-    int Q = max_L <= 512 ? 8 : 2;
-    if (const char *q = std::getenv("LATTICE_WORDS_LANES")) {
-        const int want = std::atoi(q);
-        if (want == 1 || want == 2 || want == 4 || want == 8) Q = want;
-    }
-    const int threads = words_series_threads();
-    const int capacity = words_capacity(Q, threads);
-    if (capacity <= 0) return LAT_OK;
+    // a captured kernel node would not guarantee that all blocks are resident at once
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess) (void)hipGetLastError();
+    if (capture != hipStreamCaptureStatusNone) return LAT_OK;
     // the barrier counter counts blocks x barriers: at most 2^20 barriers per
     // launch keeps it below 2^32 for any resident grid
     constexpr uint64_t kMaxBarriers = 1u << 20;
@@ -567,6 +589,10 @@ int enqueue_words_persistent(lattice *const *hs, int32_t count, const uint32_t *
     // resident blocks
     for (int32_t g0 = 0; g0 < count; g0 += kWordsBatch) {
         const int32_t n = std::min<int32_t>(kWordsBatch, count - g0);
+        const WordsShape shape = words_series_shape(hs + g0, n);
+        const int Q = shape.Q, threads = shape.threads;
+        const int capacity = words_capacity(Q, threads);
+        if (capacity <= 0) return *ran ? fail(LAT_EHIP, "persistent word launch is not possible") : LAT_OK;
         const uint32_t share = std::max<uint32_t>(1, (uint32_t)capacity / (uint32_t)n);
         uint32_t nb[kWordsBatch];
         uint32_t total = 0;

@@ -322,11 +322,11 @@ __global__ void __launch_bounds__(kMapThreads) k_map_steps(MapArgs args)
     const uint32_t *g_thr = (const uint32_t *)(scr + kScrFullTab);
     for (uint32_t i = threadIdx.x; i < (uint32_t)kTabSize; i += blockDim.x) thr[i] = g_thr[i];
     if (d.enc == 0) {
-        const uint8_t *src = (const uint8_t *)d.state;
+        const LAT_GLOBAL uint8_t *src = (const LAT_GLOBAL uint8_t *)d.state;
         for (uint32_t i = threadIdx.x; i < N; i += blockDim.x) codes[i] = src[i];
     } else {
         // 2-bit class layout: class 4*(y&1) + (x&3), (L/2) rows of L/64 words
-        const uint32_t *src = (const uint32_t *)d.state;
+        const LAT_GLOBAL uint32_t *src = (const LAT_GLOBAL uint32_t *)d.state;
         const uint32_t W = (uint32_t)L >> 6, csz = ((uint32_t)L >> 1) * W;
         for (uint32_t i = threadIdx.x; i < N; i += blockDim.x) {
             const uint32_t y = i / (uint32_t)L, x = i - y * (uint32_t)L;
@@ -374,10 +374,10 @@ __global__ void __launch_bounds__(kMapThreads) k_map_steps(MapArgs args)
     }
 
     if (d.enc == 0) {
-        uint8_t *dst = (uint8_t *)d.state;
+        LAT_GLOBAL uint8_t *dst = (LAT_GLOBAL uint8_t *)d.state;
         for (uint32_t i = threadIdx.x; i < N; i += blockDim.x) dst[i] = codes[i];
     } else {
-        uint32_t *dst = (uint32_t *)d.state;
+        LAT_GLOBAL uint32_t *dst = (LAT_GLOBAL uint32_t *)d.state;
         const uint32_t W = (uint32_t)L >> 6, H = (uint32_t)L >> 1, csz = H * W;
         for (uint32_t i = threadIdx.x; i < 8u * csz; i += blockDim.x) {
             const uint32_t c = i / csz, rem = i - c * csz, Y = rem / W, jw = rem - Y * W;

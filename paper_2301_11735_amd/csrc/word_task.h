@@ -43,7 +43,9 @@ template <bool Coh>
 __device__ __forceinline__ uint32_t ldw(const uint32_t *p, uint32_t i)
 {
     if constexpr (Coh)
-        return __hip_atomic_load(p + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // a 32-bit byte offset from the uniform base: no 64-bit address per access
+        return __hip_atomic_load((const LAT_GLOBAL uint32_t *)((const LAT_GLOBAL uint8_t *)p + (i << 2)), __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT);
     else
         return p[i];
 }
@@ -51,23 +53,24 @@ template <bool Coh>
 __device__ __forceinline__ void stw(uint32_t *p, uint32_t i, uint32_t v)
 {
     if constexpr (Coh)
-        __hip_atomic_store(p + i, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store((LAT_GLOBAL uint32_t *)((LAT_GLOBAL uint8_t *)p + (i << 2)), v, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
     else
         p[i] = v;
 }
-// 16 sites of the class row at word offset `row`, starting at class position
-// xs (periodic), as load16 but through ldw.  Device-coherent reads load the
-// second word only when xs starts mid-word (every caller's xs mod 16 depends
-// on the phase and the schedule only, so the branch is uniform): at
-// L = 1024 that saved 2.5% of a sweep.  Plain loads (LDS, or global memory
-// within a launch) keep both, which measured slightly faster there.
-template <bool Coh>
+// XOR into a word of a lattice in global memory.
+__device__ __forceinline__ void xorw(uint32_t *p, uint32_t i, uint32_t v)
+{
+    (void)__hip_atomic_fetch_xor((LAT_GLOBAL uint32_t *)((LAT_GLOBAL uint8_t *)p + (i << 2)), v, __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT);
+}
+// 16 sites of the class row at word offset `row` of a lattice in LDS (or
+// plain global memory), starting at class position xs (periodic).
 __device__ __forceinline__ uint32_t ld16(const uint32_t *st, uint32_t row, int W, int xs)
 {
     const int jw = xs >> 4, sh = xs & 15;
-    const uint32_t w0 = ldw<Coh>(st, row + (uint32_t)jw);
-    if (Coh && sh == 0) return w0;
-    const uint32_t w1 = ldw<Coh>(st, row + (uint32_t)(jw + 1 == W ? 0 : jw + 1));
+    const uint32_t w0 = st[row + (uint32_t)jw];
+    const uint32_t w1 = st[row + (uint32_t)(jw + 1 == W ? 0 : jw + 1)];
     return sh ? __builtin_amdgcn_alignbit(w1, w0, 2u * (uint32_t)sh) : w0;
 }
 
@@ -78,33 +81,75 @@ __device__ __forceinline__ uint32_t ld16(const uint32_t *st, uint32_t row, int W
 // thread waits for the others, and the block meets again.  No cache
 // write-back or invalidation is needed.  Between the halves a block may do
 // work that touches no lattice word.  The wait is bounded as in grid_barrier
-// (time-out flag, then go on), by `limit` ticks of the device wall clock.
-__device__ __forceinline__ void grid_arrive_coherent(unsigned *counter)
-{
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void grid_wait_coherent(unsigned *counter, unsigned target, unsigned *err,
-                                                   long long limit = kBarrierTimeoutTicks)
-{
-    if (threadIdx.x == 0) {
-        const long long t0 = wall_clock64();
-        while (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-            __builtin_amdgcn_s_sleep(1);
-            if (wall_clock64() - t0 > limit) {
-                atomicOr(err, 1u);
-                break;
+// (time-out flag, then go on), by `limit` ticks of the device wall clock, at the
+// first barrier kFirstWaits times as long: until then other streams' kernels
+// may hold the compute units that the last blocks need, afterwards every
+// block is resident.  A block that has given up waits no more.  Up to kFlatBarrierBlocks blocks meet on one counter.  More meet in two
+// levels: block b arrives on the counter of group b % 8 (blocks go to the
+// eight XCDs in turn, so a group shares an L2), the last of a group on the
+// common counter, and the last of all releases every group by its own flag.
+// Every block's increments at one address cost 15 ns each; measured per
+// barrier with 32 / 64 / 128 / 256 blocks: one counter 1.1 / 1.4 / 2.1 / 3.8
+// us, two levels 1.6 / 1.65 / 1.75 / 1.95 us.
+constexpr unsigned kFlatBarrierBlocks = 64, kBarrierGroups = 8, kBarrierLine = 32;  // words apart: 128 bytes
+constexpr long long kFirstWaits = 50;
+constexpr unsigned kBarrierWords = (1 + 3 * kBarrierGroups) * kBarrierLine;
+struct GridBarrier {
+    unsigned *words;  // the common counter, the group counters, the group flags, the group sums, a line each
+    unsigned block, blocks;  // this block's number among those that meet
+    unsigned rounds;         // barriers arrived at so far
+    bool gave_up;
+    __device__ __forceinline__ unsigned *group() const { return words + kBarrierLine * (1u + block % kBarrierGroups); }
+    __device__ __forceinline__ unsigned *flag(unsigned g) const { return words + kBarrierLine * (1u + kBarrierGroups + g); }
+    // six running sums of the group's blocks (series records)
+    __device__ __forceinline__ unsigned long long *sums() const
+    {
+        return (unsigned long long *)(words + kBarrierLine * (1u + 2u * kBarrierGroups + block % kBarrierGroups));
+    }
+    __device__ __forceinline__ bool flat() const { return blocks <= kFlatBarrierBlocks; }
+
+    // True in the thread that completed its group (two levels only): until its
+    // block arrives again, no other block of the group passes the barrier
+    // after this one.
+    __device__ __forceinline__ bool arrive()
+    {
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        ++rounds;
+        bool last = false;
+        if (threadIdx.x == 0) {
+            if (flat()) {
+                __hip_atomic_fetch_add(words, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            } else {
+                const unsigned g = block % kBarrierGroups;
+                const unsigned mates = (blocks + kBarrierGroups - 1u - g) / kBarrierGroups;
+                last = __hip_atomic_fetch_add(group(), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == mates * rounds;
+                if (last && __hip_atomic_fetch_add(words, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u ==
+                                kBarrierGroups * rounds)
+                    for (unsigned k = 0; k < kBarrierGroups; ++k)
+                        __hip_atomic_store(flag(k), rounds, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
+        return last;
     }
-    __syncthreads();
-}
-__device__ __forceinline__ void grid_barrier_coherent(unsigned *counter, unsigned target, unsigned *err)
-{
-    grid_arrive_coherent(counter);
-    grid_wait_coherent(counter, target, err);
-}
+    __device__ __forceinline__ void wait(unsigned *err, long long limit)
+    {
+        if (threadIdx.x == 0 && !gave_up) {
+            const unsigned *at = flat() ? words : flag(block % kBarrierGroups);
+            const unsigned target = flat() ? blocks * rounds : rounds;
+            const long long t0 = wall_clock64(), most = rounds == 1u ? kFirstWaits * limit : limit;
+            while (__hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
+                __builtin_amdgcn_s_sleep(1);
+                if (wall_clock64() - t0 > most) {
+                    atomicOr(err, 1u);
+                    gave_up = true;
+                    break;
+                }
+            }
+        }
+        __syncthreads();
+    }
+};
 
 // The fields of WordPhase for phase p of a sweep with schedule (r, m, k), on
 // a lattice of side L with key (key0, key1); s is the sweep index.
@@ -153,7 +198,6 @@ __device__ __forceinline__ int spin_sum16(uint32_t w)
 // right and lower neighbours, sum sigma, and the staggered sums.  The right
 // neighbours are the same word of the next class (or class 0 of the row,
 // one site on), the lower ones the same word of the paired row class.
-template <bool Coh = false>
 __device__ __forceinline__ void obs_word_2bit(const uint32_t *st, int L, uint32_t i, long long (&v)[7])
 {
     const int W = L >> 6, H = L >> 1, Lq = L >> 2;
@@ -162,12 +206,10 @@ __device__ __forceinline__ void obs_word_2bit(const uint32_t *st, int L, uint32_
     const uint32_t rem = i - (uint32_t)c * csz;
     const int Y = (int)(rem / W), j = (int)(rem - (uint32_t)Y * W);
     const int cx = c & 3, cy = c >> 2;
-    const uint32_t w = ldw<Coh>(st, i);
-    const uint32_t wr = cx < 3 ? ldw<Coh>(st, i + csz)
-                               : ld16<Coh>(st, (uint32_t)(4 * cy) * csz + (uint32_t)Y * W, W,
-                                           16 * j + 1 == Lq ? 0 : 16 * j + 1);
-    const uint32_t wd = cy == 0 ? ldw<Coh>(st, i + 4 * csz)
-                                : ldw<Coh>(st, (uint32_t)cx * csz + (uint32_t)(Y + 1 == H ? 0 : Y + 1) * W + j);
+    const uint32_t w = st[i];
+    const uint32_t wr = cx < 3 ? st[i + csz]
+                               : ld16(st, (uint32_t)(4 * cy) * csz + (uint32_t)Y * W, W, 16 * j + 1 == Lq ? 0 : 16 * j + 1);
+    const uint32_t wd = cy == 0 ? st[i + 4 * csz] : st[(uint32_t)cx * csz + (uint32_t)(Y + 1 == H ? 0 : Y + 1) * W + j];
     const uint32_t h = (w >> 1) & kM5, l = w & kM5;
     const int sumS = charge_sum16(w);
     const int sumG = spin_sum16(w);
@@ -184,19 +226,14 @@ __device__ __forceinline__ void obs_word_2bit(const uint32_t *st, int L, uint32_
     v[6] += sg * sumS;
 }
 
-// Barrier = true keeps the compiler from interleaving the Philox calls of a
-// task (fewer live registers, needed at 1024 threads per block); without it
-// the calls overlap each other's LDS table lookups.
-// Value of the lane XOR lanes away (XOR = 1, 2: quad permutes; 4: any lane).
+// Value of the lane XOR lanes away (quad permutes), or, with XOR = 4, of the
+// other quad of eight lanes, for values that are the same in a whole quad
+// (the half-row mirror: no LDS permute).
 template <int XOR>
 __device__ __forceinline__ uint32_t lane_xor(uint32_t v)
 {
-    if constexpr (XOR == 1)
-        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);  // quad_perm [1,0,3,2]
-    else if constexpr (XOR == 2)
-        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false);  // quad_perm [2,3,0,1]
-    else
-        return (uint32_t)__shfl_xor((int)v, XOR, 64);
+    constexpr int ctrl = XOR == 1 ? 0xB1 : XOR == 2 ? 0x4E : 0x141;  // quad_perm [1,0,3,2], [2,3,0,1], row_half_mirror
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, 0xF, 0xF, false);
 }
 
 // Philox calls a task makes: all 8 of its word (Q = 1) or 8/Q of them.  The
@@ -222,77 +259,45 @@ __device__ __forceinline__ uint32_t task_call0(const WordPhase &f, uint32_t task
     return (uint32_t)Y * (uint32_t)(f.Lq >> 1) + 8u * (uint32_t)j;
 }
 
-// Pipe (where the task's Philox draws come from): kDrawInPlace, computed
-// here as they are used; kDrawPipe, this phase's given in pre[] and those of
-// the next phase (sweep ns, phase np) computed here, between the phase's
-// dependent LDS lookups, and returned in pre[]; kDrawGiven, this phase's
-// given in pre[] (the caller makes the next phase's elsewhere).
-// Combine (lattice in global memory): the Q lanes of a word first OR their
-// code changes together (their fields are disjoint), then the word's first
-// lane stores the a-word, which no other word reads or writes in the phase,
-// and applies the two b-word changes as atomics; one store and two atomics
-// per word instead of 3Q atomics.  Every lane of a word must be active.
-// Coh: the lattice words are read and written through ldw/stw<true>.
-// Obs (with Combine): the word's first lane also adds the changes of the
-// spin sum, the staggered spin sum and the staggered charge sum over the
-// word's a-sites and b-sites to dv[0..2] (the other observable sums are the
-// tracker's: the charged-site count and the two bond sums change by exactly
-// the accepted energy-change triples, and the charge sum does not change).
-constexpr int kDrawInPlace = 0, kDrawPipe = 1, kDrawGiven = 2;
-template <int Q, bool Barrier, int Pipe = kDrawInPlace, bool Combine = false, bool Coh = false, bool Obs = false>
-__device__ __forceinline__ void word_task(uint32_t *lat, const WordPhase &f, uint32_t task, const uint2 *s_tab,
-                                          const uint8_t *s_slots, int (&tr)[3], u32x4 *pre = nullptr,
-                                          uint64_t ns = 0, int np = 0, int *dv = nullptr)
+// Changes of 16 pairs' codes from a task's accumulators, as words of 2-bit
+// fields of the a-sites and of the b-sites.
+template <int Q>
+__device__ __forceinline__ void task_changes(const uint32_t (&dacc)[Q <= 2 ? 4 : 8 / Q], int q, uint32_t &dA,
+                                             uint32_t &dB)
 {
-    static_assert(!Obs || Combine, "the observable moves are taken where a word's changes are combined");
-    constexpr int LOGQ = Q == 1 ? 0 : Q == 2 ? 1 : Q == 4 ? 2 : 3;
-    const uint32_t wi = task >> LOGQ;
-    const int q = (int)(task & (uint32_t)(Q - 1));
-    const int W = f.W, H = f.H, Lq = f.Lq;
-    const int Y = W == 1 ? (int)wi : (int)__umulhi(wi, f.magicW), j = (int)wi - Y * W;
-    int Xb = 16 * j + f.dX;
-    if (Xb >= Lq) Xb -= Lq;
-    const int Yb = Y + f.k >= H ? Y + f.k - H : Y + f.k;
-    const int xAL = f.p > 0 ? 16 * j : (j == 0 ? Lq - 1 : 16 * j - 1);
-    const int xAR = f.p < 3 ? 16 * j : 16 * j + 1;
-    const int xBL = f.pb > 0 ? Xb : (Xb == 0 ? Lq - 1 : Xb - 1);
-    const int xBR = f.pb < 3 ? Xb : (Xb + 1 == Lq ? 0 : Xb + 1);
-    const uint32_t ro = (uint32_t)Y * W, rob = (uint32_t)Yb * W;
-    const uint32_t roU = (uint32_t)(Y == 0 ? H - 1 : Y - 1) * W;
-    const uint32_t robD = (uint32_t)(Yb + 1 == H ? 0 : Yb + 1) * W;
-
-    const uint32_t A0 = ldw<Coh>(lat, f.oA0 + ro + j);
-    const uint32_t B0 = ld16<Coh>(lat, f.oB0 + rob, W, Xb);
-    SideSums sa, sb;
-    if constexpr (Q == 1) {
-        sa = side_sums(ld16<Coh>(lat, f.oAL + ro, W, xAL), ld16<Coh>(lat, f.oAR + ro, W, xAR),
-                       ldw<Coh>(lat, f.oAV + roU + j), ldw<Coh>(lat, f.oAV + ro + j));
-        sb = side_sums(ld16<Coh>(lat, f.oBL + rob, W, xBL), ld16<Coh>(lat, f.oBR + rob, W, xBR),
-                       ld16<Coh>(lat, f.oBV + rob, W, Xb), ld16<Coh>(lat, f.oBV + robD, W, Xb));
+    if constexpr (Q <= 2) {
+        dA = __builtin_amdgcn_perm(__builtin_amdgcn_perm(dacc[3], dacc[2], 0x0C0C0602u),
+                                   __builtin_amdgcn_perm(dacc[1], dacc[0], 0x0C0C0602u), 0x05040100u);
+        dB = __builtin_amdgcn_perm(__builtin_amdgcn_perm(dacc[3], dacc[2], 0x0C0C0703u),
+                                   __builtin_amdgcn_perm(dacc[1], dacc[0], 0x0C0C0703u), 0x05040100u);
     } else {
-        // The Q threads of a word are Q consecutive lanes.  Lanes of the
-        // first half sum a-side neighbour words, the others b-side ones,
-        // 8/Q words each; the partial sums (additive, nibble-wide) are
-        // combined within the group and the two sides exchanged.
-        const int side = q >= Q / 2;
-        const int k0 = (q % (Q / 2)) * (8 / Q);
-        const uint32_t base[4] = {side ? f.oBL + rob : f.oAL + ro, side ? f.oBR + rob : f.oAR + ro,
-                                  side ? f.oBV + rob : f.oAV + roU, side ? f.oBV + robD : f.oAV + ro};
-        const int xs[4] = {side ? xBL : xAL, side ? xBR : xAR, side ? Xb : 16 * j, side ? Xb : 16 * j};
-        SideSums part{0u, 0u, 0u, 0u};
+        const uint32_t last = Q == 4 ? dacc[8 / Q - 1] : 0u;
+        dA = __builtin_amdgcn_perm(last, dacc[0], 0x0C060C02u) << (8 * (q >> 1));
+        dB = __builtin_amdgcn_perm(last, dacc[0], 0x0C070C03u) << (8 * (q >> 1));
+    }
+}
+
+// The neighbour sums of a word's a-sites (sa) and b-sites (sb) from the
+// words its Q lanes hold: lane q has words q (8 / Q) .. of (left, right, up,
+// down of the a-word, the same of the b-word).  The lanes' partial sums are
+// additive and fit nibbles; the two sides are then exchanged.
+template <int Q>
+__device__ __forceinline__ void combine_sides(const uint32_t (&n)[8 / Q], int q, SideSums &sa, SideSums &sb)
+{
+    if constexpr (Q == 1) {
+        sa = side_sums(n[0], n[1], n[2], n[3]);
+        sb = side_sums(n[4], n[5], n[6], n[7]);
+    } else {
+        SideSums full{0u, 0u, 0u, 0u}, other;
+        if constexpr (Q == 2) {
+            full = side_sums(n[0], n[1], n[2], n[3]);
+        } else {
 #pragma unroll
-        for (int i = 0; i < 8 / Q; ++i) {
-            const int kk = k0 + i;
-            const uint32_t b = kk == 0 ? base[0] : kk == 1 ? base[1] : kk == 2 ? base[2] : base[3];
-            const int x = kk == 0 ? xs[0] : kk == 1 ? xs[1] : kk == 2 ? xs[2] : xs[3];
-            side_add(part, ld16<Coh>(lat, b, W, x));
-        }
-        SideSums full = part, other;
-        if constexpr (Q >= 4) {
-            full.ES += lane_xor<1>(part.ES);
-            full.OS += lane_xor<1>(part.OS);
-            full.EG += lane_xor<1>(part.EG);
-            full.OG += lane_xor<1>(part.OG);
+            for (int i = 0; i < 8 / Q; ++i) side_add(full, n[i]);
+            full.ES += lane_xor<1>(full.ES);
+            full.OS += lane_xor<1>(full.OS);
+            full.EG += lane_xor<1>(full.EG);
+            full.OG += lane_xor<1>(full.OG);
         }
         if constexpr (Q == 8) {
             full.ES += lane_xor<2>(full.ES);
@@ -304,26 +309,24 @@ __device__ __forceinline__ void word_task(uint32_t *lat, const WordPhase &f, uin
         other.OS = lane_xor<Q / 2>(full.OS);
         other.EG = lane_xor<Q / 2>(full.EG);
         other.OG = lane_xor<Q / 2>(full.OG);
+        const bool side = q >= Q / 2;
         sa = side ? other : full;
         sb = side ? full : other;
     }
+}
 
-    const uint32_t call0 = (uint32_t)Y * (uint32_t)(Lq >> 1) + 8u * (uint32_t)j;
-    // code changes of pairs 4g .. 4g+3 in dacc[g]: a-sites in byte 2, b-sites
-    // in byte 3 (Q = 4: groups q/2 and q/2 + 2 in dacc[0] and [1]; Q = 8:
-    // group q/2 in dacc[0])
-    uint32_t dacc[Q <= 2 ? 4 : 8 / Q] = {}, packed = 0u;
-    u32x4 nxt[kTaskCalls<Q>];
-    if constexpr (Pipe == kDrawPipe) {
-#pragma unroll
-        for (int i = 0; i < kTaskCalls<Q>; ++i)
-            nxt[i] = pair_draws(philox4x32_10((uint32_t)ns, (uint32_t)np, call0 + (uint32_t)call_of_task<Q>(q, i),
-                                              (uint32_t)(ns >> 32), f.key0, f.key1));
-    }
+// The pair steps of a task on its words A0 and B0 (aligned) and their
+// neighbour sums: draw(i, c) gives Philox call c of the word, the task's i-th,
+// as pair_draws.  Barrier = true keeps the compiler from interleaving the
+// calls of a task (fewer live registers, needed at 1024 threads per block);
+// without it the calls overlap each other's table lookups.
+template <int Q, bool Barrier, typename F>
+__device__ __forceinline__ void task_steps(uint32_t A0, uint32_t B0, const SideSums &sa, const SideSums &sb, int q,
+                                           const uint2 *s_tab, const uint8_t *s_slots, uint32_t &packed,
+                                           uint32_t (&dacc)[Q <= 2 ? 4 : 8 / Q], F draw)
+{
     auto do_call = [&](int i, int c, uint32_t be, uint32_t bo, uint32_t &d) {
-        const u32x4 w = Pipe != kDrawInPlace ? pre[i]
-                                             : pair_draws(philox4x32_10(f.s_lo, (uint32_t)f.p, call0 + (uint32_t)c, f.s_hi,
-                                                                        f.key0, f.key1));
+        const u32x4 w = draw(i, c);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int t = 2 * c + h;
@@ -363,56 +366,90 @@ __device__ __forceinline__ void word_task(uint32_t *lat, const WordPhase &f, uin
                     gather_byte(rOS0, rOS1, rOG0, rOG1, sel), dacc[i]);
         }
     }
-    // the changes as words: 2-bit fields of the 16 a-sites and of the b-sites
-    uint32_t dA, dB;
-    if constexpr (Q <= 2) {
-        dA = __builtin_amdgcn_perm(__builtin_amdgcn_perm(dacc[3], dacc[2], 0x0C0C0602u),
-                                   __builtin_amdgcn_perm(dacc[1], dacc[0], 0x0C0C0602u), 0x05040100u);
-        dB = __builtin_amdgcn_perm(__builtin_amdgcn_perm(dacc[3], dacc[2], 0x0C0C0703u),
-                                   __builtin_amdgcn_perm(dacc[1], dacc[0], 0x0C0C0703u), 0x05040100u);
+}
+
+// A task on a lattice in LDS.  Pipe (where its Philox draws come from):
+// kDrawInPlace, computed here as they are used; kDrawPipe, this phase's given in
+// pre[] and those of the next phase (sweep ns, phase np) computed here,
+// between the phase's dependent LDS lookups, and returned in pre[].
+constexpr int kDrawInPlace = 0, kDrawPipe = 1;
+template <int Q, bool Barrier, int Pipe = kDrawInPlace>
+__device__ __forceinline__ void word_task(uint32_t *lat, const WordPhase &f, uint32_t task, const uint2 *s_tab,
+                                          const uint8_t *s_slots, int (&tr)[3], u32x4 *pre = nullptr,
+                                          uint64_t ns = 0, int np = 0)
+{
+    constexpr int LOGQ = Q == 1 ? 0 : Q == 2 ? 1 : Q == 4 ? 2 : 3;
+    const uint32_t wi = task >> LOGQ;
+    const int q = (int)(task & (uint32_t)(Q - 1));
+    const int W = f.W, H = f.H, Lq = f.Lq;
+    const int Y = W == 1 ? (int)wi : (int)__umulhi(wi, f.magicW), j = (int)wi - Y * W;
+    int Xb = 16 * j + f.dX;
+    if (Xb >= Lq) Xb -= Lq;
+    const int Yb = Y + f.k >= H ? Y + f.k - H : Y + f.k;
+    const int xAL = f.p > 0 ? 16 * j : (j == 0 ? Lq - 1 : 16 * j - 1);
+    const int xAR = f.p < 3 ? 16 * j : 16 * j + 1;
+    const int xBL = f.pb > 0 ? Xb : (Xb == 0 ? Lq - 1 : Xb - 1);
+    const int xBR = f.pb < 3 ? Xb : (Xb + 1 == Lq ? 0 : Xb + 1);
+    const uint32_t ro = (uint32_t)Y * W, rob = (uint32_t)Yb * W;
+    const uint32_t roU = (uint32_t)(Y == 0 ? H - 1 : Y - 1) * W;
+    const uint32_t robD = (uint32_t)(Yb + 1 == H ? 0 : Yb + 1) * W;
+
+    const uint32_t A0 = lat[f.oA0 + ro + j];
+    const uint32_t B0 = ld16(lat, f.oB0 + rob, W, Xb);
+    uint32_t n[8 / Q];
+    if constexpr (Q == 1) {
+        n[0] = ld16(lat, f.oAL + ro, W, xAL);
+        n[1] = ld16(lat, f.oAR + ro, W, xAR);
+        n[2] = lat[f.oAV + roU + j];
+        n[3] = lat[f.oAV + ro + j];
+        n[4] = ld16(lat, f.oBL + rob, W, xBL);
+        n[5] = ld16(lat, f.oBR + rob, W, xBR);
+        n[6] = ld16(lat, f.oBV + rob, W, Xb);
+        n[7] = ld16(lat, f.oBV + robD, W, Xb);
     } else {
-        const uint32_t last = Q == 4 ? dacc[8 / Q - 1] : 0u;
-        dA = __builtin_amdgcn_perm(last, dacc[0], 0x0C060C02u) << (8 * (q >> 1));
-        dB = __builtin_amdgcn_perm(last, dacc[0], 0x0C070C03u) << (8 * (q >> 1));
+        // The Q threads of a word are Q consecutive lanes, 8/Q words each.
+        const int side = q >= Q / 2;
+        const int k0 = (q % (Q / 2)) * (8 / Q);
+        const uint32_t base[4] = {side ? f.oBL + rob : f.oAL + ro, side ? f.oBR + rob : f.oAR + ro,
+                                  side ? f.oBV + rob : f.oAV + roU, side ? f.oBV + robD : f.oAV + ro};
+        const int xs[4] = {side ? xBL : xAL, side ? xBR : xAR, side ? Xb : 16 * j, side ? Xb : 16 * j};
+#pragma unroll
+        for (int i = 0; i < 8 / Q; ++i) {
+            const int kk = k0 + i;
+            const uint32_t b = kk == 0 ? base[0] : kk == 1 ? base[1] : kk == 2 ? base[2] : base[3];
+            const int x = kk == 0 ? xs[0] : kk == 1 ? xs[1] : kk == 2 ? xs[2] : xs[3];
+            n[i] = ld16(lat, b, W, x);
+        }
     }
+    SideSums sa, sb;
+    combine_sides<Q>(n, q, sa, sb);
+
+    const uint32_t call0 = (uint32_t)Y * (uint32_t)(Lq >> 1) + 8u * (uint32_t)j;
+    // code changes of pairs 4g .. 4g+3 in dacc[g]: a-sites in byte 2, b-sites
+    // in byte 3 (Q = 4: groups q/2 and q/2 + 2 in dacc[0] and [1]; Q = 8:
+    // group q/2 in dacc[0])
+    uint32_t dacc[Q <= 2 ? 4 : 8 / Q] = {}, packed = 0u;
+    u32x4 nxt[kTaskCalls<Q>];
+    if constexpr (Pipe == kDrawPipe) {
+#pragma unroll
+        for (int i = 0; i < kTaskCalls<Q>; ++i)
+            nxt[i] = pair_draws(philox4x32_10((uint32_t)ns, (uint32_t)np, call0 + (uint32_t)call_of_task<Q>(q, i),
+                                              (uint32_t)(ns >> 32), f.key0, f.key1));
+    }
+    task_steps<Q, Barrier>(A0, B0, sa, sb, q, s_tab, s_slots, packed, dacc, [&](int i, int c) {
+        return Pipe != kDrawInPlace ? pre[i]
+                                    : pair_draws(philox4x32_10(f.s_lo, (uint32_t)f.p, call0 + (uint32_t)c, f.s_hi, f.key0,
+                                                               f.key1));
+    });
+    uint32_t dA, dB;
+    task_changes<Q>(dacc, q, dA, dB);
     if constexpr (Pipe == kDrawPipe) {
 #pragma unroll
         for (int i = 0; i < kTaskCalls<Q>; ++i) pre[i] = nxt[i];
     }
     unpack_tracker(packed, tr);
     const int jb = Xb >> 4, shb = Xb & 15;
-    if constexpr (Combine) {
-        uint32_t cA = dA, cB = dB;
-        if constexpr (Q >= 2) {
-            cA |= lane_xor<1>(cA);
-            cB |= lane_xor<1>(cB);
-        }
-        if constexpr (Q >= 4) {
-            cA |= lane_xor<2>(cA);
-            cB |= lane_xor<2>(cB);
-        }
-        if constexpr (Q >= 8) {
-            cA |= lane_xor<4>(cA);
-            cB |= lane_xor<4>(cB);
-        }
-        if (q == 0) {
-            if constexpr (Obs) {
-                // staggered sign of a class (cx, cy): (-1)^(cx + cy); the
-                // a-class is (p, 0), the b-class (pb, 1)
-                const int gA = spin_sum16(A0 ^ cA) - spin_sum16(A0), gB = spin_sum16(B0 ^ cB) - spin_sum16(B0);
-                const int sA = charge_sum16(A0 ^ cA) - charge_sum16(A0);
-                const int sB = charge_sum16(B0 ^ cB) - charge_sum16(B0);
-                const bool nA = f.p & 1, nB = !(f.pb & 1);
-                dv[0] += gA + gB;
-                dv[1] += (nA ? -gA : gA) + (nB ? -gB : gB);
-                dv[2] += (nA ? -sA : sA) + (nB ? -sB : sB);
-            }
-            stw<Coh>(lat, f.oA0 + ro + j, A0 ^ cA);
-            atomicXor(&lat[f.oB0 + rob + (uint32_t)jb], cB << (2 * shb));
-            const uint32_t hi = shb ? cB >> (32 - 2 * shb) : 0u;
-            atomicXor(&lat[f.oB0 + rob + (uint32_t)(jb + 1 == W ? 0 : jb + 1)], hi);
-        }
-    } else if constexpr (!Barrier) {
+    if constexpr (!Barrier) {
         // unconditional (an XOR with 0 changes nothing): branches on the
         // masks cost more than the LDS operations they would skip
         if (Q == 1)
@@ -438,6 +475,153 @@ __device__ __forceinline__ void word_task(uint32_t *lat, const WordPhase &f, uin
             }
         }
     }
+}
+
+// The same task on a lattice in global memory, in three parts, so that a
+// persistent kernel can do the first before its device-wide barrier and issue
+// all loads at once after it:
+//   word_refs   where its words are (nothing of the lattice is read),
+//   word_fetch  the loads,
+//   word_apply  the pair steps and the stores.
+// The Q lanes of a word OR their code changes together (their fields are
+// disjoint), then the word's first lane stores the a-word, which no other
+// word reads or writes in the phase, and applies the two b-word changes as
+// atomics.  Every lane of a word must be active.
+// Coh: the words are read and written at device coherence (ldw/stw<true>).
+// Both words that cover 16 sites are always loaded: skipping the second where
+// the run starts on a word boundary put a branch and a wait before the next
+// load, and at L = 1024 a phase is a chain of latencies.
+template <int Q>
+struct WordRefs {
+    uint32_t a0, blo, bhi;                       // word indices of the a-word and of the two b-words
+    uint32_t lo[8 / Q], hi[8 / Q], sh[8 / Q];    // of this lane's neighbour words, and their shifts (bits)
+};
+template <int Q>
+struct WordVals {
+    uint32_t a0, blo, bhi, lo[8 / Q], hi[8 / Q];
+};
+
+template <int Q>
+__device__ __forceinline__ WordRefs<Q> word_refs(const WordPhase &f, uint32_t task)
+{
+    constexpr int LOGQ = Q == 1 ? 0 : Q == 2 ? 1 : Q == 4 ? 2 : 3;
+    const uint32_t wi = task >> LOGQ;
+    const int q = (int)(task & (uint32_t)(Q - 1));
+    const int W = f.W, H = f.H, Lq = f.Lq;
+    const int Y = W == 1 ? (int)wi : (int)__umulhi(wi, f.magicW), j = (int)wi - Y * W;
+    int Xb = 16 * j + f.dX;
+    if (Xb >= Lq) Xb -= Lq;
+    const int Yb = Y + f.k >= H ? Y + f.k - H : Y + f.k;
+    const uint32_t ro = (uint32_t)Y * W, rob = (uint32_t)Yb * W;
+    const uint32_t roU = (uint32_t)(Y == 0 ? H - 1 : Y - 1) * W;
+    const uint32_t robD = (uint32_t)(Yb + 1 == H ? 0 : Yb + 1) * W;
+    const int xAL = f.p > 0 ? 16 * j : (j == 0 ? Lq - 1 : 16 * j - 1);
+    const int xAR = f.p < 3 ? 16 * j : 16 * j + 1;
+    const int xBL = f.pb > 0 ? Xb : (Xb == 0 ? Lq - 1 : Xb - 1);
+    const int xBR = f.pb < 3 ? Xb : (Xb + 1 == Lq ? 0 : Xb + 1);
+    const uint32_t row[8] = {f.oAL + ro,  f.oAR + ro,  f.oAV + roU, f.oAV + ro,
+                             f.oBL + rob, f.oBR + rob, f.oBV + rob, f.oBV + robD};
+    const int x[8] = {xAL, xAR, 16 * j, 16 * j, xBL, xBR, Xb, Xb};
+    WordRefs<Q> r;
+    const int jb = Xb >> 4;
+    r.a0 = f.oA0 + ro + (uint32_t)j;
+    r.blo = f.oB0 + rob + (uint32_t)jb;
+    r.bhi = f.oB0 + rob + (uint32_t)(jb + 1 == W ? 0 : jb + 1);
+#pragma unroll
+    for (int i = 0; i < 8 / Q; ++i) {
+        // neighbour word q (8 / Q) + i, picked by the bits of q
+        uint32_t rw = 0;
+        int xw = 0;
+#pragma unroll
+        for (int n = i; n < 8; n += 8 / Q)
+            if (Q == 1 || n / (8 / Q) == 0 || q == n / (8 / Q)) {
+                rw = row[n];
+                xw = x[n];
+            }
+        const int jw = xw >> 4;
+        r.lo[i] = rw + (uint32_t)jw;
+        r.hi[i] = rw + (uint32_t)(jw + 1 == W ? 0 : jw + 1);
+        r.sh[i] = 2u * (uint32_t)(xw & 15);
+    }
+    return r;
+}
+
+template <int Q, bool Coh>
+__device__ __forceinline__ WordVals<Q> word_fetch(const uint32_t *lat, const WordRefs<Q> &r)
+{
+    WordVals<Q> v;
+    v.a0 = ldw<Coh>(lat, r.a0);
+    v.blo = ldw<Coh>(lat, r.blo);
+    v.bhi = ldw<Coh>(lat, r.bhi);
+#pragma unroll
+    for (int i = 0; i < 8 / Q; ++i) {
+        v.lo[i] = ldw<Coh>(lat, r.lo[i]);
+        v.hi[i] = ldw<Coh>(lat, r.hi[i]);
+    }
+    return v;
+}
+
+// Returns the packed triples of the accepted moves (for unpack_tracker).
+// Obs: the word's first lane also adds the changes of the spin sum, the
+// staggered spin sum and the staggered charge sum over the word's a-sites and
+// b-sites to dv[0..2] (the other observable sums are the tracker's: the
+// charged-site count and the two bond sums change by exactly the accepted
+// energy-change triples, and the charge sum does not change).
+template <int Q, bool Coh, bool Obs>
+__device__ __forceinline__ uint32_t word_apply(uint32_t *lat, const WordPhase &f, const WordRefs<Q> &r,
+                                               const WordVals<Q> &v, int q, const u32x4 *draws, const uint2 *s_tab,
+                                               const uint8_t *s_slots, int *dv)
+{
+    const uint32_t shb = 2u * (uint32_t)(f.dX & 15);  // Xb mod 16 is the same for every word
+    const uint32_t A0 = v.a0, B0 = __builtin_amdgcn_alignbit(v.bhi, v.blo, shb);
+    uint32_t n[8 / Q];
+#pragma unroll
+    for (int i = 0; i < 8 / Q; ++i) n[i] = __builtin_amdgcn_alignbit(v.hi[i], v.lo[i], r.sh[i]);
+    SideSums sa, sb;
+    combine_sides<Q>(n, q, sa, sb);
+    uint32_t dacc[Q <= 2 ? 4 : 8 / Q] = {}, packed = 0u, cA, cB;
+    task_steps<Q, false>(A0, B0, sa, sb, q, s_tab, s_slots, packed, dacc, [&](int i, int) { return draws[i]; });
+    task_changes<Q>(dacc, q, cA, cB);
+    if constexpr (Q >= 2) {
+        cA |= lane_xor<1>(cA);
+        cB |= lane_xor<1>(cB);
+    }
+    if constexpr (Q >= 4) {
+        cA |= lane_xor<2>(cA);
+        cB |= lane_xor<2>(cB);
+    }
+    if constexpr (Q >= 8) {
+        cA |= lane_xor<4>(cA);
+        cB |= lane_xor<4>(cB);
+    }
+    if (q == 0) {
+        stw<Coh>(lat, r.a0, A0 ^ cA);
+        xorw(lat, r.blo, cB << shb);
+        xorw(lat, r.bhi, shb ? cB >> (32u - shb) : 0u);
+        if constexpr (Obs) {
+            // staggered sign of a class (cx, cy): (-1)^(cx + cy); the
+            // a-class is (p, 0), the b-class (pb, 1)
+            const int gA = spin_sum16(A0 ^ cA) - spin_sum16(A0), gB = spin_sum16(B0 ^ cB) - spin_sum16(B0);
+            const int sA = charge_sum16(A0 ^ cA) - charge_sum16(A0);
+            const int sB = charge_sum16(B0 ^ cB) - charge_sum16(B0);
+            const bool nA = f.p & 1, nB = !(f.pb & 1);
+            dv[0] += gA + gB;
+            dv[1] += (nA ? -gA : gA) + (nB ? -gB : gB);
+            dv[2] += (nA ? -sA : sA) + (nB ? -sB : sB);
+        }
+    }
+    return packed;
+}
+
+// The Philox draws of a task (phase p of sweep s), from its word's first call.
+template <int Q>
+__device__ __forceinline__ void word_draws(uint32_t call0, int q, uint64_t s, int p, uint32_t key0, uint32_t key1,
+                                           u32x4 (&draws)[kTaskCalls<Q>])
+{
+#pragma unroll
+    for (int i = 0; i < kTaskCalls<Q>; ++i)
+        draws[i] = pair_draws(philox4x32_10((uint32_t)s, (uint32_t)p, call0 + (uint32_t)call_of_task<Q>(q, i),
+                                            (uint32_t)(s >> 32), key0, key1));
 }
 
 }  // namespace

@@ -6,8 +6,10 @@
 // thread per word (16 pairs each, as in the large-lattice phase kernel)
 // leaves most of the chip idle and puts 16 dependent pair steps on the
 // critical path.  Here Q lanes share a word (word_task.h), a lattice spreads
-// over many 256-thread blocks, and one launch can hold several lattices
-// (the server's large requests), each at its own sweep.  The schedule of a
+// over many blocks, and one launch can hold several lattices, each at its own
+// sweep.  What bounds these sizes is the chain of a phase: the loads of words
+// that other compute units wrote, two dependent table gathers, the stores,
+// and the meeting of all blocks.  The schedule of a
 // sweep is computed on the device from the lattice's seed and sweep index,
 // so a series of launches does not depend on host state and can be
 // replayed from a HIP graph.
@@ -33,7 +35,7 @@ __global__ void __launch_bounds__(kWordsPhaseMaxThreads) k_phase_words(WordsArgs
     if (a.iter >= a.sweeps[li]) return;  // the whole block: no barrier is skipped by part of it
     uint8_t *scr = a.scratch[li];
     const LatDesc d = *(const LatDesc *)(scr + kScrDesc);
-    uint32_t *st = d.enc == 1 ? (uint32_t *)d.state : (uint32_t *)(scr + kScrWork);
+    uint32_t *st = (uint32_t *)(d.enc == 1 ? d.state : (void *)(scr + kScrWork));
     {
         const uint2 *g_tab = (const uint2 *)(scr + kScrDevTab);
         for (int i = threadIdx.x; i < kDevTabEntries; i += blockDim.x) s_tab[i] = g_tab[i];
@@ -52,27 +54,49 @@ __global__ void __launch_bounds__(kWordsPhaseMaxThreads) k_phase_words(WordsArgs
     const uint32_t task = b * blockDim.x + threadIdx.x;
     int tr[3] = {0, 0, 0};
     // tasks = Q * csz is a multiple of Q, so a word's lanes are all in or all out
-    if (task < (uint32_t)Q * csz) word_task<Q, false, kDrawInPlace, true>(st, f, task, s_tab, (const uint8_t *)s_slots, tr);
+    if (task < (uint32_t)Q * csz) {
+        const WordRefs<Q> r = word_refs<Q>(f, task);
+        const WordVals<Q> v = word_fetch<Q, false>(st, r);
+        const int q = (int)(task & (uint32_t)(Q - 1));
+        u32x4 draws[kTaskCalls<Q>];
+        word_draws<Q>(task_call0<Q>(f, task), q, s, a.p, d.key0, d.key1, draws);
+        unpack_tracker(word_apply<Q, false, false>(st, f, r, v, q, draws, s_tab, (const uint8_t *)s_slots, nullptr), tr);
+    }
     block_reduce_add<3>(tr, (unsigned long long *)(scr + kScrSlots) + 3 * (size_t)b);
 }
 
-// Adds the block's sums of m (per thread: tracker moves 0-2, spin,
-// staggered spin and staggered charge moves 3-5) to an observation record
-// (tracker 0-2, sums 3-9): m[0..2] to fields 0-2 and 4-6, m[3..5] to 7-9.
-__device__ __forceinline__ void add_record_moves(long long (&m)[6], unsigned long long *rec)
+// Block sums of m (per thread: tracker moves 0-2, spin, staggered spin and
+// staggered charge moves 3-5 of an interval): thread i < 6 gets sum i.  Below
+// kNarrowSweeps sweeps an interval a wave's sums fit 32 bits.
+constexpr uint32_t kNarrowSweeps = 16384;  // 64 lanes x 4 phases x 16 pairs x at most 16 a pair
+__device__ __forceinline__ long long block_moves(const int (&m)[6], bool narrow)
 {
     __shared__ long long part[16][6];
-    wave_partials<6, long long>(m, part);
-    __syncthreads();
-    if (threadIdx.x < 9) {
-        const int i = threadIdx.x < 6 ? (int)threadIdx.x % 3 : (int)threadIdx.x - 3;
-        const int field = threadIdx.x < 3 ? (int)threadIdx.x : (int)threadIdx.x + 1;
-        const int nw = (int)(blockDim.x >> 6);
-        long long sum = 0;
-        for (int w = 0; w < nw; ++w) sum += part[w][i];
-        if (sum != 0) atomicAdd(&rec[field], (unsigned long long)sum);
+    const int wave = threadIdx.x >> 6, nw = (int)(blockDim.x >> 6);
+    if (narrow) {
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            const int v = dpp_step_sum(m[i]);
+            if ((threadIdx.x & 63u) == 0) part[wave][i] = v;
+        }
+    } else {
+        long long v[6] = {m[0], m[1], m[2], m[3], m[4], m[5]};
+        wave_partials<6, long long>(v, part);
     }
-    __syncthreads();  // part is reused at the next interval
+    __syncthreads();
+    long long sum = 0;
+    if (threadIdx.x < 6)
+        for (int w = 0; w < nw; ++w) sum += part[w][threadIdx.x];
+    return sum;  // the barrier after it comes before part is written again
+}
+// Adds sum i (of block_moves) to its fields of a record (tracker 0-2, sums
+// 3-9): the tracker moves to the tracker and to the charged-site count and
+// the two bond sums, the others to the last three sums.
+__device__ __forceinline__ void add_to_record(unsigned long long *rec, int i, long long sum)
+{
+    if (sum == 0) return;
+    if (i < 3) atomicAdd(&rec[i], (unsigned long long)sum);
+    atomicAdd(&rec[i + 4], (unsigned long long)sum);
 }
 
 // Persistent form: the sweeps of a whole call of up to kWordsBatch lattices,
@@ -80,24 +104,27 @@ __device__ __forceinline__ void add_record_moves(long long (&m)[6], unsigned lon
 // co-resident blocks (cooperative launch); blocks first_block[i] ..
 // first_block[i+1]-1 update lattice i.  Tables are staged once; every phase
 // is one grid-stride pass over each lattice's a-word tasks by its own blocks,
-// followed by a device-wide barrier of all blocks.  Sweep it of the launch
-// (interval k, sweep e of it: it = k every + e) is sweep next_sweep + it of
-// every lattice with sweeps[i] > it; the blocks of the others only meet the
-// barriers.  All lattice words are read and written at device coherence, so
+// followed by a device-wide barrier of those blocks (the lattices do not
+// wait for each other, and one with fewer sweeps ends earlier).  Sweep it of
+// the launch (interval k, sweep e of it: it = k every + e) is sweep
+// next_sweep + it.  All lattice words are read and written at device coherence, so
 // the barrier needs no cache write-back or invalidation (measured on MI355X
 // with 128 blocks: 2.3 us a barrier, against 6.9 us with one release/acquire
 // fence pair per block and 12-14 us with a fence pair in every wave).
 //
 // Obs (a series with records, one lattice): the records start as the
 // lattice's state before the launch (k_series_init: tracker total and the
-// seven sums), and at the end of interval k every block adds its moves since
-// the launch began to record k: its tracker sums (to the tracker and to the
-// charged-site count and the two bond sums, which change by exactly them)
-// and the spin, staggered spin and staggered charge moves of the words it
-// wrote.  The lattice is not read for the records, so no barrier beyond the
-// phases' is needed; the records are whole when the launch ends.
+// seven sums), and at the end of interval k the moves of all blocks since the
+// launch began are added to record k: the tracker sums (to the tracker and to
+// the charged-site count and the two bond sums, which change by exactly them)
+// and the spin, staggered spin and staggered charge moves of the words they
+// wrote.  With one counter every block adds its own; with two levels the
+// blocks of a group add up first (32 blocks at an address instead of 256),
+// and the thread that completes the group adds its sums to the record while
+// the others wait at the barrier.  The lattice is not read for the records, so
+// no barrier beyond the phases' is needed; they are whole when the launch ends.
 template <int Q, bool Obs>
-__global__ void __launch_bounds__(kWordsThreads) k_words_series(WordsSeriesArgs a)
+__global__ void __launch_bounds__(Q >= 4 ? kWordsSeriesMaxThreads : kWordsThreads) k_words_series(WordsSeriesArgs a)
 {
     __shared__ uint2 s_tab[kDevTabEntries];
     __shared__ __align__(16) uint2 s_slots[kSlotEntries];
@@ -105,7 +132,7 @@ __global__ void __launch_bounds__(kWordsThreads) k_words_series(WordsSeriesArgs 
     while (li + 1 < a.count && blockIdx.x >= a.first_block[li + 1]) ++li;
     uint8_t *scr = a.scratch[li];
     const LatDesc d = *(const LatDesc *)(scr + kScrDesc);
-    uint32_t *st = d.enc == 1 ? (uint32_t *)d.state : (uint32_t *)(scr + kScrWork);
+    uint32_t *st = (uint32_t *)(d.enc == 1 ? d.state : (void *)(scr + kScrWork));
     {
         const uint2 *g_tab = (const uint2 *)(scr + kScrDevTab);
         for (int i = threadIdx.x; i < kDevTabEntries; i += blockDim.x) s_tab[i] = g_tab[i];
@@ -113,80 +140,115 @@ __global__ void __launch_bounds__(kWordsThreads) k_words_series(WordsSeriesArgs 
         for (int i = threadIdx.x; i < kSlotEntries; i += blockDim.x) s_slots[i] = g_slots[i];
     }
     __syncthreads();
-    unsigned *counter = (unsigned *)(a.scratch[0] + kScrBarrier), *err = (unsigned *)(scr + kScrErr);
     const uint32_t b = blockIdx.x - a.first_block[li], nb = a.first_block[li + 1] - a.first_block[li];
+    GridBarrier barrier{(unsigned *)(scr + kScrObsSlots), b, nb, 0u, false};
+    unsigned *err = (unsigned *)(scr + kScrErr);
     const uint32_t my_sweeps = a.sweeps[li];
     const uint32_t csz = (uint32_t)(d.L >> 1) * (uint32_t)(d.L >> 6);
     const uint32_t n_tasks = (uint32_t)Q * csz, stride = nb * blockDim.x;
     const uint32_t first = b * blockDim.x + threadIdx.x;
-    // At most one task a thread (uniform per lattice): its Philox draws for
-    // the next phase are made while the block waits at the barrier, where
-    // they depend on nothing the other blocks write.
+    // At most one task a thread (uniform per lattice): its Philox draws for the
+    // next phase and the places of its words are made while the block waits
+    // at the barrier, where they depend on nothing the other blocks write.
     const bool one = stride >= n_tasks, mine = one && first < n_tasks;
     const int q = (int)(first & (uint32_t)(Q - 1));
     u32x4 pre[kTaskCalls<Q>];
-    uint32_t c0 = 0;
-    auto draws = [&](uint64_t s, int p) {
-#pragma unroll
-        for (int i = 0; i < kTaskCalls<Q>; ++i)
-            pre[i] = pair_draws(philox4x32_10((uint32_t)s, (uint32_t)p, c0 + (uint32_t)call_of_task<Q>(q, i),
-                                              (uint32_t)(s >> 32), d.key0, d.key1));
-    };
+    WordRefs<Q> refs{};
+    WordPhase f;
     int r, mm[4], kk[4];
     device_schedule(d.L, d.key0, d.key1, d.next_sweep, r, mm, kk);
+    word_phase_setup(f, d.L, d.key0, d.key1, d.next_sweep, 0, r, mm, kk);
+    const uint32_t c0 = task_call0<Q>(f, mine ? first : 0u);
     if (mine && my_sweeps > 0) {
-        WordPhase f0;
-        word_phase_setup(f0, d.L, d.key0, d.key1, d.next_sweep, 0, r, mm, kk);
-        c0 = task_call0<Q>(f0, first);
-        draws(d.next_sweep, 0);
+        word_draws<Q>(c0, q, d.next_sweep, 0, d.key0, d.key1, pre);
+        refs = word_refs<Q>(f, first);
     }
     int tr[3] = {0, 0, 0};
-    int dv[3] = {0, 0, 0};  // Obs: spin, staggered spin, staggered charge moves
-    unsigned arrivals = 0;
+    int dv[3] = {0, 0, 0};  // Obs: spin, staggered spin, staggered charge moves of the interval
+    long long moves = 0;    // Obs, thread i < 6: the block's sum i of the intervals before
+    // one interval of the lattice's own number of sweeps, or (with records)
+    // intervals of `every` sweeps, which make up that number
+    const uint32_t every = a.records ? a.every : my_sweeps;
     for (uint32_t k = 0; k < a.intervals; ++k) {
-        for (uint32_t e = 0; e < a.every; ++e) {
-            const uint32_t it = k * a.every + e;
+        for (uint32_t e = 0; e < every; ++e) {
+            const uint32_t it = k * every + e;
             const uint64_t s = d.next_sweep + it;
             for (int p = 0; p < 4; ++p) {
-                if (it < my_sweeps) {
-                    WordPhase f;
-                    word_phase_setup(f, d.L, d.key0, d.key1, s, p, r, mm, kk);
+                uint32_t packed = 0u;
+                {
+                    const uint8_t *slots = (const uint8_t *)s_slots;
                     if (one) {
-                        if (mine)
-                            word_task<Q, false, kDrawGiven, true, true, Obs>(st, f, first, s_tab, (const uint8_t *)s_slots, tr, pre, 0,
-                                                                             0, dv);
+                        if (mine) {
+                            const WordVals<Q> v = word_fetch<Q, true>(st, refs);
+                            packed = word_apply<Q, true, Obs>(st, f, refs, v, q, pre, s_tab, slots, dv);
+                        }
                     } else {
                         // stride is a multiple of Q: a word's lanes are all in or all out
-                        for (uint32_t t = first; t < n_tasks; t += stride)
-                            word_task<Q, false, kDrawInPlace, true, true, Obs>(st, f, t, s_tab, (const uint8_t *)s_slots, tr, nullptr,
-                                                                               0, 0, dv);
+                        for (uint32_t t = first; t < n_tasks; t += stride) {
+                            const WordRefs<Q> at = word_refs<Q>(f, t);
+                            const WordVals<Q> v = word_fetch<Q, true>(st, at);
+                            word_draws<Q>(task_call0<Q>(f, t), q, s, p, d.key0, d.key1, pre);
+                            unpack_tracker(word_apply<Q, true, Obs>(st, f, at, v, q, pre, s_tab, slots, dv), tr);
+                        }
                     }
                 }
+                if (Obs) unpack_tracker(packed, tr);
+                unsigned long long *rec = nullptr;  // Obs: the record that this phase completes
                 if constexpr (Obs) {
-                    if (p == 3 && e + 1 == a.every) {
-                        unsigned long long *rec =
-                            (unsigned long long *)(a.records + (kSeriesRecord / 8) * (size_t)k);
-                        long long m[6] = {tr[0], tr[1], tr[2], dv[0], dv[1], dv[2]};
-                        add_record_moves(m, rec);
+                    if (p == 3 && e + 1 == every) {
+                        rec = (unsigned long long *)(a.records + (kSeriesRecord / 8) * (size_t)k);
+                        const int m[6] = {tr[0], tr[1], tr[2], dv[0], dv[1], dv[2]};
+                        const long long sum = block_moves(m, every <= kNarrowSweeps);
+                        if (threadIdx.x < 6) {
+                            moves += sum;
+                            if (barrier.flat())
+                                add_to_record(rec, (int)threadIdx.x, moves);
+                            else if (sum != 0)
+                                atomicAdd(barrier.sums() + threadIdx.x, (unsigned long long)sum);
+                        }
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) tr[i] = dv[i] = 0;
                         if (b == 0 && threadIdx.x == 0)
-                            rec[10] = (unsigned long long)(d.next_sweep + (uint64_t)(k + 1) * a.every);
+                            rec[10] = (unsigned long long)(d.next_sweep + (uint64_t)(k + 1) * every);
                     }
                 }
-                arrivals += gridDim.x;
-                grid_arrive_coherent(counter);
-                // the next phase's schedule and draws, while the others arrive
+                const bool last = barrier.arrive();
+                if (Obs && rec && last) {
+                    long long g[6];
+#pragma unroll
+                    for (int i = 0; i < 6; ++i)
+                        g[i] = (long long)__hip_atomic_load(barrier.sums() + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                    for (int i = 0; i < 6; ++i) add_to_record(rec, i, g[i]);
+                }
+                // the next phase's schedule, draws and places, while the others arrive
+                if (!Obs) unpack_tracker(packed, tr);
                 const uint32_t it_next = p < 3 ? it : it + 1;
                 const uint64_t s_next = p < 3 ? s : s + 1;
                 if (p == 3) device_schedule(d.L, d.key0, d.key1, s_next, r, mm, kk);
-                if (mine && it_next < my_sweeps) draws(s_next, p < 3 ? p + 1 : 0);
-                grid_wait_coherent(counter, arrivals, err, a.barrier_ticks);
+                word_phase_setup(f, d.L, d.key0, d.key1, s_next, p < 3 ? p + 1 : 0, r, mm, kk);
+                if (mine && it_next < my_sweeps) {
+                    word_draws<Q>(c0, q, s_next, p < 3 ? p + 1 : 0, d.key0, d.key1, pre);
+                    refs = word_refs<Q>(f, first);
+                }
+                barrier.wait(err, a.barrier_ticks);
             }
         }
     }
+    if (Obs && threadIdx.x < 3) atomicAdd((unsigned long long *)(scr + kScrSlots) + 3 * (size_t)b + threadIdx.x, (unsigned long long)moves);
     block_reduce_add<3>(tr, (unsigned long long *)(scr + kScrSlots) + 3 * (size_t)b);
     // every block read the descriptor before its first barrier
-    if (b == 0 && threadIdx.x == 0 && arrivals > 0)
+    if (b == 0 && threadIdx.x == 0 && barrier.rounds > 0)
         ((LatDesc *)(scr + kScrDesc))->next_sweep = d.next_sweep + my_sweeps;
+}
+
+// Every lattice's barrier words, which live in its scratch, in the observable
+// slots (they hold nothing between calls).
+static_assert(kScrObsSlots % 128 == 0 && kBarrierWords * 4u <= (size_t)kMaxObsSlots * 56u, "barrier words");
+__global__ void __launch_bounds__(256) k_clear_barriers(WordsSeriesArgs a)
+{
+    unsigned *w = (unsigned *)(a.scratch[blockIdx.x] + kScrObsSlots);
+    for (unsigned i = threadIdx.x; i < kBarrierWords; i += blockDim.x) w[i] = 0u;
 }
 
 // Records of a series before it runs: the tracker total so far (slots and
@@ -195,7 +257,7 @@ __global__ void __launch_bounds__(kWordsThreads) k_words_series(WordsSeriesArgs 
 __global__ void __launch_bounds__(1024) k_series_init(const uint8_t *scr, long long *records, uint32_t intervals)
 {
     const LatDesc d = *(const LatDesc *)(scr + kScrDesc);
-    const uint32_t *st = d.enc == 1 ? (const uint32_t *)d.state : (const uint32_t *)(scr + kScrWork);
+    const uint32_t *st = (uint32_t *)(d.enc == 1 ? d.state : (void *)(scr + kScrWork));
     long long t3[3] = {0, 0, 0};
     const long long *slots = (const long long *)(scr + kScrSlots);
     for (int i = threadIdx.x; i < kMaxSlots; i += blockDim.x) {
@@ -347,8 +409,8 @@ int words_persistent_capacity(int Q, int threads)
 
 hipError_t launch_words_series(const WordsSeriesArgs &a, int Q, hipStream_t s)
 {
-    // the launch's barrier counter lives in the first lattice's scratch
-    hipError_t e = launch_zero_i64((unsigned long long *)(a.scratch[0] + kScrBarrier), 1, s);
+    hipLaunchKernelGGL(k_clear_barriers, dim3((unsigned)a.count), dim3(256), 0, s, a);
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (a.records) {
         hipLaunchKernelGGL(k_series_init, dim3(1), dim3(1024), 0, s, (const uint8_t *)a.scratch[0], a.records,
