@@ -187,7 +187,7 @@ def write_counter_summary(out_md, csvs, trace_stats=None):
             name = re.sub(r"\(.*", "", r["Kernel_Name"].replace("lat::(anonymous namespace)::", "").replace("void ", ""))
             vals[name][r["Counter_Name"]].append(float(r["Counter_Value"]))
     lines = ["| kernel | counter | dispatches | mean per dispatch |", "|---|---|---|---|"]
-    keep = ("k_phase_2bit", "k_sweep_lds_w", "k_obs_2bit", "k_obs_batch", "k_fold_sums")
+    keep = ("k_phase_2bit", "k_sweep_quad", "k_sweep_lds", "k_obs_2bit", "k_obs_batch", "k_fold_sums")
     for k in sorted(v for v in vals if v.startswith(keep)):
         for c in sorted(vals[k]):
             v = vals[k][c]

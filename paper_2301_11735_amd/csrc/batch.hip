@@ -8,6 +8,7 @@
 #include <type_traits>
 
 #include "device_common.h"
+#include "onchip.h"
 #include "word_task.h"
 
 namespace lat {
@@ -79,24 +80,6 @@ __device__ __forceinline__ void unstage_lattice(const uint32_t *lat, const LatDe
     }
 }
 
-// This thread's share of a lattice's tracker slots (phase kernels) and, for
-// thread 0, its tracker base (single-block kernels).
-__device__ __forceinline__ void tracker_partial(const uint8_t *scr, long long (&t3)[3])
-{
-    const long long *slots = (const long long *)(scr + kScrSlots);
-    for (int i = threadIdx.x; i < kMaxSlots; i += blockDim.x) {
-        t3[0] += slots[3 * i];
-        t3[1] += slots[3 * i + 1];
-        t3[2] += slots[3 * i + 2];
-    }
-    if (threadIdx.x == 0) {
-        const long long *base = (const long long *)(scr + kScrTrackBase);
-        t3[0] += base[0];
-        t3[1] += base[1];
-        t3[2] += base[2];
-    }
-}
-
 // ---------------------------------------------------------------------------
 // Per-site form, one byte per site in LDS (row-major), for lattices of any
 // side up to kSiteMaxL.  A site's byte is (1 + S) | (1 + sigma) << 4, so that
@@ -121,8 +104,6 @@ __device__ __forceinline__ void tracker_partial(const uint8_t *scr, long long (&
 // 50 sweeps 521 -> 247 us; 12 of L = 300, 20 sweeps 1295 -> 726 us.
 
 constexpr uint32_t kSiteHash = 0x2B298945u;  // (byte_a | byte_b << 8) -> 4 distinct top bits for the 16 states
-constexpr uint32_t site_byte(int code) { return code == 0 ? 0x21u : code == 1 ? 0x01u : code == 2 ? 0x12u : 0x10u; }
-static_assert((site_byte(0) | site_byte(1) << 8 | site_byte(2) << 16 | site_byte(3) << 24) == kSiteBytes, "site bytes");
 
 constexpr TransSlots make_site_slots()
 {
@@ -155,14 +136,6 @@ __device__ const TransSlots kSiteSlots = make_site_slots();
 // Pairs a phase up to which a thread takes one pair: two waves a SIMD, whose
 // repeated draws still fit into the chain of a phase.
 constexpr uint32_t kSiteOnePair = 512;
-constexpr uint32_t kSchedSweeps = 16;   // sweeps whose schedule words are made at once
-
-// Four site bytes to four codes (one a byte).
-__device__ __forceinline__ uint32_t codes_from_site(uint32_t e)
-{
-    const uint32_t one = 0x01010101u;
-    return ((e >> 3) & (one << 1)) | (~((e >> 5) | (e >> 1)) & one);  // charged; sigma = -1 or S = -1
-}
 
 __device__ __forceinline__ void stage_sites(uint32_t *lat, const LatDesc &d)
 {
@@ -280,8 +253,7 @@ __device__ __forceinline__ void site_step(uint8_t *lat, const SitePos &s, const 
     const uint32_t t = na | nb << 8, x = ea | eb << 8;
     const uint32_t bpack = (t & 0x0F0Fu) | (t & 0xF0F0u) << 12;
     const uint2 tr = *(const uint2 *)(s_trans + ((((x * kSiteHash) >> 21) & 0x780u) | dr.slot8));
-    const uint32_t idx = (uint32_t)__builtin_amdgcn_sdot4((int)tr.x, (int)bpack, (int)tr.y, false);
-    const uint2 e = *(const uint2 *)(s_tab + (uint32_t)(uint16_t)(idx << 3));
+    const uint2 e = *(const uint2 *)(s_tab + tab_offset(tr, bpack));
     const bool acc = dr.ua < e.x;
     packed += acc ? e.y : 0u;
     const uint32_t nw = acc ? tr.y >> 16 : x;
@@ -289,35 +261,20 @@ __device__ __forceinline__ void site_step(uint8_t *lat, const SitePos &s, const 
     lat[q.b] = (uint8_t)(nw >> 8);
 }
 
-// Displacements of a sweep's four phases from its schedule words (uniform).
+// Displacements of a sweep's four phases (uniform).
 struct SiteSchedule {
     uint32_t Dx[4], DyL[4];
 };
 __device__ __forceinline__ SiteSchedule site_schedule(const uint32_t *Wd, uint32_t L)
 {
-    uint32_t w[9];
-#pragma unroll
-    for (int i = 0; i < 9; ++i) w[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)Wd[i]);
-    const uint32_t r = 1u + (((w[0] >> 8) * 3u) >> 24);
+    const SweepWords w = sweep_words(Wd, L);
     SiteSchedule o;
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
-        o.Dx[p] = r + 4u * mulhi_u32(w[1 + 2 * p], L >> 2);
-        o.DyL[p] = (1u + 2u * mulhi_u32(w[2 + 2 * p], L >> 1)) * L;
+        o.Dx[p] = w.r + 4u * w.m[p];
+        o.DyL[p] = (1u + 2u * w.k[p]) * L;
     }
     return o;
-}
-// Schedule words of up to kSchedSweeps sweeps from s on, one Philox call a thread.
-__device__ __forceinline__ void make_schedules(uint32_t *sched, uint64_t s, uint32_t sweeps, const LatDesc &d)
-{
-    const uint32_t t = threadIdx.x;
-    if (t >= 3u * min(kSchedSweeps, sweeps)) return;
-    const uint64_t q = s + t / 3u;
-    const u32x4 w = philox4x32_10((uint32_t)q, kDomSchedule, t % 3u, (uint32_t)(q >> 32), d.key0, d.key1);
-    sched[4u * t] = w.x;
-    sched[4u * t + 1u] = w.y;
-    sched[4u * t + 2u] = w.z;
-    sched[4u * t + 3u] = w.w;
 }
 
 // `intervals` times `every` sweeps of the lattice in LDS from sweep first on,
@@ -333,7 +290,7 @@ __device__ __forceinline__ void site_sweeps(uint8_t *lat, uint32_t *sched, const
     const uint32_t magicLq = Lq == 1u ? 0u : 0xFFFFFFFFu / Lq + 1u;
     const uint32_t tasks = N / (8u * PP), n = intervals * every;
     const bool mine = threadIdx.x < tasks;
-    make_schedules(sched, first, n, d);
+    make_schedules(sched, first, n, d.key0, d.key1);
     __syncthreads();
     SiteSchedule sc = site_schedule(sched, L);
     SitePos pos[PP];
@@ -359,7 +316,7 @@ __device__ __forceinline__ void site_sweeps(uint8_t *lat, uint32_t *sched, const
             // buffer that was last read a sweep or more ago
             const uint32_t j = i + 1u;
             if (P == 0 && j % kSchedSweeps == 0 && j < n)
-                make_schedules(sched + 12u * (j % (2u * kSchedSweeps)), s + 1, n - j, d);
+                make_schedules(sched + 12u * (j % (2u * kSchedSweeps)), s + 1, n - j, d.key0, d.key1);
             if (P == 3) next = site_schedule(sched + 12u * (j % (2u * kSchedSweeps)), L);
             if (One) {
                 if (mine) {
@@ -409,7 +366,7 @@ __device__ __forceinline__ void site_observables(const uint32_t *lat, uint32_t L
     for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
         const uint32_t y = i / Lq, X = i - y * Lq, w = lat[i];
         const uint32_t w1 = lat[X + 1u == Lq ? i + 1u - Lq : i + 1u];
-        sums.add(w, __builtin_amdgcn_alignbit(w1, w, 8u), lat[y + 1u == L ? X : i + Lq], y);
+        sums.add(w, __builtin_amdgcn_alignbit(w1, w, 8u), lat[y + 1u == L ? X : i + Lq], row_signs(y));
     }
     sums.get(v);
 }
@@ -419,8 +376,7 @@ __global__ void __launch_bounds__(1024) k_sweep_site(BatchArgs args)
     __shared__ __align__(16) uint2 s_tab[kDevTabEntries + 1];
     __shared__ __align__(16) uint32_t s_trans[2 * 256];
     __shared__ uint32_t sched[2 * 12 * kSchedSweeps];
-    __shared__ int part[16][10];
-    __shared__ long long base[3];
+    __shared__ ObsStage obs;
     extern __shared__ uint32_t lat[];
     uint8_t *scr = args.scratch[blockIdx.x];
     const LatDesc d = *(const LatDesc *)(scr + kScrDesc);
@@ -430,12 +386,7 @@ __global__ void __launch_bounds__(1024) k_sweep_site(BatchArgs args)
         for (int i = threadIdx.x; i < 2 * 256; i += blockDim.x) s_trans[i] = kSiteSlots.v[i];
     }
     stage_sites(lat, d);
-    if (args.obs_out) {
-        // the tracker total before this launch
-        long long t3[3] = {0, 0, 0};
-        tracker_partial(scr, t3);
-        block_reduce_store<3>(t3, base);
-    }
+    if (args.obs_out) tracker_before(scr, obs);
     __syncthreads();
 
     const uint32_t L = (uint32_t)d.L, N = L * L, my_sweeps = args.sweeps[blockIdx.x];
@@ -443,25 +394,11 @@ __global__ void __launch_bounds__(1024) k_sweep_site(BatchArgs args)
     const bool single = N / 8u <= min(blockDim.x, kSiteOnePair), one = N / 16u <= blockDim.x;
     const uint8_t *tab = (const uint8_t *)s_tab, *trans = (const uint8_t *)s_trans;
     int tr[3] = {0, 0, 0};
-    // no other wave writes the lattice or `part` before the next block barrier
-    // of the sweeps, and there are four of those between two intervals
     auto observe = [&](uint32_t k) {
         if (!args.obs_out) return;
-        int v[10] = {tr[0], tr[1], tr[2]};
         int o[7];
         site_observables(lat, L, o);
-#pragma unroll
-        for (int q = 0; q < 7; ++q) v[3 + q] = o[q];
-        wave_partials<10, int>(v, part);
-        __syncthreads();
-        unsigned long long *rec =
-            args.obs_out + (size_t)args.obs_stride * k + (size_t)args.obs_words * blockIdx.x;
-        if (threadIdx.x < 10) {
-            long long sum = threadIdx.x < 3 ? base[threadIdx.x] : 0ll;
-            for (uint32_t w = 0; w < blockDim.x >> 6; ++w) sum += (long long)part[w][threadIdx.x];
-            rec[threadIdx.x] = (unsigned long long)sum;
-        }
-        if (args.obs_words > 10 && threadIdx.x == 0) rec[10] = d.next_sweep + (uint64_t)my_sweeps * (k + 1u);
+        write_record(args, obs, tr, o, k, d.next_sweep + (uint64_t)my_sweeps * (k + 1u));
     };
     if (my_sweeps > 0) {
         uint8_t *bytes = (uint8_t *)lat;
@@ -550,153 +487,12 @@ __global__ void __launch_bounds__(1024) k_sweep_lds(BatchArgs args)
     block_reduce_add<3>(tr, (unsigned long long *)(scr + kScrTrackBase));
 }
 
-template <int Q, bool Barrier>
-__device__ __forceinline__ void word_sweeps(uint32_t *lat, uint32_t *sched, const LatDesc &d, uint32_t my_sweeps,
-                                            const uint2 *s_tab, const uint8_t *s_slots, int (&tr)[3])
-{
-    WordPhase f;
-    f.W = d.L >> 6;
-    f.H = d.L >> 1;
-    f.Lq = d.L >> 2;
-    f.magicW = f.W == 1 ? 0u : (uint32_t)((0x100000000ull + (uint64_t)f.W - 1u) / (uint64_t)f.W);
-    f.key0 = d.key0;
-    f.key1 = d.key1;
-    const uint32_t csz = (uint32_t)f.H * (uint32_t)f.W;
-    const uint32_t tasks = csz * (uint32_t)Q;
-    // At most one task per thread (and Q >= 2, so that the held draws stay
-    // few): each phase makes the next phase's draws of the thread's task
-    // while its own table lookups are in flight.
-    const bool pipe = Q >= 2 && tasks <= blockDim.x;
-    u32x4 pre[kTaskCalls<Q>];
-    if (pipe && threadIdx.x < tasks && my_sweeps > 0) {
-        const uint32_t c0 = task_call0<Q>(f, threadIdx.x);
-        const int q = (int)(threadIdx.x & (uint32_t)(Q - 1));
-#pragma unroll
-        for (int i = 0; i < kTaskCalls<Q>; ++i)
-            pre[i] = pair_draws(philox4x32_10((uint32_t)d.next_sweep, 0u, c0 + (uint32_t)call_of_task<Q>(q, i),
-                                              (uint32_t)(d.next_sweep >> 32), d.key0, d.key1));
-    }
-    for (uint32_t i = 0; i < my_sweeps; ++i) {
-        const uint64_t s = d.next_sweep + i;
-        const uint32_t *Wd = sched + 12u * (i & 1u);
-        const int r = __builtin_amdgcn_readfirstlane(1 + (int)(((Wd[0] >> 8) * 3u) >> 24));
-        f.s_lo = (uint32_t)s;
-        f.s_hi = (uint32_t)(s >> 32);
-        for (int p = 0; p < 4; ++p) {
-            const int m = __builtin_amdgcn_readfirstlane((int)mulhi_u32(Wd[1 + 2 * p], (uint32_t)f.Lq));
-            f.k = __builtin_amdgcn_readfirstlane((int)mulhi_u32(Wd[2 + 2 * p], (uint32_t)f.H));
-            f.p = p;
-            f.pb = (p + r) & 3;
-            const int carry = (p + r) >> 2;
-            f.dX = m + carry >= f.Lq ? m + carry - f.Lq : m + carry;
-            f.oA0 = (uint32_t)p * csz;
-            f.oAL = (uint32_t)(p > 0 ? p - 1 : 3) * csz;
-            f.oAR = (uint32_t)(p < 3 ? p + 1 : 0) * csz;
-            f.oAV = (uint32_t)(4 + p) * csz;
-            f.oB0 = (uint32_t)(4 + f.pb) * csz;
-            f.oBL = (uint32_t)(f.pb > 0 ? 4 + f.pb - 1 : 7) * csz;
-            f.oBR = (uint32_t)(f.pb < 3 ? 4 + f.pb + 1 : 4) * csz;
-            f.oBV = (uint32_t)f.pb * csz;
-            // the next sweep's schedule words, into the other buffer (read
-            // after this phase's barrier)
-            if (p == 3 && threadIdx.x < 3 && i + 1 < my_sweeps) {
-                const u32x4 w = philox4x32_10((uint32_t)(s + 1), kDomSchedule, threadIdx.x, (uint32_t)((s + 1) >> 32),
-                                              d.key0, d.key1);
-                uint32_t *o = sched + 12u * ((i + 1u) & 1u) + 4u * threadIdx.x;
-                o[0] = w.x;
-                o[1] = w.y;
-                o[2] = w.z;
-                o[3] = w.w;
-            }
-            if (pipe) {
-                if (threadIdx.x < tasks)
-                    word_task<Q, Barrier, kDrawPipe>(lat, f, threadIdx.x, s_tab, s_slots, tr, pre,
-                                                     p < 3 ? s : s + 1, p < 3 ? p + 1 : 0);
-            } else {
-                for (uint32_t t = threadIdx.x; t < tasks; t += blockDim.x)
-                    word_task<Q, Barrier>(lat, f, t, s_tab, s_slots, tr);
-            }
-            __syncthreads();
-        }
-    }
-}
-
 // This thread's share of the 7 observable sums of a 2-bit lattice in the
 // class layout, read from st (global memory or the LDS copy).
 __device__ __forceinline__ void obs_sums_2bit(const uint32_t *st, int L, long long (&v)[7])
 {
     const uint32_t n = 8u * (uint32_t)(L >> 1) * (uint32_t)(L >> 6);
     for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) obs_word_2bit(st, L, i, v);
-}
-
-// MaxThreads = 512 serves blocks of up to 512 threads (measured faster: the
-// compiler schedules for fewer waves per SIMD), 1024 the largest blocks.
-template <int MaxThreads>
-__global__ void __launch_bounds__(MaxThreads) k_sweep_lds_w(BatchArgs args)
-{
-    constexpr bool kBarrier = MaxThreads > 512;
-    __shared__ uint2 s_tab[kDevTabEntries];
-    __shared__ __align__(16) uint2 slots[kSlotEntries];
-    __shared__ uint32_t sched[24];
-    extern __shared__ uint32_t lat[];
-    uint8_t *scr = args.scratch[blockIdx.x];
-    const LatDesc d = *(const LatDesc *)(scr + kScrDesc);
-    const uint32_t my_sweeps = args.sweeps[blockIdx.x];
-    if (threadIdx.x < 3) {
-        const uint64_t s = d.next_sweep;
-        const u32x4 w = philox4x32_10((uint32_t)s, kDomSchedule, threadIdx.x, (uint32_t)(s >> 32), d.key0, d.key1);
-        sched[4 * threadIdx.x] = w.x;
-        sched[4 * threadIdx.x + 1] = w.y;
-        sched[4 * threadIdx.x + 2] = w.z;
-        sched[4 * threadIdx.x + 3] = w.w;
-    }
-    LdsGeom g;
-    g.L = d.L;
-    g.Lq = d.L >> 2;
-    g.H = d.L >> 1;
-    g.Wp = d.L >> 6;
-    g.csz = (uint32_t)g.H * g.Wp;
-    stage_lattice(lat, d, g);
-    {
-        const uint2 *g_tab = (const uint2 *)(scr + kScrDevTab);
-        const uint2 *g_slots = (const uint2 *)kWordSlots.v;
-        for (int i = threadIdx.x; i < kDevTabEntries; i += blockDim.x) s_tab[i] = g_tab[i];
-        for (int i = threadIdx.x; i < kSlotEntries; i += blockDim.x) slots[i] = g_slots[i];
-        __syncthreads();
-    }
-    const uint8_t *s_slots = (const uint8_t *)slots;
-
-    // threads per a-word: the largest Q <= 8 with Q * (a-words) <= block size
-    const uint32_t words = g.csz;
-    int Q = 1;
-    while (Q < 8 && words * (uint32_t)(2 * Q) <= blockDim.x) Q *= 2;
-    int tr[3] = {0, 0, 0};
-    switch (Q) {
-    case 1: word_sweeps<1, kBarrier>(lat, sched, d, my_sweeps, s_tab, s_slots, tr); break;
-    case 2: word_sweeps<2, kBarrier>(lat, sched, d, my_sweeps, s_tab, s_slots, tr); break;
-    case 4: word_sweeps<4, kBarrier>(lat, sched, d, my_sweeps, s_tab, s_slots, tr); break;
-    default: word_sweeps<8, kBarrier>(lat, sched, d, my_sweeps, s_tab, s_slots, tr); break;
-    }
-    if constexpr (MaxThreads <= 512) {
-        if (args.obs_out) {
-            // the interval's observables from the LDS copy, and the tracker
-            // total as k_obs_batch would read it after this launch: the
-            // slots, the base before this launch and this launch's own moves
-            unsigned long long *o = args.obs_out + (size_t)args.obs_words * blockIdx.x;
-            long long t3[3] = {tr[0], tr[1], tr[2]};
-            tracker_partial(scr, t3);
-            long long v[7] = {0, 0, 0, 0, 0, 0, 0};
-            obs_sums_2bit(lat, d.L, v);
-            if (threadIdx.x < 10) o[threadIdx.x] = 0ull;
-            if (args.obs_words > 10 && threadIdx.x == 0) o[10] = d.next_sweep + my_sweeps;
-            __syncthreads();
-            block_reduce_add<7>(v, o + 3);
-            block_reduce_add<3>(t3, o);
-        }
-    }
-    unstage_lattice(lat, d, g);
-    if (threadIdx.x == 0) ((LatDesc *)(scr + kScrDesc))->next_sweep = d.next_sweep + my_sweeps;
-    block_reduce_add<3>(tr, (unsigned long long *)(scr + kScrTrackBase));
 }
 
 __global__ void k_advance(LatDesc *desc, uint32_t sweeps)
@@ -745,39 +541,25 @@ hipError_t init_kernel_attributes()
     if (e == hipSuccess)
         e = hipFuncSetAttribute((const void *)k_sweep_site, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 kSiteMaxL * kSiteMaxL);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)k_sweep_lds_w<512>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)k_sweep_lds_w<1024>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e == hipSuccess) e = init_quad_kernel_attributes();
     return e;
 }
 
-hipError_t launch_sweep_lds(const BatchArgs &a, int max_L, int threads, bool word, hipStream_t s)
+hipError_t launch_sweep_lds(const BatchArgs &a, int max_L, int threads, bool quad, hipStream_t s)
 {
-    // default block: word form, two threads per a-word (at least 256);
-    // per-site form, one thread per pair up to kSiteOnePair pairs, else one
-    // per Philox call (two pairs); two-bit form above it, the same
+    if (quad) return launch_sweep_quad(a, max_L, threads, s);
+    // default block: one thread per pair up to kSiteOnePair pairs a phase, else
+    // one per Philox call (two pairs)
     const uint32_t sq = (uint32_t)max_L * (uint32_t)max_L;
-    const bool site = launch_fuses_intervals(max_L, word);
-    const uint32_t units = word ? std::max(256u, sq / 64u) : site && sq / 8u <= kSiteOnePair ? sq / 8u : sq / 16u;
-    uint32_t block = units < 1024u ? ((units + 63u) / 64u) * 64u : 1024u;
+    const bool site = max_L <= kSiteMaxL;
+    const uint32_t units = site && sq / 8u <= kSiteOnePair ? sq / 8u : sq / 16u;
+    uint32_t block = std::min(1024u, (units + 63u) / 64u * 64u);
     if (threads > 0) block = (uint32_t)std::min(1024, std::max(64, threads / 64 * 64));
-    if (block < 64u) block = 64u;
     if (site) {
         hipLaunchKernelGGL(k_sweep_site, dim3((unsigned)a.count), dim3(block), (size_t)sq, s, a);
         return hipGetLastError();
     }
-    const size_t lds = lds_state_words(max_L) * 4u;
-    // a.obs_out: the 512-thread word form writes the observables itself;
-    // the other forms are followed by the observables launch
-    if (word && block <= 512u) {
-        hipLaunchKernelGGL(k_sweep_lds_w<512>, dim3((unsigned)a.count), dim3(block), lds, s, a);
-        return hipGetLastError();
-    }
-    if (word)
-        hipLaunchKernelGGL(k_sweep_lds_w<1024>, dim3((unsigned)a.count), dim3(block), lds, s, a);
-    else
-        hipLaunchKernelGGL(k_sweep_lds, dim3((unsigned)a.count), dim3(block), lds, s, a);
+    hipLaunchKernelGGL(k_sweep_lds, dim3((unsigned)a.count), dim3(block), lds_state_words(max_L) * 4u, s, a);
     if (a.obs_out) hipLaunchKernelGGL(k_obs_batch, dim3((unsigned)a.count), dim3(256), 0, s, a, a.obs_out);
     return hipGetLastError();
 }

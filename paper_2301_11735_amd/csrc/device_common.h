@@ -152,6 +152,14 @@ __device__ __forceinline__ u32x4 pair_draws(const u32x4 &w)
     return u32x4{slot8_of(w.x), min(w.y, 0xFFFFFFFEu), slot8_of(w.z), min(w.w, 0xFFFFFFFEu)};
 }
 
+// Byte offset of a move's entry in the device table: 8 (dot4(coef, sums) + C),
+// from the transition entry {coef, C | changes << 16} and the packed sums.
+__device__ __forceinline__ uint32_t tab_offset(const uint2 &tr, uint32_t sums)
+{
+    const uint32_t idx = (uint32_t)__builtin_amdgcn_sdot4((int)tr.x, (int)sums, (int)tr.y, false);
+    return (uint32_t)(uint16_t)(idx << 3);
+}
+
 // One coupled-pair Metropolis step (section 3.1) from the byte offset of its
 // transition entry, the packed neighbour sums (sumS_a+4, sumS_b+4, sumsig_a+4,
 // sumsig_b+4) and the acceptance draw.  An accepted move adds its packed triple to `packed`
@@ -162,8 +170,7 @@ __device__ __forceinline__ void pair_step_slot(uint32_t entry, uint32_t bpack, u
                                                const uint2 *s_tab, uint32_t fields, uint32_t &packed, uint32_t &dacc)
 {
     const uint2 tr = *(const uint2 *)(s_slots + entry);
-    const uint32_t idx = (uint32_t)__builtin_amdgcn_sdot4((int)tr.x, (int)bpack, (int)tr.y, false);
-    const uint2 e = *(const uint2 *)((const uint8_t *)s_tab + (uint32_t)(uint16_t)(idx << 3));
+    const uint2 e = *(const uint2 *)((const uint8_t *)s_tab + tab_offset(tr, bpack));
     const bool acc = ua < e.x;
     packed += acc ? e.y : 0u;
     dacc |= tr.y & (acc ? fields : 0u);
@@ -431,16 +438,19 @@ __device__ __forceinline__ int charge_of(uint32_t c) { return (c & 2u) ? 1 - 2 *
 constexpr uint32_t kSiteBytes = 0x21u | 0x01u << 8 | 0x12u << 16 | 0x10u << 24;  // per code
 __device__ __forceinline__ uint32_t site_from_codes(uint32_t c) { return __builtin_amdgcn_perm(0u, kSiteBytes, c); }
 
+// Staggered signs of four sites x = 4X .. 4X + 3 of row y.
+__device__ __forceinline__ int row_signs(uint32_t y) { return (int)((y & 1u) ? 0x01FF01FFu : 0xFF01FF01u); }
+
 struct SiteSums {
     uint32_t su = 0, sg = 0, suu = 0, bu = 0, bg = 0, cnt = 0;
     int stu = 0, stg = 0;
 
-    // w: four sites of row y; wr, wd: their right and lower neighbours.
-    __device__ __forceinline__ void add(uint32_t w, uint32_t wr, uint32_t wd, uint32_t y)
+    // w: four sites; wr, wd: their right and lower neighbours; sign: the
+    // sites' staggered signs, a byte each.
+    __device__ __forceinline__ void add(uint32_t w, uint32_t wr, uint32_t wd, int sign)
     {
         const uint32_t m4 = 0x0F0F0F0Fu, ones = 0x01010101u;
         const uint32_t u = w & m4, g = (w >> 4) & m4;
-        const int sign = (int)((y & 1u) ? 0x01FF01FFu : 0xFF01FF01u);
         su = __builtin_amdgcn_udot4(u, ones, su, false);
         sg = __builtin_amdgcn_udot4(g, ones, sg, false);
         suu = __builtin_amdgcn_udot4(u, u, suu, false);
@@ -499,7 +509,7 @@ __device__ __forceinline__ void obs_group_int8(const uint8_t *st, uint32_t L, ui
     e[NW] = site_from_codes(after);
 #pragma unroll
     for (int i = 0; i < NW; ++i)
-        s.add(e[i], __builtin_amdgcn_alignbit(e[i + 1], e[i], 8u), site_from_codes(d[i]), y);
+        s.add(e[i], __builtin_amdgcn_alignbit(e[i + 1], e[i], 8u), site_from_codes(d[i]), row_signs(y));
 }
 
 // Block-level sum of K values written (not added) to dst[0..K): no atomics.

@@ -133,13 +133,12 @@ bool barrier_may_time_out(const lattice *h);
 // v = (tracker nD, nV, nJ, sum S, sum S^2, bonds SS, bonds ss, M, M_st, C_st).
 void fill_obs(const lattice *h, const int64_t *v, lat_obs *out);
 
-// Launch-shape autotuner for the batched kernel.  For every (largest L,
-// batch size) it tries each candidate block size on one real call, timed with
-// HIP events on the call's stream, then keeps the fastest per site update.
-// The chain does not depend on the launch shape, so tuning runs real work.
-// LATTICE_BATCH_THREADS=<n> pins the block size instead.
-int batch_threads_for(int max_L, int count, bool word, hipStream_t stream, hipEvent_t *start, hipEvent_t *stop,
-                      int *slot);
+// Launch-shape autotuner for batches of the two-bit on-chip form.  For every
+// (largest L, batch size) it tries each candidate block size on one real call,
+// timed with HIP events on the call's stream, then keeps the fastest per site
+// update.  The chain does not depend on the launch shape, so tuning runs real
+// work.  LATTICE_BATCH_THREADS=<n> pins the block size of every form instead.
+int batch_threads_for(int max_L, int count, hipEvent_t *start, hipEvent_t *stop, int *slot);
 void batch_threads_done(int slot, double site_updates);
 
 }  // namespace detail

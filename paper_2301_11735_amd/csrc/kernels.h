@@ -99,8 +99,13 @@ inline size_t lds_state_words(int L) { return (size_t)8 * (L / 2) * ((L / 4 + 15
 // bits per site.
 constexpr int kSiteMaxL = 384;
 
+// The quad form (k_sweep_quad): sides that are a multiple of 16, one byte per
+// site by sublattice class, each class row with kQuadHalo bytes behind it.
+constexpr int kQuadMaxL = 368;
+constexpr uint32_t kQuadHalo = 8;
+inline size_t quad_lds_bytes(int L) { return (size_t)8 * (size_t)(L / 2) * ((size_t)(L / 4) + kQuadHalo); }
 // One launch of the batched kernel: block b advances lattice b by sweeps[b],
-// `intervals` times over in the per-site form (1 in the others).
+// `intervals` times over in the per-site and quad forms (1 in the others).
 constexpr int kMaxBatch = 256;
 struct BatchArgs {
     int count;
@@ -109,16 +114,14 @@ struct BatchArgs {
     // non-null: after the sweeps of interval k, lattice b's observables and
     // tracker total go to obs_out[obs_stride k + obs_words b ..] in
     // k_obs_batch's layout (written by the sweep kernel itself in the per-site
-    // form and the 512-thread word form, else by k_obs_batch); obs_words = 11
+    // and quad forms, else by k_obs_batch); obs_words = 11
     // appends the lattice's next sweep index (a series record), else 10
     unsigned long long *obs_out;
     uint32_t intervals, obs_words, obs_stride;
 };
-// Sweeps of one launch of the per-site form over several intervals: bounds
+// Sweeps of one launch of the per-site or quad form over several intervals: bounds
 // how long a launch runs (about half a second at L = 384).
 constexpr uint32_t kFusedSweeps = 16384;
-// Whether one launch may hold several observation intervals.
-inline bool launch_fuses_intervals(int max_L, bool word) { return !word && max_L <= kSiteMaxL; }
 
 // One phase of one sweep: phase p, displacement D = (r + 4m, 1 + 2k).
 struct PhaseArgs {
@@ -262,9 +265,12 @@ hipError_t launch_mu_half(const MuArgs &a, hipStream_t s);
 
 // One-time kernel set-up (dynamic LDS limits); called before the first launch.
 hipError_t init_kernel_attributes();
-// Batched sweeps with each lattice resident in LDS.  word = every lattice of
-// the batch has L % 64 == 0 (word-parallel form); otherwise the per-site form.
-hipError_t launch_sweep_lds(const BatchArgs &a, int max_L, int threads, bool word, hipStream_t s);
+// Batched sweeps with each lattice resident in LDS.  quad: the quad form
+// (every side a multiple of 16, at most kQuadMaxL); else the per-site form up
+// to kSiteMaxL and two bits per site above.
+hipError_t launch_sweep_lds(const BatchArgs &a, int max_L, int threads, bool quad, hipStream_t s);
+hipError_t launch_sweep_quad(const BatchArgs &a, int max_L, int threads, hipStream_t s);
+hipError_t init_quad_kernel_attributes();
 // desc->next_sweep += sweeps (after host-scheduled phase launches).
 hipError_t launch_advance(LatDesc *desc, uint32_t sweeps, hipStream_t s);
 // Observables of `count` lattices in one launch: out[10*b .. 10*b+9] =

@@ -694,7 +694,7 @@ int enqueue_offchip_sweeps(lattice *const *hs, int32_t count, const uint32_t *sw
     return LAT_OK;
 }
 
-// ---- autotuner for the batched kernel's block size ----
+// ---- autotuner for the block size of the two-bit on-chip form ----
 namespace {
 
 struct TuneEntry {
@@ -706,7 +706,7 @@ struct TuneEntry {
     int best = -1;
 };
 
-using TuneKey = std::pair<int, int>;  // (max L | word form << 20, batch size rounded up to a power of 2)
+using TuneKey = std::pair<int, int>;  // (max L, batch size rounded up to a power of 2)
 std::mutex g_tune_mu;
 std::map<TuneKey, TuneEntry> g_tune;
 std::vector<std::pair<TuneKey, int>> g_tune_slots;  // (shape, candidate) of each timed launch handed out
@@ -717,11 +717,11 @@ int pinned_batch_threads()
     return v ? std::atoi(v) : 0;
 }
 
-TuneKey tune_key(int max_L, int count, bool word)
+TuneKey tune_key(int max_L, int count)
 {
     int bucket = 1;
     while (bucket < count) bucket *= 2;
-    return std::make_pair(max_L | (word ? 1 << 20 : 0), bucket);
+    return std::make_pair(max_L, bucket);
 }
 
 // Reads the timed launches of a shape that have completed (never waits), and
@@ -759,27 +759,18 @@ void harvest(TuneEntry &t)
 // batch_threads_done.  No call waits: each of the first calls for a new
 // shape times one candidate that has not been timed yet, and the timings
 // are read by later calls once their launches have completed.
-int batch_threads_for(int max_L, int count, bool word, hipStream_t stream, hipEvent_t *start, hipEvent_t *stop,
-                      int *slot)
+int batch_threads_for(int max_L, int count, hipEvent_t *start, hipEvent_t *stop, int *slot)
 {
-    (void)stream;
     *start = *stop = nullptr;
     *slot = -1;
     if (const int pinned = pinned_batch_threads()) return pinned;
     std::lock_guard<std::mutex> lock(g_tune_mu);
-    const TuneKey key = tune_key(max_L, count, word);
+    const TuneKey key = tune_key(max_L, count);
     TuneEntry &t = g_tune[key];
     if (t.candidates.empty()) {
-        if (word) {
-            // at most 8 threads per a-word are used
-            const int words = max_L * max_L / 128;
-            for (int c : {1024, 512, 256, 128})
-                if (c <= std::max(128, 8 * words) && (c >= 256 || words <= 128)) t.candidates.push_back(c);
-        } else {
-            const int calls = max_L * max_L / 16;
-            for (int c : {1024, 512, 256})
-                if (c / 2 < calls || c == 256) t.candidates.push_back(c);
-        }
+        const int calls = max_L * max_L / 16;
+        for (int c : {1024, 512, 256})
+            if (c / 2 < calls || c == 256) t.candidates.push_back(c);
         const size_t n = t.candidates.size();
         t.ns_per_update.assign(n, -1.0);
         t.in_flight.assign(n, 0.0);
@@ -824,11 +815,11 @@ void batch_threads_done(int slot, double site_updates)
 
 // The tuned block size for a batch shape if tuning has finished (reading
 // completed timings first), else 0 (the default); never launches anything.
-int batch_threads_tuned(int max_L, int count, bool word)
+int batch_threads_tuned(int max_L, int count)
 {
     if (const int pinned = pinned_batch_threads()) return pinned;
     std::lock_guard<std::mutex> lock(g_tune_mu);
-    const auto it = g_tune.find(tune_key(max_L, count, word));
+    const auto it = g_tune.find(tune_key(max_L, count));
     if (it == g_tune.end()) return 0;
     harvest(it->second);
     return it->second.best >= 0 ? it->second.candidates[(size_t)it->second.best] : 0;
@@ -846,6 +837,12 @@ int enqueue_observables_batch(lattice *const *hs, int32_t count, unsigned long l
     return LAT_OK;
 }
 
+// Batches whose sides are all multiples of 16 take the quad form from this
+// largest side on: below, its few threads leave the chain of a phase longer than
+// the per-site form's (us a sweep, quad / per site: L = 48 2.9 / 2.0, L = 64
+// 2.9 / 2.2, L = 80 3.0 / 3.2, L = 128 4.1 / 4.7, L = 256 15.0 / 22.0).
+constexpr int kQuadMinL = 80;
+
 // Batched path: lattices resident in LDS, up to kMaxBatch per launch.
 int enqueue_lds_sweeps(lattice *const *hs, int32_t count, const uint32_t *sweeps, uint32_t uniform,
                        hipStream_t stream, bool tune, const ObsTarget *obs)
@@ -858,18 +855,19 @@ int enqueue_lds_sweeps(lattice *const *hs, int32_t count, const uint32_t *sweeps
         a.count = std::min<int32_t>(kMaxBatch, count - b);
         int max_L = 0;
         double updates = 0;
-        bool word = !force_site;
+        bool quad = !force_site;
         for (int i = 0; i < a.count; ++i) {
             a.scratch[i] = hs[b + i]->d_scratch;
             a.sweeps[i] = sweeps ? sweeps[b + i] : uniform;
             max_L = std::max(max_L, hs[b + i]->L);
             updates += (double)hs[b + i]->N * a.sweeps[i];
-            word = word && hs[b + i]->L % 64 == 0;
+            quad = quad && hs[b + i]->L % 16 == 0;
         }
+        quad = quad && max_L >= kQuadMinL && max_L <= kQuadMaxL;
         const uint32_t intervals = obs ? obs->intervals : 1u;
-        // per-site form: its block size follows from the largest side, and one
-        // launch holds as many intervals as kFusedSweeps sweeps allow
-        const bool fused = launch_fuses_intervals(max_L, word);
+        // per-site and quad forms: the block size follows from the largest side,
+        // and one launch holds as many intervals as kFusedSweeps sweeps allow
+        const bool fused = quad || max_L <= kSiteMaxL;
         const uint32_t most = *std::max_element(a.sweeps, a.sweeps + a.count);
         const uint32_t per_launch = fused ? std::max(1u, kFusedSweeps / std::max(1u, most)) : 1u;
         a.obs_words = obs ? obs->words : 10u;
@@ -879,10 +877,10 @@ int enqueue_lds_sweeps(lattice *const *hs, int32_t count, const uint32_t *sweeps
             a.obs_out = obs ? obs->dev + (size_t)obs->stride * k + (size_t)obs->words * (size_t)b : nullptr;
             hipEvent_t t0 = nullptr, t1 = nullptr;
             int slot = -1;
-            const int threads = tune && !fused ? batch_threads_for(max_L, a.count, word, stream, &t0, &t1, &slot)
-                                               : batch_threads_tuned(max_L, a.count, word);
+            const int threads = tune && !fused ? batch_threads_for(max_L, a.count, &t0, &t1, &slot)
+                                               : batch_threads_tuned(max_L, a.count);
             if (t0) (void)hipEventRecord(t0, stream);
-            hipError_t e = launch_sweep_lds(a, max_L, threads, word, stream);
+            hipError_t e = launch_sweep_lds(a, max_L, threads, quad, stream);
             if (e != hipSuccess) return hip_fail(e, "batched kernel launch");
             if (t1) {
                 (void)hipEventRecord(t1, stream);

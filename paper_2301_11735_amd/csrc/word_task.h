@@ -317,10 +317,8 @@ __device__ __forceinline__ void combine_sides(const uint32_t (&n)[8 / Q], int q,
 
 // The pair steps of a task on its words A0 and B0 (aligned) and their
 // neighbour sums: draw(i, c) gives Philox call c of the word, the task's i-th,
-// as pair_draws.  Barrier = true keeps the compiler from interleaving the
-// calls of a task (fewer live registers, needed at 1024 threads per block);
-// without it the calls overlap each other's table lookups.
-template <int Q, bool Barrier, typename F>
+// as pair_draws.
+template <int Q, typename F>
 __device__ __forceinline__ void task_steps(uint32_t A0, uint32_t B0, const SideSums &sa, const SideSums &sb, int q,
                                            const uint2 *s_tab, const uint8_t *s_slots, uint32_t &packed,
                                            uint32_t (&dacc)[Q <= 2 ? 4 : 8 / Q], F draw)
@@ -349,7 +347,6 @@ __device__ __forceinline__ void task_steps(uint32_t A0, uint32_t B0, const SideS
             for (int kk = 0; kk < 4; ++kk) {  // pairs 4kk .. 4kk+3
                 const int slot = Q == 1 ? 4 * hh + kk : kk;
                 do_call(slot, 2 * kk + half, ge[kk], go[kk], dacc[kk]);
-                if (Barrier) __builtin_amdgcn_sched_barrier(0);
             }
         }
     } else {
@@ -368,116 +365,7 @@ __device__ __forceinline__ void task_steps(uint32_t A0, uint32_t B0, const SideS
     }
 }
 
-// A task on a lattice in LDS.  Pipe (where its Philox draws come from):
-// kDrawInPlace, computed here as they are used; kDrawPipe, this phase's given in
-// pre[] and those of the next phase (sweep ns, phase np) computed here,
-// between the phase's dependent LDS lookups, and returned in pre[].
-constexpr int kDrawInPlace = 0, kDrawPipe = 1;
-template <int Q, bool Barrier, int Pipe = kDrawInPlace>
-__device__ __forceinline__ void word_task(uint32_t *lat, const WordPhase &f, uint32_t task, const uint2 *s_tab,
-                                          const uint8_t *s_slots, int (&tr)[3], u32x4 *pre = nullptr,
-                                          uint64_t ns = 0, int np = 0)
-{
-    constexpr int LOGQ = Q == 1 ? 0 : Q == 2 ? 1 : Q == 4 ? 2 : 3;
-    const uint32_t wi = task >> LOGQ;
-    const int q = (int)(task & (uint32_t)(Q - 1));
-    const int W = f.W, H = f.H, Lq = f.Lq;
-    const int Y = W == 1 ? (int)wi : (int)__umulhi(wi, f.magicW), j = (int)wi - Y * W;
-    int Xb = 16 * j + f.dX;
-    if (Xb >= Lq) Xb -= Lq;
-    const int Yb = Y + f.k >= H ? Y + f.k - H : Y + f.k;
-    const int xAL = f.p > 0 ? 16 * j : (j == 0 ? Lq - 1 : 16 * j - 1);
-    const int xAR = f.p < 3 ? 16 * j : 16 * j + 1;
-    const int xBL = f.pb > 0 ? Xb : (Xb == 0 ? Lq - 1 : Xb - 1);
-    const int xBR = f.pb < 3 ? Xb : (Xb + 1 == Lq ? 0 : Xb + 1);
-    const uint32_t ro = (uint32_t)Y * W, rob = (uint32_t)Yb * W;
-    const uint32_t roU = (uint32_t)(Y == 0 ? H - 1 : Y - 1) * W;
-    const uint32_t robD = (uint32_t)(Yb + 1 == H ? 0 : Yb + 1) * W;
-
-    const uint32_t A0 = lat[f.oA0 + ro + j];
-    const uint32_t B0 = ld16(lat, f.oB0 + rob, W, Xb);
-    uint32_t n[8 / Q];
-    if constexpr (Q == 1) {
-        n[0] = ld16(lat, f.oAL + ro, W, xAL);
-        n[1] = ld16(lat, f.oAR + ro, W, xAR);
-        n[2] = lat[f.oAV + roU + j];
-        n[3] = lat[f.oAV + ro + j];
-        n[4] = ld16(lat, f.oBL + rob, W, xBL);
-        n[5] = ld16(lat, f.oBR + rob, W, xBR);
-        n[6] = ld16(lat, f.oBV + rob, W, Xb);
-        n[7] = ld16(lat, f.oBV + robD, W, Xb);
-    } else {
-        // The Q threads of a word are Q consecutive lanes, 8/Q words each.
-        const int side = q >= Q / 2;
-        const int k0 = (q % (Q / 2)) * (8 / Q);
-        const uint32_t base[4] = {side ? f.oBL + rob : f.oAL + ro, side ? f.oBR + rob : f.oAR + ro,
-                                  side ? f.oBV + rob : f.oAV + roU, side ? f.oBV + robD : f.oAV + ro};
-        const int xs[4] = {side ? xBL : xAL, side ? xBR : xAR, side ? Xb : 16 * j, side ? Xb : 16 * j};
-#pragma unroll
-        for (int i = 0; i < 8 / Q; ++i) {
-            const int kk = k0 + i;
-            const uint32_t b = kk == 0 ? base[0] : kk == 1 ? base[1] : kk == 2 ? base[2] : base[3];
-            const int x = kk == 0 ? xs[0] : kk == 1 ? xs[1] : kk == 2 ? xs[2] : xs[3];
-            n[i] = ld16(lat, b, W, x);
-        }
-    }
-    SideSums sa, sb;
-    combine_sides<Q>(n, q, sa, sb);
-
-    const uint32_t call0 = (uint32_t)Y * (uint32_t)(Lq >> 1) + 8u * (uint32_t)j;
-    // code changes of pairs 4g .. 4g+3 in dacc[g]: a-sites in byte 2, b-sites
-    // in byte 3 (Q = 4: groups q/2 and q/2 + 2 in dacc[0] and [1]; Q = 8:
-    // group q/2 in dacc[0])
-    uint32_t dacc[Q <= 2 ? 4 : 8 / Q] = {}, packed = 0u;
-    u32x4 nxt[kTaskCalls<Q>];
-    if constexpr (Pipe == kDrawPipe) {
-#pragma unroll
-        for (int i = 0; i < kTaskCalls<Q>; ++i)
-            nxt[i] = pair_draws(philox4x32_10((uint32_t)ns, (uint32_t)np, call0 + (uint32_t)call_of_task<Q>(q, i),
-                                              (uint32_t)(ns >> 32), f.key0, f.key1));
-    }
-    task_steps<Q, Barrier>(A0, B0, sa, sb, q, s_tab, s_slots, packed, dacc, [&](int i, int c) {
-        return Pipe != kDrawInPlace ? pre[i]
-                                    : pair_draws(philox4x32_10(f.s_lo, (uint32_t)f.p, call0 + (uint32_t)c, f.s_hi, f.key0,
-                                                               f.key1));
-    });
-    uint32_t dA, dB;
-    task_changes<Q>(dacc, q, dA, dB);
-    if constexpr (Pipe == kDrawPipe) {
-#pragma unroll
-        for (int i = 0; i < kTaskCalls<Q>; ++i) pre[i] = nxt[i];
-    }
-    unpack_tracker(packed, tr);
-    const int jb = Xb >> 4, shb = Xb & 15;
-    if constexpr (!Barrier) {
-        // unconditional (an XOR with 0 changes nothing): branches on the
-        // masks cost more than the LDS operations they would skip
-        if (Q == 1)
-            lat[f.oA0 + ro + j] = A0 ^ dA;
-        else
-            atomicXor(&lat[f.oA0 + ro + j], dA);
-        atomicXor(&lat[f.oB0 + rob + (uint32_t)jb], dB << (2 * shb));
-        const uint32_t hi = shb ? dB >> (32 - 2 * shb) : 0u;
-        atomicXor(&lat[f.oB0 + rob + (uint32_t)(jb + 1 == W ? 0 : jb + 1)], hi);
-    } else {
-        // the 1024-thread build keeps the branches: without them it needs
-        // more registers than 16 waves a compute unit leave
-        if (Q == 1) {
-            if (dA) lat[f.oA0 + ro + j] = A0 ^ dA;
-        } else if (dA) {
-            atomicXor(&lat[f.oA0 + ro + j], dA);
-        }
-        if (dB) {
-            atomicXor(&lat[f.oB0 + rob + (uint32_t)jb], dB << (2 * shb));
-            if (shb) {
-                const uint32_t hi = dB >> (32 - 2 * shb);
-                if (hi) atomicXor(&lat[f.oB0 + rob + (uint32_t)(jb + 1 == W ? 0 : jb + 1)], hi);
-            }
-        }
-    }
-}
-
-// The same task on a lattice in global memory, in three parts, so that a
+// A task, in three parts, so that a
 // persistent kernel can do the first before its device-wide barrier and issue
 // all loads at once after it:
 //   word_refs   where its words are (nothing of the lattice is read),
@@ -580,7 +468,7 @@ __device__ __forceinline__ uint32_t word_apply(uint32_t *lat, const WordPhase &f
     SideSums sa, sb;
     combine_sides<Q>(n, q, sa, sb);
     uint32_t dacc[Q <= 2 ? 4 : 8 / Q] = {}, packed = 0u, cA, cB;
-    task_steps<Q, false>(A0, B0, sa, sb, q, s_tab, s_slots, packed, dacc, [&](int i, int) { return draws[i]; });
+    task_steps<Q>(A0, B0, sa, sb, q, s_tab, s_slots, packed, dacc, [&](int i, int) { return draws[i]; });
     task_changes<Q>(dacc, q, cA, cB);
     if constexpr (Q >= 2) {
         cA |= lane_xor<1>(cA);
