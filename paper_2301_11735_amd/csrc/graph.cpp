@@ -149,17 +149,14 @@ int lattice_batch_graph_read(lat_batch_graph *g, lat_obs *out)
         if (!graph_live(g)) return fail(LAT_ESTATE, "null or destroyed batch graph");
         if (!out) return fail(LAT_EINVAL, "null output");
         const size_t n = g->hs.size();
-        std::vector<int64_t> v(n * 10 * g->intervals);
-        hipError_t e = hipMemcpyAsync(v.data(), g->d_out, v.size() * 8, hipMemcpyDeviceToHost, g->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(g->stream);
-        if (e != hipSuccess) return hip_fail(e, "lattice_batch_graph_read");
-        for (uint32_t k = 0; k < g->intervals; ++k)
-            for (size_t i = 0; i < n; ++i) {
-                lat_obs &o = out[k * n + i];
-                fill_obs(g->hs[i], &v[10 * (k * n + i)], &o);
-                o.sweep -= (uint64_t)g->sweeps * (g->intervals - 1u - k);
-            }
-        return LAT_OK;
+        size_t i = 0;
+        uint32_t k = 0;
+        return read_records("lattice_batch_graph_read", g->d_out, 10, n * g->intervals, nullptr, 0, false, g->stream,
+                            [&](size_t at, const int64_t *v) {
+                                fill_obs(g->hs[i], v, &out[at]);
+                                out[at].sweep -= (uint64_t)g->sweeps * (g->intervals - 1u - k);
+                                if (++i == n) i = 0, ++k;
+                            });
     });
 }
 

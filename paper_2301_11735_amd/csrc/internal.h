@@ -6,6 +6,7 @@
 
 #include <cstdint>
 #include <exception>
+#include <functional>
 #include <new>
 #include <string>
 
@@ -69,24 +70,28 @@ int guarded(const char *what, F &&body) noexcept
         return fail_nothrow(LAT_EHIP, what, "unknown exception");
     }
 }
-// A pinned, device-visible block of kPinnedBytes of host memory for one call's
-// small transfers (kernels may write results into it): pageable copies of a
-// few hundred bytes cost 5-10 us more each.  Taken from a pool of the process
-// and given back by the destructor; the pool keeps at most kPinnedKeep blocks,
-// others are freed.  The holder gives a block back only after it has waited for
-// the device work that uses it; abandon() drops a block whose work may still run
-// (a failed wait).  p is null when no pinned memory can be had: callers then
-// use ordinary memory and copies.
-constexpr size_t kPinnedBytes = 24576;
-constexpr size_t kPinnedKeep = 8;
+// A pinned, device-visible block of host memory for one call's transfers
+// (kernels may write results into it): kPinnedBytes for small ones (pageable
+// copies of a few hundred bytes cost 5-10 us more each), or kPinnedLarge.  Taken
+// from a pool of the process and given back by the destructor; the pool keeps at
+// most kPinnedKeep small and kPinnedLargeKeep large blocks, others are freed.  The
+// holder gives a block back only after it has waited for the device work that
+// uses it; abandon() drops a block whose work may still run (a failed wait).  p is
+// null when no pinned memory can be had: callers then use ordinary memory and
+// copies.
+constexpr size_t kPinnedBytes = 24576, kPinnedLarge = 2u << 20;
+constexpr size_t kPinnedKeep = 8, kPinnedLargeKeep = 2;
 class PinnedBlock {
   public:
-    PinnedBlock();
+    explicit PinnedBlock(bool large = false);
     ~PinnedBlock();
     PinnedBlock(const PinnedBlock &) = delete;
     PinnedBlock &operator=(const PinnedBlock &) = delete;
     void *p = nullptr;
     void abandon() { p = nullptr; }
+
+  private:
+    const bool large_;
 };
 
 // Advance lattices resident in LDS; lattice i by sweeps[i] (null: `uniform`).
@@ -130,6 +135,12 @@ int validate_params(const lat_params *p, int64_t *Q, int64_t *Nc);
 // The lattice has run a persistent kernel, whose bounded device-wide barrier
 // flags a time-out in its error word.
 bool barrier_may_time_out(const lattice *h);
+// Waits for the stream and hands the n records (`words` int64 each) at dev to
+// fill(k, record) in order.  Also reads the error
+// flags of those of the `count` lattices hs that ran a device-wide barrier
+// (always: of all of them): a time-out is an error.  what: the entry point's name.
+int read_records(const char *what, const void *dev, uint32_t words, size_t n, lattice *const *hs, size_t count,
+                 bool always, hipStream_t stream, const std::function<void(size_t, const int64_t *)> &fill);
 // v = (tracker nD, nV, nJ, sum S, sum S^2, bonds SS, bonds ss, M, M_st, C_st).
 void fill_obs(const lattice *h, const int64_t *v, lat_obs *out);
 
