@@ -146,8 +146,8 @@ inline uint32_t magic_div(uint32_t W) { return W <= 1 ? 0u : (uint32_t)((0x10000
 constexpr long long kBarrierTimeoutTicks = 20000000;
 
 // One phase of up to kWordsBatch lattices in the 2-bit class layout (int8
-// ones through their packed copy), spread over many blocks per lattice:
-// blocks first_block[i] .. first_block[i+1]-1 update lattice i, Q lanes per
+// ones through their packed copy), spread over many blocks per lattice: row i of
+// the grid updates lattice i with its first `blocks` blocks, Q lanes per
 // a-word.  Sweep iter of the series (sweep next_sweep + iter of each lattice,
 // schedule computed on the device); a lattice with sweeps[i] <= iter is
 // skipped.  Block b of a lattice adds its tracker sums to tracker slot b.
@@ -158,9 +158,11 @@ struct WordsArgs {
     int count;
     int p;
     uint32_t iter;
+    uint32_t threads;  // of a block
+    uint32_t max_blocks;
     uint8_t *scratch[kWordsBatch];
     uint32_t sweeps[kWordsBatch];
-    uint32_t first_block[kWordsBatch + 1];
+    uint32_t blocks[kWordsBatch];
 };
 // Lanes per a-word for side L (fewer for larger lattices, whose words fill
 // the chip anyway), and the blocks one lattice takes.

@@ -450,18 +450,18 @@ int enqueue_words_sweeps(lattice *const *hs, int32_t count, const uint32_t *swee
             if (want == 1 || want == 2 || want == 4 || want == 8) Q = want;
         }
         const int threads = words_phase_threads();
-        uint32_t blocks = 0, most = 0;
+        a.threads = (uint32_t)threads;
+        uint32_t most = 0;
         for (int i = 0; i < a.count; ++i) {
             const lattice *h = hs[b + i];
             const uint32_t nb = words_blocks(h->L, Q, threads);
             if (nb > (uint32_t)kMaxSlots) return fail(LAT_EINVAL, "lattice too large for the multi-block word kernel");
             a.scratch[i] = h->d_scratch;
             a.sweeps[i] = sweeps ? sweeps[b + i] : uniform;
-            a.first_block[i] = blocks;
-            blocks += nb;
+            a.blocks[i] = nb;
+            a.max_blocks = std::max(a.max_blocks, nb);
             most = std::max(most, a.sweeps[i]);
         }
-        a.first_block[a.count] = blocks;
         if (most == 0) continue;
         for (uint32_t it = 0; it < most; ++it) {
             a.iter = it;

@@ -24,45 +24,76 @@
 namespace lat {
 namespace {
 
+// One phase of every lattice of a batch, row i of the grid for lattice i.  What
+// bounds it: its chain, since a launch waits for the one before and memory that
+// another kernel wrote is beyond the caches.  The rounds of that chain are the
+// arguments (one wait), the lattice's descriptor with the tables behind it, and
+// the state, whose loads and draws are issued before the tables go to LDS.  Ten
+// lattices of L = 512 or one: 7.5 us a launch with the tables loaded entry by
+// entry ahead of the state and the block's lattice looked up among the arguments,
+// 5.6 with all loads at once, 5.0 with a row of the grid for each lattice, 4.4
+// with the launch shape in the arguments' first line and a wave's sums added
+// without a barrier.  The waves go first where they share a compute unit with
+// other kernels (the server runs batches of small lattices beside them): the
+// last block of a launch is waited for (served burst of 40 requests 173 ms
+// without and 147 with priority; all of it 180 -> 126).
+constexpr int kTabAhead = 4;  // all of the threshold table in blocks of kWordsThreads
+static_assert(kTabAhead * kWordsThreads >= kDevTabEntries, "k_phase_words' loads");
+
 template <int Q>
 __global__ void __launch_bounds__(kWordsPhaseMaxThreads) k_phase_words(WordsArgs a)
 {
     __shared__ uint2 s_tab[kDevTabEntries];
     __shared__ __align__(16) uint2 s_slots[kSlotEntries];
-    // the lattice of this block (uniform; at most kWordsBatch lattices)
-    int li = 0;
-    while (li + 1 < a.count && blockIdx.x >= a.first_block[li + 1]) ++li;
-    if (a.iter >= a.sweeps[li]) return;  // the whole block: no barrier is skipped by part of it
-    uint8_t *scr = a.scratch[li];
+    uint8_t *scr = a.scratch[blockIdx.y];
+    const uint32_t sweeps = a.sweeps[blockIdx.y], blocks = a.blocks[blockIdx.y];
+    // the whole block: no barrier is skipped by part of it (one condition of all
+    // three arguments, for one wait)
+    if ((scr == nullptr) | (a.iter >= sweeps) | (blockIdx.x >= blocks)) return;
+    const uint32_t threads = a.threads;  // (the launch's own count is in a further line of arguments)
+    const uint2 *g_tab = (const uint2 *)(scr + kScrDevTab);
+    const uint2 *g_slots = (const uint2 *)kWordSlots.v;
+    // the first entries of the tables, to be stored behind the state's loads
+    uint2 tab[kTabAhead];
+#pragma unroll
+    for (int k = 0; k < kTabAhead; ++k)
+        tab[k] = g_tab[min((int)(threadIdx.x + k * threads), kDevTabEntries - 1)];
+    const uint2 slot = g_slots[min((int)threadIdx.x, kSlotEntries - 1)];
     const LatDesc d = *(const LatDesc *)(scr + kScrDesc);
     uint32_t *st = (uint32_t *)(d.enc == 1 ? d.state : (void *)(scr + kScrWork));
-    {
-        const uint2 *g_tab = (const uint2 *)(scr + kScrDevTab);
-        for (int i = threadIdx.x; i < kDevTabEntries; i += blockDim.x) s_tab[i] = g_tab[i];
-        const uint2 *g_slots = (const uint2 *)kWordSlots.v;
-        for (int i = threadIdx.x; i < kSlotEntries; i += blockDim.x) s_slots[i] = g_slots[i];
-    }
+    // after the descriptor's loads, which would not be scalar behind it
+    __builtin_amdgcn_s_setprio(3);
     const uint64_t s = d.next_sweep + a.iter;
     int r, mm[4], kk[4];
     device_schedule(d.L, d.key0, d.key1, s, r, mm, kk);
     WordPhase f;
     word_phase_setup(f, d.L, d.key0, d.key1, s, a.p, r, mm, kk);
     const uint32_t csz = (uint32_t)f.H * (uint32_t)f.W;
+    const uint32_t task = blockIdx.x * threads + threadIdx.x;
+    // tasks = Q * csz is a multiple of Q, so a word's lanes are all in or all
+    // out; those that are out load the first word's lanes again
+    const int q = (int)(task & (uint32_t)(Q - 1));
+    const bool mine = task < (uint32_t)Q * csz;
+    const uint32_t at = mine ? task : (uint32_t)q;
+    const WordRefs<Q> refs = word_refs<Q>(f, at);
+    const WordVals<Q> v = word_fetch<Q, false>(st, refs);
+    u32x4 draws[kTaskCalls<Q>];
+    word_draws<Q>(task_call0<Q>(f, at), q, s, a.p, d.key0, d.key1, draws);
+#pragma unroll
+    for (int k = 0; k < kTabAhead; ++k)
+        if (threadIdx.x + k * threads < kDevTabEntries) s_tab[threadIdx.x + k * threads] = tab[k];
+    if (threadIdx.x < kSlotEntries) s_slots[threadIdx.x] = slot;
+    for (int i = threadIdx.x + kTabAhead * threads; i < kDevTabEntries; i += threads) s_tab[i] = g_tab[i];
+    for (int i = threadIdx.x + threads; i < kSlotEntries; i += threads) s_slots[i] = g_slots[i];
     __syncthreads();
 
-    const uint32_t b = blockIdx.x - a.first_block[li];
-    const uint32_t task = b * blockDim.x + threadIdx.x;
     int tr[3] = {0, 0, 0};
-    // tasks = Q * csz is a multiple of Q, so a word's lanes are all in or all out
-    if (task < (uint32_t)Q * csz) {
-        const WordRefs<Q> r = word_refs<Q>(f, task);
-        const WordVals<Q> v = word_fetch<Q, false>(st, r);
-        const int q = (int)(task & (uint32_t)(Q - 1));
-        u32x4 draws[kTaskCalls<Q>];
-        word_draws<Q>(task_call0<Q>(f, task), q, s, a.p, d.key0, d.key1, draws);
-        unpack_tracker(word_apply<Q, false, false>(st, f, r, v, q, draws, s_tab, (const uint8_t *)s_slots, nullptr), tr);
-    }
-    block_reduce_add<3>(tr, (unsigned long long *)(scr + kScrSlots) + 3 * (size_t)b);
+    if (mine) unpack_tracker(word_apply<Q, false, false>(st, f, refs, v, q, draws, s_tab, (const uint8_t *)s_slots, nullptr), tr);
+    // a wave's sums: one atomic each, without a further barrier
+    const int t0 = dpp_step_sum(tr[0]), t1 = dpp_step_sum(tr[1]), t2 = dpp_step_sum(tr[2]);
+    const int lane = (int)(threadIdx.x & 63u), t = lane == 0 ? t0 : lane == 1 ? t1 : t2;
+    if (lane < 3 && t != 0)
+        atomicAdd((unsigned long long *)(scr + kScrSlots) + 3 * (size_t)blockIdx.x + lane, (unsigned long long)(long long)t);
 }
 
 // Block sums of m (per thread: tracker moves 0-2, spin, staggered spin and
@@ -363,7 +394,7 @@ int words_lanes(int L)
 
 hipError_t launch_phase_words(const WordsArgs &a, int Q, int threads, hipStream_t s)
 {
-    const dim3 grid(a.first_block[a.count]), block((unsigned)threads);
+    const dim3 grid(a.max_blocks, (unsigned)a.count), block((unsigned)threads);
     switch (Q) {
     case 1: hipLaunchKernelGGL(k_phase_words<1>, grid, block, 0, s, a); break;
     case 2: hipLaunchKernelGGL(k_phase_words<2>, grid, block, 0, s, a); break;
