@@ -9,7 +9,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblattice.so")
-SOURCES = [os.path.join(CSRC, n) for n in ("lattice_api.cpp", "server.cpp", "graph.cpp", "maps.cpp", "penalty.cpp", "phase.hip", "obs.hip", "batch.hip", "quad.hip", "words.hip",
+SOURCES = [os.path.join(CSRC, n) for n in ("lattice_api.cpp", "server.cpp", "graph.cpp", "maps.cpp", "penalty.cpp", "phase.hip", "obs.hip", "batch.hip", "quad.hip", "words.hip", "seed.hip",
                                               "maps.hip", "penalty.hip", "noalloc.hip")]
 ARCH = os.environ.get("LATTICE_OFFLOAD_ARCH", "gfx950")
 

@@ -267,6 +267,23 @@ hipError_t launch_mu_half(const MuArgs &a, hipStream_t s);
 
 // One-time kernel set-up (dynamic LDS limits); called before the first launch.
 hipError_t init_kernel_attributes();
+// Seeded initial state (stage 1 of section 3.1) written into the state, with the
+// scratch's slot regions as working space: the `rank[0]` sites with the smallest
+// keys are +1, those up to rank[1] -1.  *overflow (device-visible) is set to
+// 1 if more than cap (at most kSeedCap) keys share their upper 22 bits at a
+// rank; the state is then not the seed's, and 0 otherwise.  Weak: a program
+// that links the host sources alone has none, and seeds on the host.
+constexpr uint32_t kSeedCap = 512;
+struct SeedArgs {
+    void *state;
+    uint8_t *scratch;
+    uint32_t *overflow;
+    uint32_t sites, L, enc, key0, key1;
+    uint32_t rank[2];
+    uint32_t cap;
+};
+hipError_t launch_seed(const SeedArgs &a, hipStream_t s) __attribute__((weak));
+
 // Batched sweeps with each lattice resident in LDS.  quad: the quad form
 // (every side a multiple of 16, at most kQuadMaxL); else the per-site form up
 // to kSiteMaxL and two bits per site above.

@@ -145,7 +145,7 @@ int charge_target(int32_t L, double n, int64_t n_req, int64_t *Q_out, int64_t *N
     return LAT_OK;
 }
 
-// Stage 1 of section 3.1: site i gets key (w0 << 32 | w1) of Philox counter
+// Stage 1 of section 3.1 where the device cannot decide it (seed.hip): site i gets key (w0 << 32 | w1) of Philox counter
 // (0, 0x200, i, 0); the N+ smallest (key, i) become +1, the next N- become -1,
 // the others are spins with sigma from bit 0 of w2.  Selection (two
 // nth_element passes) gives the same sets as a full sort.
@@ -312,6 +312,36 @@ void to_device_layout(int32_t L, int32_t enc, const std::vector<int8_t> &codes, 
     out.resize(N / 4);
     std::memcpy(out.data(), words.data(), N / 4);
 }
+
+// The initial state of lattice_create in the device encoding.
+void initial_state(const lat_params &p, int64_t Q, int64_t Nc, std::vector<uint8_t> &dev)
+{
+    std::vector<int8_t> codes;
+    if (p.init_codes)
+        codes.assign(p.init_codes, p.init_codes + (int64_t)p.L * p.L);
+    else
+        seeded_init(p.L, p.seed, (Nc + Q) / 2, (Nc - Q) / 2, codes);
+    to_device_layout(p.L, p.encoding, codes, dev);
+}
+
+// Seeded states are made on the device at every side (L = 8: 0.117 ms a lattice
+// with the host's keys, 0.102 with the device's; L = 64 0.149 and 0.088).
+bool seeds_on_device(const lat_params &p) { return launch_seed && !p.init_codes; }
+
+// Elements the device keeps at a rank; LATTICE_SEED_CANDIDATES lowers it (tests
+// take the host's way out with 0).
+uint32_t seed_candidates()
+{
+    const char *v = std::getenv("LATTICE_SEED_CANDIDATES");
+    return v ? (uint32_t)std::min(std::max(std::atoi(v), 0), (int)kSeedCap) : kSeedCap;
+}
+
+// Staging of lattice_create: the scratch up to its observable slots, the full
+// threshold table, the delta table, and the seeding's overflow flag.
+constexpr size_t kCreateTransD = kScrObsSlots + ((size_t)kTabSize * 4 + 255) / 256 * 256;
+constexpr size_t kCreateFlag = kCreateTransD + (size_t)kTransEntries * 16;
+constexpr size_t kCreateBytes = kCreateFlag + 256;
+static_assert(kCreateBytes <= kPinnedLarge, "lattice_create's staging");
 
 void from_device_layout(int32_t L, int32_t enc, const std::vector<uint8_t> &dev, int8_t *codes)
 {
@@ -1085,18 +1115,6 @@ int lattice_create(const lat_params *p, void *d_state, size_t state_bytes, void 
         if (state_bytes < lattice_state_bytes(p->L, p->encoding)) return fail(LAT_ENOMEM, "state buffer too small");
         if (scratch_bytes < lattice_scratch_bytes(p->L, p->encoding)) return fail(LAT_ENOMEM, "scratch buffer too small");
 
-        const int64_t N = (int64_t)p->L * p->L;
-        std::vector<int8_t> codes;
-        if (p->init_codes)
-            codes.assign(p->init_codes, p->init_codes + N);
-        else
-            seeded_init(p->L, p->seed, (Nc + Q) / 2, (Nc - Q) / 2, codes);
-        std::vector<uint8_t> dev;
-        to_device_layout(p->L, p->encoding, codes, dev);
-        std::vector<uint32_t> tab, dev_tab, trans, trans_d;
-        build_threshold_table(p->Delta, p->V, p->J, p->T, tab);
-        build_device_table(tab, dev_tab);
-        build_transition_table(trans, trans_d);
         {
             static std::once_flag once;
             static hipError_t init_err = hipSuccess;
@@ -1110,7 +1128,7 @@ int lattice_create(const lat_params *p, void *d_state, size_t state_bytes, void 
         lattice *h = new lattice();
         h->L = p->L;
         h->enc = p->encoding;
-        h->N = N;
+        h->N = (int64_t)p->L * p->L;
         h->Q = Q;
         h->Nc = Nc;
         h->n = p->n;
@@ -1135,23 +1153,54 @@ int lattice_create(const lat_params *p, void *d_state, size_t state_bytes, void 
         desc.key1 = (uint32_t)(p->seed >> 32);
         desc.next_sweep = p->start_sweep;
 
-        hipError_t e = hipMemcpyAsync(d_state, dev.data(), dev.size(), hipMemcpyHostToDevice, h->stream);
+        // the seeded state is made on the device while the tables are made here
+        PinnedBlock stage(/*large=*/true);
+        std::vector<uint8_t> own;
+        if (!stage.p) own.resize(kCreateBytes);
+        uint8_t *img = stage.p ? (uint8_t *)stage.p : own.data();
+        std::memset(img, 0, kCreateBytes);
+        uint32_t *overflow = (uint32_t *)(img + kCreateFlag);
+        const bool on_device = seeds_on_device(*p);
+        hipError_t e = hipSuccess;
+        std::vector<uint8_t> dev;
+        if (on_device) {
+            const SeedArgs s{d_state, h->d_scratch, stage.p ? overflow : (uint32_t *)(h->d_scratch + kScrErr),
+                             (uint32_t)h->N, (uint32_t)h->L, (uint32_t)h->enc, desc.key0, desc.key1,
+                             {(uint32_t)((Nc + Q) / 2), (uint32_t)Nc}, seed_candidates()};
+            e = launch_seed(s, h->stream);
+            if (e == hipSuccess && !stage.p)
+                e = hipMemcpyAsync(overflow, s.overflow, sizeof(uint32_t), hipMemcpyDeviceToHost, h->stream);
+        } else {
+            initial_state(*p, Q, Nc, dev);
+            e = hipMemcpyAsync(d_state, dev.data(), dev.size(), hipMemcpyHostToDevice, h->stream);
+        }
+        std::vector<uint32_t> tab, dev_tab, trans, trans_d;
+        build_threshold_table(p->Delta, p->V, p->J, p->T, tab);
+        build_device_table(tab, dev_tab);
+        build_transition_table(trans, trans_d);
+        // tables, descriptor and a cleared tracker in two copies
+        std::memcpy(img + kScrDevTab, dev_tab.data(), dev_tab.size() * 4);
+        std::memcpy(img + kScrTrans, trans.data(), trans.size() * 4);
+        std::memcpy(img + kScrDesc, &desc, sizeof(desc));
+        std::memcpy(img + kScrObsSlots, tab.data(), tab.size() * 4);
+        std::memcpy(img + kCreateTransD, trans_d.data(), trans_d.size() * 4);
+        if (e == hipSuccess) e = hipMemcpyAsync(h->d_scratch, img, kScrObsSlots, hipMemcpyHostToDevice, h->stream);
         if (e == hipSuccess)
-            e = hipMemcpyAsync(h->d_scratch + kScrDevTab, dev_tab.data(), dev_tab.size() * 4, hipMemcpyHostToDevice,
+            e = hipMemcpyAsync(h->d_scratch + kScrFullTab, img + kScrObsSlots, tab.size() * 4, hipMemcpyHostToDevice,
                                h->stream);
         if (e == hipSuccess)
-            e = hipMemcpyAsync(h->d_scratch + kScrTrans, trans.data(), trans.size() * 4, hipMemcpyHostToDevice, h->stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(h->d_scratch + kScrTransD, trans_d.data(), trans_d.size() * 4, hipMemcpyHostToDevice,
+            e = hipMemcpyAsync(h->d_scratch + kScrTransD, img + kCreateTransD, trans_d.size() * 4, hipMemcpyHostToDevice,
                                h->stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(h->d_scratch + kScrFullTab, tab.data(), tab.size() * 4, hipMemcpyHostToDevice, h->stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(h->d_scratch + kScrDesc, &desc, sizeof(desc), hipMemcpyHostToDevice, h->stream);
-        if (e == hipSuccess) e = launch_zero_i64((unsigned long long *)(h->d_scratch + kScrTrack), 11, h->stream);
-        if (e == hipSuccess) e = launch_zero_i64((unsigned long long *)(h->d_scratch + kScrTrackBase), 3, h->stream);
         if (e == hipSuccess) e = launch_zero_i64((unsigned long long *)(h->d_scratch + kScrSlots), 3 * kMaxSlots, h->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(h->stream);  // host staging buffers die with this frame
+        hipError_t waited = hipStreamSynchronize(h->stream);  // host staging buffers die with this frame
+        if (e == hipSuccess) e = waited;
+        if (e == hipSuccess && on_device && *overflow != 0) {
+            initial_state(*p, Q, Nc, dev);
+            e = hipMemcpyAsync(d_state, dev.data(), dev.size(), hipMemcpyHostToDevice, h->stream);
+            waited = hipStreamSynchronize(h->stream);
+            if (e == hipSuccess) e = waited;
+        }
+        if (waited != hipSuccess) stage.abandon();
         if (e != hipSuccess) {
             h->magic = 0;
             delete h;
