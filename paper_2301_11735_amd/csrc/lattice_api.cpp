@@ -10,6 +10,7 @@
 
 #include <algorithm>
 #include <map>
+#include <memory>
 #include <tuple>
 #include <mutex>
 #include <cmath>
@@ -326,7 +327,13 @@ void initial_state(const lat_params &p, int64_t Q, int64_t Nc, std::vector<uint8
 
 // Seeded states are made on the device at every side (L = 8: 0.117 ms a lattice
 // with the host's keys, 0.102 with the device's; L = 64 0.149 and 0.088).
-bool seeds_on_device(const lat_params &p) { return launch_seed && !p.init_codes; }
+// Without a device the host's state is still made first, and what it lacks for
+// that is what the caller is told.
+bool seeds_on_device(const lat_params &p)
+{
+    int device = 0;
+    return launch_seed && !p.init_codes && hipGetDevice(&device) == hipSuccess;
+}
 
 // Elements the device keeps at a rank; LATTICE_SEED_CANDIDATES lowers it (tests
 // take the host's way out with 0).
@@ -1115,6 +1122,9 @@ int lattice_create(const lat_params *p, void *d_state, size_t state_bytes, void 
         if (state_bytes < lattice_state_bytes(p->L, p->encoding)) return fail(LAT_ENOMEM, "state buffer too small");
         if (scratch_bytes < lattice_scratch_bytes(p->L, p->encoding)) return fail(LAT_ENOMEM, "scratch buffer too small");
 
+        const bool on_device = seeds_on_device(*p);
+        std::vector<uint8_t> dev;
+        if (!on_device) initial_state(*p, Q, Nc, dev);
         {
             static std::once_flag once;
             static hipError_t init_err = hipSuccess;
@@ -1125,7 +1135,8 @@ int lattice_create(const lat_params *p, void *d_state, size_t state_bytes, void 
             if (init_err != hipSuccess) return hip_fail(init_err, "kernel set-up");
         }
 
-        lattice *h = new lattice();
+        std::unique_ptr<lattice> made(new lattice());
+        lattice *h = made.get();
         h->L = p->L;
         h->enc = p->encoding;
         h->N = (int64_t)p->L * p->L;
@@ -1153,16 +1164,20 @@ int lattice_create(const lat_params *p, void *d_state, size_t state_bytes, void 
         desc.key1 = (uint32_t)(p->seed >> 32);
         desc.next_sweep = p->start_sweep;
 
-        // the seeded state is made on the device while the tables are made here
+        // The seeded state is made on the device while the tables are made here;
+        // nothing is allocated in between, so that the wait below is reached.
+        std::vector<uint32_t> tab, dev_tab, trans, trans_d;
+        tab.reserve(kTabSize);
+        dev_tab.reserve(2 * (size_t)kDevTabEntries);
+        trans.reserve(2 * (size_t)kTransEntries);
+        trans_d.reserve(4 * (size_t)kTransEntries);
         PinnedBlock stage(/*large=*/true);
         std::vector<uint8_t> own;
         if (!stage.p) own.resize(kCreateBytes);
         uint8_t *img = stage.p ? (uint8_t *)stage.p : own.data();
         std::memset(img, 0, kCreateBytes);
         uint32_t *overflow = (uint32_t *)(img + kCreateFlag);
-        const bool on_device = seeds_on_device(*p);
         hipError_t e = hipSuccess;
-        std::vector<uint8_t> dev;
         if (on_device) {
             const SeedArgs s{d_state, h->d_scratch, stage.p ? overflow : (uint32_t *)(h->d_scratch + kScrErr),
                              (uint32_t)h->N, (uint32_t)h->L, (uint32_t)h->enc, desc.key0, desc.key1,
@@ -1171,14 +1186,12 @@ int lattice_create(const lat_params *p, void *d_state, size_t state_bytes, void 
             if (e == hipSuccess && !stage.p)
                 e = hipMemcpyAsync(overflow, s.overflow, sizeof(uint32_t), hipMemcpyDeviceToHost, h->stream);
         } else {
-            initial_state(*p, Q, Nc, dev);
             e = hipMemcpyAsync(d_state, dev.data(), dev.size(), hipMemcpyHostToDevice, h->stream);
         }
-        std::vector<uint32_t> tab, dev_tab, trans, trans_d;
         build_threshold_table(p->Delta, p->V, p->J, p->T, tab);
         build_device_table(tab, dev_tab);
         build_transition_table(trans, trans_d);
-        // tables, descriptor and a cleared tracker in two copies
+        // tables, descriptor and a cleared tracker in three copies
         std::memcpy(img + kScrDevTab, dev_tab.data(), dev_tab.size() * 4);
         std::memcpy(img + kScrTrans, trans.data(), trans.size() * 4);
         std::memcpy(img + kScrDesc, &desc, sizeof(desc));
@@ -1203,10 +1216,9 @@ int lattice_create(const lat_params *p, void *d_state, size_t state_bytes, void 
         if (waited != hipSuccess) stage.abandon();
         if (e != hipSuccess) {
             h->magic = 0;
-            delete h;
             return hip_fail(e, "lattice_create");
         }
-        *out = h;
+        *out = made.release();
         return LAT_OK;
     });
 }
