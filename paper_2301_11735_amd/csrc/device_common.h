@@ -144,6 +144,33 @@ constexpr TransSlots make_word_slots()
 __device__ const TransSlots kWordSlots = make_word_slots();
 constexpr int kSlotEntries = 256;
 
+// The tables of the per-phase kernels in two steps: load() issues the loads of
+// all that a block of kWordsThreads needs, store() puts them into LDS (and loads
+// what smaller blocks still lack), so that a phase's other loads are issued
+// in between.
+constexpr int kTabAhead = 4;
+static_assert(kTabAhead * kWordsThreads >= kDevTabEntries, "the whole table in blocks of kWordsThreads");
+struct TableLoads {
+    const uint2 *g_tab;
+    uint2 tab[kTabAhead], slot;
+    __device__ __forceinline__ void load(const uint2 *g, uint32_t threads)
+    {
+        g_tab = g;
+#pragma unroll
+        for (int k = 0; k < kTabAhead; ++k) tab[k] = g[min((int)(threadIdx.x + k * threads), kDevTabEntries - 1)];
+        slot = ((const uint2 *)kWordSlots.v)[min((int)threadIdx.x, kSlotEntries - 1)];
+    }
+    __device__ __forceinline__ void store(uint2 *s_tab, uint2 *s_slots, uint32_t threads) const
+    {
+#pragma unroll
+        for (int k = 0; k < kTabAhead; ++k)
+            if (threadIdx.x + k * threads < kDevTabEntries) s_tab[threadIdx.x + k * threads] = tab[k];
+        if (threadIdx.x < kSlotEntries) s_slots[threadIdx.x] = slot;
+        for (int i = threadIdx.x + kTabAhead * threads; i < kDevTabEntries; i += threads) s_tab[i] = g_tab[i];
+        for (int i = threadIdx.x + threads; i < kSlotEntries; i += threads) s_slots[i] = ((const uint2 *)kWordSlots.v)[i];
+    }
+};
+
 // A Philox call as the two pairs' {slot offset, acceptance draw}: the draw is
 // compared as min(u, 2^32 - 2) < threshold, so that the reserved "always"
 // threshold 2^32 - 1 accepts every draw.
@@ -258,6 +285,15 @@ __device__ __forceinline__ void block_reduce_add(T (&v)[K], unsigned long long *
             if (w < nw) s += (long long)part[w][threadIdx.x];
         if (s != 0) atomicAdd(&dst[threadIdx.x], (unsigned long long)s);
     }
+}
+
+// A wave's sums of the three tracker values, added with one atomic each (no
+// block barrier).  Every lane of the wave must be active.
+__device__ __forceinline__ void wave_reduce_add3(const int (&v)[3], unsigned long long *dst)
+{
+    const int v0 = dpp_step_sum(v[0]), v1 = dpp_step_sum(v[1]), v2 = dpp_step_sum(v[2]);
+    const int lane = (int)(threadIdx.x & 63u), sum = lane == 0 ? v0 : lane == 1 ? v1 : v2;
+    if (lane < 3 && sum != 0) atomicAdd(&dst[lane], (unsigned long long)(long long)sum);
 }
 
 // Neighbour contribution of a code c to the packed sums: byte 0 (a side) or

@@ -15,16 +15,19 @@
 
 // How a lattice is swept (chosen at create from L and the encoding):
 //   kPathLds    one block holds the whole lattice in LDS for all the sweeps of
-//               a launch (batch.hip); by default L <= 256 when L % 64 == 0,
-//               else L <= 512;
+//               a launch (batch.hip, quad.hip); by default L <= 256 when
+//               L % 64 == 0, else L <= 384;
 //   kPathWords  many blocks per lattice, Q lanes per a-word, schedule
 //               computed on the device (words.hip): one persistent launch
 //               per call, or one launch per phase in graphs and in the
 //               server; L % 64 == 0, L <= 2048;
-//   kPathPhase  one launch per phase, one thread per a-word (phase.hip).
-// Int8 lattices with L % 64 == 0 on the last two paths are swept on a 2-bit
+//   kPathPhase  one launch per phase (phase.hip): one thread per a-word, or two
+//               pairs a thread for int8 lattices that are not packed;
+//   kPathBytes  the latter for 384 < L <= 512, L % 64 != 0: batch graphs take
+//               these sides and not those of kPathPhase.
+// Int8 lattices with L % 64 == 0 off the chip are swept on a 2-bit
 // copy in their scratch (packed before the sweeps of a call, unpacked after).
-enum : int { kPathLds = 0, kPathWords = 1, kPathPhase = 2 };
+enum : int { kPathLds = 0, kPathWords = 1, kPathPhase = 2, kPathBytes = 3 };
 
 struct lattice {
     int L = 0, enc = 0;

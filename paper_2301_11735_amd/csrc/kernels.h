@@ -176,6 +176,15 @@ inline uint32_t words_blocks(int L, int Q, int threads = kWordsThreads)
 // (every block stages the tables, so larger blocks stage them fewer times).
 constexpr int kWordsPhaseMaxThreads = 1024;
 hipError_t launch_phase_words(const WordsArgs &a, int Q, int threads, hipStream_t s);
+// The same for int8 lattices as they are (Q = 0 above; sides that are not a
+// multiple of 64): two pairs a thread, at most kBytesMaxBlocks blocks a lattice.
+constexpr int kBytesMaxBlocks = 2048;
+inline uint32_t bytes_blocks(int L, int threads = kWordsThreads)
+{
+    const uint32_t calls = (uint32_t)L * (uint32_t)L / 16u, nb = (calls + (uint32_t)threads - 1) / (uint32_t)threads;
+    return nb < (uint32_t)kBytesMaxBlocks ? nb : (uint32_t)kBytesMaxBlocks;
+}
+hipError_t launch_phase_bytes(const WordsArgs &a, int threads, hipStream_t s);
 // desc->next_sweep += sweeps[i] for every lattice of the series.
 hipError_t launch_advance_words(const WordsArgs &a, hipStream_t s);
 // Persistent multi-block form: up to kWordsBatch lattices (blocks
@@ -213,7 +222,6 @@ struct Tuning2Bit {
     int persistent;  // 1: one cooperative launch per lattice_sweep call (2-bit), 0: a launch per phase
 };
 
-hipError_t launch_phase_int8(const PhaseArgs &a, hipStream_t s);
 hipError_t launch_phase_2bit(const PhaseArgs &a, const Tuning2Bit &t, hipStream_t s);
 // Persistent 2-bit sweeps (one cooperative launch, device-wide barrier per
 // phase); hipErrorNotSupported when co-residency cannot be guaranteed.

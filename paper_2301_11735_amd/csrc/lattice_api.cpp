@@ -418,9 +418,8 @@ int enqueue_phase_sweeps(lattice *h, uint32_t sweeps, hipStream_t stream)
     a.magicW = magic_div((uint32_t)h->L >> 6);
     a.key0 = (uint32_t)h->seed;
     a.key1 = (uint32_t)(h->seed >> 32);
-    const int enc = swept_enc(h);
     uint32_t left = sweeps;
-    if (enc == LAT_ENC_2BIT && h->tuning.persistent) {
+    if (h->tuning.persistent) {
         // one cooperative launch per chunk; the barrier counter stays far below 2^32
         constexpr uint32_t kChunk = 65536;
         while (left > 0) {
@@ -445,8 +444,7 @@ int enqueue_phase_sweeps(lattice *h, uint32_t sweeps, hipStream_t stream)
             a.p = p;
             a.m = sc.m[p];
             a.k = sc.k[p];
-            const hipError_t e =
-                enc == LAT_ENC_INT8 ? launch_phase_int8(a, stream) : launch_phase_2bit(a, h->tuning, stream);
+            const hipError_t e = launch_phase_2bit(a, h->tuning, stream);
             if (e != hipSuccess) return hip_fail(e, "phase kernel launch");
         }
     }
@@ -472,17 +470,18 @@ int words_phase_threads()
 // group skips the sweeps past sweeps[i]), then the device sweep counters
 // are advanced.  Q (lanes per a-word) is chosen by the largest L of the
 // group; every lattice's blocks must fit its kMaxSlots tracker slots.
+// bytes: int8 lattices as they are.
 int enqueue_words_sweeps(lattice *const *hs, int32_t count, const uint32_t *sweeps, uint32_t uniform,
-                         hipStream_t stream)
+                         hipStream_t stream, bool bytes)
 {
     for (int32_t b = 0; b < count; b += kWordsBatch) {
         WordsArgs a{};
         a.count = std::min<int32_t>(kWordsBatch, count - b);
         int max_L = 0;
         for (int i = 0; i < a.count; ++i) max_L = std::max(max_L, hs[b + i]->L);
-        int Q = words_lanes(max_L);
+        int Q = bytes ? 0 : words_lanes(max_L);
         // LATTICE_WORDS_PHASE_LANES (1, 2, 4 or 8) overrides the lanes per a-word
-        if (const char *v = std::getenv("LATTICE_WORDS_PHASE_LANES")) {
+        if (const char *v = bytes ? nullptr : std::getenv("LATTICE_WORDS_PHASE_LANES")) {
             const int want = std::atoi(v);
             if (want == 1 || want == 2 || want == 4 || want == 8) Q = want;
         }
@@ -491,8 +490,8 @@ int enqueue_words_sweeps(lattice *const *hs, int32_t count, const uint32_t *swee
         uint32_t most = 0;
         for (int i = 0; i < a.count; ++i) {
             const lattice *h = hs[b + i];
-            const uint32_t nb = words_blocks(h->L, Q, threads);
-            if (nb > (uint32_t)kMaxSlots) return fail(LAT_EINVAL, "lattice too large for the multi-block word kernel");
+            const uint32_t nb = bytes ? bytes_blocks(h->L, threads) : words_blocks(h->L, Q, threads);
+            if (!bytes && nb > (uint32_t)kMaxSlots) return fail(LAT_EINVAL, "lattice too large for the multi-block word kernel");
             a.scratch[i] = h->d_scratch;
             a.sweeps[i] = sweeps ? sweeps[b + i] : uniform;
             a.blocks[i] = nb;
@@ -711,12 +710,15 @@ int enqueue_offchip_sweeps(lattice *const *hs, int32_t count, const uint32_t *sw
                                               (uint32_t *)(hs[i]->d_scratch + kScrWork), hs[i]->L, stream);
         if (e != hipSuccess) return hip_fail(e, "int8 pack launch");
     }
-    std::vector<lattice *> words;
-    std::vector<uint32_t> words_n;
+    std::vector<lattice *> words, bytes;
+    std::vector<uint32_t> words_n, bytes_n;
     for (int32_t i = 0; i < count; ++i) {
         if (hs[i]->path == kPathWords) {
             words.push_back(hs[i]);
             words_n.push_back(n_of(i));
+        } else if (swept_enc(hs[i]) == LAT_ENC_INT8) {
+            bytes.push_back(hs[i]);
+            bytes_n.push_back(n_of(i));
         } else {
             const int rc = enqueue_phase_sweeps(hs[i], n_of(i), stream);
             if (rc) return rc;
@@ -728,7 +730,11 @@ int enqueue_offchip_sweeps(lattice *const *hs, int32_t count, const uint32_t *sw
                                                        nullptr, stream, &ran)
                             : LAT_OK;
         if (rc == LAT_OK && !ran)
-            rc = enqueue_words_sweeps(words.data(), (int32_t)words.size(), words_n.data(), 0, stream);
+            rc = enqueue_words_sweeps(words.data(), (int32_t)words.size(), words_n.data(), 0, stream, /*bytes=*/false);
+        if (rc) return rc;
+    }
+    if (!bytes.empty()) {
+        const int rc = enqueue_words_sweeps(bytes.data(), (int32_t)bytes.size(), bytes_n.data(), 0, stream, /*bytes=*/true);
         if (rc) return rc;
     }
     for (int32_t i = 0; i < count && convert; ++i) {
@@ -1078,7 +1084,8 @@ int choose_path(int L, int enc)
     if (const char *force = std::getenv("LATTICE_FORCE_PHASE_KERNELS"))
         if (std::atoi(force) != 0) return kPathPhase;
     (void)enc;
-    if (L <= (L % 64 == 0 ? kLdsRouteMaxL : kLdsMaxL)) return kPathLds;
+    if (L <= (L % 64 == 0 ? kLdsRouteMaxL : kSiteMaxL)) return kPathLds;
+    if (L % 64 != 0 && L <= kLdsMaxL) return kPathBytes;
     return words_ok ? kPathWords : kPathPhase;
 }
 

@@ -25,50 +25,122 @@ namespace lat {
 namespace {
 
 // ---------------------------------------------------------------------------
-// int8 layout: one code per byte, row-major.  Thread t owns Philox call t,
-// i.e. pairs 2t and 2t+1 (words 0,1 and 2,3 of the call).
-__global__ void __launch_bounds__(256) k_phase_int8(PhaseArgs a)
+// int8 layout: one code per byte, row-major, any side.  Row i of the grid updates
+// lattice i; a thread owns Philox calls t, i.e. pairs 2t and 2t+1 (words 0,1
+// and 2,3 of the call).  As in k_phase_words, what bounds a launch at medium
+// sides is its chain: the arguments, the descriptor with the tables behind
+// it, and the sites of both pairs, all loaded at once.  A site and its left and
+// right neighbours are mostly bytes of the aligned group of four that holds it:
+// one 32-bit load, and a byte more in the phases whose column is the group's
+// first or last.
+struct ByteVals {
+    uint32_t A, B;                    // the groups of the a-site and of the b-site
+    uint32_t ae, be;                  // their neighbours outside the groups
+    uint32_t au, ad, bu, bd;          // upper and lower neighbours
+    uint32_t oa, ob;                  // offsets of the two sites
+};
+// The phase on a lattice of side L: columns p and pb of the groups, the
+// partners' shift (dX groups, k double rows).
+struct BytePhase {
+    uint32_t L, Lq, p, pb, dX, k;
+};
+
+__device__ __forceinline__ ByteVals byte_fetch(const LAT_GLOBAL uint8_t *st, const BytePhase &f, uint32_t X, uint32_t Y)
+{
+    ByteVals v;
+    const uint32_t L = f.L, ra = 2u * Y * L, rau = Y == 0 ? (L - 1u) * L : ra - L;
+    uint32_t Xb = X + f.dX, Yb = Y + f.k;
+    Xb = min(Xb, Xb - f.Lq);  // x mod n for x < 2n
+    Yb = min(Yb, Yb - (L >> 1));
+    const uint32_t rb = (2u * Yb + 1u) * L, rbd = 2u * Yb + 2u == L ? 0u : rb + L;
+    const uint32_t xa = 4u * X, xb = 4u * Xb;
+    v.oa = ra + xa + f.p;
+    v.ob = rb + xb + f.pb;
+    v.A = *(const LAT_GLOBAL word_any *)(st + (ra + xa));
+    v.B = *(const LAT_GLOBAL word_any *)(st + (rb + xb));
+    v.au = st[rau + xa + f.p];
+    v.ad = st[v.oa + L];
+    v.bu = st[v.ob - L];
+    v.bd = st[rbd + xb + f.pb];
+    // (loaded in every phase: a condition would wait for all the loads before it)
+    auto beyond = [&](uint32_t row, uint32_t x, uint32_t X4, uint32_t c) {
+        const uint32_t left = (X4 == 0 ? L : X4) - 1u, right = X4 + 4u == L ? 0u : X4 + 4u;
+        return row + (c == 0u ? left : c == 3u ? right : x);
+    };
+    v.ae = st[beyond(ra, xa + f.p, xa, f.p)];
+    v.be = st[beyond(rb, xb + f.pb, xb, f.pb)];
+    return v;
+}
+
+__device__ __forceinline__ void byte_apply(LAT_GLOBAL uint8_t *st, const BytePhase &f, const ByteVals &v, uint32_t slot8,
+                                           uint32_t ua, const uint2 *s_tab, const uint8_t *s_slots, uint32_t &packed)
+{
+    auto site = [](uint32_t group, uint32_t c) { return (group >> (8u * c)) & 255u; };
+    const uint32_t ca = site(v.A, f.p), cb = site(v.B, f.pb);
+    const uint32_t al = f.p == 0u ? v.ae : site(v.A, f.p - 1u), ar = f.p == 3u ? v.ae : site(v.A, f.p + 1u);
+    const uint32_t bl = f.pb == 0u ? v.be : site(v.B, f.pb - 1u), br = f.pb == 3u ? v.be : site(v.B, f.pb + 1u);
+    const uint32_t bpack = contrib_a(al) + contrib_a(ar) + contrib_a(v.au) + contrib_a(v.ad) + contrib_b(bl) +
+                           contrib_b(br) + contrib_b(v.bu) + contrib_b(v.bd);
+    uint32_t change = 0u;
+    pair_step_slot((ca | cb << 2) << 7 | slot8, bpack, ua, s_slots, s_tab, 0x03030000u, packed, change);
+    if (change) {
+        st[v.oa] = (uint8_t)(ca ^ (change >> 16 & 3u));
+        st[v.ob] = (uint8_t)(cb ^ change >> 24);
+    }
+}
+
+__global__ void __launch_bounds__(kWordsPhaseMaxThreads) k_phase_bytes(WordsArgs a)
 {
     __shared__ uint2 s_tab[kDevTabEntries];
-    __shared__ uint2 s_trans[kTransEntries];
-    stage_tables(s_tab, s_trans, a.dev_tab, a.trans);
-    const int L = a.L, Lq = L >> 2;
-    const uint32_t n_calls = (uint32_t)L * (uint32_t)L / 16u;
-    int8_t *st = (int8_t *)a.state;
-    const int Dx = a.r + 4 * a.m, Dy = 1 + 2 * a.k;
+    __shared__ __align__(16) uint2 s_slots[kSlotEntries];
+    uint8_t *scr = a.scratch[blockIdx.y];
+    const uint32_t sweeps = a.sweeps[blockIdx.y], blocks = a.blocks[blockIdx.y];
+    // the whole block: no barrier is skipped by part of it (one condition of all
+    // three arguments, for one wait)
+    if ((scr == nullptr) | (a.iter >= sweeps) | (blockIdx.x >= blocks)) return;
+    const uint32_t threads = a.threads;  // (the launch's own count is in a further line of arguments)
+    TableLoads tables;
+    tables.load((const uint2 *)(scr + kScrDevTab), threads);
+    const LatDesc d = *(const LatDesc *)(scr + kScrDesc);
+    LAT_GLOBAL uint8_t *st = (LAT_GLOBAL uint8_t *)d.state;
+    // after the descriptor's loads, which would not be scalar behind it
+    __builtin_amdgcn_s_setprio(3);
+    const uint64_t s = d.next_sweep + a.iter;
+    int r, mm[4], kk[4];
+    device_schedule(d.L, d.key0, d.key1, s, r, mm, kk);
+    BytePhase f;
+    f.L = (uint32_t)d.L;
+    f.Lq = f.L >> 2;
+    f.p = (uint32_t)a.p;
+    f.pb = (f.p + (uint32_t)r) & 3u;
+    f.dX = (uint32_t)mm[a.p] + ((f.p + (uint32_t)r) >> 2);
+    f.dX = min(f.dX, f.dX - f.Lq);
+    f.k = (uint32_t)kk[a.p];
+    const uint32_t calls = f.L * f.L / 16u, step = blocks * threads;
+    uint32_t t = blockIdx.x * threads + threadIdx.x;
+    ByteVals v[2];
+    u32x4 w;
+    // threads past the last call load the first one's sites
+    auto fetch = [&](uint32_t call) {
+        const uint32_t pi = 2u * call, Y = pi / f.Lq, X = pi - Y * f.Lq;
+        const bool wraps = X + 1u == f.Lq;
+        v[0] = byte_fetch(st, f, X, Y);
+        v[1] = byte_fetch(st, f, wraps ? 0u : X + 1u, wraps ? Y + 1u : Y);
+        w = pair_draws(philox4x32_10((uint32_t)s, f.p, call, (uint32_t)(s >> 32), d.key0, d.key1));
+    };
+    fetch(t < calls ? t : 0u);
+    tables.store(s_tab, s_slots, threads);
+    __syncthreads();
     int tr[3] = {0, 0, 0};
-    for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < n_calls; t += gridDim.x * blockDim.x) {
-        const u32x4 w = philox4x32_10(a.s_lo, (uint32_t)a.p, t, a.s_hi, a.key0, a.key1);
+    while (t < calls) {
         uint32_t packed = 0;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const uint32_t pi = 2u * t + (uint32_t)h;
-            const int Y = (int)(pi / (uint32_t)Lq);
-            const int x = 4 * ((int)pi - Y * Lq) + a.p, y = 2 * Y;
-            int xb = x + Dx, yb = y + Dy;
-            if (xb >= L) xb -= L;
-            if (yb >= L) yb -= L;
-            const int xl = x == 0 ? L - 1 : x - 1, xr = x == L - 1 ? 0 : x + 1;
-            const int yu = y == 0 ? L - 1 : y - 1, yd = y == L - 1 ? 0 : y + 1;
-            const int xbl = xb == 0 ? L - 1 : xb - 1, xbr = xb == L - 1 ? 0 : xb + 1;
-            const int ybu = yb == 0 ? L - 1 : yb - 1, ybd = yb == L - 1 ? 0 : yb + 1;
-            const size_t ia = (size_t)y * L + x, ib = (size_t)yb * L + xb;
-            const uint32_t ca = (uint32_t)st[ia], cb = (uint32_t)st[ib];
-            const uint32_t bpack =
-                contrib_a(st[(size_t)y * L + xl]) + contrib_a(st[(size_t)y * L + xr]) +
-                contrib_a(st[(size_t)yu * L + x]) + contrib_a(st[(size_t)yd * L + x]) +
-                contrib_b(st[(size_t)yb * L + xbl]) + contrib_b(st[(size_t)yb * L + xbr]) +
-                contrib_b(st[(size_t)ybu * L + xb]) + contrib_b(st[(size_t)ybd * L + xb]);
-            const uint32_t s0 = ca | (cb << 2);
-            const uint32_t ns = pair_step(s0, bpack, h ? w.z : w.x, h ? w.w : w.y, s_trans, s_tab, packed);
-            if (ns != s0) {
-                st[ia] = (int8_t)(ns & 3u);
-                st[ib] = (int8_t)(ns >> 2);
-            }
-        }
+        byte_apply(st, f, v[0], w.x, w.y, s_tab, (const uint8_t *)s_slots, packed);
+        byte_apply(st, f, v[1], w.z, w.w, s_tab, (const uint8_t *)s_slots, packed);
         unpack_tracker(packed, tr);
+        t += step;
+        if (t < calls) fetch(t);
     }
-    block_reduce_add<3>(tr, a.track + 3 * (size_t)blockIdx.x);
+    wave_reduce_add3(tr, (unsigned long long *)(scr + kScrSlots) + 3 * (size_t)(blockIdx.x % kMaxSlots));
 }
 
 // ---------------------------------------------------------------------------
@@ -340,15 +412,9 @@ int num_cus()
 }  // namespace
 
 // ---------------------------------------------------------------------------
-hipError_t launch_phase_int8(const PhaseArgs &a, hipStream_t s)
+hipError_t launch_phase_bytes(const WordsArgs &a, int threads, hipStream_t s)
 {
-    const uint32_t n_calls = (uint32_t)a.L * (uint32_t)a.L / 16u;
-    const uint32_t block = 256;
-    uint32_t grid = (n_calls + block - 1) / block;
-    uint32_t cap = 4u * (uint32_t)num_cus();
-    if (cap > (uint32_t)kMaxSlots) cap = (uint32_t)kMaxSlots;
-    if (grid > cap) grid = cap;
-    hipLaunchKernelGGL(k_phase_int8, dim3(grid), dim3(block), 0, s, a);
+    hipLaunchKernelGGL(k_phase_bytes, dim3(a.max_blocks, (unsigned)a.count), dim3((unsigned)threads), 0, s, a);
     return hipGetLastError();
 }
 

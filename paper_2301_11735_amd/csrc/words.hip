@@ -37,9 +37,6 @@ namespace {
 // other kernels (the server runs batches of small lattices beside them): the
 // last block of a launch is waited for (served burst of 40 requests 173 ms
 // without and 147 with priority; all of it 180 -> 126).
-constexpr int kTabAhead = 4;  // all of the threshold table in blocks of kWordsThreads
-static_assert(kTabAhead * kWordsThreads >= kDevTabEntries, "k_phase_words' loads");
-
 template <int Q>
 __global__ void __launch_bounds__(kWordsPhaseMaxThreads) k_phase_words(WordsArgs a)
 {
@@ -51,14 +48,8 @@ __global__ void __launch_bounds__(kWordsPhaseMaxThreads) k_phase_words(WordsArgs
     // three arguments, for one wait)
     if ((scr == nullptr) | (a.iter >= sweeps) | (blockIdx.x >= blocks)) return;
     const uint32_t threads = a.threads;  // (the launch's own count is in a further line of arguments)
-    const uint2 *g_tab = (const uint2 *)(scr + kScrDevTab);
-    const uint2 *g_slots = (const uint2 *)kWordSlots.v;
-    // the first entries of the tables, to be stored behind the state's loads
-    uint2 tab[kTabAhead];
-#pragma unroll
-    for (int k = 0; k < kTabAhead; ++k)
-        tab[k] = g_tab[min((int)(threadIdx.x + k * threads), kDevTabEntries - 1)];
-    const uint2 slot = g_slots[min((int)threadIdx.x, kSlotEntries - 1)];
+    TableLoads tables;
+    tables.load((const uint2 *)(scr + kScrDevTab), threads);
     const LatDesc d = *(const LatDesc *)(scr + kScrDesc);
     uint32_t *st = (uint32_t *)(d.enc == 1 ? d.state : (void *)(scr + kScrWork));
     // after the descriptor's loads, which would not be scalar behind it
@@ -79,21 +70,12 @@ __global__ void __launch_bounds__(kWordsPhaseMaxThreads) k_phase_words(WordsArgs
     const WordVals<Q> v = word_fetch<Q, false>(st, refs);
     u32x4 draws[kTaskCalls<Q>];
     word_draws<Q>(task_call0<Q>(f, at), q, s, a.p, d.key0, d.key1, draws);
-#pragma unroll
-    for (int k = 0; k < kTabAhead; ++k)
-        if (threadIdx.x + k * threads < kDevTabEntries) s_tab[threadIdx.x + k * threads] = tab[k];
-    if (threadIdx.x < kSlotEntries) s_slots[threadIdx.x] = slot;
-    for (int i = threadIdx.x + kTabAhead * threads; i < kDevTabEntries; i += threads) s_tab[i] = g_tab[i];
-    for (int i = threadIdx.x + threads; i < kSlotEntries; i += threads) s_slots[i] = g_slots[i];
+    tables.store(s_tab, s_slots, threads);
     __syncthreads();
 
     int tr[3] = {0, 0, 0};
     if (mine) unpack_tracker(word_apply<Q, false, false>(st, f, refs, v, q, draws, s_tab, (const uint8_t *)s_slots, nullptr), tr);
-    // a wave's sums: one atomic each, without a further barrier
-    const int t0 = dpp_step_sum(tr[0]), t1 = dpp_step_sum(tr[1]), t2 = dpp_step_sum(tr[2]);
-    const int lane = (int)(threadIdx.x & 63u), t = lane == 0 ? t0 : lane == 1 ? t1 : t2;
-    if (lane < 3 && t != 0)
-        atomicAdd((unsigned long long *)(scr + kScrSlots) + 3 * (size_t)blockIdx.x + lane, (unsigned long long)(long long)t);
+    wave_reduce_add3(tr, (unsigned long long *)(scr + kScrSlots) + 3 * (size_t)blockIdx.x);
 }
 
 // Block sums of m (per thread: tracker moves 0-2, spin, staggered spin and
@@ -394,6 +376,7 @@ int words_lanes(int L)
 
 hipError_t launch_phase_words(const WordsArgs &a, int Q, int threads, hipStream_t s)
 {
+    if (Q == 0) return launch_phase_bytes(a, threads, s);
     const dim3 grid(a.max_blocks, (unsigned)a.count), block((unsigned)threads);
     switch (Q) {
     case 1: hipLaunchKernelGGL(k_phase_words<1>, grid, block, 0, s, a); break;
