@@ -253,7 +253,8 @@ __device__ __forceinline__ void site_step(uint8_t *lat, const SitePos &s, const 
     const uint32_t t = na | nb << 8, x = ea | eb << 8;
     const uint32_t bpack = (t & 0x0F0Fu) | (t & 0xF0F0u) << 12;
     const uint2 tr = *(const uint2 *)(s_trans + ((((x * kSiteHash) >> 21) & 0x780u) | dr.slot8));
-    const uint2 e = *(const uint2 *)(s_tab + tab_offset(tr, bpack));
+    const uint32_t idx = (uint32_t)__builtin_amdgcn_sdot4((int)tr.x, (int)bpack, (int)tr.y, false);
+    const uint2 e = *(const uint2 *)(s_tab + (uint32_t)(uint16_t)(idx << 3));
     const bool acc = dr.ua < e.x;
     packed += acc ? e.y : 0u;
     const uint32_t nw = acc ? tr.y >> 16 : x;

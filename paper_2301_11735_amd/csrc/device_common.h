@@ -179,14 +179,6 @@ __device__ __forceinline__ u32x4 pair_draws(const u32x4 &w)
     return u32x4{slot8_of(w.x), min(w.y, 0xFFFFFFFEu), slot8_of(w.z), min(w.w, 0xFFFFFFFEu)};
 }
 
-// Byte offset of a move's entry in the device table: 8 (dot4(coef, sums) + C),
-// from the transition entry {coef, C | changes << 16} and the packed sums.
-__device__ __forceinline__ uint32_t tab_offset(const uint2 &tr, uint32_t sums)
-{
-    const uint32_t idx = (uint32_t)__builtin_amdgcn_sdot4((int)tr.x, (int)sums, (int)tr.y, false);
-    return (uint32_t)(uint16_t)(idx << 3);
-}
-
 // One coupled-pair Metropolis step (section 3.1) from the byte offset of its
 // transition entry, the packed neighbour sums (sumS_a+4, sumS_b+4, sumsig_a+4,
 // sumsig_b+4) and the acceptance draw.  An accepted move adds its packed triple to `packed`
@@ -197,7 +189,8 @@ __device__ __forceinline__ void pair_step_slot(uint32_t entry, uint32_t bpack, u
                                                const uint2 *s_tab, uint32_t fields, uint32_t &packed, uint32_t &dacc)
 {
     const uint2 tr = *(const uint2 *)(s_slots + entry);
-    const uint2 e = *(const uint2 *)((const uint8_t *)s_tab + tab_offset(tr, bpack));
+    const uint32_t idx = (uint32_t)__builtin_amdgcn_sdot4((int)tr.x, (int)bpack, (int)tr.y, false);
+    const uint2 e = *(const uint2 *)((const uint8_t *)s_tab + (uint32_t)(uint16_t)(idx << 3));
     const bool acc = ua < e.x;
     packed += acc ? e.y : 0u;
     dacc |= tr.y & (acc ? fields : 0u);

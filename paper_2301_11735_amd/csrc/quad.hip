@@ -232,7 +232,8 @@ __device__ __forceinline__ void quad_step(uint8_t *lat, const QuadGeom &g, const
         const u32x4 &w = d.c[i >> 1];
         const uint32_t row = i == 0 ? id << 5 : id >> (i == 0 ? 0 : 8 * i - 5);
         const uint2 tr2 = *(const uint2 *)(s_slots + ((row & 0x780u) | ((i & 1) ? w.z : w.x)));
-        const uint2 e = *(const uint2 *)((const uint8_t *)s_tab + tab_offset(tr2, n[i]));
+        const uint32_t idx = (uint32_t)__builtin_amdgcn_sdot4((int)tr2.x, (int)n[i], (int)tr2.y, false);
+        const uint2 e = *(const uint2 *)((const uint8_t *)s_tab + (uint32_t)(uint16_t)(idx << 3));
         const bool acc = ((i & 1) ? w.w : w.y) < e.x;
         packed += acc ? e.y : 0u;
         ch[i] = acc ? tr2.y : 0u;
