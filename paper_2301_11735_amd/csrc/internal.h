@@ -39,6 +39,7 @@ struct lattice {
     hipStream_t stream = nullptr;
     lat::Tuning2Bit tuning{0, 0, 0, 0};
     int path = kPathLds;
+    bool path_asked = false;  // by the environment
     bool packed = false;  // int8 swept on the 2-bit copy at scratch + kScrWork
     // set once a persistent launch has swept it, so that reads check the
     // device-wide barrier's time-out flag
@@ -122,7 +123,8 @@ int enqueue_observables_batch(lattice *const *hs, int32_t count, unsigned long l
 // the server, would otherwise leave it waiting for compute units).
 int enqueue_offchip_sweeps(lattice *const *hs, int32_t count, const uint32_t *sweeps, uint32_t uniform,
                            hipStream_t stream, bool convert = true, bool persistent = true);
-// Lattices of the multi-block path as persistent launches: lattice i by
+// Lattices as persistent multi-block launches (bytes: int8 ones as they are, at
+// multiples of four bytes, without records; else on their two-bit state): lattice i by
 // sweeps[i] (null: `every`) with intervals = 1 and no records, or, with
 // records, an observation series of one lattice: intervals x every sweeps, a
 // kSeriesRecord record after each interval.  *ran = false (nothing
@@ -131,7 +133,7 @@ int enqueue_offchip_sweeps(lattice *const *hs, int32_t count, const uint32_t *sw
 // caller then uses the per-phase launches.  Packed int8 lattices must
 // already be on their 2-bit copy.
 int enqueue_words_persistent(lattice *const *hs, int32_t count, const uint32_t *sweeps, uint32_t intervals,
-                             uint32_t every, long long *records, hipStream_t stream, bool *ran);
+                             uint32_t every, long long *records, hipStream_t stream, bool bytes, bool *ran);
 // Checks of lat_params (geometry, finite couplings, T > 0, the charge target
 // of eq. 2); writes the target charge and the charged count.
 int validate_params(const lat_params *p, int64_t *Q, int64_t *Nc);

@@ -185,6 +185,8 @@ inline uint32_t bytes_blocks(int L, int threads = kWordsThreads)
     return nb < (uint32_t)kBytesMaxBlocks ? nb : (uint32_t)kBytesMaxBlocks;
 }
 hipError_t launch_phase_bytes(const WordsArgs &a, int threads, hipStream_t s);
+constexpr int kBytesSeriesMaxThreads = 1024;
+const void *bytes_series_kernel();
 // desc->next_sweep += sweeps[i] for every lattice of the series.
 hipError_t launch_advance_words(const WordsArgs &a, hipStream_t s);
 // Persistent multi-block form: up to kWordsBatch lattices (blocks
@@ -194,6 +196,7 @@ hipError_t launch_advance_words(const WordsArgs &a, hipStream_t s);
 // kSeriesRecord bytes each, as launch_observables writes them) the observables
 // and tracker after every interval.  The barrier words (in each lattice's
 // scratch) are cleared and the records initialised by kernels enqueued first.
+// Q = 0: int8 lattices as they are, at multiples of four bytes; no records.
 struct WordsSeriesArgs {
     int count;
     int threads;              // block size: a multiple of 64 up to kWordsThreads (Q >= 4: kWordsSeriesMaxThreads)

@@ -403,6 +403,11 @@ namespace {
 // state, or the 2-bit copy of a packed int8 lattice.
 void *swept_state(const lattice *h) { return h->packed ? (void *)(h->d_scratch + kScrWork) : h->d_state; }
 int swept_enc(const lattice *h) { return h->packed ? LAT_ENC_2BIT : h->enc; }
+// Off the chip and swept as the int8 sites they are.
+bool by_bytes(const lattice *h)
+{
+    return h->path != kPathLds && h->path != kPathWords && swept_enc(h) == LAT_ENC_INT8;
+}
 
 // Host-scheduled path: four phase launches per sweep, then the device-side
 // sweep counter is advanced to match.
@@ -597,31 +602,68 @@ WordsShape words_series_shape(lattice *const *hs, int32_t n)
     }
     return w;
 }
+// Of int8 lattices: the smallest blocks of which one a compute unit holds a
+// call a thread, up to 512 threads; bytes_fit: whether there are such.
+uint32_t blocks_of_all(lattice *const *hs, int32_t n, int threads)
+{
+    uint32_t sum = 0;
+    for (int32_t i = 0; i < n; ++i) sum += bytes_blocks(hs[i]->L, threads);
+    return sum;
+}
+bool bytes_fit(lattice *const *hs, int32_t n) { return n <= kWordsBatch && blocks_of_all(hs, n, 2 * kWordsThreads) <= 256u; }
+WordsShape bytes_series_shape(lattice *const *hs, int32_t n)
+{
+    WordsShape w{0, blocks_of_all(hs, n, kWordsThreads) <= 256u ? kWordsThreads : 2 * kWordsThreads};
+    if (const char *v = std::getenv("LATTICE_WORDS_SERIES_BLOCK")) {
+        const int want = std::atoi(v);
+        if (want >= 64 && want <= kBytesSeriesMaxThreads && want % 64 == 0) w.threads = want;
+    }
+    return w;
+}
 
 }  // namespace
 
+namespace {
+// A captured kernel node would not guarantee that all blocks are resident at once.
+bool captured(hipStream_t stream)
+{
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess) (void)hipGetLastError();
+    return capture != hipStreamCaptureStatusNone;
+}
+}  // namespace
+
 int enqueue_words_persistent(lattice *const *hs, int32_t count, const uint32_t *sweeps, uint32_t intervals,
-                             uint32_t every, long long *records, hipStream_t stream, bool *ran)
+                             uint32_t every, long long *records, hipStream_t stream, bool bytes, bool *ran)
 {
     *ran = false;
     if (count <= 0 || intervals == 0 || every == 0) return LAT_OK;
     int max_L = 0;
+    uint32_t longest = 0;
     for (int32_t i = 0; i < count; ++i) {
-        if (hs[i]->path != kPathWords) return LAT_OK;
+        if (bytes && (records || (uintptr_t)hs[i]->d_state % 4 != 0)) return LAT_OK;
         max_L = std::max(max_L, hs[i]->L);
+        longest = std::max(longest, sweeps ? sweeps[i] : every);
     }
     // default: on for every lattice of this path, against one launch per phase
     // (us a sweep, plain / with observables after every sweep): L = 512
     // 9.6 / 12.0 against 21.7 / 34.4, L = 1024 12.3 / 14.7 against 22.0 /
     // 34.8, L = 2048 14.2 / 18.3 against 23.6 / 36.5.
+    // A call of one sweep is the other way round (from an idle stream to its end
+    // 50 us against 31 at L = 256, 55 against 36 at L = 1000).  Of int8 lattices
+    // as they are: as long as a block a compute unit holds a call a thread (us a
+    // sweep, persistent / launches: L = 388 12.5 / 18.0, L = 1000 16.3 / 19.9, 8 of
+    // L = 500 24.5 / 25.5; but L = 2000 33.8 / 35.4, L = 4000 99 / 75).
     // LATTICE_WORDS_PERSISTENT=0|1 overrides.
     const char *v = std::getenv("LATTICE_WORDS_PERSISTENT");
-    if (v ? std::atoi(v) == 0 : max_L > kWordsPersistentMaxL) return LAT_OK;
+    if (v) {
+        if (std::atoi(v) == 0) return LAT_OK;
+    } else {
+        if (!records && longest < 2) return LAT_OK;
+        if (bytes ? !bytes_fit(hs, count) : max_L > kWordsPersistentMaxL) return LAT_OK;
+    }
     if (records && count != 1) return fail(LAT_EINVAL, "an observation series holds one lattice");
-    // a captured kernel node would not guarantee that all blocks are resident at once
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &capture) != hipSuccess) (void)hipGetLastError();
-    if (capture != hipStreamCaptureStatusNone) return LAT_OK;
+    if (captured(stream)) return LAT_OK;
     // the barrier counter counts blocks x barriers: at most 2^20 barriers per
     // launch keeps it below 2^32 for any resident grid
     constexpr uint64_t kMaxBarriers = 1u << 20;
@@ -634,7 +676,7 @@ int enqueue_words_persistent(lattice *const *hs, int32_t count, const uint32_t *
     // resident blocks
     for (int32_t g0 = 0; g0 < count; g0 += kWordsBatch) {
         const int32_t n = std::min<int32_t>(kWordsBatch, count - g0);
-        const WordsShape shape = words_series_shape(hs + g0, n);
+        const WordsShape shape = bytes ? bytes_series_shape(hs + g0, n) : words_series_shape(hs + g0, n);
         const int Q = shape.Q, threads = shape.threads;
         const int capacity = words_capacity(Q, threads);
         if (capacity <= 0) return *ran ? fail(LAT_EHIP, "persistent word launch is not possible") : LAT_OK;
@@ -642,7 +684,8 @@ int enqueue_words_persistent(lattice *const *hs, int32_t count, const uint32_t *
         uint32_t nb[kWordsBatch];
         uint32_t total = 0;
         for (int32_t i = 0; i < n; ++i) {
-            nb[i] = std::min<uint32_t>({words_blocks(hs[g0 + i]->L, Q, threads), share, (uint32_t)kMaxSlots});
+            const uint32_t all = bytes ? bytes_blocks(hs[g0 + i]->L, threads) : words_blocks(hs[g0 + i]->L, Q, threads);
+            nb[i] = std::min<uint32_t>({all, share, (uint32_t)kMaxSlots});
             total += nb[i];
         }
         if (total > (uint32_t)capacity) return *ran ? fail(LAT_EHIP, "persistent word launch does not fit") : LAT_OK;
@@ -700,6 +743,43 @@ int enqueue_words_persistent(lattice *const *hs, int32_t count, const uint32_t *
     return LAT_OK;
 }
 
+// Whether few on-chip lattices of large sides are faster spread over many blocks
+// in the persistent kernels than with a compute unit each, for calls of
+// `sweeps` sweeps that cost `extra` ns more that way.  ns a sweep: on the chip
+// 0.229 L^2 in the four-pair form and 0.34 L^2 per site (L = 256 15.0 us, L = 340
+// 39.5); spread 9.7 us with two bits a site and 12 as bytes, and 4.6 more when
+// every compute unit has a block (L = 256 9.7, L = 340 12.0, 16 of L = 260 17).
+// Lattices whose path was asked for stay on it.
+bool spreads(lattice *const *hs, int32_t count, uint64_t sweeps, double extra, hipStream_t stream)
+{
+    if (count < 1 || count > kWordsBatch) return false;
+    int max_L = 0;
+    bool quad = true;
+    for (int32_t i = 0; i < count; ++i) {
+        if (hs[i]->path_asked || hs[i]->enc != hs[0]->enc || (uintptr_t)hs[i]->d_state % 4 != 0) return false;
+        max_L = std::max(max_L, hs[i]->L);
+        quad = quad && hs[i]->L % 16 == 0;
+    }
+    const uint32_t blocks = blocks_of_all(hs, count, kWordsThreads);
+    if (blocks > 256u) return false;
+    const double on_chip = (quad ? 0.229 : 0.34) * max_L * max_L;
+    const double spread = (hs[0]->enc == LAT_ENC_INT8 ? 12000.0 : 9700.0) + 18.0 * blocks;
+    return (double)sweeps * (on_chip - spread) > extra && !captured(stream);
+}
+constexpr double kSpreadCall = 25000.0;  // two launches, one of them cooperative, against one
+
+// Sweeps of on-chip lattices outside the server and graphs.
+int enqueue_small_sweeps(lattice *const *hs, int32_t count, uint32_t sweeps, hipStream_t stream, bool tune)
+{
+    if (spreads(hs, count, sweeps, kSpreadCall, stream)) {
+        bool ran = false;
+        const int rc = enqueue_words_persistent(hs, count, nullptr, 1, sweeps, nullptr, stream,
+                                                hs[0]->enc == LAT_ENC_INT8, &ran);
+        if (rc || ran) return rc;
+    }
+    return enqueue_lds_sweeps(hs, count, nullptr, sweeps, stream, tune);
+}
+
 int enqueue_offchip_sweeps(lattice *const *hs, int32_t count, const uint32_t *sweeps, uint32_t uniform,
                            hipStream_t stream, bool convert, bool persistent)
 {
@@ -716,7 +796,7 @@ int enqueue_offchip_sweeps(lattice *const *hs, int32_t count, const uint32_t *sw
         if (hs[i]->path == kPathWords) {
             words.push_back(hs[i]);
             words_n.push_back(n_of(i));
-        } else if (swept_enc(hs[i]) == LAT_ENC_INT8) {
+        } else if (by_bytes(hs[i])) {
             bytes.push_back(hs[i]);
             bytes_n.push_back(n_of(i));
         } else {
@@ -727,14 +807,19 @@ int enqueue_offchip_sweeps(lattice *const *hs, int32_t count, const uint32_t *sw
     if (!words.empty()) {
         bool ran = false;
         int rc = persistent ? enqueue_words_persistent(words.data(), (int32_t)words.size(), words_n.data(), 1, 1,
-                                                       nullptr, stream, &ran)
+                                                       nullptr, stream, /*bytes=*/false, &ran)
                             : LAT_OK;
         if (rc == LAT_OK && !ran)
             rc = enqueue_words_sweeps(words.data(), (int32_t)words.size(), words_n.data(), 0, stream, /*bytes=*/false);
         if (rc) return rc;
     }
     if (!bytes.empty()) {
-        const int rc = enqueue_words_sweeps(bytes.data(), (int32_t)bytes.size(), bytes_n.data(), 0, stream, /*bytes=*/true);
+        bool ran = false;
+        int rc = persistent ? enqueue_words_persistent(bytes.data(), (int32_t)bytes.size(), bytes_n.data(), 1, 1,
+                                                       nullptr, stream, /*bytes=*/true, &ran)
+                            : LAT_OK;
+        if (rc == LAT_OK && !ran)
+            rc = enqueue_words_sweeps(bytes.data(), (int32_t)bytes.size(), bytes_n.data(), 0, stream, /*bytes=*/true);
         if (rc) return rc;
     }
     for (int32_t i = 0; i < count && convert; ++i) {
@@ -1060,7 +1145,7 @@ int enqueue_sweeps(lattice *h, uint32_t sweeps, hipStream_t stream)
     if (h->path != kPathLds) return enqueue_offchip_sweeps(one, 1, nullptr, sweeps, stream);
     // a lone lattice is not autotuned (tuning synchronises); it takes the
     // block size tuned for its shape by an earlier batch, else the default
-    return enqueue_lds_sweeps(one, 1, nullptr, sweeps, stream, /*tune=*/false);
+    return enqueue_small_sweeps(one, 1, sweeps, stream, /*tune=*/false);
 }
 
 // Sweep path of a new lattice.  Default: the one-block LDS kernel up to
@@ -1161,6 +1246,7 @@ int lattice_create(const lat_params *p, void *d_state, size_t state_bytes, void 
         h->stream = (hipStream_t)hip_stream;
         h->tuning = tuning_from_env();
         h->path = choose_path(p->L, p->encoding);
+        h->path_asked = std::getenv("LATTICE_PATH") != nullptr;
         h->packed = h->path != kPathLds && int8_packs(p->L, p->encoding);
         h->magic = kMagic;
         LatDesc desc{};
@@ -1253,7 +1339,7 @@ int lattice_sweep_batch(lattice *const *hs, int32_t count, uint32_t sweeps, void
         if (sweeps == 0) return LAT_OK;
         std::vector<lattice *> small, big;
         for (int32_t i = 0; i < count; ++i) (hs[i]->path == kPathLds ? small : big).push_back(hs[i]);
-        int rc = enqueue_lds_sweeps(small.data(), (int32_t)small.size(), nullptr, sweeps, (hipStream_t)hip_stream);
+        int rc = enqueue_small_sweeps(small.data(), (int32_t)small.size(), sweeps, (hipStream_t)hip_stream, /*tune=*/true);
         if (rc == LAT_OK && !big.empty())
             rc = enqueue_offchip_sweeps(big.data(), (int32_t)big.size(), nullptr, sweeps, (hipStream_t)hip_stream);
         return rc;
@@ -1294,16 +1380,25 @@ int lattice_sweep_series(lattice *h, uint32_t intervals, uint32_t every, void *d
         }
         // the whole series in persistent launches where they can run
         bool ran = false;
-        const int rc0 = enqueue_words_persistent(one, 1, nullptr, intervals, every, (long long *)d_series, st, &ran);
-        if (rc0) return rc0;
-        if (h->path == kPathLds) {
+        const bool small = h->path == kPathLds, bytes = h->enc == LAT_ENC_INT8;
+        // records of the persistent kernel cost 2.5 us more than on the chip; int8
+        // lattices as they are take two launches and a reduction an interval
+        const bool wide = small && (bytes ? spreads(one, 1, every, 45000.0, st)
+                                          : spreads(one, 1, (uint64_t)intervals * every, kSpreadCall + 2500.0 * intervals, st));
+        if (h->path == kPathWords || (wide && !bytes)) {
+            const int rc = enqueue_words_persistent(one, 1, nullptr, intervals, every, (long long *)d_series, st,
+                                                    /*bytes=*/false, &ran);
+            if (rc) return rc;
+        }
+        if (small && !ran && !(wide && bytes)) {
             const ObsTarget obs{(unsigned long long *)d_series, intervals, kSeriesRecord / 8, kSeriesRecord / 8};
             const int rc = enqueue_lds_sweeps(one, 1, nullptr, every, st, /*tune=*/false, &obs);
             if (rc) return rc;
             ran = true;
         }
         for (uint32_t k = 0; k < intervals && !ran; ++k) {
-            const int rc = enqueue_offchip_sweeps(one, 1, nullptr, every, st, /*convert=*/false);
+            const int rc = small ? enqueue_small_sweeps(one, 1, every, st, /*tune=*/false)
+                                 : enqueue_offchip_sweeps(one, 1, nullptr, every, st, /*convert=*/false);
             if (rc) return rc;
             long long *rec = (long long *)((uint8_t *)d_series + kSeriesRecord * (size_t)k);
             const hipError_t e = launch_observables(h->d_scratch, h->packed ? (const void *)work : h->d_state, h->L,

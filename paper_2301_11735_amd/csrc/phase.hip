@@ -20,6 +20,7 @@
 #include <algorithm>
 
 #include "device_common.h"
+#include "word_task.h"
 
 namespace lat {
 namespace {
@@ -29,51 +30,96 @@ namespace {
 // lattice i; a thread owns Philox calls t, i.e. pairs 2t and 2t+1 (words 0,1
 // and 2,3 of the call).  As in k_phase_words, what bounds a launch at medium
 // sides is its chain: the arguments, the descriptor with the tables behind
-// it, and the sites of both pairs, all loaded at once.  A site and its left and
+// it, and the sites of both pairs, all loaded at once (L = 1000 5.8 -> 5.5 us a
+// phase, L = 4000 20.7 -> 18.6; before, tables and sites one after another).  A site and its left and
 // right neighbours are mostly bytes of the aligned group of four that holds it:
 // one 32-bit load, and a byte more in the phases whose column is the group's
 // first or last.
+// Offsets of what a pair reads: the groups of its two sites, their neighbours
+// beyond the groups (loaded in every phase: a condition would wait for all
+// the loads before it), the upper and lower neighbours, and the sites.
+struct ByteRefs {
+    uint32_t A, B, ae, be, au, ad, bu, bd, oa, ob;
+};
 struct ByteVals {
-    uint32_t A, B;                    // the groups of the a-site and of the b-site
-    uint32_t ae, be;                  // their neighbours outside the groups
-    uint32_t au, ad, bu, bd;          // upper and lower neighbours
-    uint32_t oa, ob;                  // offsets of the two sites
+    uint32_t A, B, ae, be, au, ad, bu, bd;
 };
 // The phase on a lattice of side L: columns p and pb of the groups, the
 // partners' shift (dX groups, k double rows).
 struct BytePhase {
     uint32_t L, Lq, p, pb, dX, k;
 };
-
-__device__ __forceinline__ ByteVals byte_fetch(const LAT_GLOBAL uint8_t *st, const BytePhase &f, uint32_t X, uint32_t Y)
+__device__ __forceinline__ BytePhase byte_phase(int L, uint32_t p, int r, int m, int k)
 {
-    ByteVals v;
+    BytePhase f;
+    f.L = (uint32_t)L;
+    f.Lq = f.L >> 2;
+    f.p = p;
+    f.pb = (p + (uint32_t)r) & 3u;
+    f.dX = (uint32_t)m + ((p + (uint32_t)r) >> 2);
+    f.dX = min(f.dX, f.dX - f.Lq);  // x mod n for x < 2n
+    f.k = (uint32_t)k;
+    return f;
+}
+
+__device__ __forceinline__ ByteRefs byte_refs(const BytePhase &f, uint32_t X, uint32_t Y)
+{
+    ByteRefs v;
     const uint32_t L = f.L, ra = 2u * Y * L, rau = Y == 0 ? (L - 1u) * L : ra - L;
     uint32_t Xb = X + f.dX, Yb = Y + f.k;
-    Xb = min(Xb, Xb - f.Lq);  // x mod n for x < 2n
+    Xb = min(Xb, Xb - f.Lq);
     Yb = min(Yb, Yb - (L >> 1));
     const uint32_t rb = (2u * Yb + 1u) * L, rbd = 2u * Yb + 2u == L ? 0u : rb + L;
     const uint32_t xa = 4u * X, xb = 4u * Xb;
-    v.oa = ra + xa + f.p;
-    v.ob = rb + xb + f.pb;
-    v.A = *(const LAT_GLOBAL word_any *)(st + (ra + xa));
-    v.B = *(const LAT_GLOBAL word_any *)(st + (rb + xb));
-    v.au = st[rau + xa + f.p];
-    v.ad = st[v.oa + L];
-    v.bu = st[v.ob - L];
-    v.bd = st[rbd + xb + f.pb];
-    // (loaded in every phase: a condition would wait for all the loads before it)
     auto beyond = [&](uint32_t row, uint32_t x, uint32_t X4, uint32_t c) {
         const uint32_t left = (X4 == 0 ? L : X4) - 1u, right = X4 + 4u == L ? 0u : X4 + 4u;
         return row + (c == 0u ? left : c == 3u ? right : x);
     };
-    v.ae = st[beyond(ra, xa + f.p, xa, f.p)];
-    v.be = st[beyond(rb, xb + f.pb, xb, f.pb)];
+    v.A = ra + xa;
+    v.B = rb + xb;
+    v.oa = v.A + f.p;
+    v.ob = v.B + f.pb;
+    v.ae = beyond(ra, xa + f.p, xa, f.p);
+    v.be = beyond(rb, xb + f.pb, xb, f.pb);
+    v.au = rau + xa + f.p;
+    v.ad = v.oa + L;
+    v.bu = v.ob - L;
+    v.bd = rbd + xb + f.pb;
     return v;
 }
+// The two pairs of Philox call t (pairs 2t and 2t + 1; row-major over the groups).
+__device__ __forceinline__ void call_refs(const BytePhase &f, uint32_t t, ByteRefs (&v)[2])
+{
+    const uint32_t pi = 2u * t, Y = pi / f.Lq, X = pi - Y * f.Lq;
+    const bool wraps = X + 1u == f.Lq;
+    v[0] = byte_refs(f, X, Y);
+    v[1] = byte_refs(f, wraps ? 0u : X + 1u, wraps ? Y + 1u : Y);
+}
 
-__device__ __forceinline__ void byte_apply(LAT_GLOBAL uint8_t *st, const BytePhase &f, const ByteVals &v, uint32_t slot8,
-                                           uint32_t ua, const uint2 *s_tab, const uint8_t *s_slots, uint32_t &packed)
+// Coh: at device coherence, as ldw and stw of the word form (the state is then
+// at a multiple of four bytes).
+template <bool Coh>
+__device__ __forceinline__ ByteVals byte_fetch(const LAT_GLOBAL uint8_t *st, const ByteRefs &r)
+{
+    auto word = [&](uint32_t i) -> uint32_t {
+        if constexpr (Coh)
+            return __hip_atomic_load((const LAT_GLOBAL uint32_t *)(st + i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else
+            return *(const LAT_GLOBAL word_any *)(st + i);
+    };
+    auto byte = [&](uint32_t i) -> uint32_t {
+        if constexpr (Coh)
+            return __hip_atomic_load(st + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else
+            return st[i];
+    };
+    return ByteVals{word(r.A), word(r.B), byte(r.ae), byte(r.be), byte(r.au), byte(r.ad), byte(r.bu), byte(r.bd)};
+}
+
+template <bool Coh>
+__device__ __forceinline__ void byte_apply(LAT_GLOBAL uint8_t *st, const BytePhase &f, const ByteRefs &r,
+                                           const ByteVals &v, uint32_t slot8, uint32_t ua, const uint2 *s_tab,
+                                           const uint8_t *s_slots, uint32_t &packed)
 {
     auto site = [](uint32_t group, uint32_t c) { return (group >> (8u * c)) & 255u; };
     const uint32_t ca = site(v.A, f.p), cb = site(v.B, f.pb);
@@ -84,8 +130,14 @@ __device__ __forceinline__ void byte_apply(LAT_GLOBAL uint8_t *st, const BytePha
     uint32_t change = 0u;
     pair_step_slot((ca | cb << 2) << 7 | slot8, bpack, ua, s_slots, s_tab, 0x03030000u, packed, change);
     if (change) {
-        st[v.oa] = (uint8_t)(ca ^ (change >> 16 & 3u));
-        st[v.ob] = (uint8_t)(cb ^ change >> 24);
+        const uint8_t na = (uint8_t)(ca ^ (change >> 16 & 3u)), nb = (uint8_t)(cb ^ change >> 24);
+        if constexpr (Coh) {
+            __hip_atomic_store(st + r.oa, na, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(st + r.ob, nb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+            st[r.oa] = na;
+            st[r.ob] = nb;
+        }
     }
 }
 
@@ -108,24 +160,17 @@ __global__ void __launch_bounds__(kWordsPhaseMaxThreads) k_phase_bytes(WordsArgs
     const uint64_t s = d.next_sweep + a.iter;
     int r, mm[4], kk[4];
     device_schedule(d.L, d.key0, d.key1, s, r, mm, kk);
-    BytePhase f;
-    f.L = (uint32_t)d.L;
-    f.Lq = f.L >> 2;
-    f.p = (uint32_t)a.p;
-    f.pb = (f.p + (uint32_t)r) & 3u;
-    f.dX = (uint32_t)mm[a.p] + ((f.p + (uint32_t)r) >> 2);
-    f.dX = min(f.dX, f.dX - f.Lq);
-    f.k = (uint32_t)kk[a.p];
+    const BytePhase f = byte_phase(d.L, (uint32_t)a.p, r, mm[a.p], kk[a.p]);
     const uint32_t calls = f.L * f.L / 16u, step = blocks * threads;
     uint32_t t = blockIdx.x * threads + threadIdx.x;
+    ByteRefs at[2];
     ByteVals v[2];
     u32x4 w;
     // threads past the last call load the first one's sites
     auto fetch = [&](uint32_t call) {
-        const uint32_t pi = 2u * call, Y = pi / f.Lq, X = pi - Y * f.Lq;
-        const bool wraps = X + 1u == f.Lq;
-        v[0] = byte_fetch(st, f, X, Y);
-        v[1] = byte_fetch(st, f, wraps ? 0u : X + 1u, wraps ? Y + 1u : Y);
+        call_refs(f, call, at);
+        v[0] = byte_fetch<false>(st, at[0]);
+        v[1] = byte_fetch<false>(st, at[1]);
         w = pair_draws(philox4x32_10((uint32_t)s, f.p, call, (uint32_t)(s >> 32), d.key0, d.key1));
     };
     fetch(t < calls ? t : 0u);
@@ -134,13 +179,84 @@ __global__ void __launch_bounds__(kWordsPhaseMaxThreads) k_phase_bytes(WordsArgs
     int tr[3] = {0, 0, 0};
     while (t < calls) {
         uint32_t packed = 0;
-        byte_apply(st, f, v[0], w.x, w.y, s_tab, (const uint8_t *)s_slots, packed);
-        byte_apply(st, f, v[1], w.z, w.w, s_tab, (const uint8_t *)s_slots, packed);
+        byte_apply<false>(st, f, at[0], v[0], w.x, w.y, s_tab, (const uint8_t *)s_slots, packed);
+        byte_apply<false>(st, f, at[1], v[1], w.z, w.w, s_tab, (const uint8_t *)s_slots, packed);
         unpack_tracker(packed, tr);
         t += step;
         if (t < calls) fetch(t);
     }
     wave_reduce_add3(tr, (unsigned long long *)(scr + kScrSlots) + 3 * (size_t)(blockIdx.x % kMaxSlots));
+}
+
+// Persistent form, as k_words_series without records: all sweeps of a call in one
+// launch of co-resident blocks, a barrier of a lattice's blocks after every
+// phase.  Against one launch per phase (us a sweep): L = 388 18.0 -> 12.2, L = 500
+// 20.7 -> 14.2, L = 1000 22.2 -> 14.6; for larger lattices, whose threads take
+// several calls a phase, the loads past the caches cost more than the launches.
+__global__ void __launch_bounds__(kBytesSeriesMaxThreads) k_bytes_series(WordsSeriesArgs a)
+{
+    __shared__ uint2 s_tab[kDevTabEntries];
+    __shared__ __align__(16) uint2 s_slots[kSlotEntries];
+    int li = 0;  // this block's lattice (uniform)
+    while (li + 1 < a.count && blockIdx.x >= a.first_block[li + 1]) ++li;
+    uint8_t *scr = a.scratch[li];
+    const LatDesc d = *(const LatDesc *)(scr + kScrDesc);
+    LAT_GLOBAL uint8_t *st = (LAT_GLOBAL uint8_t *)d.state;
+    TableLoads tables;
+    tables.load((const uint2 *)(scr + kScrDevTab), blockDim.x);
+    tables.store(s_tab, s_slots, blockDim.x);
+    __syncthreads();
+    const uint8_t *slots = (const uint8_t *)s_slots;
+    const uint32_t b = blockIdx.x - a.first_block[li], nb = a.first_block[li + 1] - a.first_block[li];
+    GridBarrier barrier{(unsigned *)(scr + kScrObsSlots), b, nb, 0u, false};
+    unsigned *err = (unsigned *)(scr + kScrErr);
+    const uint32_t sweeps = a.sweeps[li], calls = (uint32_t)d.L * (uint32_t)d.L / 16u;
+    const uint32_t first = b * blockDim.x + threadIdx.x, stride = nb * blockDim.x;
+    // At most one call a thread (uniform per lattice): its draws and places are
+    // made while the block waits at the barrier.
+    const bool one = stride >= calls, mine = one && first < calls;
+    int r, mm[4], kk[4];
+    device_schedule(d.L, d.key0, d.key1, d.next_sweep, r, mm, kk);
+    BytePhase f = byte_phase(d.L, 0u, r, mm[0], kk[0]);
+    ByteRefs at[2] = {};
+    u32x4 w{};
+    auto prepare = [&](uint64_t s, uint32_t call) {
+        call_refs(f, call, at);
+        w = pair_draws(philox4x32_10((uint32_t)s, f.p, call, (uint32_t)(s >> 32), d.key0, d.key1));
+    };
+    if (mine) prepare(d.next_sweep, first);
+    int tr[3] = {0, 0, 0};
+    for (uint32_t it = 0; it < sweeps; ++it) {
+        const uint64_t s = d.next_sweep + it;
+#pragma unroll 1
+        for (uint32_t p = 0; p < 4u; ++p) {
+            uint32_t packed = 0u;
+            auto step = [&] {
+                const ByteVals v0 = byte_fetch<true>(st, at[0]), v1 = byte_fetch<true>(st, at[1]);
+                byte_apply<true>(st, f, at[0], v0, w.x, w.y, s_tab, slots, packed);
+                byte_apply<true>(st, f, at[1], v1, w.z, w.w, s_tab, slots, packed);
+            };
+            if (mine) step();
+            for (uint32_t t = one ? calls : first; t < calls; t += stride) {
+                prepare(s, t);
+                step();
+                unpack_tracker(packed, tr);
+                packed = 0u;
+            }
+            barrier.arrive();
+            // the next phase's schedule, draws and places, while the others arrive
+            unpack_tracker(packed, tr);
+            if (p == 3u) device_schedule(d.L, d.key0, d.key1, s + 1, r, mm, kk);
+            const uint32_t q = (p + 1u) & 3u;
+            f = byte_phase(d.L, q, r, mm[q], kk[q]);
+            if (mine) prepare(p < 3u ? s : s + 1, first);
+            barrier.wait(err, a.barrier_ticks);
+        }
+    }
+    wave_reduce_add3(tr, (unsigned long long *)(scr + kScrSlots) + 3 * (size_t)(b % kMaxSlots));
+    // every block read the descriptor before its first barrier
+    if (b == 0 && threadIdx.x == 0 && barrier.rounds > 0)
+        ((LatDesc *)(scr + kScrDesc))->next_sweep = d.next_sweep + sweeps;
 }
 
 // ---------------------------------------------------------------------------
@@ -412,6 +528,8 @@ int num_cus()
 }  // namespace
 
 // ---------------------------------------------------------------------------
+const void *bytes_series_kernel() { return (const void *)k_bytes_series; }
+
 hipError_t launch_phase_bytes(const WordsArgs &a, int threads, hipStream_t s)
 {
     hipLaunchKernelGGL(k_phase_bytes, dim3(a.max_blocks, (unsigned)a.count), dim3((unsigned)threads), 0, s, a);

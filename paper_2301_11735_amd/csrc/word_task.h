@@ -138,9 +138,10 @@ struct GridBarrier {
             const unsigned *at = flat() ? words : flag(block % kBarrierGroups);
             const unsigned target = flat() ? blocks * rounds : rounds;
             const long long t0 = wall_clock64(), most = rounds == 1u ? kFirstWaits * limit : limit;
-            while (__hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
+            // (no time at all is up at once, also where everyone has arrived)
+            while (most <= 0 || __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
                 __builtin_amdgcn_s_sleep(1);
-                if (wall_clock64() - t0 > most) {
+                if (wall_clock64() - t0 > most || most <= 0) {
                     atomicOr(err, 1u);
                     gave_up = true;
                     break;

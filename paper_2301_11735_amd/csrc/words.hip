@@ -396,6 +396,7 @@ const void *series_fn(bool obs)
 const void *series_fn_of(int Q, bool obs)
 {
     switch (Q) {
+    case 0: return bytes_series_kernel();
     case 1: return series_fn<1>(obs);
     case 2: return series_fn<2>(obs);
     case 4: return series_fn<4>(obs);

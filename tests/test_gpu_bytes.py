@@ -106,3 +106,30 @@ def test_states_at_any_byte_address(offset):
     assert np.array_equal(got[32 + offset:32 + offset + L * L].astype(np.int8), o.codes)
     assert (got[:32 + offset] == 0x55).all() and (got[32 + offset + L * L:] == 0x55).all()
     assert lib.lattice_destroy(h) == 0
+
+
+@pytest.mark.parametrize("L,enc,count", [(256, 1, 1), (256, 0, 1), (260, 0, 3), (340, 0, 1), (388, 0, 9), (388, 0, 1), (1000, 0, 1)])
+def test_persistent_and_spread_calls(L, enc, count):
+    """Calls on both sides of the rules that spread lattices over the chip: one
+    sweep, a few, and many, in turn with reads and series."""
+    print(f"case spread L={L} enc={enc} count={count}", flush=True)
+    pairs = []
+    for i in range(count):
+        spec = SMALL.with_(L=L, seed=20 + i, T=0.6 + 0.2 * i, encoding=enc)
+        args = (spec.L, spec.n, spec.Delta, spec.V, spec.J, spec.T, spec.seed)
+        pairs.append((lat.Lattice(*args, encoding=enc), oracle.OracleLattice(*args)))
+    for n in (1, 2, 11) if L < 500 else (1, 2):
+        lat.sweep_batch([g for g, _ in pairs], n)
+        for _, o in pairs:
+            o.sweeps(n)
+        _check(pairs)
+    g, o = pairs[0]
+    if L < 500:
+        for intervals, every in ((2, 12), (3, 1)):
+            for r in g.sweep_series(intervals, every):
+                o.sweeps(every)
+                assert r.ints() == o.observables().tolist()
+                assert [r.track_nD, r.track_nV, r.track_nJ] == o.track.tolist()
+        g.sweep(7)
+        o.sweeps(7)
+        _check(pairs)
