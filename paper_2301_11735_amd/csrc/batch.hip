@@ -15,72 +15,6 @@ namespace lat {
 namespace {
 
 // ---------------------------------------------------------------------------
-// Batched lattices (section 3.2: several lattice copies processed together),
-// one block per lattice, the whole lattice resident in LDS for all sweeps of
-// the launch.  LDS layout: the 8 sublattice classes, each (L/2) rows of
-// Wp = ceil(L/64) words, site X of a class row at bits 2*(X&15) of word X>>4.
-// Each thread owns Philox calls t = tid, tid + blockDim, ...: pairs 2t and
-// 2t+1.  A pair's two sites are in words other pairs of the phase also own
-// fields of, so the new codes are merged with LDS atomic xor; every read of
-// an updated word extracts only the reader's own field, which nobody else
-// writes, and neighbour words are never written in the phase.
-
-struct LdsGeom {
-    int L, Lq, H, Wp;
-    uint32_t csz;  // words per class
-    __device__ __forceinline__ uint32_t word(int c, int Y, int X) const
-    {
-        return (uint32_t)c * csz + (uint32_t)Y * Wp + (uint32_t)(X >> 4);
-    }
-};
-
-__device__ __forceinline__ uint32_t lds_code(const uint32_t *lat, const LdsGeom &g, int c, int Y, int X)
-{
-    return (lat[g.word(c, Y, X)] >> (2 * (X & 15))) & 3u;
-}
-
-// Copy a lattice from its global state into the LDS class arrays (rows of
-// Wp words, 16 sites per word; int8 states are packed on the way in), and back.
-__device__ __forceinline__ void stage_lattice(uint32_t *lat, const LatDesc &d, const LdsGeom &g)
-{
-    const int L = g.L, Lq = g.Lq;
-    const uint32_t nwords = 8u * g.csz;
-    if (d.enc == 1) {
-        const LAT_GLOBAL uint32_t *src = (const LAT_GLOBAL uint32_t *)d.state;  // same layout, Wp = L/64
-        for (uint32_t i = threadIdx.x; i < nwords; i += blockDim.x) lat[i] = src[i];
-    } else {
-        const LAT_GLOBAL int8_t *src = (const LAT_GLOBAL int8_t *)d.state;
-        for (uint32_t i = threadIdx.x; i < nwords; i += blockDim.x) {
-            const int c = (int)(i / g.csz);
-            const uint32_t rem = i - (uint32_t)c * g.csz;
-            const int Y = (int)(rem / g.Wp), w = (int)(rem - (uint32_t)Y * g.Wp);
-            const int x0 = c & 3, y = 2 * Y + (c >> 2);
-            uint32_t v = 0;
-            for (int t = 0; t < 16; ++t) {
-                const int X = 16 * w + t;
-                if (X < Lq) v |= ((uint32_t)src[(size_t)y * L + 4 * X + x0] & 3u) << (2 * t);
-            }
-            lat[i] = v;
-        }
-    }
-}
-
-__device__ __forceinline__ void unstage_lattice(const uint32_t *lat, const LatDesc &d, const LdsGeom &g)
-{
-    const int L = g.L;
-    if (d.enc == 1) {
-        LAT_GLOBAL uint32_t *dst = (LAT_GLOBAL uint32_t *)d.state;
-        for (uint32_t i = threadIdx.x; i < 8u * g.csz; i += blockDim.x) dst[i] = lat[i];
-    } else {
-        LAT_GLOBAL int8_t *dst = (LAT_GLOBAL int8_t *)d.state;
-        for (uint32_t i = threadIdx.x; i < (uint32_t)L * L; i += blockDim.x) {
-            const int y = (int)(i / L), x = (int)(i - (uint32_t)y * L);
-            dst[i] = (int8_t)lds_code(lat, g, 4 * (y & 1) + (x & 3), y >> 1, x >> 2);
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
 // Per-site form, one byte per site in LDS (row-major), for lattices of any
 // side up to kSiteMaxL.  A site's byte is (1 + S) | (1 + sigma) << 4, so that
 // the bytes of four neighbours add up to both neighbour sums at once (at
@@ -415,79 +349,6 @@ __global__ void __launch_bounds__(1024) k_sweep_site(BatchArgs args)
     block_reduce_add<3>(tr, (unsigned long long *)(scr + kScrTrackBase));
 }
 
-// Two bits per site, any side: where the per-site form's bytes do not fit.
-__global__ void __launch_bounds__(1024) k_sweep_lds(BatchArgs args)
-{
-    __shared__ uint2 s_tab[kDevTabEntries];
-    __shared__ uint2 s_trans[kTransEntries];
-    extern __shared__ uint32_t lat[];
-    uint8_t *scr = args.scratch[blockIdx.x];
-    const LatDesc d = *(const LatDesc *)(scr + kScrDesc);
-    stage_tables(s_tab, s_trans, (const uint2 *)(scr + kScrDevTab), (const uint2 *)(scr + kScrTrans));
-    LdsGeom g;
-    g.L = d.L;
-    g.Lq = d.L >> 2;
-    g.H = d.L >> 1;
-    g.Wp = (g.Lq + 15) >> 4;
-    g.csz = (uint32_t)g.H * g.Wp;
-    const int L = g.L, Lq = g.Lq, H = g.H;
-
-    stage_lattice(lat, d, g);
-    __syncthreads();
-
-    const uint32_t n_calls = (uint32_t)L * (uint32_t)L / 16u;
-    int tr[3] = {0, 0, 0};
-    const uint32_t my_sweeps = args.sweeps[blockIdx.x];
-    for (uint64_t s = d.next_sweep; s < d.next_sweep + my_sweeps; ++s) {
-        int r, mm[4], kk[4];
-        device_schedule(L, d.key0, d.key1, s, r, mm, kk);
-        for (int p = 0; p < 4; ++p) {
-            const int pb = (p + r) & 3, carry = (p + r) >> 2;
-            int dX = mm[p] + carry;
-            if (dX >= Lq) dX -= Lq;
-            const int cAL = p > 0 ? p - 1 : 3, cAR = p < 3 ? p + 1 : 0;
-            const int cBL = pb > 0 ? 4 + pb - 1 : 7, cBR = pb < 3 ? 4 + pb + 1 : 4;
-            for (uint32_t t = threadIdx.x; t < n_calls; t += blockDim.x) {
-                const u32x4 w = philox4x32_10((uint32_t)s, (uint32_t)p, t, (uint32_t)(s >> 32), d.key0, d.key1);
-                uint32_t packed = 0;
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const uint32_t pi = 2u * t + (uint32_t)h;
-                    const int Y = (int)(pi / (uint32_t)Lq), X = (int)pi - Y * Lq;
-                    int Yb = Y + kk[p], Xb = X + dX;
-                    if (Yb >= H) Yb -= H;
-                    if (Xb >= Lq) Xb -= Lq;
-                    const int Xl = X == 0 ? Lq - 1 : X - 1, Xr = X + 1 == Lq ? 0 : X + 1;
-                    const int Xbl = Xb == 0 ? Lq - 1 : Xb - 1, Xbr = Xb + 1 == Lq ? 0 : Xb + 1;
-                    const uint32_t ca = lds_code(lat, g, p, Y, X);
-                    const uint32_t cb = lds_code(lat, g, 4 + pb, Yb, Xb);
-                    const uint32_t bpack =
-                        contrib_a(lds_code(lat, g, cAL, Y, p > 0 ? X : Xl)) +
-                        contrib_a(lds_code(lat, g, cAR, Y, p < 3 ? X : Xr)) +
-                        contrib_a(lds_code(lat, g, 4 + p, Y == 0 ? H - 1 : Y - 1, X)) +
-                        contrib_a(lds_code(lat, g, 4 + p, Y, X)) +
-                        contrib_b(lds_code(lat, g, cBL, Yb, pb > 0 ? Xb : Xbl)) +
-                        contrib_b(lds_code(lat, g, cBR, Yb, pb < 3 ? Xb : Xbr)) +
-                        contrib_b(lds_code(lat, g, pb, Yb, Xb)) +
-                        contrib_b(lds_code(lat, g, pb, Yb + 1 == H ? 0 : Yb + 1, Xb));
-                    const uint32_t s0 = ca | (cb << 2);
-                    const uint32_t ns = pair_step(s0, bpack, h ? w.z : w.x, h ? w.w : w.y, s_trans, s_tab, packed);
-                    if (ns != s0) {
-                        atomicXor(&lat[g.word(p, Y, X)], ((ns ^ s0) & 3u) << (2 * (X & 15)));
-                        atomicXor(&lat[g.word(4 + pb, Yb, Xb)], ((ns ^ s0) >> 2) << (2 * (Xb & 15)));
-                    }
-                }
-                unpack_tracker(packed, tr);
-            }
-            __syncthreads();
-        }
-    }
-
-    unstage_lattice(lat, d, g);
-    if (threadIdx.x == 0) ((LatDesc *)(scr + kScrDesc))->next_sweep = d.next_sweep + my_sweeps;
-    block_reduce_add<3>(tr, (unsigned long long *)(scr + kScrTrackBase));
-}
-
 // This thread's share of the 7 observable sums of a 2-bit lattice in the
 // class layout, read from st (global memory or the LDS copy).
 __device__ __forceinline__ void obs_sums_2bit(const uint32_t *st, int L, long long (&v)[7])
@@ -536,12 +397,9 @@ __global__ void __launch_bounds__(256) k_obs_batch(BatchArgs args, unsigned long
 
 hipError_t init_kernel_attributes()
 {
-    // allow more than the default 64 KiB of dynamic LDS (L = 512 needs 64 KiB + tables)
-    const int bytes = (int)(lds_state_words(kLdsMaxL) * 4u);
-    hipError_t e = hipFuncSetAttribute((const void *)k_sweep_lds, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)k_sweep_site, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                kSiteMaxL * kSiteMaxL);
+    // allow more than the default 64 KiB of dynamic LDS
+    hipError_t e = hipFuncSetAttribute((const void *)k_sweep_site, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       kSiteMaxL * kSiteMaxL);
     if (e == hipSuccess) e = init_quad_kernel_attributes();
     return e;
 }
@@ -552,16 +410,10 @@ hipError_t launch_sweep_lds(const BatchArgs &a, int max_L, int threads, bool qua
     // default block: one thread per pair up to kSiteOnePair pairs a phase, else
     // one per Philox call (two pairs)
     const uint32_t sq = (uint32_t)max_L * (uint32_t)max_L;
-    const bool site = max_L <= kSiteMaxL;
-    const uint32_t units = site && sq / 8u <= kSiteOnePair ? sq / 8u : sq / 16u;
+    const uint32_t units = sq / 8u <= kSiteOnePair ? sq / 8u : sq / 16u;
     uint32_t block = std::min(1024u, (units + 63u) / 64u * 64u);
     if (threads > 0) block = (uint32_t)std::min(1024, std::max(64, threads / 64 * 64));
-    if (site) {
-        hipLaunchKernelGGL(k_sweep_site, dim3((unsigned)a.count), dim3(block), (size_t)sq, s, a);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL(k_sweep_lds, dim3((unsigned)a.count), dim3(block), lds_state_words(max_L) * 4u, s, a);
-    if (a.obs_out) hipLaunchKernelGGL(k_obs_batch, dim3((unsigned)a.count), dim3(256), 0, s, a, a.obs_out);
+    hipLaunchKernelGGL(k_sweep_site, dim3((unsigned)a.count), dim3(block), (size_t)sq, s, a);
     return hipGetLastError();
 }
 

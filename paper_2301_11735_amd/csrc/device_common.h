@@ -19,23 +19,6 @@ constexpr uint32_t kM0F = 0x0F0F0F0Fu; // low nibble of every byte
 
 constexpr int charge_c(int c) { return (c & 2) ? 1 - 2 * (c & 1) : 0; }
 
-// Half the number of configurations k_q of the same-charge set, for every
-// pair state st = code_a | code_b << 2 (2 bits per state): 3 for q = 0
-// (k_q = 6), 2 for q = +-1 (k_q = 4), and 0 for the frozen |q| = 2 states,
-// whose configuration index is then always 0 (their single entry is the null
-// move).  j = floor(k_q u / 2^24) = floor((k_q/2) u / 2^23) for the 24-bit u.
-constexpr uint32_t make_kq2()
-{
-    uint32_t v = 0;
-    for (int st = 0; st < 16; ++st) {
-        const int q = charge_c(st & 3) + charge_c(st >> 2);
-        const uint32_t k2 = (q == 2 || q == -2) ? 0u : (q == 0 ? 3u : 2u);
-        v |= k2 << (2 * st);
-    }
-    return v;
-}
-constexpr uint32_t kKq2 = make_kq2();
-
 // Pair states of 8 pairs: nibble u of the result is code_a | code_b << 2 of
 // pair 8*half + u, for the aligned (a-word, b-word) couple (A, B).  One byte
 // permute gathers (A byte, B byte) pairs, then two swap stages interleave
@@ -47,40 +30,6 @@ __device__ __forceinline__ uint32_t pair_states8(uint32_t A, uint32_t B, int hal
     x ^= t ^ (t << 4);
     t = (x ^ (x >> 2)) & 0x0C0C0C0Cu;
     return x ^ t ^ (t << 2);
-}
-
-__device__ __forceinline__ void stage_tables(uint2 *s_tab, uint2 *s_trans, const uint2 *__restrict__ g_tab,
-                                             const uint2 *__restrict__ g_trans)
-{
-    for (int i = threadIdx.x; i < kDevTabEntries; i += blockDim.x) s_tab[i] = g_tab[i];
-    for (int i = threadIdx.x; i < kTransEntries; i += blockDim.x) s_trans[i] = g_trans[i];
-    __syncthreads();
-}
-
-// One coupled-pair Metropolis step (section 3.1).  bpack holds the neighbour
-// sums (sumS_a+4, sumS_b+4, sumsig_a+4, sumsig_b+4) as bytes; uc picks the
-// configuration j = floor(k_q * (uc >> 8) / 2^24); ua is the acceptance draw,
-// compared as min(ua, 2^32-2) < thr so that the reserved "always" threshold
-// 2^32-1 accepts every draw.  Returns the new pair state and adds the
-// accepted move's packed triple to `packed`.
-__device__ __forceinline__ uint32_t pair_step_k2(uint32_t st, uint32_t kq2, uint32_t bpack, uint32_t uc, uint32_t ua,
-                                                 const uint2 *__restrict__ s_trans, const uint2 *__restrict__ s_tab,
-                                                 uint32_t &packed)
-{
-    const uint32_t j = ((uc >> 8) * kq2) >> 23;
-    const uint2 tr = s_trans[st * 6u + j];
-    const int idx = __builtin_amdgcn_sdot4((int)tr.x, (int)bpack, (int)(tr.y & 0xFFFFu), false);
-    const uint2 e = s_tab[idx];
-    const bool acc = min(ua, 0xFFFFFFFEu) < e.x;
-    packed += acc ? e.y : 0u;
-    return acc ? (tr.y >> 16) : st;
-}
-
-__device__ __forceinline__ uint32_t pair_step(uint32_t st, uint32_t bpack, uint32_t uc, uint32_t ua,
-                                              const uint2 *__restrict__ s_trans, const uint2 *__restrict__ s_tab,
-                                              uint32_t &packed)
-{
-    return pair_step_k2(st, (kKq2 >> (2u * st)) & 3u, bpack, uc, ua, s_trans, s_tab, packed);
 }
 
 // Transition table of section 3.1's coupled-pair move with 12 choice slots a

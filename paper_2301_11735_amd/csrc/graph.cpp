@@ -94,7 +94,7 @@ int lattice_batch_graph_create(lattice *const *hs, int32_t count, uint32_t sweep
                 // an interval's sweeps and observables are one launch in the
                 // word form, and many intervals are one in the per-site form
                 const ObsTarget obs{(unsigned long long *)d_out, intervals, 10u, 10u * (uint32_t)count};
-                rc = enqueue_lds_sweeps(g->hs.data(), count, nullptr, sweeps, cs, /*tune=*/false, &obs);
+                rc = enqueue_lds_sweeps(g->hs.data(), count, nullptr, sweeps, cs, &obs);
             }
             for (uint32_t k = 0; k < intervals && rc == LAT_OK && !big.empty(); ++k) {
                 unsigned long long *slot = (unsigned long long *)d_out + 10 * (size_t)count * k;
@@ -103,7 +103,7 @@ int lattice_batch_graph_create(lattice *const *hs, int32_t count, uint32_t sweep
                 // one launch per phase, since a graph's kernel node does not
                 // guarantee the co-residency that the persistent form's
                 // device-wide barrier needs
-                rc = enqueue_lds_sweeps(small.data(), (int32_t)small.size(), nullptr, sweeps, cs, false);
+                rc = enqueue_lds_sweeps(small.data(), (int32_t)small.size(), nullptr, sweeps, cs);
                 if (rc == LAT_OK)
                     rc = enqueue_offchip_sweeps(big.data(), (int32_t)big.size(), nullptr, sweeps, cs,
                                                 /*convert=*/true, /*persistent=*/false);

@@ -99,8 +99,7 @@ class PinnedBlock {
 };
 
 // Advance lattices resident in LDS; lattice i by sweeps[i] (null: `uniform`).
-// tune = false: no autotuning launches (the tuned or default block size),
-// as needed under stream capture.  obs non-null: `intervals` times over, each
+// obs non-null: `intervals` times over, each
 // time followed by the lattices' observables in obs->dev (obs->words int64 a
 // lattice as enqueue_observables_batch, obs->stride int64 from one interval to
 // the next), written from LDS by the sweep launch where its form does that.
@@ -111,7 +110,7 @@ struct ObsTarget {
     uint32_t stride;
 };
 int enqueue_lds_sweeps(lattice *const *hs, int32_t count, const uint32_t *sweeps, uint32_t uniform,
-                       hipStream_t stream, bool tune = true, const ObsTarget *obs = nullptr);
+                       hipStream_t stream, const ObsTarget *obs = nullptr);
 // One batched observables launch per 256 lattices into dev (10 int64 each).
 int enqueue_observables_batch(lattice *const *hs, int32_t count, unsigned long long *dev, hipStream_t stream);
 // Lattices on the off-chip paths (words, phase): lattice i by sweeps[i]
@@ -148,14 +147,6 @@ int read_records(const char *what, const void *dev, uint32_t words, size_t n, la
                  bool always, hipStream_t stream, const std::function<void(size_t, const int64_t *)> &fill);
 // v = (tracker nD, nV, nJ, sum S, sum S^2, bonds SS, bonds ss, M, M_st, C_st).
 void fill_obs(const lattice *h, const int64_t *v, lat_obs *out);
-
-// Launch-shape autotuner for batches of the two-bit on-chip form.  For every
-// (largest L, batch size) it tries each candidate block size on one real call,
-// timed with HIP events on the call's stream, then keeps the fastest per site
-// update.  The chain does not depend on the launch shape, so tuning runs real
-// work.  LATTICE_BATCH_THREADS=<n> pins the block size of every form instead.
-int batch_threads_for(int max_L, int count, hipEvent_t *start, hipEvent_t *stop, int *slot);
-void batch_threads_done(int slot, double site_updates);
 
 }  // namespace detail
 }  // namespace lat

@@ -39,7 +39,7 @@ constexpr int kTransEntries = 16 * 6;
 // block b's sums into observable slot b, single-block kernels add into the
 // tracker base; k_fold_sums folds slots into the totals.
 constexpr size_t kScrDevTab = 0;                      // 933 x 8 = 7464
-constexpr size_t kScrTrans = 7680;                    // 96 x 8 = 768
+constexpr size_t kScrTrans = 7680;                    // reserved (768)
 constexpr size_t kScrTrack = 8448;                    // 3 x int64: tracker total (output)
 constexpr size_t kScrObs = kScrTrack + 3 * 8;         // 7 x int64: observable sums (output)
 constexpr size_t kScrErr = kScrObs + 7 * 8;           // uint32 error flags (bit 0: barrier time-out)
@@ -63,14 +63,7 @@ constexpr int kMuTabSize = 16 * 137;  // 2192
 constexpr int kMuChargeSlots = 32, kMuChargeStride = 8;
 constexpr size_t kScrMuTab = kScrFullTab + ((size_t)kTabSize * 4 + 255) / 256 * 256;  // 71168
 static_assert(kScrMuTab + (size_t)kMuTabSize * 4 <= 88576, "the penalty table ends before the delta table");
-// Delta form of the transition table, read by the 2-bit phase kernel: entry
-// st*6 + j is {coef, C, R, 0} with coef and C as in the transition table and
-// R = (d_a * 0x5555) | (d_b * 0x5555) << 16, where d_a and d_b are the XOR of
-// the new and the old code of site a and of site b: every 2-bit field of the
-// low half holds d_a and every field of the high half d_b, so that one AND
-// with a field mask places an accepted move's code changes at any pair
-// position.
-constexpr size_t kScrTransD = 88576;
+constexpr size_t kScrTransD = 88576;                  // reserved
 constexpr size_t kScrBytes = kScrTransD + (size_t)kTransEntries * 16;                 // 90112
 
 // Int8 lattices with L % 64 == 0 that are swept by the phase kernels keep a
@@ -89,14 +82,11 @@ struct LatDesc {
     uint64_t next_sweep;
 };
 
-// Lattices whose whole state fits one block's LDS run in the batched kernel:
-// 8 sublattice classes of (L/2) rows x ceil(L/64) words (2 bits per site).
+// The largest side that the server and batch graphs take on any path.
 constexpr int kLdsMaxL = 512;
-inline size_t lds_state_words(int L) { return (size_t)8 * (L / 2) * ((L / 4 + 15) / 16); }
 
 // The per-site form (k_sweep_site) keeps one byte per site in LDS: sides up to
-// 384, whose 144 KiB leave room for its tables; above, k_sweep_lds keeps two
-// bits per site.
+// 384, whose 144 KiB leave room for its tables.
 constexpr int kSiteMaxL = 384;
 
 // The quad form (k_sweep_quad): sides that are a multiple of 16, one byte per
@@ -127,8 +117,6 @@ constexpr uint32_t kFusedSweeps = 16384;
 struct PhaseArgs {
     void *state;
     const uint2 *dev_tab;    // kDevTabEntries
-    const uint2 *trans;      // kTransEntries
-    const uint4 *trans_d;    // kTransEntries, delta form
     unsigned long long *track;  // tracker slots: block b adds its 3 sums at track[3b..3b+2]
     int L;
     int p, r, m, k;

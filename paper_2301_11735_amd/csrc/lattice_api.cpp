@@ -244,7 +244,9 @@ void build_device_table(const std::vector<uint32_t> &tab, std::vector<uint32_t> 
 // charge, dS_a + dS_b = 0 and the +4 offsets of the charge sums cancel; the
 // spin offsets 4*(dsig_a + dsig_b) are folded into C.  The frozen states
 // (|q| = 2) get one null move.  trans_d is the delta form (4 words an entry).
-void build_transition_table(std::vector<uint32_t> &trans, std::vector<uint32_t> &trans_d)
+// The kernels' own tables (slots of device_common.h, quad.hip and batch.hip) are
+// made at compile time; this one lists the moves for the host check of the tables.
+[[maybe_unused]] void build_transition_table(std::vector<uint32_t> &trans, std::vector<uint32_t> &trans_d)
 {
     static const int kS[4] = {0, 0, 1, -1}, kG[4] = {1, -1, 0, 0};
     static const int kPlus1[4][2] = {{2, 0}, {2, 1}, {0, 2}, {1, 2}};
@@ -344,9 +346,8 @@ uint32_t seed_candidates()
 }
 
 // Staging of lattice_create: the scratch up to its observable slots, the full
-// threshold table, the delta table, and the seeding's overflow flag.
-constexpr size_t kCreateTransD = kScrObsSlots + ((size_t)kTabSize * 4 + 255) / 256 * 256;
-constexpr size_t kCreateFlag = kCreateTransD + (size_t)kTransEntries * 16;
+// threshold table, and the seeding's overflow flag.
+constexpr size_t kCreateFlag = kScrObsSlots + ((size_t)kTabSize * 4 + 255) / 256 * 256;
 constexpr size_t kCreateBytes = kCreateFlag + 256;
 static_assert(kCreateBytes <= kPinnedLarge, "lattice_create's staging");
 
@@ -416,8 +417,6 @@ int enqueue_phase_sweeps(lattice *h, uint32_t sweeps, hipStream_t stream)
     PhaseArgs a{};
     a.state = swept_state(h);
     a.dev_tab = (const uint2 *)(h->d_scratch + kScrDevTab);
-    a.trans = (const uint2 *)(h->d_scratch + kScrTrans);
-    a.trans_d = (const uint4 *)(h->d_scratch + kScrTransD);
     a.track = (unsigned long long *)(h->d_scratch + kScrSlots);
     a.L = h->L;
     a.magicW = magic_div((uint32_t)h->L >> 6);
@@ -769,7 +768,7 @@ bool spreads(lattice *const *hs, int32_t count, uint64_t sweeps, double extra, h
 constexpr double kSpreadCall = 25000.0;  // two launches, one of them cooperative, against one
 
 // Sweeps of on-chip lattices outside the server and graphs.
-int enqueue_small_sweeps(lattice *const *hs, int32_t count, uint32_t sweeps, hipStream_t stream, bool tune)
+int enqueue_small_sweeps(lattice *const *hs, int32_t count, uint32_t sweeps, hipStream_t stream)
 {
     if (spreads(hs, count, sweeps, kSpreadCall, stream)) {
         bool ran = false;
@@ -777,7 +776,7 @@ int enqueue_small_sweeps(lattice *const *hs, int32_t count, uint32_t sweeps, hip
                                                 hs[0]->enc == LAT_ENC_INT8, &ran);
         if (rc || ran) return rc;
     }
-    return enqueue_lds_sweeps(hs, count, nullptr, sweeps, stream, tune);
+    return enqueue_lds_sweeps(hs, count, nullptr, sweeps, stream);
 }
 
 int enqueue_offchip_sweeps(lattice *const *hs, int32_t count, const uint32_t *sweeps, uint32_t uniform,
@@ -831,137 +830,6 @@ int enqueue_offchip_sweeps(lattice *const *hs, int32_t count, const uint32_t *sw
     return LAT_OK;
 }
 
-// ---- autotuner for the block size of the two-bit on-chip form ----
-namespace {
-
-struct TuneEntry {
-    std::vector<int> candidates;
-    std::vector<double> ns_per_update;  // < 0: not measured yet
-    std::vector<double> in_flight;      // > 0: site updates of a timed launch not yet read;
-                                        // < 0: handed out, not yet enqueued
-    std::vector<hipEvent_t> start, stop;
-    int best = -1;
-};
-
-using TuneKey = std::pair<int, int>;  // (max L, batch size rounded up to a power of 2)
-std::mutex g_tune_mu;
-std::map<TuneKey, TuneEntry> g_tune;
-std::vector<std::pair<TuneKey, int>> g_tune_slots;  // (shape, candidate) of each timed launch handed out
-
-int pinned_batch_threads()
-{
-    const char *v = std::getenv("LATTICE_BATCH_THREADS");
-    return v ? std::atoi(v) : 0;
-}
-
-TuneKey tune_key(int max_L, int count)
-{
-    int bucket = 1;
-    while (bucket < count) bucket *= 2;
-    return std::make_pair(max_L, bucket);
-}
-
-// Reads the timed launches of a shape that have completed (never waits), and
-// picks the fastest candidate once all are measured.  Caller holds g_tune_mu.
-void harvest(TuneEntry &t)
-{
-    bool all = true;
-    for (size_t i = 0; i < t.candidates.size(); ++i) {
-        if (t.in_flight[i] > 0) {
-            const hipError_t q = hipEventQuery(t.stop[i]);
-            if (q == hipErrorNotReady) {
-                all = false;
-                continue;
-            }
-            float ms = 0.f;
-            if (q == hipSuccess && hipEventElapsedTime(&ms, t.start[i], t.stop[i]) == hipSuccess)
-                t.ns_per_update[i] = (double)ms * 1e6 / t.in_flight[i];
-            else
-                t.ns_per_update[i] = 1e30;  // not usable: ranks last
-            t.in_flight[i] = 0;
-        }
-        all = all && t.ns_per_update[i] >= 0;
-    }
-    if (all && t.best < 0) {
-        t.best = 0;
-        for (size_t i = 1; i < t.ns_per_update.size(); ++i)
-            if (t.ns_per_update[i] < t.ns_per_update[(size_t)t.best]) t.best = (int)i;
-    }
-}
-
-}  // namespace
-
-// Returns the block size to use (0 = default) and, while the shape is being
-// tuned, events to record around the launch plus a slot for
-// batch_threads_done.  No call waits: each of the first calls for a new
-// shape times one candidate that has not been timed yet, and the timings
-// are read by later calls once their launches have completed.
-int batch_threads_for(int max_L, int count, hipEvent_t *start, hipEvent_t *stop, int *slot)
-{
-    *start = *stop = nullptr;
-    *slot = -1;
-    if (const int pinned = pinned_batch_threads()) return pinned;
-    std::lock_guard<std::mutex> lock(g_tune_mu);
-    const TuneKey key = tune_key(max_L, count);
-    TuneEntry &t = g_tune[key];
-    if (t.candidates.empty()) {
-        const int calls = max_L * max_L / 16;
-        for (int c : {1024, 512, 256})
-            if (c / 2 < calls || c == 256) t.candidates.push_back(c);
-        const size_t n = t.candidates.size();
-        t.ns_per_update.assign(n, -1.0);
-        t.in_flight.assign(n, 0.0);
-        t.start.assign(n, nullptr);
-        t.stop.assign(n, nullptr);
-    }
-    harvest(t);
-    if (t.best >= 0) return t.candidates[(size_t)t.best];
-    for (size_t i = 0; i < t.candidates.size(); ++i) {
-        if (t.ns_per_update[i] < 0 && t.in_flight[i] == 0) {
-            if (!t.start[i]) {
-                if (hipEventCreate(&t.start[i]) != hipSuccess) return 0;
-                if (hipEventCreate(&t.stop[i]) != hipSuccess) {
-                    (void)hipEventDestroy(t.start[i]);
-                    t.start[i] = nullptr;
-                    return 0;
-                }
-            }
-            *start = t.start[i];
-            *stop = t.stop[i];
-            t.in_flight[i] = -1.0;  // no other call takes these events meanwhile
-            const auto entry = std::make_pair(key, (int)i);
-            auto it = std::find(g_tune_slots.begin(), g_tune_slots.end(), entry);
-            if (it == g_tune_slots.end()) it = g_tune_slots.insert(g_tune_slots.end(), entry);
-            *slot = (int)(it - g_tune_slots.begin());
-            return t.candidates[i];
-        }
-    }
-    return 0;  // every untimed candidate has a launch in flight: the default meanwhile
-}
-
-// The launch timed for `slot` has been enqueued between its events with
-// `site_updates` site updates; its time is read by a later call.
-void batch_threads_done(int slot, double site_updates)
-{
-    if (slot < 0) return;
-    std::lock_guard<std::mutex> lock(g_tune_mu);
-    const auto &entry = g_tune_slots[(size_t)slot];
-    TuneEntry &t = g_tune[entry.first];
-    t.in_flight[(size_t)entry.second] = site_updates > 0 ? site_updates : 1.0;
-}
-
-// The tuned block size for a batch shape if tuning has finished (reading
-// completed timings first), else 0 (the default); never launches anything.
-int batch_threads_tuned(int max_L, int count)
-{
-    if (const int pinned = pinned_batch_threads()) return pinned;
-    std::lock_guard<std::mutex> lock(g_tune_mu);
-    const auto it = g_tune.find(tune_key(max_L, count));
-    if (it == g_tune.end()) return 0;
-    harvest(it->second);
-    return it->second.best >= 0 ? it->second.candidates[(size_t)it->second.best] : 0;
-}
-
 int enqueue_observables_batch(lattice *const *hs, int32_t count, unsigned long long *dev, hipStream_t stream)
 {
     for (int32_t b = 0; b < count; b += kMaxBatch) {
@@ -982,8 +850,11 @@ constexpr int kQuadMinL = 80;
 
 // Batched path: lattices resident in LDS, up to kMaxBatch per launch.
 int enqueue_lds_sweeps(lattice *const *hs, int32_t count, const uint32_t *sweeps, uint32_t uniform,
-                       hipStream_t stream, bool tune, const ObsTarget *obs)
+                       hipStream_t stream, const ObsTarget *obs)
 {
+    // LATTICE_BATCH_THREADS pins the block size
+    const char *pinned = std::getenv("LATTICE_BATCH_THREADS");
+    const int threads = pinned ? std::atoi(pinned) : 0;
     // LATTICE_LDS_SITE=1 keeps every batch on the per-site form (tests compare the two)
     const char *env = std::getenv("LATTICE_LDS_SITE");
     const bool force_site = env && env[0] == '1';
@@ -991,38 +862,25 @@ int enqueue_lds_sweeps(lattice *const *hs, int32_t count, const uint32_t *sweeps
         BatchArgs a{};
         a.count = std::min<int32_t>(kMaxBatch, count - b);
         int max_L = 0;
-        double updates = 0;
         bool quad = !force_site;
         for (int i = 0; i < a.count; ++i) {
             a.scratch[i] = hs[b + i]->d_scratch;
             a.sweeps[i] = sweeps ? sweeps[b + i] : uniform;
             max_L = std::max(max_L, hs[b + i]->L);
-            updates += (double)hs[b + i]->N * a.sweeps[i];
             quad = quad && hs[b + i]->L % 16 == 0;
         }
         quad = quad && max_L >= kQuadMinL && max_L <= kQuadMaxL;
         const uint32_t intervals = obs ? obs->intervals : 1u;
-        // per-site and quad forms: the block size follows from the largest side,
-        // and one launch holds as many intervals as kFusedSweeps sweeps allow
-        const bool fused = quad || max_L <= kSiteMaxL;
+        // one launch holds as many intervals as kFusedSweeps sweeps allow
         const uint32_t most = *std::max_element(a.sweeps, a.sweeps + a.count);
-        const uint32_t per_launch = fused ? std::max(1u, kFusedSweeps / std::max(1u, most)) : 1u;
+        const uint32_t per_launch = std::max(1u, kFusedSweeps / std::max(1u, most));
         a.obs_words = obs ? obs->words : 10u;
         a.obs_stride = obs ? obs->stride : 0u;
         for (uint32_t k = 0; k < intervals; k += per_launch) {
             a.intervals = std::min(per_launch, intervals - k);
             a.obs_out = obs ? obs->dev + (size_t)obs->stride * k + (size_t)obs->words * (size_t)b : nullptr;
-            hipEvent_t t0 = nullptr, t1 = nullptr;
-            int slot = -1;
-            const int threads = tune && !fused ? batch_threads_for(max_L, a.count, &t0, &t1, &slot)
-                                               : batch_threads_tuned(max_L, a.count);
-            if (t0) (void)hipEventRecord(t0, stream);
-            hipError_t e = launch_sweep_lds(a, max_L, threads, quad, stream);
+            const hipError_t e = launch_sweep_lds(a, max_L, threads, quad, stream);
             if (e != hipSuccess) return hip_fail(e, "batched kernel launch");
-            if (t1) {
-                (void)hipEventRecord(t1, stream);
-                batch_threads_done(slot, updates);
-            }
             for (int i = 0; i < a.count; ++i) hs[b + i]->done += (uint64_t)a.sweeps[i] * a.intervals;
         }
     }
@@ -1143,9 +1001,7 @@ int enqueue_sweeps(lattice *h, uint32_t sweeps, hipStream_t stream)
     lattice *one[1] = {h};
     // the multi-block path takes the persistent launch where it can run
     if (h->path != kPathLds) return enqueue_offchip_sweeps(one, 1, nullptr, sweeps, stream);
-    // a lone lattice is not autotuned (tuning synchronises); it takes the
-    // block size tuned for its shape by an earlier batch, else the default
-    return enqueue_small_sweeps(one, 1, sweeps, stream, /*tune=*/false);
+    return enqueue_small_sweeps(one, 1, sweeps, stream);
 }
 
 // Sweep path of a new lattice.  Default: the one-block LDS kernel up to
@@ -1162,7 +1018,7 @@ int choose_path(int L, int enc)
     const bool words_ok = L % 64 == 0 && L <= kWordsMaxL;
     if (const char *v = std::getenv("LATTICE_PATH")) {
         const std::string want(v);
-        if (want == "lds" && L <= kLdsMaxL) return kPathLds;
+        if (want == "lds" && L <= kSiteMaxL) return kPathLds;
         if (want == "words" && words_ok) return kPathWords;
         if (want == "phase") return kPathPhase;
     }
@@ -1259,11 +1115,9 @@ int lattice_create(const lat_params *p, void *d_state, size_t state_bytes, void 
 
         // The seeded state is made on the device while the tables are made here;
         // nothing is allocated in between, so that the wait below is reached.
-        std::vector<uint32_t> tab, dev_tab, trans, trans_d;
+        std::vector<uint32_t> tab, dev_tab;
         tab.reserve(kTabSize);
         dev_tab.reserve(2 * (size_t)kDevTabEntries);
-        trans.reserve(2 * (size_t)kTransEntries);
-        trans_d.reserve(4 * (size_t)kTransEntries);
         PinnedBlock stage(/*large=*/true);
         std::vector<uint8_t> own;
         if (!stage.p) own.resize(kCreateBytes);
@@ -1283,19 +1137,13 @@ int lattice_create(const lat_params *p, void *d_state, size_t state_bytes, void 
         }
         build_threshold_table(p->Delta, p->V, p->J, p->T, tab);
         build_device_table(tab, dev_tab);
-        build_transition_table(trans, trans_d);
-        // tables, descriptor and a cleared tracker in three copies
+        // tables, descriptor and a cleared tracker in two copies
         std::memcpy(img + kScrDevTab, dev_tab.data(), dev_tab.size() * 4);
-        std::memcpy(img + kScrTrans, trans.data(), trans.size() * 4);
         std::memcpy(img + kScrDesc, &desc, sizeof(desc));
         std::memcpy(img + kScrObsSlots, tab.data(), tab.size() * 4);
-        std::memcpy(img + kCreateTransD, trans_d.data(), trans_d.size() * 4);
         if (e == hipSuccess) e = hipMemcpyAsync(h->d_scratch, img, kScrObsSlots, hipMemcpyHostToDevice, h->stream);
         if (e == hipSuccess)
             e = hipMemcpyAsync(h->d_scratch + kScrFullTab, img + kScrObsSlots, tab.size() * 4, hipMemcpyHostToDevice,
-                               h->stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(h->d_scratch + kScrTransD, img + kCreateTransD, trans_d.size() * 4, hipMemcpyHostToDevice,
                                h->stream);
         if (e == hipSuccess) e = launch_zero_i64((unsigned long long *)(h->d_scratch + kScrSlots), 3 * kMaxSlots, h->stream);
         hipError_t waited = hipStreamSynchronize(h->stream);  // host staging buffers die with this frame
@@ -1339,7 +1187,7 @@ int lattice_sweep_batch(lattice *const *hs, int32_t count, uint32_t sweeps, void
         if (sweeps == 0) return LAT_OK;
         std::vector<lattice *> small, big;
         for (int32_t i = 0; i < count; ++i) (hs[i]->path == kPathLds ? small : big).push_back(hs[i]);
-        int rc = enqueue_small_sweeps(small.data(), (int32_t)small.size(), sweeps, (hipStream_t)hip_stream, /*tune=*/true);
+        int rc = enqueue_small_sweeps(small.data(), (int32_t)small.size(), sweeps, (hipStream_t)hip_stream);
         if (rc == LAT_OK && !big.empty())
             rc = enqueue_offchip_sweeps(big.data(), (int32_t)big.size(), nullptr, sweeps, (hipStream_t)hip_stream);
         return rc;
@@ -1392,12 +1240,12 @@ int lattice_sweep_series(lattice *h, uint32_t intervals, uint32_t every, void *d
         }
         if (small && !ran && !(wide && bytes)) {
             const ObsTarget obs{(unsigned long long *)d_series, intervals, kSeriesRecord / 8, kSeriesRecord / 8};
-            const int rc = enqueue_lds_sweeps(one, 1, nullptr, every, st, /*tune=*/false, &obs);
+            const int rc = enqueue_lds_sweeps(one, 1, nullptr, every, st, &obs);
             if (rc) return rc;
             ran = true;
         }
         for (uint32_t k = 0; k < intervals && !ran; ++k) {
-            const int rc = small ? enqueue_small_sweeps(one, 1, every, st, /*tune=*/false)
+            const int rc = small ? enqueue_small_sweeps(one, 1, every, st)
                                  : enqueue_offchip_sweeps(one, 1, nullptr, every, st, /*convert=*/false);
             if (rc) return rc;
             long long *rec = (long long *)((uint8_t *)d_series + kSeriesRecord * (size_t)k);
