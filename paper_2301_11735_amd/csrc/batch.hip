@@ -146,14 +146,18 @@ __device__ __forceinline__ SitePos site_pos(uint32_t pi, uint32_t L, uint32_t Lq
 struct SiteDraw {
     uint32_t slot8, ua;
 };
+// The call of a task, and its draws from the call's words.
 template <int PP>
-__device__ __forceinline__ void site_draws(uint64_t s, uint32_t p, uint32_t task, uint32_t key0, uint32_t key1,
-                                           SiteDraw (&o)[PP])
+__device__ __forceinline__ PhiloxRun site_call(uint64_t s, uint32_t p, uint32_t task, uint32_t key0, uint32_t key1)
 {
-    const u32x4 w = philox4x32_10((uint32_t)s, p, PP == 2 ? task : task >> 1, (uint32_t)(s >> 32), key0, key1);
+    return PhiloxRun{(uint32_t)s, p, PP == 2 ? task : task >> 1, (uint32_t)(s >> 32), key0, key1};
+}
+template <int PP>
+__device__ __forceinline__ void site_draws(const PhiloxRun &w, uint32_t task, SiteDraw (&o)[PP])
+{
     const bool odd = PP == 1 && (task & 1u);
-    o[0] = SiteDraw{slot8_of(odd ? w.z : w.x), min(odd ? w.w : w.y, 0xFFFFFFFEu)};
-    if constexpr (PP == 2) o[1] = SiteDraw{slot8_of(w.z), min(w.w, 0xFFFFFFFEu)};
+    o[0] = SiteDraw{slot8_of(odd ? w.c2 : w.c0), min(odd ? w.c3 : w.c1, 0xFFFFFFFEu)};
+    if constexpr (PP == 2) o[1] = SiteDraw{slot8_of(w.c2), min(w.c3, 0xFFFFFFFEu)};
 }
 
 // Byte offsets of a pair's second site in phase P with displacement (Dx, Dy),
@@ -174,26 +178,47 @@ __device__ __forceinline__ SiteB site_b(const SitePos &s, uint32_t L, uint32_t N
     return SiteB{rb + xb, rb + min(xb - 1u, xb - 1u + L), rb + min(xb + 1u, xb + 1u - L), rd + xb};
 }
 
-// One coupled-pair step in phase P on the sites s and q.
+// One coupled-pair step in phase P on the sites s and q, in its four stages:
+// the loads, the transition entry, the move's entry, and the stores.  A stage
+// waits for the LDS once, so other work fits between them.
+struct SiteLoads {
+    uint32_t ea, eb, na[4], nb[4];
+};
 template <int P>
-__device__ __forceinline__ void site_step(uint8_t *lat, const SitePos &s, const SiteB &q, uint32_t L,
-                                          const SiteDraw &dr, const uint8_t *s_tab, const uint8_t *s_trans,
-                                          uint32_t &packed)
+__device__ __forceinline__ SiteLoads site_load(const uint8_t *lat, const SitePos &s, const SiteB &q, uint32_t L)
 {
-    const uint32_t ea = lat[s.a + P], eb = lat[q.b];
-    const uint32_t na = (uint32_t)lat[P > 0 ? s.a + P - 1 : s.l] + lat[P < 3 ? s.a + P + 1 : s.r] + lat[s.u + P] +
-                        lat[s.d + P];
-    const uint32_t nb = (uint32_t)lat[q.l] + lat[q.r] + lat[q.b - L] + lat[q.d];
-    const uint32_t t = na | nb << 8, x = ea | eb << 8;
-    const uint32_t bpack = (t & 0x0F0Fu) | (t & 0xF0F0u) << 12;
-    const uint2 tr = *(const uint2 *)(s_trans + ((((x * kSiteHash) >> 21) & 0x780u) | dr.slot8));
-    const uint32_t idx = (uint32_t)__builtin_amdgcn_sdot4((int)tr.x, (int)bpack, (int)tr.y, false);
-    const uint2 e = *(const uint2 *)(s_tab + (uint32_t)(uint16_t)(idx << 3));
+    return SiteLoads{lat[s.a + P],
+                     lat[q.b],
+                     {lat[P > 0 ? s.a + P - 1 : s.l], lat[P < 3 ? s.a + P + 1 : s.r], lat[s.u + P], lat[s.d + P]},
+                     {lat[q.l], lat[q.r], lat[q.b - L], lat[q.d]}};
+}
+struct SiteMove {
+    uint32_t x, bpack;  // the two site bytes, the packed neighbour sums
+    uint2 tr;
+};
+__device__ __forceinline__ SiteMove site_move(const SiteLoads &v, const SiteDraw &dr, const uint8_t *s_trans)
+{
+    SiteMove m;
+    m.x = v.ea | v.eb << 8;
+    m.tr = *(const uint2 *)(s_trans + ((((m.x * kSiteHash) >> 21) & 0x780u) | dr.slot8));
+    const uint32_t t = (v.na[0] + v.na[1] + v.na[2] + v.na[3]) | (v.nb[0] + v.nb[1] + v.nb[2] + v.nb[3]) << 8;
+    m.bpack = (t & 0x0F0Fu) | (t & 0xF0F0u) << 12;
+    return m;
+}
+__device__ __forceinline__ uint2 site_entry(const SiteMove &m, const uint8_t *s_tab)
+{
+    const uint32_t idx = (uint32_t)__builtin_amdgcn_sdot4((int)m.tr.x, (int)m.bpack, (int)m.tr.y, false);
+    return *(const uint2 *)(s_tab + (uint32_t)(uint16_t)(idx << 3));
+}
+template <int P>
+__device__ __forceinline__ void site_store(uint8_t *lat, const SitePos &s, uint32_t qb, const SiteDraw &dr,
+                                           const SiteMove &m, const uint2 &e, uint32_t &packed)
+{
     const bool acc = dr.ua < e.x;
     packed += acc ? e.y : 0u;
-    const uint32_t nw = acc ? tr.y >> 16 : x;
+    const uint32_t nw = acc ? m.tr.y >> 16 : m.x;
     lat[s.a + P] = (uint8_t)nw;
-    lat[q.b] = (uint8_t)(nw >> 8);
+    lat[qb] = (uint8_t)(nw >> 8);
 }
 
 // Displacements of a sweep's four phases (uniform).
@@ -232,7 +257,9 @@ __device__ __forceinline__ void site_sweeps(uint8_t *lat, uint32_t *sched, const
     SiteDraw dr[PP];
     SiteB q[PP];
     if (One) {
-        site_draws<PP>(first, 0u, threadIdx.x, d.key0, d.key1, dr);
+        PhiloxRun call = site_call<PP>(first, 0u, threadIdx.x, d.key0, d.key1);
+        philox_rounds<10>(call);
+        site_draws<PP>(call, threadIdx.x, dr);
 #pragma unroll
         for (int h = 0; h < PP; ++h) {
             pos[h] = site_pos(mine ? threadIdx.x * PP + (uint32_t)h : 0u, L, Lq, N, magicLq);
@@ -256,23 +283,57 @@ __device__ __forceinline__ void site_sweeps(uint8_t *lat, uint32_t *sched, const
             if (One) {
                 if (mine) {
                     SiteDraw nd[PP];
-                    site_draws<PP>(P < 3 ? s : s + 1, P1, threadIdx.x, d.key0, d.key1, nd);
+                    PhiloxRun call = site_call<PP>(P < 3 ? s : s + 1, P1, threadIdx.x, d.key0, d.key1);
+                    auto next_b = [&](int h) {
+                        return site_b<P1>(pos[h], L, N, P < 3 ? sc.Dx[P1] : next.Dx[0], P < 3 ? sc.DyL[P1] : next.DyL[0]);
+                    };
+                    if constexpr (PP == 1) {
+                        // The next phase's call in three parts between the stages:
+                        // left to itself the compiler draws first and loads then
+                        // (L = 32, 100 intervals of 10 sweeps: 1690 us, so 1460).
+                        const uint32_t b = q[0].b;
+                        const SiteLoads v = site_load<P>(lat, pos[0], q[0], L);
+                        __builtin_amdgcn_sched_barrier(0);
+                        philox_rounds<4>(call);
+                        __builtin_amdgcn_sched_barrier(0);
+                        const SiteMove m = site_move(v, dr[0], s_trans);
+                        __builtin_amdgcn_sched_barrier(0);
+                        philox_rounds<3>(call);
+                        __builtin_amdgcn_sched_barrier(0);
+                        const uint2 e = site_entry(m, s_tab);
+                        __builtin_amdgcn_sched_barrier(0);
+                        philox_rounds<3>(call);
+                        site_draws<PP>(call, threadIdx.x, nd);
+                        q[0] = next_b(0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        site_store<P>(lat, pos[0], b, dr[0], m, e, packed);
+                        dr[0] = nd[0];
+                    } else {
+                        // two pairs a thread have enough waves to fill the gaps
+                        // (40 of L = 100, 50 sweeps: in stages 241 us, so 227)
+                        philox_rounds<10>(call);
+                        site_draws<PP>(call, threadIdx.x, nd);
 #pragma unroll
-                    for (int h = 0; h < PP; ++h) {
-                        site_step<P>(lat, pos[h], q[h], L, dr[h], s_tab, s_trans, packed);
-                        dr[h] = nd[h];
-                        q[h] = site_b<P1>(pos[h], L, N, P < 3 ? sc.Dx[P1] : next.Dx[0], P < 3 ? sc.DyL[P1] : next.DyL[0]);
+                        for (int h = 0; h < PP; ++h) {
+                            const SiteMove m = site_move(site_load<P>(lat, pos[h], q[h], L), dr[h], s_trans);
+                            site_store<P>(lat, pos[h], q[h].b, dr[h], m, site_entry(m, s_tab), packed);
+                            dr[h] = nd[h];
+                            q[h] = next_b(h);
+                        }
                     }
                 }
             } else {
                 for (uint32_t t = threadIdx.x; t < tasks; t += blockDim.x) {
-                    site_draws<PP>(s, P, t, d.key0, d.key1, dr);
+                    PhiloxRun call = site_call<PP>(s, P, t, d.key0, d.key1);
+                    philox_rounds<10>(call);
+                    site_draws<PP>(call, t, dr);
                     packed = 0u;
 #pragma unroll
                     for (int h = 0; h < PP; ++h) {
                         const SitePos at = site_pos(t * PP + (uint32_t)h, L, Lq, N, magicLq);
-                        site_step<P>(lat, at, site_b<P>(at, L, N, sc.Dx[P], sc.DyL[P]), L, dr[h], s_tab, s_trans,
-                                     packed);
+                        const SiteB to = site_b<P>(at, L, N, sc.Dx[P], sc.DyL[P]);
+                        const SiteMove m = site_move(site_load<P>(lat, at, to, L), dr[h], s_trans);
+                        site_store<P>(lat, at, to.b, dr[h], m, site_entry(m, s_tab), packed);
                     }
                     unpack_tracker(packed, tr);
                 }

@@ -24,29 +24,41 @@ constexpr uint32_t kPhiloxW1 = 0xBB67AE85u;
 constexpr uint32_t kDomSchedule = 0x100u;
 constexpr uint32_t kDomInit = 0x200u;
 
+// A call on its way: counter words and round key.  philox_rounds lets a kernel
+// put other work between a call's rounds.
+struct PhiloxRun {
+    uint32_t c0, c1, c2, c3, k0, k1;
+};
+template <int Rounds>
+__host__ __device__ __forceinline__ void philox_rounds(PhiloxRun &r)
+{
+#pragma unroll
+    for (int i = 0; i < Rounds; ++i) {
+        const uint64_t p0 = (uint64_t)kPhiloxM0 * r.c0;
+        const uint64_t p1 = (uint64_t)kPhiloxM1 * r.c2;
+#if defined(__HIP_DEVICE_COMPILE__)
+        // gfx950 three-input boolean op; truth table 0x96 is a ^ b ^ c
+        const uint32_t n0 = __builtin_amdgcn_bitop3_b32((uint32_t)(p1 >> 32), r.c1, r.k0, 0x96);
+        const uint32_t n2 = __builtin_amdgcn_bitop3_b32((uint32_t)(p0 >> 32), r.c3, r.k1, 0x96);
+#else
+        const uint32_t n0 = (uint32_t)(p1 >> 32) ^ r.c1 ^ r.k0;
+        const uint32_t n2 = (uint32_t)(p0 >> 32) ^ r.c3 ^ r.k1;
+#endif
+        r.c1 = (uint32_t)p1;
+        r.c3 = (uint32_t)p0;
+        r.c0 = n0;
+        r.c2 = n2;
+        r.k0 += kPhiloxW0;
+        r.k1 += kPhiloxW1;
+    }
+}
+
 __host__ __device__ __forceinline__ u32x4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2,
                                                         uint32_t c3, uint32_t k0, uint32_t k1)
 {
-#pragma unroll
-    for (int i = 0; i < 10; ++i) {
-        const uint64_t p0 = (uint64_t)kPhiloxM0 * c0;
-        const uint64_t p1 = (uint64_t)kPhiloxM1 * c2;
-#if defined(__HIP_DEVICE_COMPILE__)
-        // gfx950 three-input boolean op; truth table 0x96 is a ^ b ^ c
-        const uint32_t n0 = __builtin_amdgcn_bitop3_b32((uint32_t)(p1 >> 32), c1, k0, 0x96);
-        const uint32_t n2 = __builtin_amdgcn_bitop3_b32((uint32_t)(p0 >> 32), c3, k1, 0x96);
-#else
-        const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
-        const uint32_t n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
-#endif
-        c1 = (uint32_t)p1;
-        c3 = (uint32_t)p0;
-        c0 = n0;
-        c2 = n2;
-        k0 += kPhiloxW0;
-        k1 += kPhiloxW1;
-    }
-    return {c0, c1, c2, c3};
+    PhiloxRun r{c0, c1, c2, c3, k0, k1};
+    philox_rounds<10>(r);
+    return {r.c0, r.c1, r.c2, r.c3};
 }
 
 __host__ __device__ __forceinline__ uint32_t mulhi_u32(uint32_t a, uint32_t b)
