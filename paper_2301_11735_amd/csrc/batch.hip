@@ -160,15 +160,16 @@ __device__ __forceinline__ void site_draws(const PhiloxRun &w, uint32_t task, Si
     if constexpr (PP == 2) o[1] = SiteDraw{slot8_of(w.c2), min(w.c3, 0xFFFFFFFEu)};
 }
 
-// Byte offsets of a pair's second site in phase P with displacement (Dx, Dy),
-// DyL = Dy L, and of its neighbours.  x mod n for x < 2 n is min(x, x - n) in
+// Byte offsets of a pair's second site in phase P, displaced by (r + 4 m, 1 + 2 k),
+// and of its neighbours.  x mod n for x < 2 n is min(x, x - n) in
 // unsigned arithmetic.
 struct SiteB {
     uint32_t b, l, r, d;
 };
 template <int P>
-__device__ __forceinline__ SiteB site_b(const SitePos &s, uint32_t L, uint32_t N, uint32_t Dx, uint32_t DyL)
+__device__ __forceinline__ SiteB site_b(const SitePos &s, uint32_t L, uint32_t N, const SweepWords &w)
 {
+    const uint32_t Dx = w.r + 4u * w.m[P], DyL = (1u + 2u * w.k[P]) * L;
     uint32_t xb = s.x4 + P + Dx;
     xb = min(xb, xb - L);
     uint32_t rb = s.row + DyL;
@@ -221,22 +222,6 @@ __device__ __forceinline__ void site_store(uint8_t *lat, const SitePos &s, uint3
     lat[qb] = (uint8_t)(nw >> 8);
 }
 
-// Displacements of a sweep's four phases (uniform).
-struct SiteSchedule {
-    uint32_t Dx[4], DyL[4];
-};
-__device__ __forceinline__ SiteSchedule site_schedule(const uint32_t *Wd, uint32_t L)
-{
-    const SweepWords w = sweep_words(Wd, L);
-    SiteSchedule o;
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        o.Dx[p] = w.r + 4u * w.m[p];
-        o.DyL[p] = (1u + 2u * w.k[p]) * L;
-    }
-    return o;
-}
-
 // `intervals` times `every` sweeps of the lattice in LDS from sweep first on,
 // each interval followed by observe(k).  PP pairs a task; One: every thread
 // has at most one task, whose draws and second sites of the next phase are
@@ -250,9 +235,9 @@ __device__ __forceinline__ void site_sweeps(uint8_t *lat, uint32_t *sched, const
     const uint32_t magicLq = Lq == 1u ? 0u : 0xFFFFFFFFu / Lq + 1u;
     const uint32_t tasks = N / (8u * PP), n = intervals * every;
     const bool mine = threadIdx.x < tasks;
-    make_schedules(sched, first, n, d.key0, d.key1);
+    make_schedules(sched, first, n, d.key0, d.key1, L);
     __syncthreads();
-    SiteSchedule sc = site_schedule(sched, L);
+    SweepWords sc = sweep_words(sweep_loads(sched));
     SitePos pos[PP];
     SiteDraw dr[PP];
     SiteB q[PP];
@@ -263,13 +248,14 @@ __device__ __forceinline__ void site_sweeps(uint8_t *lat, uint32_t *sched, const
 #pragma unroll
         for (int h = 0; h < PP; ++h) {
             pos[h] = site_pos(mine ? threadIdx.x * PP + (uint32_t)h : 0u, L, Lq, N, magicLq);
-            q[h] = site_b<0>(pos[h], L, N, sc.Dx[0], sc.DyL[0]);
+            q[h] = site_b<0>(pos[h], L, N, sc);
         }
     }
     uint32_t left = every, k = 0;  // sweeps left of interval k
     for (uint32_t i = 0; i < n; ++i) {
         const uint64_t s = first + i;
-        SiteSchedule next = sc;
+        SweepWords next = sc;
+        SweepLoads coming{};  // of the next sweep's schedule
         uint32_t packed = 0u;  // One: at most 8 accepted moves a sweep
         auto phase = [&](auto pc) {
             constexpr int P = decltype(pc)::value;
@@ -278,14 +264,15 @@ __device__ __forceinline__ void site_sweeps(uint8_t *lat, uint32_t *sched, const
             // buffer that was last read a sweep or more ago
             const uint32_t j = i + 1u;
             if (P == 0 && j % kSchedSweeps == 0 && j < n)
-                make_schedules(sched + 12u * (j % (2u * kSchedSweeps)), s + 1, n - j, d.key0, d.key1);
-            if (P == 3) next = site_schedule(sched + 12u * (j % (2u * kSchedSweeps)), L);
+                make_schedules(sched + 12u * (j % (2u * kSchedSweeps)), s + 1, n - j, d.key0, d.key1, L);
+            if (P == 2) coming = sweep_loads(sched + 12u * (j % (2u * kSchedSweeps)));
+            if (P == 3) next = sweep_words(coming);
             if (One) {
                 if (mine) {
                     SiteDraw nd[PP];
                     PhiloxRun call = site_call<PP>(P < 3 ? s : s + 1, P1, threadIdx.x, d.key0, d.key1);
                     auto next_b = [&](int h) {
-                        return site_b<P1>(pos[h], L, N, P < 3 ? sc.Dx[P1] : next.Dx[0], P < 3 ? sc.DyL[P1] : next.DyL[0]);
+                        return site_b<P1>(pos[h], L, N, P < 3 ? sc : next);
                     };
                     if constexpr (PP == 1) {
                         // The next phase's call in three parts between the stages:
@@ -331,7 +318,7 @@ __device__ __forceinline__ void site_sweeps(uint8_t *lat, uint32_t *sched, const
 #pragma unroll
                     for (int h = 0; h < PP; ++h) {
                         const SitePos at = site_pos(t * PP + (uint32_t)h, L, Lq, N, magicLq);
-                        const SiteB to = site_b<P>(at, L, N, sc.Dx[P], sc.DyL[P]);
+                        const SiteB to = site_b<P>(at, L, N, sc);
                         const SiteMove m = site_move(site_load<P>(lat, at, to, L), dr[h], s_trans);
                         site_store<P>(lat, at, to.b, dr[h], m, site_entry(m, s_tab), packed);
                     }

@@ -18,38 +18,42 @@ __device__ __forceinline__ uint32_t codes_from_site(uint32_t e)
     return ((e >> 3) & (one << 1)) | (~((e >> 5) | (e >> 1)) & one);  // charged; sigma = -1 or S = -1
 }
 
-// Schedule words of up to kSchedSweeps sweeps from s on, 12 a sweep, one
-// Philox call a thread.
+// Schedules of up to kSchedSweeps sweeps from s on, one Philox call (4 of a
+// sweep's 12 words) a thread: r, then m_p and k_p of the four phases.
 constexpr uint32_t kSchedSweeps = 16;
 __device__ __forceinline__ void make_schedules(uint32_t *sched, uint64_t s, uint32_t sweeps, uint32_t key0,
-                                               uint32_t key1)
+                                               uint32_t key1, uint32_t L)
 {
     const uint32_t t = threadIdx.x;
     if (t >= 3u * min(kSchedSweeps, sweeps)) return;
     const uint64_t q = s + t / 3u;
     const u32x4 w = philox4x32_10((uint32_t)q, kDomSchedule, t % 3u, (uint32_t)(q >> 32), key0, key1);
-    sched[4u * t] = w.x;
-    sched[4u * t + 1u] = w.y;
-    sched[4u * t + 2u] = w.z;
-    sched[4u * t + 3u] = w.w;
+    sched[4u * t] = t % 3u == 0u ? 1u + (((w.x >> 8) * 3u) >> 24) : mulhi_u32(w.x, L >> 1);
+    sched[4u * t + 1u] = mulhi_u32(w.y, L >> 2);
+    sched[4u * t + 2u] = mulhi_u32(w.z, L >> 1);
+    sched[4u * t + 3u] = mulhi_u32(w.w, L >> 2);
 }
-// The schedule (r, m_p, k_p) of a sweep from its words, in scalar registers.
+// A sweep's schedule on its way to scalar registers: loaded a phase before it is
+// needed.
+struct SweepLoads {
+    uint32_t w[9];
+};
+__device__ __forceinline__ SweepLoads sweep_loads(const uint32_t *sched)
+{
+    SweepLoads v;
+#pragma unroll
+    for (int i = 0; i < 9; ++i) v.w[i] = sched[i];
+    return v;
+}
 struct SweepWords {
     uint32_t r, m[4], k[4];
 };
-__device__ __forceinline__ SweepWords sweep_words(const uint32_t *Wd, uint32_t L)
+__device__ __forceinline__ SweepWords sweep_words(const SweepLoads &v)
 {
     uint32_t w[9];
 #pragma unroll
-    for (int i = 0; i < 9; ++i) w[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)Wd[i]);
-    SweepWords o;
-    o.r = 1u + (((w[0] >> 8) * 3u) >> 24);
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        o.m[p] = mulhi_u32(w[1 + 2 * p], L >> 2);
-        o.k[p] = mulhi_u32(w[2 + 2 * p], L >> 1);
-    }
-    return o;
+    for (int i = 0; i < 9; ++i) w[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)v.w[i]);
+    return SweepWords{w[0], {w[1], w[3], w[5], w[7]}, {w[2], w[4], w[6], w[8]}};
 }
 
 // This thread's share of a lattice's tracker slots (phase kernels) and, for

@@ -266,7 +266,7 @@ __device__ __forceinline__ void quad_sweeps(uint8_t *lat, uint32_t *sched, const
     const uint32_t tasks = g.H * q_row, n = intervals * every;
     const uint64_t first = d.next_sweep;
     const bool mine = threadIdx.x < tasks;
-    make_schedules(sched, first, n, d.key0, d.key1);
+    make_schedules(sched, first, n, d.key0, d.key1, g.L);
     __syncthreads();
     QuadPos pos{};
     QuadDraws dr{};
@@ -274,16 +274,18 @@ __device__ __forceinline__ void quad_sweeps(uint8_t *lat, uint32_t *sched, const
         pos = quad_pos(mine ? threadIdx.x : 0u, g, magic);
         dr = quad_draws(first, 0u, threadIdx.x, d.key0, d.key1);
     }
+    SweepLoads coming = sweep_loads(sched);  // of the next sweep's schedule
     uint32_t left = every, k = 0;  // sweeps left of interval k
     for (uint32_t i = 0; i < n; ++i) {
         const uint64_t s = first + i;
         uint32_t packed = 0u;  // One: at most 16 accepted moves a sweep
-        const SweepWords w = sweep_words(sched + 12u * (i % (2u * kSchedSweeps)), g.L);
+        const SweepWords w = sweep_words(coming);
         auto phase = [&](auto pc) {
             constexpr int P = decltype(pc)::value;
             const uint32_t j = i + 1u;
             if (P == 0 && j % kSchedSweeps == 0 && j < n)
-                make_schedules(sched + 12u * (j % (2u * kSchedSweeps)), s + 1, n - j, d.key0, d.key1);
+                make_schedules(sched + 12u * (j % (2u * kSchedSweeps)), s + 1, n - j, d.key0, d.key1, g.L);
+            if (P == 3) coming = sweep_loads(sched + 12u * (j % (2u * kSchedSweeps)));
             QuadPhase f;
             f.pb = (P + w.r) & 3u;
             f.dX = w.m[P] + ((P + w.r) >> 2);
