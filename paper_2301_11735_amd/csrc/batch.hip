@@ -342,12 +342,12 @@ __device__ __forceinline__ void site_sweeps(uint8_t *lat, uint32_t *sched, const
 }
 
 // This thread's share of the seven observable sums.
-__device__ __forceinline__ void site_observables(const uint32_t *lat, uint32_t L, int (&v)[7])
+__device__ __forceinline__ void site_observables(const uint32_t *lat, uint32_t L, uint32_t magicLq, int (&v)[7])
 {
     const uint32_t Lq = L >> 2, n = L * Lq;
     SiteSums sums;
     for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
-        const uint32_t y = i / Lq, X = i - y * Lq, w = lat[i];
+        const uint32_t y = Lq == 1u ? i : __umulhi(i, magicLq), X = i - y * Lq, w = lat[i];
         const uint32_t w1 = lat[X + 1u == Lq ? i + 1u - Lq : i + 1u];
         sums.add(w, __builtin_amdgcn_alignbit(w1, w, 8u), lat[y + 1u == L ? X : i + Lq], row_signs(y));
     }
@@ -376,11 +376,12 @@ __global__ void __launch_bounds__(1024) k_sweep_site(BatchArgs args)
     const uint32_t intervals = args.obs_out ? args.intervals : 1u;
     const bool single = N / 8u <= min(blockDim.x, kSiteOnePair), one = N / 16u <= blockDim.x;
     const uint8_t *tab = (const uint8_t *)s_tab, *trans = (const uint8_t *)s_trans;
+    const uint32_t magicLq = L == 4u ? 0u : 0xFFFFFFFFu / (L >> 2) + 1u;
     int tr[3] = {0, 0, 0};
     auto observe = [&](uint32_t k) {
         if (!args.obs_out) return;
         int o[7];
-        site_observables(lat, L, o);
+        site_observables(lat, L, magicLq, o);
         write_record(args, obs, tr, o, k, d.next_sweep + (uint64_t)my_sweeps * (k + 1u));
     };
     if (my_sweeps > 0) {
