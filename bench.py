@@ -43,12 +43,12 @@ BYTES_PER_SITE_UPDATE_2BIT = 0.5
 # 32x32->64 multiplies and two three-input xors, all full-rate on gfx950, so
 # 40 lane-ops per call.  Reported only as a lower bound on ALU use.
 PHILOX_OPS_PER_SITE_UPDATE = 10.0
-# LDS bytes per site update in the phase kernel: per pair one 16-byte
-# transition entry and one 8-byte threshold entry (12 B per update), and the
+# LDS bytes per site update in the phase kernel: per pair one 8-byte
+# transition entry and one 8-byte threshold entry (8 B per update), and the
 # b-word exchange, a 4-byte write and a 4-byte read per thread for its 32
 # updates (0.25 B).  The tables' staging (9 KB per block, about 2% more at
 # L = 8192) is left out.  Peak: 128 B per clock per CU x 256 CUs x 2.4 GHz.
-LDS_BYTES_PER_SITE_UPDATE = 12.25
+LDS_BYTES_PER_SITE_UPDATE = 8.25
 LDS_PEAK_GBS = 128 * 256 * 2.4
 
 
@@ -187,7 +187,7 @@ def write_counter_summary(out_md, csvs, trace_stats=None):
             name = re.sub(r"\(.*", "", r["Kernel_Name"].replace("lat::(anonymous namespace)::", "").replace("void ", ""))
             vals[name][r["Counter_Name"]].append(float(r["Counter_Value"]))
     lines = ["| kernel | counter | dispatches | mean per dispatch |", "|---|---|---|---|"]
-    keep = ("k_phase_2bit", "k_sweep_quad", "k_sweep_lds", "k_obs_2bit", "k_obs_batch", "k_fold_sums")
+    keep = ("k_phase_2bit", "k_sweep_quad", "k_sweep_site", "k_obs_2bit", "k_obs_batch", "k_fold_sums")
     for k in sorted(v for v in vals if v.startswith(keep)):
         for c in sorted(vals[k]):
             v = vals[k][c]
@@ -311,8 +311,8 @@ def batched_run(torch, lat, b2b_sample: int = 8, b2b_sweeps: int = 1000) -> dict
     its 100 intervals (batched sweep launch + batched observable reduction
     into that interval's slot, the series read back once at the end), and
     eagerly, one batched sweep call and one observables read per interval.
-    Lattice creation, graph capture and the launch-shape autotuning (the first
-    calls for a new batch shape) are not timed.  Beside them, a sample of the
+    Lattice creation, graph capture and the first calls are not timed.  Beside
+    them, a sample of the
     same lattices run back to back through the single-lattice call."""
     specs = workloads.batched_specs()
     every, total = specs[0].every, specs[0].sweeps
@@ -322,7 +322,7 @@ def batched_run(torch, lat, b2b_sample: int = 8, b2b_sweeps: int = 1000) -> dict
     def fresh():
         return [lat.Lattice(s.L, s.n, s.Delta, s.V, s.J, s.T, s.seed, encoding=s.encoding) for s in specs]
 
-    # autotune the batch shape on throw-away lattices
+    # first calls on throw-away lattices
     warm = fresh()
     wobs = lat.BatchObservables(len(warm))
     for _ in range(6):

@@ -26,16 +26,16 @@ namespace {
 // table gathers, the store, the block barrier), not the work: L = 32 has 128
 // pairs a phase on one compute unit.  So the pairs of a phase are spread over
 // as many threads as help (one pair a thread up to kSiteOnePair pairs, else the
-// two pairs of a Philox call), a thread with one task makes the next phase's
-// draws while its own loads are in flight, the choice slot of a draw does
-// not depend on the state, and a launch holds a whole series of observation
-// intervals with the observables taken from LDS in between.
+// two pairs of a Philox call), a thread with one pair draws the next phase's
+// call in the waits of its own loads, the choice slot of a draw does not depend
+// on the state, and a launch holds a whole series of observation intervals
+// with the observables taken from LDS in between.
 //
-// Measured against the two-bit form, whose neighbours are ten shifted word
-// reads and whose codes are merged with LDS atomics: L = 32, 1000 sweeps with
-// observables every 10 as one series 6197 -> 1696 us; 224 lattices of L = 16,
-// 200 intervals of one sweep in a graph 3611 -> 816 us; 40 lattices of L = 100,
-// 50 sweeps 521 -> 247 us; 12 of L = 300, 20 sweeps 1295 -> 726 us.
+// Measured against two bits per site, with neighbours from ten shifted word
+// reads and codes merged by LDS atomics: L = 32, 1000 sweeps with observables
+// every 10 as one series 6230 -> 1381 us; 224 lattices of L = 16, 200 intervals of
+// one sweep in a graph 3629 -> 715 us; 40 lattices of L = 100, 50 sweeps 522 ->
+// 224 us; 12 of L = 300, 20 sweeps 1295 -> 655 us.
 
 constexpr uint32_t kSiteHash = 0x2B298945u;  // (byte_a | byte_b << 8) -> 4 distinct top bits for the 16 states
 
@@ -432,9 +432,8 @@ __global__ void __launch_bounds__(256) k_obs_batch(BatchArgs args, unsigned long
     } else {
         obs_sums_2bit((const uint32_t *)d.state, L, v);
     }
-    unsigned long long *o = out + (size_t)(args.obs_words > 10 ? 11 : 10) * blockIdx.x;
+    unsigned long long *o = out + 10 * (size_t)blockIdx.x;
     if (threadIdx.x < 10) o[threadIdx.x] = 0ull;
-    if (args.obs_words > 10 && threadIdx.x == 0) o[10] = d.next_sweep;
     __syncthreads();
     block_reduce_add<7>(v, o + 3);
     long long t3[3] = {0, 0, 0};

@@ -91,8 +91,7 @@ int lattice_batch_graph_create(lattice *const *hs, int32_t count, uint32_t sweep
             std::vector<lattice *> small, big;
             for (lattice *h : g->hs) (h->path == kPathLds ? small : big).push_back(h);
             if (big.empty()) {
-                // an interval's sweeps and observables are one launch in the
-                // word form, and many intervals are one in the per-site form
+                // many intervals, sweeps and observables, are one launch
                 const ObsTarget obs{(unsigned long long *)d_out, intervals, 10u, 10u * (uint32_t)count};
                 rc = enqueue_lds_sweeps(g->hs.data(), count, nullptr, sweeps, cs, &obs);
             }

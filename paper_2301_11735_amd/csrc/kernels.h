@@ -62,7 +62,7 @@ constexpr int kMuTabSize = 16 * 137;  // 2192
 // every 64 bytes, so that few atomics meet at an address.
 constexpr int kMuChargeSlots = 32, kMuChargeStride = 8;
 constexpr size_t kScrMuTab = kScrFullTab + ((size_t)kTabSize * 4 + 255) / 256 * 256;  // 71168
-static_assert(kScrMuTab + (size_t)kMuTabSize * 4 <= 88576, "the penalty table ends before the delta table");
+static_assert(kScrMuTab + (size_t)kMuTabSize * 4 <= 88576, "the penalty table ends before the reserved tail");
 constexpr size_t kScrTransD = 88576;                  // reserved
 constexpr size_t kScrBytes = kScrTransD + (size_t)kTransEntries * 16;                 // 90112
 
@@ -95,7 +95,7 @@ constexpr int kQuadMaxL = 368;
 constexpr uint32_t kQuadHalo = 8;
 inline size_t quad_lds_bytes(int L) { return (size_t)8 * (size_t)(L / 2) * ((size_t)(L / 4) + kQuadHalo); }
 // One launch of the batched kernel: block b advances lattice b by sweeps[b],
-// `intervals` times over in the per-site and quad forms (1 in the others).
+// `intervals` times over.
 constexpr int kMaxBatch = 256;
 struct BatchArgs {
     int count;
@@ -103,9 +103,8 @@ struct BatchArgs {
     uint32_t sweeps[kMaxBatch];
     // non-null: after the sweeps of interval k, lattice b's observables and
     // tracker total go to obs_out[obs_stride k + obs_words b ..] in
-    // k_obs_batch's layout (written by the sweep kernel itself in the per-site
-    // and quad forms, else by k_obs_batch); obs_words = 11
-    // appends the lattice's next sweep index (a series record), else 10
+    // k_obs_batch's layout; obs_words = 11 appends the lattice's next sweep index (a
+    // series record), else 10
     unsigned long long *obs_out;
     uint32_t intervals, obs_words, obs_stride;
 };
@@ -284,8 +283,8 @@ struct SeedArgs {
 hipError_t launch_seed(const SeedArgs &a, hipStream_t s) __attribute__((weak));
 
 // Batched sweeps with each lattice resident in LDS.  quad: the quad form
-// (every side a multiple of 16, at most kQuadMaxL); else the per-site form up
-// to kSiteMaxL and two bits per site above.
+// (every side a multiple of 16, at most kQuadMaxL); else the per-site form (up
+// to kSiteMaxL).
 hipError_t launch_sweep_lds(const BatchArgs &a, int max_L, int threads, bool quad, hipStream_t s);
 hipError_t launch_sweep_quad(const BatchArgs &a, int max_L, int threads, hipStream_t s);
 hipError_t init_quad_kernel_attributes();
