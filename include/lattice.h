@@ -164,11 +164,12 @@ int lattice_read_state(lattice *h, int8_t *host_codes);
  * 3.2: several lattice copies processed together).  Lattices may differ in
  * L, encoding, parameters and seed; results are identical to calling
  * lattice_sweep on each.  Lattices on the on-chip path (L <= 256 with
- * L % 64 == 0, L <= 512 otherwise) advance together in one launch per 256 of
- * them, each resident in on-chip memory for all the sweeps; those with
- * L % 64 == 0 up to 2048 advance together on the multi-block word kernel (one
- * cooperative launch per 64 of them, as lattice_sweep); larger ones one after
- * another.  The caller orders hip_stream
+ * L % 64 == 0, L <= 384 otherwise) advance together in one launch per 256 of
+ * them, each resident in on-chip memory for all the sweeps, or spread over the
+ * device where that is faster; those with L % 64 == 0 up to 2048 and int8 ones
+ * of other sides advance together on the multi-block kernels (one
+ * cooperative launch per 64 of them, as lattice_sweep, or one per phase);
+ * larger ones one after another.  The caller orders hip_stream
  * after any pending work of the lattices' own streams.  A lattice may appear
  * only once.  Errors: LAT_EINVAL, LAT_ESTATE, LAT_EHIP. */
 int lattice_sweep_batch(lattice *const *hs, int32_t count, uint32_t sweeps, void *hip_stream);
@@ -201,9 +202,8 @@ int lattice_observables_batch_noalloc(lattice *const *hs, int32_t count, lat_obs
  * observables into its own slot of the device buffer d_out (slot k at byte
  * 80*count*k, 80 bytes per lattice, as lattice_observables_batch), so a whole
  * observable series is produced with one graph launch and read with one copy.
- * Every lattice must take the on-chip batched path (L <= 256 with
- * L % 64 == 0, L <= 512 otherwise) or the multi-block word path (L % 64 == 0
- * up to 2048, one launch per phase in the graph).  The capture runs on a
+ * Every lattice must have L <= 512, or L % 64 == 0 up to 2048; the sides above
+ * the on-chip ones take one launch per phase in the graph.  The capture runs on a
  * private stream and launches nothing; replays run on hip_stream, which the
  * caller orders after the lattices' other work.  The lattices and d_out must
  * outlive the graph.
