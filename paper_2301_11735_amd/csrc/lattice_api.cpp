@@ -520,7 +520,7 @@ int enqueue_words_sweeps(lattice *const *hs, int32_t count, const uint32_t *swee
 
 }  // namespace
 
-constexpr int kWordsPersistentMaxL = 2048;
+constexpr int kWordsPersistentMaxL = 2048, kWordsSharedMaxL = 1024;
 
 namespace {
 
@@ -653,6 +653,9 @@ int enqueue_words_persistent(lattice *const *hs, int32_t count, const uint32_t *
     // as they are: as long as a block a compute unit holds a call a thread (us a
     // sweep, persistent / launches: L = 388 12.5 / 18.0, L = 1000 16.3 / 19.9, 8 of
     // L = 500 24.5 / 25.5; but L = 2000 33.8 / 35.4, L = 4000 99 / 75).
+    // On a stream of their own, where other lattices may run beside them, only
+    // the word kernel up to kWordsSharedMaxL is persistent: a cooperative
+    // launch takes the device's one cooperative queue.
     // LATTICE_WORDS_PERSISTENT=0|1 overrides.
     const char *v = std::getenv("LATTICE_WORDS_PERSISTENT");
     if (v) {
@@ -660,6 +663,7 @@ int enqueue_words_persistent(lattice *const *hs, int32_t count, const uint32_t *
     } else {
         if (!records && longest < 2) return LAT_OK;
         if (bytes ? !bytes_fit(hs, count) : max_L > kWordsPersistentMaxL) return LAT_OK;
+        if (stream && (bytes || max_L > kWordsSharedMaxL)) return LAT_OK;
     }
     if (records && count != 1) return fail(LAT_EINVAL, "an observation series holds one lattice");
     if (captured(stream)) return LAT_OK;
@@ -748,10 +752,11 @@ int enqueue_words_persistent(lattice *const *hs, int32_t count, const uint32_t *
 // 0.229 L^2 in the four-pair form and 0.34 L^2 per site (L = 256 15.0 us, L = 340
 // 39.5); spread 9.7 us with two bits a site and 12 as bytes, and 4.6 more when
 // every compute unit has a block (L = 256 9.7, L = 340 12.0, 16 of L = 260 17).
-// Lattices whose path was asked for stay on it.
+// Lattices whose path was asked for stay on it, and so do those on a stream of
+// their own: side by side with others, a compute unit each is the better use.
 bool spreads(lattice *const *hs, int32_t count, uint64_t sweeps, double extra, hipStream_t stream)
 {
-    if (count < 1 || count > kWordsBatch) return false;
+    if (count < 1 || count > kWordsBatch || stream) return false;
     int max_L = 0;
     bool quad = true;
     for (int32_t i = 0; i < count; ++i) {

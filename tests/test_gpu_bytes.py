@@ -133,3 +133,19 @@ def test_persistent_and_spread_calls(L, enc, count):
         g.sweep(7)
         o.sweeps(7)
         _check(pairs)
+
+
+def test_on_a_stream_of_its_own():
+    """No lattice spreads and none of these is persistent there; same results."""
+    import torch
+
+    print("case bytes and on-chip lattices on a stream of their own", flush=True)
+    s = torch.cuda.Stream()
+    for L, n in ((340, 12), (388, 6), (516, 3)):
+        g = lat.Lattice(L, 0.1, 0.1, 0.5, 1.0, 1.0, 60 + L, stream=s)
+        o = oracle.OracleLattice(L, 0.1, 0.1, 0.5, 1.0, 1.0, 60 + L)
+        g.sweep(n)
+        o.sweeps(n)
+        assert np.array_equal(g.read_state(), o.codes), L
+        assert g.observables().ints() == o.observables().tolist(), L
+        g.destroy()
