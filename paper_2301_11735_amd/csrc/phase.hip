@@ -541,11 +541,14 @@ hipError_t launch_phase_bytes(const WordsArgs &a, int threads, hipStream_t s)
 // holds whole class rows.  For one launch per phase the default is blocks of
 // at most 512 threads, two per compute unit (16 waves, as one 1024-thread
 // block): measured 1.5% faster than one 1024-thread block at L = 8192.
+// Never fewer threads than a block has tracker sums, each of which one thread
+// adds, whatever number of rows is asked for.
+constexpr int kTrackSums = 3;
 static int rows_per_block_2bit(int W, int requested, int max_threads)
 {
     const int cap = requested > 0 ? requested : 32;
     int r = 1;
-    while (r < 32 && 2 * r <= cap && 2 * r * W <= max_threads) r *= 2;
+    while (r < 32 && ((2 * r <= cap && 2 * r * W <= max_threads) || r * W < kTrackSums)) r *= 2;
     return r;
 }
 
