@@ -247,20 +247,33 @@ __device__ __forceinline__ uint32_t contrib_a(uint32_t c) { return __builtin_amd
 __device__ __forceinline__ uint32_t contrib_b(uint32_t c) { return __builtin_amdgcn_perm(kVG, kVS, 0x040C000Cu + c * 0x01000100u); }
 
 // Schedule of sweep s (same definition as the host's): r in {1,2,3};
-// phase p has D_p = (r + 4 m_p, 1 + 2 k_p).  Every lane of the wave must be
-// active: lanes 0 to 2 draw one of the three calls each (one after another, in
-// scalar registers, they are most of a microsecond).
+// phase p has D_p = (r + 4 m_p, 1 + 2 k_p).  Whole (every lane of every wave is
+// active): lanes 0 to 2 draw one of the three calls each (one after another, in
+// scalar registers, they are most of a microsecond).  Blocks whose last wave may
+// have fewer lanes draw all three in every lane.
+template <bool Whole = true>
 __device__ __forceinline__ void device_schedule(int L, uint32_t k0, uint32_t k1, uint64_t s, int &r, int (&m)[4],
                                                 int (&k)[4])
 {
-    const u32x4 w = philox4x32_10((uint32_t)s, kDomSchedule, threadIdx.x & 3u, (uint32_t)(s >> 32), k0, k1);
     uint32_t Wd[12];
+    if constexpr (Whole) {
+        const u32x4 w = philox4x32_10((uint32_t)s, kDomSchedule, threadIdx.x & 3u, (uint32_t)(s >> 32), k0, k1);
 #pragma unroll
-    for (int t = 0; t < 3; ++t) {
-        Wd[4 * t] = (uint32_t)__builtin_amdgcn_readlane((int)w.x, t);
-        Wd[4 * t + 1] = (uint32_t)__builtin_amdgcn_readlane((int)w.y, t);
-        Wd[4 * t + 2] = (uint32_t)__builtin_amdgcn_readlane((int)w.z, t);
-        Wd[4 * t + 3] = (uint32_t)__builtin_amdgcn_readlane((int)w.w, t);
+        for (int t = 0; t < 3; ++t) {
+            Wd[4 * t] = (uint32_t)__builtin_amdgcn_readlane((int)w.x, t);
+            Wd[4 * t + 1] = (uint32_t)__builtin_amdgcn_readlane((int)w.y, t);
+            Wd[4 * t + 2] = (uint32_t)__builtin_amdgcn_readlane((int)w.z, t);
+            Wd[4 * t + 3] = (uint32_t)__builtin_amdgcn_readlane((int)w.w, t);
+        }
+    } else {
+#pragma unroll
+        for (uint32_t t = 0; t < 3u; ++t) {
+            const u32x4 w = philox4x32_10((uint32_t)s, kDomSchedule, t, (uint32_t)(s >> 32), k0, k1);
+            Wd[4 * t] = w.x;
+            Wd[4 * t + 1] = w.y;
+            Wd[4 * t + 2] = w.z;
+            Wd[4 * t + 3] = w.w;
+        }
     }
     r = 1 + (int)(((Wd[0] >> 8) * 3u) >> 24);
 #pragma unroll

@@ -491,7 +491,8 @@ __global__ void __launch_bounds__(1024, MinWaves) k_sweeps_2bit(PhaseArgs a, int
     for (uint32_t i = 0; i < sweeps; ++i) {
         const uint64_t s = s0 + i;
         int r, mm[4], kk[4];
-        device_schedule(a.L, a.key0, a.key1, s, r, mm, kk);
+        // rows x W threads: the last wave may be a partial one
+        device_schedule<false>(a.L, a.key0, a.key1, s, r, mm, kk);
         PhaseArgs b = a;
         b.s_lo = (uint32_t)s;
         b.s_hi = (uint32_t)(s >> 32);
