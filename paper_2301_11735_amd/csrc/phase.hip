@@ -295,10 +295,18 @@ static_assert((kLdsSlots * 8) % 16 == 0 && kLdsTabUnits % 2 == 0, "slot table al
 static_assert(kScrTrans >= (size_t)kLdsSlots * 8, "the last device-table pair reads scratch, not past it");
 
 // Units 2i and 2i+1 of the LDS tables from the lattice's scratch.  The pair
-// holding the pad unit reads the scratch bytes after the device table.
+// holding the pad unit reads the scratch bytes after the device table.  Both
+// sources are said to be global memory: a flat load counts as an LDS access too,
+// and the wait for the arguments, and the one for the tables, then waited for
+// every load of the prologue (50 sweeps, with flat loads and now: L = 2112 1448 ->
+// 1406 us, L = 4096 1457 -> 1384, L = 8192 3264 -> 3188).
 __device__ __forceinline__ uint4 table_pair(const PhaseArgs &a, int i)
 {
-    return 2 * i < kLdsSlots ? *(const uint4 *)(a.dev_tab + 2 * i) : ((const uint4 *)kWordSlots.v)[i - kLdsSlots / 2];
+    typedef uint32_t quad __attribute__((ext_vector_type(4)));
+    const LAT_GLOBAL quad *src = 2 * i < kLdsSlots ? (const LAT_GLOBAL quad *)a.dev_tab + i
+                                                   : (const LAT_GLOBAL quad *)kWordSlots.v + (i - kLdsSlots / 2);
+    const quad v = *src;
+    return make_uint4(v.x, v.y, v.z, v.w);
 }
 
 // One phase of the 2-bit lattice by this block: row groups blockIdx.x,
