@@ -46,7 +46,7 @@ __device__ __forceinline__ void site_neighbours(int L, uint32_t magic, uint32_t 
 
 __device__ __forceinline__ uint32_t marked(const uint32_t *bitmap, uint32_t s)
 {
-    return (((const volatile uint32_t *)bitmap)[s >> 5] >> (s & 31u)) & 1u;
+    return (__hip_atomic_load(&bitmap[s >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >> (s & 31u)) & 1u;
 }
 __device__ __forceinline__ uint32_t mark(uint32_t *bitmap, uint32_t s)
 {
