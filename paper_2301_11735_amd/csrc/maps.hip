@@ -252,6 +252,76 @@ __device__ void build_map(uint32_t *bitmap, uint32_t *pairs, int L, uint32_t mag
     }
 }
 
+// The same map by the walk itself, one draw after another with uniform control
+// flow, for the smallest lattices: there most of a window's 64 draws interact or
+// are not needed.  The lanes hold the next 256 draws; a draw that was marked when
+// they were taken is rejected without touching LDS, any other is looked up in
+// the live bitmap (a broadcast read, behind the marks already issued).
+template <bool NN>
+__device__ __forceinline__ void walk_map(uint32_t *bitmap, uint32_t *pairs, int L, uint32_t magic, uint32_t N,
+                                         uint32_t n_pairs, uint32_t m_lo, uint32_t m_hi, uint32_t key0, uint32_t key1)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    uint32_t k = 0, count = 0, site_a = 0;
+    bool pend = false;              // site_a waits for its partner
+    uint32_t an[4] = {0, 0, 0, 0};  // its neighbours
+    auto all = [](uint32_t v, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); };
+    auto is_marked = [&](uint32_t s) { return __builtin_amdgcn_readfirstlane((int)marked(bitmap, s)) != 0; };
+    while (count < n_pairs) {
+        const u32x4 w = philox4x32_10(m_lo, kDomMap, (k >> 2) + lane, m_hi, key0, key1);
+        const uint32_t raw[4] = {w.x, w.y, w.z, w.w};
+        uint32_t site[4], nb[4][4];
+        uint64_t was[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            site[q] = mulhi_u32(raw[q], N);
+            site_neighbours(L, magic, site[q], nb[q]);
+            was[q] = __ballot(marked(bitmap, site[q]));
+        }
+        for (int l = 0; l < 64 && count < n_pairs; ++l) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (count >= n_pairs) continue;
+                uint32_t b, bn[4];
+                if (NN && pend) {  // the draw's direction picks b
+                    const uint32_t dir = all(raw[q], l) >> 30;
+                    b = dir == 0 ? an[0] : dir == 1 ? an[1] : dir == 2 ? an[2] : an[3];
+                    pend = false;
+                    if (is_marked(b)) continue;
+                    site_neighbours(L, magic, b, bn);
+                    if (lane == 0) mark(bitmap, site_a);
+                } else {
+                    if ((was[q] >> l) & 1u) continue;
+                    b = all(site[q], l);
+                    if (is_marked(b)) continue;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) bn[e] = all(nb[q][e], l);
+                    if (!pend) {
+                        if (!NN && lane == 0) mark(bitmap, b);
+                        site_a = b;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) an[e] = bn[e];
+                        pend = true;
+                        continue;
+                    }
+                    pend = false;
+                }
+                if (lane == 0) {
+                    pairs[count] = site_a | (b << 16);
+                    mark(bitmap, b);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        mark(bitmap, an[e]);
+                        mark(bitmap, bn[e]);
+                    }
+                }
+                ++count;
+            }
+        }
+        k += 256u;
+    }
+}
+
 // Sums of S and sigma over the neighbours of s other than `other`; adj = 1 if
 // `other` is one of them.
 __device__ __forceinline__ void side_sum(const uint8_t *codes, int L, uint32_t magic, uint32_t s, uint32_t other,
@@ -302,6 +372,13 @@ __device__ __forceinline__ void map_pair_step(uint8_t *codes, const uint32_t *th
     }
 }
 
+// Largest sides of the walk, for either partner rule.
+// us a call of 256 lattices, one map / 20 maps, walk and windows: any partner,
+// L = 4 43 / 68 and 54 / 107, L = 12 54 / 113 and 55 / 125, L = 16 62 / 133 and 55 / 122;
+// nearest neighbours, L = 16 51 / 108 and 59 / 121, L = 28 67 / 158 and 74 / 148,
+// L = 32 75 / 177 and 76 / 152.
+constexpr int kWalkMaxL[2] = {12, 28};
+
 __global__ void __launch_bounds__(kMapThreads) k_map_steps(MapArgs args)
 {
     extern __shared__ uint32_t smem[];
@@ -346,12 +423,19 @@ __global__ void __launch_bounds__(kMapThreads) k_map_steps(MapArgs args)
         __syncthreads();
         if (wave < group) {
             const uint64_t m = first + m0 + wave;
-            if (args.nn)
-                build_map<true>(bitmaps + wave * bwords, pairs + wave * n_pairs, L, magic, N, n_pairs,
-                                (uint32_t)m, (uint32_t)(m >> 32), d.key0, d.key1);
-            else
-                build_map<false>(bitmaps + wave * bwords, pairs + wave * n_pairs, L, magic, N, n_pairs,
-                                 (uint32_t)m, (uint32_t)(m >> 32), d.key0, d.key1);
+            uint32_t *bm = bitmaps + wave * bwords, *pr = pairs + wave * n_pairs;
+            const uint32_t m_lo = (uint32_t)m, m_hi = (uint32_t)(m >> 32);
+            if (args.nn) {
+                if (L <= kWalkMaxL[1])
+                    walk_map<true>(bm, pr, L, magic, N, n_pairs, m_lo, m_hi, d.key0, d.key1);
+                else
+                    build_map<true>(bm, pr, L, magic, N, n_pairs, m_lo, m_hi, d.key0, d.key1);
+            } else {
+                if (L <= kWalkMaxL[0])
+                    walk_map<false>(bm, pr, L, magic, N, n_pairs, m_lo, m_hi, d.key0, d.key1);
+                else
+                    build_map<false>(bm, pr, L, magic, N, n_pairs, m_lo, m_hi, d.key0, d.key1);
+            }
         }
         __syncthreads();
         // ...then apply them in map order
@@ -402,9 +486,7 @@ hipError_t launch_map_steps(const MapArgs &a, int max_L, hipStream_t s)
     while (most > 1 && map_lds_bytes(max_L, most) > kMapLdsMax) --most;
     const uint32_t rounds = (a.n_maps + (uint32_t)most - 1u) / (uint32_t)most;
     b.builders = (int32_t)((a.n_maps + rounds - 1u) / rounds);
-    // half the waves where neither the builders nor the pairs of a map need more
-    const uint32_t threads = b.builders <= 8 && max_L <= 100 ? kMapThreads / 2 : kMapThreads;
-    hipLaunchKernelGGL(k_map_steps, dim3((unsigned)b.count), dim3(threads), map_lds_bytes(max_L, b.builders), s,
+    hipLaunchKernelGGL(k_map_steps, dim3((unsigned)b.count), dim3(kMapThreads), map_lds_bytes(max_L, b.builders), s,
                        b);
     return hipGetLastError();
 }
