@@ -249,6 +249,17 @@ inline size_t map_lds_bytes(int L, int builders)
 }
 // Dynamic LDS a map block may use (160 KiB per workgroup, less the static reduction buffer).
 constexpr size_t kMapLdsMax = 160 * 1024 - 1024;
+// Maps that are built at once: as many as LDS allows for side L, at most one a
+// wave, shared evenly over the rounds that n_maps then take (10 maps with room
+// for 14 are one round, 20 two rounds of 10).
+inline int map_builders(int L, uint32_t n_maps)
+{
+    uint32_t most = kMapThreads / 64;
+    while (most > 1 && map_lds_bytes(L, (int)most) > kMapLdsMax) --most;
+    if (n_maps == 0) return 1;
+    const uint32_t rounds = (n_maps - 1u) / most + 1u;
+    return (int)((n_maps - 1u) / rounds + 1u);
+}
 hipError_t launch_map_steps(const MapArgs &a, int max_L, hipStream_t s);
 hipError_t init_map_kernel_attributes();
 

@@ -416,8 +416,9 @@ __global__ void __launch_bounds__(kMapThreads) k_map_steps(MapArgs args)
     int tr[3] = {0, 0, 0};
     const uint64_t first = ((uint64_t)args.first_map_hi << 32) | args.first_map_lo;
     const uint32_t wave = threadIdx.x >> 6;
-    for (uint32_t m0 = 0; m0 < args.n_maps; m0 += G) {
-        const uint32_t group = min(G, args.n_maps - m0);
+    uint32_t m0 = 0, left = args.n_maps;  // m0 + left is n_maps, so m0 never passes it
+    for (uint32_t group = 0; left > 0; m0 += group, left -= group) {
+        group = min(G, left);
         // maps depend only on the seed and their index: build `group` of them at once
         for (uint32_t i = threadIdx.x; i < group * bwords; i += blockDim.x) bitmaps[i] = 0u;
         __syncthreads();
@@ -478,14 +479,8 @@ __global__ void __launch_bounds__(kMapThreads) k_map_steps(MapArgs args)
 
 hipError_t launch_map_steps(const MapArgs &a, int max_L, hipStream_t s)
 {
-    // as many concurrent builders (at most one per wave) as LDS allows, shared
-    // evenly over the rounds that the maps then take (10 maps with room for
-    // 14 builders are one round, 20 two rounds of 10)
     MapArgs b = a;
-    int most = kMapThreads / 64;
-    while (most > 1 && map_lds_bytes(max_L, most) > kMapLdsMax) --most;
-    const uint32_t rounds = (a.n_maps + (uint32_t)most - 1u) / (uint32_t)most;
-    b.builders = (int32_t)((a.n_maps + rounds - 1u) / rounds);
+    b.builders = map_builders(max_L, a.n_maps);
     hipLaunchKernelGGL(k_map_steps, dim3((unsigned)b.count), dim3(kMapThreads), map_lds_bytes(max_L, b.builders), s,
                        b);
     return hipGetLastError();
