@@ -150,7 +150,7 @@ int lattice_batch_graph_read(lat_batch_graph *g, lat_obs *out)
         const size_t n = g->hs.size();
         size_t i = 0;
         uint32_t k = 0;
-        return read_records("lattice_batch_graph_read", g->d_out, 10, n * g->intervals, nullptr, 0, false, g->stream,
+        return read_records("lattice_batch_graph_read", g->d_out, 10, n * g->intervals, g->hs.data(), n, false, g->stream,
                             [&](size_t at, const int64_t *v) {
                                 fill_obs(g->hs[i], v, &out[at]);
                                 out[at].sweep -= (uint64_t)g->sweeps * (g->intervals - 1u - k);

@@ -52,6 +52,8 @@ namespace detail {
 
 int fail(int code, const std::string &msg);
 int hip_fail(hipError_t e, const char *what);
+// The error of every read of a lattice whose device-wide barrier timed out.
+int barrier_timed_out();
 // fail() for exception handlers: records "what: msg" without throwing (if
 // even that string cannot be allocated, a fixed message is kept instead).
 int fail_nothrow(int code, const char *what, const char *msg) noexcept;

@@ -65,6 +65,8 @@ int hip_fail(hipError_t e, const char *what)
     return fail(LAT_EHIP, std::string(what) + ": " + hipGetErrorString(e));
 }
 
+int barrier_timed_out() { return fail(LAT_EHIP, "a device-wide phase barrier timed out; the state is invalid"); }
+
 bool live(const lattice *h) { return h != nullptr && h->magic == kMagic; }
 
 namespace {
@@ -939,8 +941,7 @@ int read_records(const char *what, const void *dev, uint32_t words, size_t n, la
         if (e != hipSuccess) return hip_fail(e, what);
         if (k == 0)
             for (size_t i = 0; i < flags.size(); ++i)
-                if (((const uint32_t *)base)[i] & 1u)
-                    return fail(LAT_EHIP, "a device-wide phase barrier timed out; the state is invalid");
+                if (((const uint32_t *)base)[i] & 1u) return barrier_timed_out();
         const int64_t *v = (const int64_t *)(ring + half * piece * size);
         const size_t m = std::min(piece, n - k);
         if (k + m < n) e = copy(k + m, half ^= 1u);
@@ -1302,7 +1303,7 @@ int lattice_observables(lattice *h, lat_obs *out)
         if (waited != hipSuccess) stage.abandon();
         if (e == hipSuccess) e = waited;
         if (e != hipSuccess) return hip_fail(e, "lattice_observables");
-        if ((uint32_t)v[11] & 1u) return fail(LAT_EHIP, "a device-wide phase barrier timed out; the state is invalid");
+        if ((uint32_t)v[11] & 1u) return barrier_timed_out();
         fill_obs(h, v, out);
         return LAT_OK;
     });
@@ -1314,9 +1315,13 @@ int lattice_read_state(lattice *h, int8_t *host_codes)
         if (!live(h)) return fail(LAT_ESTATE, "null or destroyed handle");
         if (!host_codes) return fail(LAT_EINVAL, "null output");
         std::vector<uint8_t> dev(lattice_state_bytes(h->L, h->enc));
+        uint32_t err = 0;
         hipError_t e = hipMemcpyAsync(dev.data(), h->d_state, dev.size(), hipMemcpyDeviceToHost, h->stream);
+        if (e == hipSuccess && barrier_may_time_out(h))
+            e = hipMemcpyAsync(&err, h->d_scratch + kScrErr, sizeof(err), hipMemcpyDeviceToHost, h->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
         if (e != hipSuccess) return hip_fail(e, "lattice_read_state");
+        if (err & 1u) return barrier_timed_out();
         from_device_layout(h->L, h->enc, dev, host_codes);
         return LAT_OK;
     });

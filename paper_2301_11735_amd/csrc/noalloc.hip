@@ -75,7 +75,7 @@ extern "C" int lattice_observables_batch_noalloc(lattice *const *hs, int32_t cou
             uint32_t err = 0;
             const hipError_t e = hipMemcpy(&err, hs[i]->d_scratch + lat::kScrErr, sizeof(err), hipMemcpyDeviceToHost);
             if (e != hipSuccess) return hip_fail(e, "lattice_observables_batch_noalloc");
-            if (err & 1u) return fail(LAT_EHIP, "a device-wide phase barrier timed out; the state is invalid");
+            if (err & 1u) return barrier_timed_out();
         }
         return LAT_OK;
     });

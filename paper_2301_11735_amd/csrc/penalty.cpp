@@ -47,6 +47,7 @@ struct MuStage {
     uint32_t tab[kMuTabSize];
     int64_t charge[kMuChargeSlots * kMuChargeStride];
     int64_t sum_S;  // before the call's first sweep
+    uint32_t err;   // the lattice's error flags
 };
 static_assert(sizeof(MuStage) <= kPinnedBytes, "a pinned block holds a call's copies");
 static_assert(kScrObsSlots + sizeof(MuStage::charge) <= kScrSlots, "the charge sums fit the observable slots");
@@ -68,6 +69,7 @@ int lattice_mu_sweeps(lattice *h, uint64_t first_sweep, uint32_t n_sweeps, doubl
         if (!pinned.p) own = std::make_unique<MuStage>();
         MuStage &st = pinned.p ? *(MuStage *)pinned.p : *own;
         std::memset(st.tab, 0, sizeof(st.tab));
+        st.err = 0;
         MuArgs a{};
         a.state = (int8_t *)h->d_state;
         a.tab = (const uint32_t *)(h->d_scratch + kScrMuTab);
@@ -80,6 +82,8 @@ int lattice_mu_sweeps(lattice *h, uint64_t first_sweep, uint32_t n_sweeps, doubl
         hipError_t e = launch_observables(h->d_scratch, h->d_state, h->L, h->enc, h->stream);
         if (e == hipSuccess)
             e = hipMemcpyAsync(&st.sum_S, h->d_scratch + kScrObs, sizeof(st.sum_S), hipMemcpyDeviceToHost, h->stream);
+        if (e == hipSuccess && barrier_may_time_out(h))
+            e = hipMemcpyAsync(&st.err, h->d_scratch + kScrErr, sizeof(st.err), hipMemcpyDeviceToHost, h->stream);
         if (e == hipSuccess) e = launch_zero_i64(a.charge, kMuChargeSlots * kMuChargeStride, h->stream);
         for (uint32_t i = 0; i < n_sweeps; ++i) {
             const uint64_t s = first_sweep + i;
@@ -98,6 +102,7 @@ int lattice_mu_sweeps(lattice *h, uint64_t first_sweep, uint32_t n_sweeps, doubl
             if (waited != hipSuccess) pinned.abandon();
             if (e == hipSuccess) e = waited;
             if (e != hipSuccess) return hip_fail(e, "lattice_mu_sweeps");
+            if (st.err & 1u) return barrier_timed_out();
             int64_t sumS = st.sum_S;
             for (int k = 0; k < kMuChargeSlots; ++k) sumS += st.charge[k * kMuChargeStride];
             if (mu_series) mu_series[i] = *mu;
