@@ -353,15 +353,10 @@ constexpr size_t kCreateFlag = kScrObsSlots + ((size_t)kTabSize * 4 + 255) / 256
 constexpr size_t kCreateBytes = kCreateFlag + 256;
 static_assert(kCreateBytes <= kPinnedLarge, "lattice_create's staging");
 
-void from_device_layout(int32_t L, int32_t enc, const std::vector<uint8_t> &dev, int8_t *codes)
+// Codes of a state in the 2-bit class layout.
+void codes_from_words(int32_t L, const uint32_t *words, int8_t *codes)
 {
-    const size_t N = (size_t)L * L;
-    if (enc == LAT_ENC_INT8) {
-        std::memcpy(codes, dev.data(), N);
-        return;
-    }
     const size_t W = (size_t)L / 64, H = (size_t)L / 2, csz = H * W;
-    const uint32_t *words = (const uint32_t *)dev.data();
     for (size_t y = 0; y < (size_t)L; ++y)
         for (size_t x = 0; x < (size_t)L; ++x) {
             const size_t c = 4 * (y & 1) + (x & 3), X = x >> 2, Y = y >> 1;
@@ -1314,15 +1309,25 @@ int lattice_read_state(lattice *h, int8_t *host_codes)
     return guarded("lattice_read_state", [&]() -> int {
         if (!live(h)) return fail(LAT_ESTATE, "null or destroyed handle");
         if (!host_codes) return fail(LAT_EINVAL, "null output");
-        std::vector<uint8_t> dev(lattice_state_bytes(h->L, h->enc));
+        // int8 codes go to the caller's memory as they are; packed ones through
+        // pinned memory, or ordinary memory that is not cleared first
+        const size_t bytes = lattice_state_bytes(h->L, h->enc);
+        const bool packed = h->enc == LAT_ENC_2BIT, pinned = packed && bytes <= kPinnedLarge;
+        std::unique_ptr<PinnedBlock> stage;
+        if (pinned) stage = std::make_unique<PinnedBlock>(/*large=*/bytes > kPinnedBytes);
+        std::unique_ptr<uint8_t[]> own;
+        if (packed && !(stage && stage->p)) own.reset(new uint8_t[bytes]);
+        uint8_t *dev = !packed ? (uint8_t *)host_codes : own ? own.get() : (uint8_t *)stage->p;
         uint32_t err = 0;
-        hipError_t e = hipMemcpyAsync(dev.data(), h->d_state, dev.size(), hipMemcpyDeviceToHost, h->stream);
+        hipError_t e = hipMemcpyAsync(dev, h->d_state, bytes, hipMemcpyDeviceToHost, h->stream);
         if (e == hipSuccess && barrier_may_time_out(h))
             e = hipMemcpyAsync(&err, h->d_scratch + kScrErr, sizeof(err), hipMemcpyDeviceToHost, h->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+        const hipError_t waited = hipStreamSynchronize(h->stream);
+        if (waited != hipSuccess && stage) stage->abandon();
+        if (e == hipSuccess) e = waited;
         if (e != hipSuccess) return hip_fail(e, "lattice_read_state");
         if (err & 1u) return barrier_timed_out();
-        from_device_layout(h->L, h->enc, dev, host_codes);
+        if (packed) codes_from_words(h->L, (const uint32_t *)dev, host_codes);
         return LAT_OK;
     });
 }
