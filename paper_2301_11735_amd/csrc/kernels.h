@@ -304,5 +304,8 @@ hipError_t launch_advance(LatDesc *desc, uint32_t sweeps, hipStream_t s);
 // Observables of `count` lattices in one launch: out[10*b .. 10*b+9] =
 // (tracker nD, nV, nJ, then the 7 sums) of lattice b.
 hipError_t launch_observables_batch(const BatchArgs &a, unsigned long long *out, hipStream_t s);
+// *out (device-visible) = the error flags of all lattices of a, ORed.  Weak, as
+// launch_seed: without it each lattice's flags are copied.
+hipError_t launch_gather_flags(const BatchArgs &a, uint32_t *out, hipStream_t s) __attribute__((weak));
 
 }  // namespace lat

@@ -130,11 +130,32 @@ __global__ void __launch_bounds__(1024) k_obs_one(uint8_t *scr, const uint8_t *s
     if (stamp && threadIdx.x == 0) dst[10] = (long long)((const LatDesc *)(scr + kScrDesc))->next_sweep;
 }
 
+// The error flags of a batch's lattices (one thread each) in one word.
+static_assert(kMaxBatch <= 256, "a thread a lattice");
+__global__ void __launch_bounds__(256) k_gather_flags(BatchArgs a, uint32_t *out)
+{
+    __shared__ uint32_t all;
+    if (threadIdx.x == 0) all = 0u;
+    __syncthreads();
+    if ((int)threadIdx.x < a.count) {
+        const uint32_t flags = *(const uint32_t *)(a.scratch[threadIdx.x] + kScrErr);
+        if (flags) atomicOr(&all, flags);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) *out = all;
+}
+
 }  // namespace
 
 hipError_t launch_zero_i64(unsigned long long *p, int n, hipStream_t s)
 {
     hipLaunchKernelGGL(k_zero_i64, dim3((n + 63) / 64), dim3(64), 0, s, p, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_gather_flags(const BatchArgs &a, uint32_t *out, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_gather_flags, dim3(1), dim3(256), 0, s, a, out);
     return hipGetLastError();
 }
 

@@ -38,3 +38,19 @@ def test_every_read_reports_a_time_out(L, enc, monkeypatch):
     _fails(g.read_series, buf, 2)
     _fails(g.read_state)
     g.destroy()
+
+
+def test_one_time_out_among_many_lattices(monkeypatch):
+    """The flags of several lattices are gathered, 256 a launch."""
+    print("case barrier reads, 300 lattices", flush=True)
+    gs = [lat.Lattice(320, 0.1, 0.25, 0.5, 1.0, 0.9, i, encoding=1) for i in range(300)]
+    obs = lat.BatchObservables(300)
+    lat.sweep_batch(gs, 2)
+    assert len(obs(gs)) == 300
+    monkeypatch.setenv("LATTICE_BARRIER_TICKS", "0")
+    gs[299].sweep(20)
+    monkeypatch.delenv("LATTICE_BARRIER_TICKS")
+    _fails(obs, gs)
+    assert len(obs(gs[:299])) == 299
+    _fails(obs, gs[297:])
+    _fails(obs, gs[298:])
