@@ -182,7 +182,8 @@ hipError_t launch_advance_words(const WordsArgs &a, hipStream_t s);
 // after every phase.  With records (one lattice, intervals x every sweeps,
 // kSeriesRecord bytes each, as launch_observables writes them) the observables
 // and tracker after every interval.  The barrier words (in each lattice's
-// scratch) are cleared and the records initialised by kernels enqueued first.
+// scratch) are cleared by a kernel enqueued first, which also copies record 0, the
+// lattice's observables before the launch (launch_observables), to the others.
 // Q = 0: int8 lattices as they are, at multiples of four bytes; no records.
 struct WordsSeriesArgs {
     int count;

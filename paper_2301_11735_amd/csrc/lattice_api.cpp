@@ -646,7 +646,8 @@ int enqueue_words_persistent(lattice *const *hs, int32_t count, const uint32_t *
     // 9.6 / 12.0 against 21.7 / 34.4, L = 1024 12.3 / 14.7 against 22.0 /
     // 34.8, L = 2048 14.2 / 18.3 against 23.6 / 36.5.
     // A call of one sweep is the other way round (from an idle stream to its end
-    // 50 us against 31 at L = 256, 55 against 36 at L = 1000).  Of int8 lattices
+    // 50 us against 31 at L = 256, 55 against 36 at L = 1000; one sweep and its record
+    // at L = 1088 64 against 50).  Of int8 lattices
     // as they are: as long as a block a compute unit holds a call a thread (us a
     // sweep, persistent / launches: L = 388 12.5 / 18.0, L = 1000 16.3 / 19.9, 8 of
     // L = 500 24.5 / 25.5; but L = 2000 33.8 / 35.4, L = 4000 99 / 75).
@@ -658,7 +659,7 @@ int enqueue_words_persistent(lattice *const *hs, int32_t count, const uint32_t *
     if (v) {
         if (std::atoi(v) == 0) return LAT_OK;
     } else {
-        if (!records && longest < 2) return LAT_OK;
+        if (longest < 2 && intervals == 1) return LAT_OK;
         if (bytes ? !bytes_fit(hs, count) : max_L > kWordsPersistentMaxL) return LAT_OK;
         if (stream && (bytes || max_L > kWordsSharedMaxL)) return LAT_OK;
     }
@@ -703,7 +704,10 @@ int enqueue_words_persistent(lattice *const *hs, int32_t count, const uint32_t *
                 a.sweeps[0] = a.intervals * every;
                 a.first_block[0] = 0;
                 a.first_block[1] = nb[0];
-                const hipError_t e = launch_words_series(a, Q, stream);
+                // the state before the launch into its first record, by the reduction
+                // over many blocks (one block took 60 us at L = 1024 and 200 at L = 2048)
+                hipError_t e = launch_observables(h->d_scratch, swept_state(h), h->L, LAT_ENC_2BIT, stream, a.records);
+                if (e == hipSuccess) e = launch_words_series(a, Q, stream);
                 if (e != hipSuccess) return hip_fail(e, "persistent word kernel launch");
                 h->done += (uint64_t)a.sweeps[0];
             }

@@ -126,7 +126,7 @@ __device__ __forceinline__ void add_to_record(unsigned long long *rec, int i, lo
 // fence pair per block and 12-14 us with a fence pair in every wave).
 //
 // Obs (a series with records, one lattice): the records start as the
-// lattice's state before the launch (k_series_init: tracker total and the
+// lattice's state before the launch (k_series_begin: tracker total and the
 // seven sums), and at the end of interval k the moves of all blocks since the
 // launch began are added to record k: the tracker sums (to the tracker and to
 // the charged-site count and the two bond sums, which change by exactly them)
@@ -255,47 +255,21 @@ __global__ void __launch_bounds__(Q >= 4 ? kWordsSeriesMaxThreads : kWordsThread
         ((LatDesc *)(scr + kScrDesc))->next_sweep = d.next_sweep + my_sweeps;
 }
 
-// Every lattice's barrier words, which live in its scratch, in the observable
-// slots (they hold nothing between calls).
+// Before a persistent launch: clears every lattice's barrier words, which live in
+// its scratch, in the observable slots (they hold nothing between calls), and
+// copies a series' first record, the state before it, to the others.
 static_assert(kScrObsSlots % 128 == 0 && kBarrierWords * 4u <= (size_t)kMaxObsSlots * 56u, "barrier words");
-__global__ void __launch_bounds__(256) k_clear_barriers(WordsSeriesArgs a)
+constexpr uint32_t kBeginThreads = 256;
+__global__ void __launch_bounds__(kBeginThreads) k_series_begin(WordsSeriesArgs a)
 {
-    unsigned *w = (unsigned *)(a.scratch[blockIdx.x] + kScrObsSlots);
-    for (unsigned i = threadIdx.x; i < kBarrierWords; i += blockDim.x) w[i] = 0u;
-}
-
-// Records of a series before it runs: the tracker total so far (slots and
-// base) and the seven observable sums of the lattice's current state (its
-// 2-bit copy for an int8 lattice), in every record.  One block.
-__global__ void __launch_bounds__(1024) k_series_init(const uint8_t *scr, long long *records, uint32_t intervals)
-{
-    const LatDesc d = *(const LatDesc *)(scr + kScrDesc);
-    const uint32_t *st = (uint32_t *)(d.enc == 1 ? d.state : (void *)(scr + kScrWork));
-    long long t3[3] = {0, 0, 0};
-    const long long *slots = (const long long *)(scr + kScrSlots);
-    for (int i = threadIdx.x; i < kMaxSlots; i += blockDim.x) {
-        t3[0] += slots[3 * i];
-        t3[1] += slots[3 * i + 1];
-        t3[2] += slots[3 * i + 2];
+    if ((int)blockIdx.x < a.count) {
+        unsigned *w = (unsigned *)(a.scratch[blockIdx.x] + kScrObsSlots);
+        for (unsigned i = threadIdx.x; i < kBarrierWords; i += kBeginThreads) w[i] = 0u;
     }
-    if (threadIdx.x == 0) {
-        const long long *base = (const long long *)(scr + kScrTrackBase);
-        t3[0] += base[0];
-        t3[1] += base[1];
-        t3[2] += base[2];
-    }
-    long long v[7] = {0, 0, 0, 0, 0, 0, 0};
-    const uint32_t n = 8u * (uint32_t)(d.L >> 1) * (uint32_t)(d.L >> 6);
-    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) obs_word_2bit(st, d.L, i, v);
-    __shared__ long long tot[10];
-    block_reduce_store<3>(t3, tot);
-    block_reduce_store<7>(v, tot + 3);
-    __syncthreads();
-    for (uint32_t k = threadIdx.x; k < intervals; k += blockDim.x) {
-        long long *rec = records + (kSeriesRecord / 8) * (size_t)k;
-        for (int q = 0; q < 10; ++q) rec[q] = tot[q];
-        rec[10] = 0;
-    }
+    constexpr uint32_t kFields = kSeriesRecord / 8;
+    const uint64_t n = a.records ? (uint64_t)kFields * a.intervals : 0u;
+    for (uint64_t i = kFields + blockIdx.x * kBeginThreads + threadIdx.x; i < n; i += gridDim.x * kBeginThreads)
+        a.records[i] = a.records[i % kFields];
 }
 
 __global__ void k_advance_words(WordsArgs a)
@@ -424,15 +398,11 @@ int words_persistent_capacity(int Q, int threads)
 
 hipError_t launch_words_series(const WordsSeriesArgs &a, int Q, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_clear_barriers, dim3((unsigned)a.count), dim3(256), 0, s, a);
-    hipError_t e = hipGetLastError();
+    const uint32_t fields = a.records ? a.intervals * (uint32_t)(kSeriesRecord / 8) : 0u;
+    const uint32_t blocks = std::max((uint32_t)a.count, std::min(256u, (fields + kBeginThreads - 1) / kBeginThreads));
+    hipLaunchKernelGGL(k_series_begin, dim3(blocks), dim3(kBeginThreads), 0, s, a);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (a.records) {
-        hipLaunchKernelGGL(k_series_init, dim3(1), dim3(1024), 0, s, (const uint8_t *)a.scratch[0], a.records,
-                           a.intervals);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
     WordsSeriesArgs args = a;
     void *kargs[] = {&args};
     return hipLaunchCooperativeKernel(series_fn_of(Q, a.records != nullptr), dim3(a.first_block[a.count]),
