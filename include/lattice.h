@@ -117,18 +117,19 @@ int lattice_create(const lat_params *p, void *d_state, size_t state_bytes, void 
 /* Advance by `sweeps` sweeps (section 3.1 update, section 3.2 parallel form):
  * each sweep is four phases of N/8 non-interacting coupled pairs, so every
  * site is updated once per sweep.  Asynchronous on the handle's stream.
- * Lattices with L % 64 == 0 and 256 < L <= 2048 advance in one cooperative
- * launch per call, whose blocks must all be resident at once, with a
- * device-wide barrier after every phase: kernels of other streams running
- * at the same time can delay it, and a barrier that waits longer than about
- * 0.2 s, or 10 s at the start of the launch, where its last blocks may wait for
- * such kernels (LATTICE_BARRIER_TICKS: another bound than 0.2 s, in 10 ns
- * ticks of the device clock) marks the state invalid, which the next read
- * (lattice_observables, lattice_observables_batch, lattice_series_read)
- * reports as LAT_EHIP.  LATTICE_WORDS_PERSISTENT=0 in the environment at the
- * call selects one launch per phase instead; calls captured into a HIP graph
- * take that form by themselves, since a graph's kernel nodes do not guarantee
- * that all blocks are resident at once.
+ * Calls of two or more sweeps of lattices that one compute unit's memory does not
+ * hold (L % 64 == 0 up to 2048, and int8 ones of other sides up to about 1000, at
+ * an address that is a multiple of 4), or that are faster without it (from about
+ * L = 200 on), advance in one launch whose blocks meet at a device-wide barrier
+ * after every phase.  The blocks start once all of them are on the device.  While
+ * kernels of other streams keep some of them away, the others wait, for at most 10 s
+ * (LATTICE_ASSEMBLE_TICKS: another bound, in 10 ns ticks of the device clock);
+ * then one block a lattice does the call's sweeps, slowly, with the same result.  A
+ * later barrier that waits longer than 0.2 s (LATTICE_BARRIER_TICKS), which takes
+ * a device that stops running blocks it has started, marks the state invalid, and
+ * every later call that returns data of the lattice reports that as LAT_EHIP.
+ * LATTICE_WORDS_PERSISTENT=0 in the environment at the call selects one launch per
+ * phase instead; calls captured into a HIP graph take that form by themselves.
  * Errors: LAT_ESTATE, LAT_EHIP. */
 int lattice_sweep(lattice *h, uint32_t sweeps);
 
@@ -168,7 +169,7 @@ int lattice_read_state(lattice *h, int8_t *host_codes);
  * them, each resident in on-chip memory for all the sweeps, or spread over the
  * device where that is faster; those with L % 64 == 0 up to 2048 and int8 ones
  * of other sides advance together on the multi-block kernels (one
- * cooperative launch per 64 of them, as lattice_sweep, or one per phase);
+ * launch per 64 of them, as lattice_sweep, or one per phase);
  * larger ones one after another.  The caller orders hip_stream
  * after any pending work of the lattices' own streams.  A lattice may appear
  * only once.  Errors: LAT_EINVAL, LAT_ESTATE, LAT_EHIP. */

@@ -176,28 +176,35 @@ constexpr int kBytesSeriesMaxThreads = 1024;
 const void *bytes_series_kernel();
 // desc->next_sweep += sweeps[i] for every lattice of the series.
 hipError_t launch_advance_words(const WordsArgs &a, hipStream_t s);
+// Bound of the first meeting of a persistent launch's blocks: 10 s.
+constexpr long long kAssembleTicks = 50 * kBarrierTimeoutTicks;
 // Persistent multi-block form: up to kWordsBatch lattices (blocks
 // first_block[i] .. first_block[i+1]-1 update lattice i) for sweeps[i] sweeps
-// each in one cooperative launch, a device-wide barrier of a lattice's blocks
+// each in one launch, a device-wide barrier of a lattice's blocks
 // after every phase.  With records (one lattice, intervals x every sweeps,
 // kSeriesRecord bytes each, as launch_observables writes them) the observables
 // and tracker after every interval.  The barrier words (in each lattice's
 // scratch) are cleared by a kernel enqueued first, which also copies record 0, the
-// lattice's observables before the launch (launch_observables), to the others.
+// lattice's observables before the launch (launch_observables), to the others.  The
+// blocks go to work once all of a lattice's are there; should they not come
+// together in assemble_ticks, the same kernel enqueued behind, a block a lattice,
+// does that lattice's sweeps.
 // Q = 0: int8 lattices as they are, at multiples of four bytes; no records.
 struct WordsSeriesArgs {
     int count;
     int threads;              // block size: a multiple of 64 up to kWordsThreads (Q >= 4: kWordsSeriesMaxThreads)
+    int alone;                // 1: a block a lattice, for those whose launch was called off (set by the launch)
     long long barrier_ticks;  // bound of each device-wide barrier wait (device wall-clock ticks)
+    long long assemble_ticks; // of the first meeting
     uint32_t intervals, every;
     long long *records;  // null: no observables
     uint8_t *scratch[kWordsBatch];
     uint32_t sweeps[kWordsBatch];
     uint32_t first_block[kWordsBatch + 1];
 };
-// Blocks of the persistent launch that can be resident at once (0 when
-// co-residency cannot be guaranteed: no cooperative launch); the caller then
-// uses the per-phase launches.
+// Blocks of the persistent launch that can be resident at once on an otherwise idle
+// device (0 when that cannot be found out); the caller then uses the per-phase
+// launches.
 int words_persistent_capacity(int Q, int threads);
 hipError_t launch_words_series(const WordsSeriesArgs &a, int Q, hipStream_t s);
 // int8 codes (row-major) <-> the 2-bit class layout, for L % 64 == 0.

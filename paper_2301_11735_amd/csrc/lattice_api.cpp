@@ -536,18 +536,23 @@ int words_capacity(int Q, int threads)
     return it->second;
 }
 
-// Bound of each device-wide barrier wait of the persistent word kernel:
-// kBarrierTimeoutTicks unless LATTICE_BARRIER_TICKS asks for another
-// (non-negative) count; tests use a tiny one to force the time-out path,
-// whose kernels still end normally (a wait that times out flags the state
-// invalid and goes on).
-long long words_barrier_ticks()
+// Bounds of the waits of the persistent kernels, in ticks: of each device-wide
+// barrier, kBarrierTimeoutTicks, and of the blocks' first meeting, kAssembleTicks,
+// unless the environment asks for another (non-negative) count.  Tests use 0 to
+// force the way out of a wait that takes too long: a barrier flags the state
+// invalid and goes on, the first meeting calls the launch off.
+long long ticks_from_env(const char *name, long long ticks)
 {
-    if (const char *v = std::getenv("LATTICE_BARRIER_TICKS")) {
+    if (const char *v = std::getenv(name)) {
         const long long want = std::atoll(v);
         if (want >= 0) return want;
     }
-    return kBarrierTimeoutTicks;
+    return ticks;
+}
+void set_bounds(WordsSeriesArgs &a)
+{
+    a.barrier_ticks = ticks_from_env("LATTICE_BARRIER_TICKS", kBarrierTimeoutTicks);
+    a.assemble_ticks = ticks_from_env("LATTICE_ASSEMBLE_TICKS", kAssembleTicks);
 }
 
 // Lanes per a-word and block size of the persistent word kernel for the n
@@ -696,7 +701,7 @@ int enqueue_words_persistent(lattice *const *hs, int32_t count, const uint32_t *
                 WordsSeriesArgs a{};
                 a.count = 1;
                 a.threads = threads;
-                a.barrier_ticks = words_barrier_ticks();
+                set_bounds(a);
                 a.intervals = std::min(intervals_cap, intervals - k);
                 a.every = every;
                 a.records = records + (kSeriesRecord / 8) * (size_t)k;
@@ -720,7 +725,7 @@ int enqueue_words_persistent(lattice *const *hs, int32_t count, const uint32_t *
         for (uint32_t c = 0; c < most; c += sweeps_cap) {
             WordsSeriesArgs a{};
             a.threads = threads;
-            a.barrier_ticks = words_barrier_ticks();
+            set_bounds(a);
             a.intervals = 1;
             a.every = 0;
             uint32_t blocks = 0;

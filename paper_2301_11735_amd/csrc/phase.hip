@@ -189,7 +189,7 @@ __global__ void __launch_bounds__(kWordsPhaseMaxThreads) k_phase_bytes(WordsArgs
 }
 
 // Persistent form, as k_words_series without records: all sweeps of a call in one
-// launch of co-resident blocks, a barrier of a lattice's blocks after every
+// launch of blocks that are all resident at once, a barrier of a lattice's blocks after every
 // phase.  Against one launch per phase (us a sweep): L = 388 18.0 -> 12.2, L = 500
 // 20.7 -> 14.2, L = 1000 22.2 -> 14.6; for larger lattices, whose threads take
 // several calls a phase, the loads past the caches cost more than the launches.
@@ -197,19 +197,26 @@ __global__ void __launch_bounds__(kBytesSeriesMaxThreads) k_bytes_series(WordsSe
 {
     __shared__ uint2 s_tab[kDevTabEntries];
     __shared__ __align__(16) uint2 s_slots[kSlotEntries];
-    int li = 0;  // this block's lattice (uniform)
-    while (li + 1 < a.count && blockIdx.x >= a.first_block[li + 1]) ++li;
+    int li = a.alone ? (int)blockIdx.x : 0;  // this block's lattice (uniform)
+    while (!a.alone && li + 1 < a.count && blockIdx.x >= a.first_block[li + 1]) ++li;
     uint8_t *scr = a.scratch[li];
+    // ahead of the meeting: its atomics would make the descriptor's loads vector loads
     const LatDesc d = *(const LatDesc *)(scr + kScrDesc);
     LAT_GLOBAL uint8_t *st = (LAT_GLOBAL uint8_t *)d.state;
+    const uint32_t b = a.alone ? 0u : blockIdx.x - a.first_block[li];
+    const uint32_t nb = a.alone ? 1u : a.first_block[li + 1] - a.first_block[li];
+    GridBarrier barrier{(unsigned *)(scr + kScrObsSlots), b, nb, 0u, false};
+    unsigned *err = (unsigned *)(scr + kScrErr);
+    if (a.alone) {
+        if (!barrier.alone()) return;
+    } else {
+        barrier.first_arrive(a.assemble_ticks);
+    }
     TableLoads tables;
     tables.load((const uint2 *)(scr + kScrDevTab), blockDim.x);
     tables.store(s_tab, s_slots, blockDim.x);
     __syncthreads();
     const uint8_t *slots = (const uint8_t *)s_slots;
-    const uint32_t b = blockIdx.x - a.first_block[li], nb = a.first_block[li + 1] - a.first_block[li];
-    GridBarrier barrier{(unsigned *)(scr + kScrObsSlots), b, nb, 0u, false};
-    unsigned *err = (unsigned *)(scr + kScrErr);
     const uint32_t sweeps = a.sweeps[li], calls = (uint32_t)d.L * (uint32_t)d.L / 16u;
     const uint32_t first = b * blockDim.x + threadIdx.x, stride = nb * blockDim.x;
     // At most one call a thread (uniform per lattice): its draws and places are
@@ -225,6 +232,7 @@ __global__ void __launch_bounds__(kBytesSeriesMaxThreads) k_bytes_series(WordsSe
         w = pair_draws(philox4x32_10((uint32_t)s, f.p, call, (uint32_t)(s >> 32), d.key0, d.key1));
     };
     if (mine) prepare(d.next_sweep, first);
+    if (!a.alone && !barrier.assemble(a.assemble_ticks)) return;
     int tr[3] = {0, 0, 0};
     for (uint32_t it = 0; it < sweeps; ++it) {
         const uint64_t s = d.next_sweep + it;
@@ -254,8 +262,8 @@ __global__ void __launch_bounds__(kBytesSeriesMaxThreads) k_bytes_series(WordsSe
         }
     }
     wave_reduce_add3(tr, (unsigned long long *)(scr + kScrSlots) + 3 * (size_t)(b % kMaxSlots));
-    // every block read the descriptor before its first barrier
-    if (b == 0 && threadIdx.x == 0 && barrier.rounds > 0)
+    // every block read the descriptor before its first phase's barrier
+    if (b == 0 && threadIdx.x == 0 && sweeps > 0)
         ((LatDesc *)(scr + kScrDesc))->next_sweep = d.next_sweep + sweeps;
 }
 

@@ -81,10 +81,19 @@ __device__ __forceinline__ uint32_t ld16(const uint32_t *st, uint32_t row, int W
 // thread waits for the others, and the block meets again.  No cache
 // write-back or invalidation is needed.  Between the halves a block may do
 // work that touches no lattice word.  The wait is bounded as in grid_barrier
-// (time-out flag, then go on), by `limit` ticks of the device wall clock, at the
-// first barrier kFirstWaits times as long: until then other streams' kernels
-// may hold the compute units that the last blocks need, afterwards every
-// block is resident.  A block that has given up waits no more.  Up to kFlatBarrierBlocks blocks meet on one counter.  More meet in two
+// (time-out flag, then go on), by `limit` ticks of the device wall clock; a block
+// that has given up waits no more.
+//
+// The first meeting of a launch (arrive, then assemble in the place of wait)
+// comes before any block touches the lattice.  Nothing guarantees that all blocks
+// get a place while kernels of other streams hold compute units: blocks that have
+// waited for the others longer than their limit call the launch off, all of its
+// blocks end without having changed anything, and a second launch, a block a
+// lattice, then does the work (alone()).  Either all blocks of a lattice go on or
+// none does: the common counter holds kCalledOff or reaches its full count, never
+// both.
+//
+// Up to kFlatBarrierBlocks blocks meet on one counter.  More meet in two
 // levels: block b arrives on the counter of group b % 8 (blocks go to the
 // eight XCDs in turn, so a group shares an L2), the last of a group on the
 // common counter, and the last of all releases every group by its own flag.
@@ -92,13 +101,21 @@ __device__ __forceinline__ uint32_t ld16(const uint32_t *st, uint32_t row, int W
 // barrier with 32 / 64 / 128 / 256 blocks: one counter 1.1 / 1.4 / 2.1 / 3.8
 // us, two levels 1.6 / 1.65 / 1.75 / 1.95 us.
 constexpr unsigned kFlatBarrierBlocks = 64, kBarrierGroups = 8, kBarrierLine = 32;  // words apart: 128 bytes
-constexpr long long kFirstWaits = 50;
 constexpr unsigned kBarrierWords = (1 + 3 * kBarrierGroups) * kBarrierLine;
+constexpr unsigned kCalledOff = 0x80000000u;  // counts stay below it
 struct GridBarrier {
     unsigned *words;  // the common counter, the group counters, the group flags, the group sums, a line each
     unsigned block, blocks;  // this block's number among those that meet
     unsigned rounds;         // barriers arrived at so far
     bool gave_up;
+    __device__ __forceinline__ static unsigned load(const unsigned *p)
+    {
+        return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ __forceinline__ static void store(unsigned *p, unsigned v)
+    {
+        __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     __device__ __forceinline__ unsigned *group() const { return words + kBarrierLine * (1u + block % kBarrierGroups); }
     __device__ __forceinline__ unsigned *flag(unsigned g) const { return words + kBarrierLine * (1u + kBarrierGroups + g); }
     // six running sums of the group's blocks (series records)
@@ -126,8 +143,7 @@ struct GridBarrier {
                 last = __hip_atomic_fetch_add(group(), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == mates * rounds;
                 if (last && __hip_atomic_fetch_add(words, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u ==
                                 kBarrierGroups * rounds)
-                    for (unsigned k = 0; k < kBarrierGroups; ++k)
-                        __hip_atomic_store(flag(k), rounds, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    for (unsigned k = 0; k < kBarrierGroups; ++k) store(flag(k), rounds);
             }
         }
         return last;
@@ -137,11 +153,11 @@ struct GridBarrier {
         if (threadIdx.x == 0 && !gave_up) {
             const unsigned *at = flat() ? words : flag(block % kBarrierGroups);
             const unsigned target = flat() ? blocks * rounds : rounds;
-            const long long t0 = wall_clock64(), most = rounds == 1u ? kFirstWaits * limit : limit;
+            const long long t0 = wall_clock64();
             // (no time at all is up at once, also where everyone has arrived)
-            while (most <= 0 || __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
+            while (limit <= 0 || load(at) < target) {
                 __builtin_amdgcn_s_sleep(1);
-                if (wall_clock64() - t0 > most || most <= 0) {
+                if (wall_clock64() - t0 > limit || limit <= 0) {
                     atomicOr(err, 1u);
                     gave_up = true;
                     break;
@@ -149,6 +165,59 @@ struct GridBarrier {
             }
         }
         __syncthreads();
+    }
+
+    // One thread: calls the launch off unless all have arrived at its first
+    // meeting.  True if it is called off.
+    __device__ bool call_off()
+    {
+        const unsigned all = flat() ? blocks : kBarrierGroups;
+        unsigned n = load(words);
+        while (n < all) {
+            if (__hip_atomic_compare_exchange_strong(words, &n, n | kCalledOff, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT)) {
+                for (unsigned k = 0; k < kBarrierGroups && !flat(); ++k) store(flag(k), kCalledOff);
+                return true;
+            }
+        }
+        return (n & kCalledOff) != 0;
+    }
+    // The first meeting's arrival (limit: assemble's).
+    __device__ __forceinline__ void first_arrive(long long limit)
+    {
+        // (no time at all: before block 0 has arrived, so that it is certain)
+        if (limit <= 0 && block == 0 && threadIdx.x == 0) call_off();
+        arrive();
+    }
+    // False, for the whole block, if the launch is called off.
+    __device__ __forceinline__ bool assemble(long long limit)
+    {
+        __shared__ unsigned s_off;
+        if (threadIdx.x == 0) {
+            const unsigned *at = flat() ? words : flag(block % kBarrierGroups);
+            const unsigned target = flat() ? blocks : 1u;
+            const long long t0 = wall_clock64();
+            unsigned n;
+            while ((n = load(at)) < target) {  // kCalledOff is above any target
+                __builtin_amdgcn_s_sleep(1);
+                if (wall_clock64() - t0 > limit) {
+                    n = call_off() ? kCalledOff : 0u;
+                    break;
+                }
+            }
+            s_off = n & kCalledOff;
+        }
+        __syncthreads();
+        return s_off == 0u;
+    }
+    // A launch of one block a lattice behind the one that may have been called
+    // off: true if it was, and the counter is then clear for this block.
+    __device__ __forceinline__ bool alone()
+    {
+        const bool off = (load(words) & kCalledOff) != 0;
+        __syncthreads();
+        if (threadIdx.x == 0 && off) store(words, 0u);
+        return off;
     }
 };
 

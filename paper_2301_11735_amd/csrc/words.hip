@@ -114,7 +114,7 @@ __device__ __forceinline__ void add_to_record(unsigned long long *rec, int i, lo
 
 // Persistent form: the sweeps of a whole call of up to kWordsBatch lattices,
 // or a whole observation series of one lattice, in one launch of
-// co-resident blocks (cooperative launch); blocks first_block[i] ..
+// blocks that are all resident at once (GridBarrier: assemble); blocks first_block[i] ..
 // first_block[i+1]-1 update lattice i.  Tables are staged once; every phase
 // is one grid-stride pass over each lattice's a-word tasks by its own blocks,
 // followed by a device-wide barrier of those blocks (the lattices do not
@@ -141,11 +141,21 @@ __global__ void __launch_bounds__(Q >= 4 ? kWordsSeriesMaxThreads : kWordsThread
 {
     __shared__ uint2 s_tab[kDevTabEntries];
     __shared__ __align__(16) uint2 s_slots[kSlotEntries];
-    int li = 0;  // this block's lattice (uniform)
-    while (li + 1 < a.count && blockIdx.x >= a.first_block[li + 1]) ++li;
+    int li = a.alone ? (int)blockIdx.x : 0;  // this block's lattice (uniform)
+    while (!a.alone && li + 1 < a.count && blockIdx.x >= a.first_block[li + 1]) ++li;
     uint8_t *scr = a.scratch[li];
+    // ahead of the meeting: its atomics would make the descriptor's loads vector loads
     const LatDesc d = *(const LatDesc *)(scr + kScrDesc);
     uint32_t *st = (uint32_t *)(d.enc == 1 ? d.state : (void *)(scr + kScrWork));
+    const uint32_t b = a.alone ? 0u : blockIdx.x - a.first_block[li];
+    const uint32_t nb = a.alone ? 1u : a.first_block[li + 1] - a.first_block[li];
+    GridBarrier barrier{(unsigned *)(scr + kScrObsSlots), b, nb, 0u, false};
+    unsigned *err = (unsigned *)(scr + kScrErr);
+    if (a.alone) {
+        if (!barrier.alone()) return;
+    } else {
+        barrier.first_arrive(a.assemble_ticks);
+    }
     {
         const uint2 *g_tab = (const uint2 *)(scr + kScrDevTab);
         for (int i = threadIdx.x; i < kDevTabEntries; i += blockDim.x) s_tab[i] = g_tab[i];
@@ -153,9 +163,6 @@ __global__ void __launch_bounds__(Q >= 4 ? kWordsSeriesMaxThreads : kWordsThread
         for (int i = threadIdx.x; i < kSlotEntries; i += blockDim.x) s_slots[i] = g_slots[i];
     }
     __syncthreads();
-    const uint32_t b = blockIdx.x - a.first_block[li], nb = a.first_block[li + 1] - a.first_block[li];
-    GridBarrier barrier{(unsigned *)(scr + kScrObsSlots), b, nb, 0u, false};
-    unsigned *err = (unsigned *)(scr + kScrErr);
     const uint32_t my_sweeps = a.sweeps[li];
     const uint32_t csz = (uint32_t)(d.L >> 1) * (uint32_t)(d.L >> 6);
     const uint32_t n_tasks = (uint32_t)Q * csz, stride = nb * blockDim.x;
@@ -176,6 +183,7 @@ __global__ void __launch_bounds__(Q >= 4 ? kWordsSeriesMaxThreads : kWordsThread
         word_draws<Q>(c0, q, d.next_sweep, 0, d.key0, d.key1, pre);
         refs = word_refs<Q>(f, first);
     }
+    if (!a.alone && !barrier.assemble(a.assemble_ticks)) return;
     int tr[3] = {0, 0, 0};
     int dv[3] = {0, 0, 0};  // Obs: spin, staggered spin, staggered charge moves of the interval
     long long moves = 0;    // Obs, thread i < 6: the block's sum i of the intervals before
@@ -250,8 +258,8 @@ __global__ void __launch_bounds__(Q >= 4 ? kWordsSeriesMaxThreads : kWordsThread
     }
     if (Obs && threadIdx.x < 3) atomicAdd((unsigned long long *)(scr + kScrSlots) + 3 * (size_t)b + threadIdx.x, (unsigned long long)moves);
     block_reduce_add<3>(tr, (unsigned long long *)(scr + kScrSlots) + 3 * (size_t)b);
-    // every block read the descriptor before its first barrier
-    if (b == 0 && threadIdx.x == 0 && barrier.rounds > 0)
+    // every block read the descriptor before its first phase's barrier
+    if (b == 0 && threadIdx.x == 0 && my_sweeps > 0)
         ((LatDesc *)(scr + kScrDesc))->next_sweep = d.next_sweep + my_sweeps;
 }
 
@@ -381,9 +389,8 @@ const void *series_fn_of(int Q, bool obs)
 
 int words_persistent_capacity(int Q, int threads)
 {
-    int dev = 0, coop = 0, per_cu = 0, cus = 0;
+    int dev = 0, per_cu = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
-    if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) return 0;
     // the smaller of the two forms' (with and without records) resident blocks
     for (const bool obs : {false, true}) {
@@ -403,10 +410,17 @@ hipError_t launch_words_series(const WordsSeriesArgs &a, int Q, hipStream_t s)
     hipLaunchKernelGGL(k_series_begin, dim3(blocks), dim3(kBeginThreads), 0, s, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    // An ordinary launch: the blocks find out themselves whether they are all
+    // there.  A cooperative one promises no more than the capacity that the
+    // caller has checked, and costs a switch of queues.
     WordsSeriesArgs args = a;
     void *kargs[] = {&args};
-    return hipLaunchCooperativeKernel(series_fn_of(Q, a.records != nullptr), dim3(a.first_block[a.count]),
-                                      dim3((unsigned)a.threads), kargs, 0, s);
+    const void *fn = series_fn_of(Q, a.records != nullptr);
+    args.alone = 0;
+    const hipError_t ran = hipLaunchKernel(fn, dim3(a.first_block[a.count]), dim3((unsigned)a.threads), kargs, 0, s);
+    if (ran != hipSuccess) return ran;
+    args.alone = 1;
+    return hipLaunchKernel(fn, dim3((unsigned)a.count), dim3((unsigned)a.threads), kargs, 0, s);
 }
 
 hipError_t launch_advance_words(const WordsArgs &a, hipStream_t s)
