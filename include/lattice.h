@@ -128,8 +128,10 @@ int lattice_create(const lat_params *p, void *d_state, size_t state_bytes, void 
  * later barrier that waits longer than 0.2 s (LATTICE_BARRIER_TICKS), which takes
  * a device that stops running blocks it has started, marks the state invalid, and
  * every later call that returns data of the lattice reports that as LAT_EHIP.
- * LATTICE_WORDS_PERSISTENT=0 in the environment at the call selects one launch per
- * phase instead; calls captured into a HIP graph take that form by themselves.
+ * That form is taken on the default stream only: on a stream of the caller's own, and
+ * in calls captured into a HIP graph, the lattices take one launch per phase, or
+ * the on-chip form, as they do with LATTICE_WORDS_PERSISTENT=0 in the environment at
+ * the call.
  * Errors: LAT_ESTATE, LAT_EHIP. */
 int lattice_sweep(lattice *h, uint32_t sweeps);
 

@@ -119,7 +119,7 @@ int enqueue_observables_batch(lattice *const *hs, int32_t count, unsigned long l
 // (null: `uniform`); int8 ones are packed before and unpacked after.
 // convert = false: packed lattices are already on (and stay on) their copy.
 // persistent = false: the multi-block lattices take one launch per phase,
-// never the cooperative persistent launch, whose blocks must all be resident
+// never the persistent launch, whose blocks must all be resident
 // at once (callers whose other streams run kernels at the same time, like
 // the server, would otherwise leave it waiting for compute units).
 int enqueue_offchip_sweeps(lattice *const *hs, int32_t count, const uint32_t *sweeps, uint32_t uniform,
@@ -129,8 +129,8 @@ int enqueue_offchip_sweeps(lattice *const *hs, int32_t count, const uint32_t *sw
 // sweeps[i] (null: `every`) with intervals = 1 and no records, or, with
 // records, an observation series of one lattice: intervals x every sweeps, a
 // kSeriesRecord record after each interval.  *ran = false (nothing
-// enqueued) when the persistent form is off (LATTICE_WORDS_PERSISTENT=0, or
-// the stream is being captured) or cannot be launched here; the
+// enqueued) when the persistent form is off (LATTICE_WORDS_PERSISTENT=0, a
+// stream other than the default one) or cannot be launched here; the
 // caller then uses the per-phase launches.  Packed int8 lattices must
 // already be on their 2-bit copy.
 int enqueue_words_persistent(lattice *const *hs, int32_t count, const uint32_t *sweeps, uint32_t intervals,

@@ -420,7 +420,7 @@ int enqueue_phase_sweeps(lattice *h, uint32_t sweeps, hipStream_t stream)
     a.key0 = (uint32_t)h->seed;
     a.key1 = (uint32_t)(h->seed >> 32);
     uint32_t left = sweeps;
-    if (h->tuning.persistent) {
+    if (h->tuning.persistent && !stream) {  // as enqueue_words_persistent: on the default stream only
         // one cooperative launch per chunk; the barrier counter stays far below 2^32
         constexpr uint32_t kChunk = 65536;
         while (left > 0) {
@@ -517,7 +517,7 @@ int enqueue_words_sweeps(lattice *const *hs, int32_t count, const uint32_t *swee
 
 }  // namespace
 
-constexpr int kWordsPersistentMaxL = 2048, kWordsSharedMaxL = 1024;
+constexpr int kWordsPersistentMaxL = 2048;
 
 namespace {
 
@@ -638,7 +638,7 @@ int enqueue_words_persistent(lattice *const *hs, int32_t count, const uint32_t *
                              uint32_t every, long long *records, hipStream_t stream, bool bytes, bool *ran)
 {
     *ran = false;
-    if (count <= 0 || intervals == 0 || every == 0) return LAT_OK;
+    if (count <= 0 || intervals == 0 || every == 0 || stream) return LAT_OK;
     int max_L = 0;
     uint32_t longest = 0;
     for (int32_t i = 0; i < count; ++i) {
@@ -656,17 +656,18 @@ int enqueue_words_persistent(lattice *const *hs, int32_t count, const uint32_t *
     // as they are: as long as a block a compute unit holds a call a thread (us a
     // sweep, persistent / launches: L = 388 12.5 / 18.0, L = 1000 16.3 / 19.9, 8 of
     // L = 500 24.5 / 25.5; but L = 2000 33.8 / 35.4, L = 4000 99 / 75).
-    // On a stream of their own, where other lattices may run beside them, only
-    // the word kernel up to kWordsSharedMaxL is persistent: a cooperative
-    // launch takes the device's one cooperative queue.
-    // LATTICE_WORDS_PERSISTENT=0|1 overrides.
+    // Never on a stream of the caller's own, whatever is asked for: launches of
+    // several streams would take places that the blocks of the others wait for, and a
+    // program that ran them (as cooperative launches) from six threads with a
+    // stream each ended in a segmentation fault at its exit whose cause is not
+    // known.
+    // LATTICE_WORDS_PERSISTENT=0|1 overrides the other rules.
     const char *v = std::getenv("LATTICE_WORDS_PERSISTENT");
     if (v) {
         if (std::atoi(v) == 0) return LAT_OK;
     } else {
         if (longest < 2 && intervals == 1) return LAT_OK;
         if (bytes ? !bytes_fit(hs, count) : max_L > kWordsPersistentMaxL) return LAT_OK;
-        if (stream && (bytes || max_L > kWordsSharedMaxL)) return LAT_OK;
     }
     if (records && count != 1) return fail(LAT_EINVAL, "an observation series holds one lattice");
     if (captured(stream)) return LAT_OK;
