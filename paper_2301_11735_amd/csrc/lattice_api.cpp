@@ -687,14 +687,20 @@ int enqueue_words_persistent(lattice *const *hs, int32_t count, const uint32_t *
         const int Q = shape.Q, threads = shape.threads;
         const int capacity = words_capacity(Q, threads);
         if (capacity <= 0) return *ran ? fail(LAT_EHIP, "persistent word launch is not possible") : LAT_OK;
-        const uint32_t share = std::max<uint32_t>(1, (uint32_t)capacity / (uint32_t)n);
+        // every lattice the blocks it asks for, or, where they are not resident
+        // together, at most an equal share
         uint32_t nb[kWordsBatch];
-        uint32_t total = 0;
-        for (int32_t i = 0; i < n; ++i) {
-            const uint32_t all = bytes ? bytes_blocks(hs[g0 + i]->L, threads) : words_blocks(hs[g0 + i]->L, Q, threads);
-            nb[i] = std::min<uint32_t>({all, share, (uint32_t)kMaxSlots});
-            total += nb[i];
-        }
+        auto give = [&](uint32_t most) {
+            uint32_t sum = 0;
+            for (int32_t i = 0; i < n; ++i) {
+                const int L = hs[g0 + i]->L;
+                sum += nb[i] = std::min(bytes ? bytes_blocks(L, threads) : words_blocks(L, Q, threads), most);
+            }
+            return sum;
+        };
+        uint32_t total = give((uint32_t)kMaxSlots);
+        if (total > (uint32_t)capacity)
+            total = give(std::min((uint32_t)kMaxSlots, std::max(1u, (uint32_t)capacity / (uint32_t)n)));
         if (total > (uint32_t)capacity) return *ran ? fail(LAT_EHIP, "persistent word launch does not fit") : LAT_OK;
         if (records) {
             lattice *h = hs[g0];
