@@ -398,6 +398,172 @@ __global__ void __launch_bounds__(1024) k_sweep_site(BatchArgs args)
     block_reduce_add<3>(tr, (unsigned long long *)(scr + kScrTrackBase));
 }
 
+// ---------------------------------------------------------------------------
+// Half-byte form, for sides above kSiteMaxL up to kLdsMaxL, whose bytes do not
+// fit: row-major, sites 2j and 2j + 1 as the codes in the low and the high half of
+// byte j.  In a phase only one site of a byte can change (the updated sites of a
+// row are of one class), so its pair's lane writes the byte with a plain store;
+// a site's byte also holds one of its two neighbours in the row, and which half
+// any of them is in depends on the phase alone.
+//
+// One compute unit takes longer for such a lattice than the whole chip (a lattice
+// of L = 500 116 us a sweep, spread over the chip 13.6), so this form is for
+// calls that bring many: 256 of L = 500, 20 sweeps, 6460 us together on the chip,
+// 3370 with two bits a site in LDS and atomics, 2371 in this form; of L = 388 4945, 2066 and 1451.
+template <int P>
+__device__ __forceinline__ void half_step(uint8_t *lat, const SitePos &s, const SiteB &q, uint32_t L, uint32_t pb,
+                                          uint32_t slot8, uint32_t ua, const uint2 *s_tab, const uint8_t *s_slots,
+                                          uint32_t &packed)
+{
+    constexpr uint32_t ha = 4u * (P & 1u);
+    const uint32_t hb = 4u * (pb & 1u);
+    const uint32_t a = (s.a + P) >> 1, b = q.b >> 1;
+    // the neighbour beside the byte: the left one of an even x, the right one of an odd x
+    const uint32_t ea = P == 0 ? s.l : P == 3 ? s.r : P == 1 ? s.a + 2u : s.a + 1u;
+    const uint32_t A = lat[a], B = lat[b], Ae = lat[ea >> 1], Be = lat[(hb ? q.r : q.l) >> 1];
+    const uint32_t Au = lat[(s.u + P) >> 1], Ad = lat[(s.d + P) >> 1], Bu = lat[(q.b - L) >> 1], Bd = lat[q.d >> 1];
+    const uint32_t ca = (A >> ha) & 3u, cb = (B >> hb) & 3u;
+    const uint32_t bpack = contrib_a((A >> (4u - ha)) & 3u) + contrib_a((Ae >> (4u - ha)) & 3u) + contrib_a((Au >> ha) & 3u) +
+                           contrib_a((Ad >> ha) & 3u) + contrib_b((B >> (4u - hb)) & 3u) + contrib_b((Be >> (4u - hb)) & 3u) +
+                           contrib_b((Bu >> hb) & 3u) + contrib_b((Bd >> hb) & 3u);
+    uint32_t change = 0u;
+    pair_step_slot((ca | cb << 2) << 7 | slot8, bpack, ua, s_slots, s_tab, 0x03030000u, packed, change);
+    lat[a] = (uint8_t)(A ^ ((change >> 16) & 3u) << ha);
+    lat[b] = (uint8_t)(B ^ (change >> 24) << hb);
+}
+
+// Four codes, one a byte, to two bytes of this form, and back.
+__device__ __forceinline__ uint32_t halves_of(uint32_t c)
+{
+    const uint32_t x = c & 0x03030303u, y = x | x >> 4;
+    return (y & 0xFFu) | (y >> 8 & 0xFF00u);
+}
+__device__ __forceinline__ uint32_t codes_of_halves(uint32_t h)
+{
+    const uint32_t x = (h & 0xFFu) | (h & 0xFF00u) << 8;
+    return (x & 0x00030003u) | (x & 0x00300030u) << 4;
+}
+
+__device__ __forceinline__ void stage_halves(uint16_t *lat, const LatDesc &d)
+{
+    const uint32_t L = (uint32_t)d.L;
+    if (d.enc == 0) {
+        const LAT_GLOBAL word_any *src = (const LAT_GLOBAL word_any *)d.state;
+        for (uint32_t i = threadIdx.x; i < L * L / 4u; i += blockDim.x) lat[i] = (uint16_t)halves_of(src[i]);
+    } else {
+        // words j of the four classes of a row: 64 sites of it
+        const LAT_GLOBAL uint32_t *src = (const LAT_GLOBAL uint32_t *)d.state;
+        const uint32_t W = L >> 6, csz = (L >> 1) * W;
+        for (uint32_t i = threadIdx.x; i < L * W; i += blockDim.x) {
+            const uint32_t y = i / W, j = i - y * W, at = 4u * (y & 1u) * csz + (y >> 1) * W + j;
+            const uint32_t w0 = src[at], w1 = src[at + csz], w2 = src[at + 2u * csz], w3 = src[at + 3u * csz];
+            for (uint32_t t = 0; t < 16u; ++t)
+                lat[16u * i + t] = (uint16_t)(((w0 >> 2u * t) & 3u) | ((w1 >> 2u * t) & 3u) << 4 | ((w2 >> 2u * t) & 3u) << 8 |
+                                              ((w3 >> 2u * t) & 3u) << 12);
+        }
+    }
+}
+
+__device__ __forceinline__ void unstage_halves(const uint16_t *lat, const LatDesc &d)
+{
+    const uint32_t L = (uint32_t)d.L;
+    if (d.enc == 0) {
+        LAT_GLOBAL word_any *dst = (LAT_GLOBAL word_any *)d.state;
+        for (uint32_t i = threadIdx.x; i < L * L / 4u; i += blockDim.x) dst[i] = codes_of_halves(lat[i]);
+    } else {
+        LAT_GLOBAL uint32_t *dst = (LAT_GLOBAL uint32_t *)d.state;
+        const uint32_t W = L >> 6, csz = (L >> 1) * W;
+        for (uint32_t i = threadIdx.x; i < L * W; i += blockDim.x) {
+            const uint32_t y = i / W, j = i - y * W, at = 4u * (y & 1u) * csz + (y >> 1) * W + j;
+            uint32_t w[4] = {0u, 0u, 0u, 0u};
+            for (uint32_t t = 0; t < 16u; ++t)
+#pragma unroll
+                for (uint32_t c = 0; c < 4u; ++c) w[c] |= ((uint32_t)lat[16u * i + t] >> (4u * c) & 3u) << (2u * t);
+#pragma unroll
+            for (uint32_t c = 0; c < 4u; ++c) dst[at + c * csz] = w[c];
+        }
+    }
+}
+
+// This thread's share of the seven observable sums.
+__device__ __forceinline__ void half_observables(const uint16_t *lat, uint32_t L, uint32_t magicLq, int (&v)[7])
+{
+    const uint32_t Lq = L >> 2, n = L * Lq;
+    auto sites = [&](uint32_t i) { return site_from_codes(codes_of_halves(lat[i])); };
+    SiteSums sums;
+    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
+        const uint32_t y = Lq == 1u ? i : __umulhi(i, magicLq), X = i - y * Lq, w = sites(i);
+        const uint32_t w1 = sites(X + 1u == Lq ? i + 1u - Lq : i + 1u);
+        sums.add(w, __builtin_amdgcn_alignbit(w1, w, 8u), sites(y + 1u == L ? X : i + Lq), row_signs(y));
+    }
+    sums.get(v);
+}
+
+__global__ void __launch_bounds__(1024) k_sweep_half(BatchArgs args)
+{
+    __shared__ __align__(16) uint2 s_tab[kDevTabEntries + 1];
+    __shared__ __align__(16) uint2 s_slots[kSlotEntries];
+    __shared__ uint32_t sched[2 * 12 * kSchedSweeps];
+    __shared__ ObsStage obs;
+    extern __shared__ uint32_t smem[];
+    uint8_t *lat = (uint8_t *)smem;
+    uint8_t *scr = args.scratch[blockIdx.x];
+    const LatDesc d = *(const LatDesc *)(scr + kScrDesc);
+    {
+        const uint2 *g_tab = (const uint2 *)(scr + kScrDevTab), *g_slots = (const uint2 *)kWordSlots.v;
+        for (int i = threadIdx.x; i < kDevTabEntries; i += blockDim.x) s_tab[i] = g_tab[i];
+        for (int i = threadIdx.x; i < kSlotEntries; i += blockDim.x) s_slots[i] = g_slots[i];
+    }
+    stage_halves((uint16_t *)lat, d);
+    if (args.obs_out) tracker_before(scr, obs);
+    const uint32_t L = (uint32_t)d.L, Lq = L >> 2, N = L * L, my_sweeps = args.sweeps[blockIdx.x];
+    const uint32_t intervals = args.obs_out ? args.intervals : 1u, n = intervals * my_sweeps;
+    const uint32_t magicLq = Lq == 1u ? 0u : 0xFFFFFFFFu / Lq + 1u;
+    if (n > 0) make_schedules(sched, d.next_sweep, n, d.key0, d.key1, L);
+    __syncthreads();
+    int tr[3] = {0, 0, 0};
+    uint32_t left = my_sweeps, k = 0;  // sweeps left of interval k
+    for (uint32_t i = 0; i < n; ++i) {
+        const uint64_t s = d.next_sweep + i;
+        const SweepWords sc = sweep_words(sweep_loads(sched + 12u * (i % (2u * kSchedSweeps))));
+        auto phase = [&](auto pc) {
+            constexpr int P = decltype(pc)::value;
+            const uint32_t j = i + 1u;
+            if (P == 0 && j % kSchedSweeps == 0 && j < n)
+                make_schedules(sched + 12u * (j % (2u * kSchedSweeps)), s + 1, n - j, d.key0, d.key1, L);
+            const uint32_t pb = (P + sc.r) & 3u;
+            for (uint32_t t = threadIdx.x; t < N / 16u; t += blockDim.x) {
+                const u32x4 w = pair_draws(philox4x32_10((uint32_t)s, (uint32_t)P, t, (uint32_t)(s >> 32), d.key0, d.key1));
+                uint32_t packed = 0u;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const SitePos at = site_pos(2u * t + (uint32_t)h, L, Lq, N, magicLq);
+                    half_step<P>(lat, at, site_b<P>(at, L, N, sc), L, pb, h ? w.z : w.x, h ? w.w : w.y, s_tab,
+                                 (const uint8_t *)s_slots, packed);
+                }
+                unpack_tracker(packed, tr);
+            }
+            __syncthreads();
+        };
+        phase(std::integral_constant<int, 0>{});
+        phase(std::integral_constant<int, 1>{});
+        phase(std::integral_constant<int, 2>{});
+        phase(std::integral_constant<int, 3>{});
+        if (--left == 0) {
+            if (args.obs_out) {
+                int o[7];
+                half_observables((const uint16_t *)lat, L, magicLq, o);
+                write_record(args, obs, tr, o, k, d.next_sweep + (uint64_t)my_sweeps * (k + 1u));
+            }
+            ++k;
+            left = my_sweeps;
+        }
+    }
+    unstage_halves((const uint16_t *)lat, d);
+    if (threadIdx.x == 0) ((LatDesc *)(scr + kScrDesc))->next_sweep = d.next_sweep + n;
+    block_reduce_add<3>(tr, (unsigned long long *)(scr + kScrTrackBase));
+}
+
 // This thread's share of the 7 observable sums of a 2-bit lattice in the
 // class layout, read from st (global memory or the LDS copy).
 __device__ __forceinline__ void obs_sums_2bit(const uint32_t *st, int L, long long (&v)[7])
@@ -448,6 +614,8 @@ hipError_t init_kernel_attributes()
     // allow more than the default 64 KiB of dynamic LDS
     hipError_t e = hipFuncSetAttribute((const void *)k_sweep_site, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        kSiteMaxL * kSiteMaxL);
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute((const void *)k_sweep_half, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsMaxL * kLdsMaxL / 2);
     if (e == hipSuccess) e = init_quad_kernel_attributes();
     return e;
 }
@@ -461,7 +629,10 @@ hipError_t launch_sweep_lds(const BatchArgs &a, int max_L, int threads, bool qua
     const uint32_t units = sq / 8u <= kSiteOnePair ? sq / 8u : sq / 16u;
     uint32_t block = std::min(1024u, (units + 63u) / 64u * 64u);
     if (threads > 0) block = (uint32_t)std::min(1024, std::max(64, threads / 64 * 64));
-    hipLaunchKernelGGL(k_sweep_site, dim3((unsigned)a.count), dim3(block), (size_t)sq, s, a);
+    if (max_L > kSiteMaxL)
+        hipLaunchKernelGGL(k_sweep_half, dim3((unsigned)a.count), dim3(block), (size_t)sq / 2, s, a);
+    else
+        hipLaunchKernelGGL(k_sweep_site, dim3((unsigned)a.count), dim3(block), (size_t)sq, s, a);
     return hipGetLastError();
 }
 

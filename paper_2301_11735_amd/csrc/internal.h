@@ -24,7 +24,8 @@
 //   kPathPhase  one launch per phase (phase.hip): one thread per a-word, or two
 //               pairs a thread for int8 lattices that are not packed;
 //   kPathBytes  the latter for 384 < L <= 512, L % 64 != 0: batch graphs take
-//               these sides and not those of kPathPhase.
+//               these sides and not those of kPathPhase, and many of them in one
+//               call are swept as on kPathLds.
 // Int8 lattices with L % 64 == 0 off the chip are swept on a 2-bit
 // copy in their scratch (packed before the sweeps of a call, unpacked after).
 enum : int { kPathLds = 0, kPathWords = 1, kPathPhase = 2, kPathBytes = 3 };

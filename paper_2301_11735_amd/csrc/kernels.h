@@ -86,7 +86,8 @@ struct LatDesc {
 constexpr int kLdsMaxL = 512;
 
 // The per-site form (k_sweep_site) keeps one byte per site in LDS: sides up to
-// 384, whose 144 KiB leave room for its tables.
+// 384, whose 144 KiB leave room for its tables; the half-byte form (k_sweep_half)
+// two sites a byte, up to kLdsMaxL.
 constexpr int kSiteMaxL = 384;
 
 // The quad form (k_sweep_quad): sides that are a multiple of 16, one byte per
@@ -303,7 +304,7 @@ hipError_t launch_seed(const SeedArgs &a, hipStream_t s) __attribute__((weak));
 
 // Batched sweeps with each lattice resident in LDS.  quad: the quad form
 // (every side a multiple of 16, at most kQuadMaxL); else the per-site form (up
-// to kSiteMaxL).
+// to kSiteMaxL) or the half-byte form.
 hipError_t launch_sweep_lds(const BatchArgs &a, int max_L, int threads, bool quad, hipStream_t s);
 hipError_t launch_sweep_quad(const BatchArgs &a, int max_L, int threads, hipStream_t s);
 hipError_t init_quad_kernel_attributes();

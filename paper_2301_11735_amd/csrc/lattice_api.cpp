@@ -785,6 +785,9 @@ bool spreads(lattice *const *hs, int32_t count, uint64_t sweeps, double extra, h
 }
 constexpr double kSpreadCall = 25000.0;  // two launches, one of them cooperative, against one
 
+// Lattices that the whole chip does together in the time of one on its compute unit.
+constexpr double kUnitsWorth = 75.0;
+
 // Sweeps of on-chip lattices outside the server and graphs.
 int enqueue_small_sweeps(lattice *const *hs, int32_t count, uint32_t sweeps, hipStream_t stream)
 {
@@ -795,6 +798,24 @@ int enqueue_small_sweeps(lattice *const *hs, int32_t count, uint32_t sweeps, hip
         if (rc || ran) return rc;
     }
     return enqueue_lds_sweeps(hs, count, nullptr, sweeps, stream);
+}
+
+// Whether int8 lattices off the chip (lattice i by sweeps[i]) are faster with a
+// compute unit each, all side by side, than spread over the chip together: the
+// longest of them takes 0.46 ns a site and sweep that way, all of them together
+// 0.0050 to 0.0067 ns this way (us for 20 sweeps of 64 / 80 / 96 / 256 lattices, a unit
+// each and together: L = 388 1418 / 1420 / 1422 / 1451 and 1226 / 1787 / 2017 / 4945, L = 500
+// 2329 / 2330 / 2330 / 2371 and 1588 / 2276 / 2687 / 6460).
+bool one_unit_each(lattice *const *hs, const uint32_t *sweeps, size_t n)
+{
+    double sum = 0, longest = 0;
+    for (size_t i = 0; i < n; ++i) {
+        if (hs[i]->path != kPathBytes) return false;
+        const double sites = (double)hs[i]->N * sweeps[i];
+        sum += sites;
+        longest = std::max(longest, sites);
+    }
+    return sum > kUnitsWorth * longest;
 }
 
 int enqueue_offchip_sweeps(lattice *const *hs, int32_t count, const uint32_t *sweeps, uint32_t uniform,
@@ -829,6 +850,18 @@ int enqueue_offchip_sweeps(lattice *const *hs, int32_t count, const uint32_t *sw
         if (rc == LAT_OK && !ran)
             rc = enqueue_words_sweeps(words.data(), (int32_t)words.size(), words_n.data(), 0, stream, /*bytes=*/false);
         if (rc) return rc;
+    }
+    // as many as there are compute units: one each
+    for (size_t b = 0; b < bytes.size();) {
+        const size_t n = std::min(bytes.size() - b, (size_t)kMaxBatch);
+        if (!one_unit_each(&bytes[b], &bytes_n[b], n)) {
+            b += n;
+            continue;
+        }
+        const int rc = enqueue_lds_sweeps(&bytes[b], (int32_t)n, &bytes_n[b], 0, stream);
+        if (rc) return rc;
+        bytes.erase(bytes.begin() + (ptrdiff_t)b, bytes.begin() + (ptrdiff_t)(b + n));
+        bytes_n.erase(bytes_n.begin() + (ptrdiff_t)b, bytes_n.begin() + (ptrdiff_t)(b + n));
     }
     if (!bytes.empty()) {
         bool ran = false;
@@ -1051,7 +1084,7 @@ int choose_path(int L, int enc)
     const bool words_ok = L % 64 == 0 && L <= kWordsMaxL;
     if (const char *v = std::getenv("LATTICE_PATH")) {
         const std::string want(v);
-        if (want == "lds" && L <= kSiteMaxL) return kPathLds;
+        if (want == "lds" && L <= kLdsMaxL) return kPathLds;
         if (want == "words" && words_ok) return kPathWords;
         if (want == "phase") return kPathPhase;
     }
