@@ -135,7 +135,9 @@ constexpr long long kBarrierTimeoutTicks = 20000000;
 
 // One phase of up to kWordsBatch lattices in the 2-bit class layout (int8
 // ones through their packed copy), spread over many blocks per lattice: row i of
-// the grid updates lattice i with its first `blocks` blocks, Q lanes per
+// the grid is a run of up to max_blocks blocks of a lattice, from block first on
+// of its `blocks` (a lattice with many blocks takes several rows, so that few blocks
+// of the grid have nothing to do), Q lanes per
 // a-word.  Sweep iter of the series (sweep next_sweep + iter of each lattice,
 // schedule computed on the device); a lattice with sweeps[i] <= iter is
 // skipped.  Block b of a lattice adds its tracker sums to tracker slot b.
@@ -150,7 +152,7 @@ struct WordsArgs {
     uint32_t max_blocks;
     uint8_t *scratch[kWordsBatch];
     uint32_t sweeps[kWordsBatch];
-    uint32_t blocks[kWordsBatch];
+    uint32_t run[kWordsBatch];  // first | blocks << 16
 };
 // Lanes per a-word for side L (fewer for larger lattices, whose words fill
 // the chip anyway), and the blocks one lattice takes.

@@ -26,8 +26,8 @@ namespace lat {
 namespace {
 
 // ---------------------------------------------------------------------------
-// int8 layout: one code per byte, row-major, any side.  Row i of the grid updates
-// lattice i; a thread owns Philox calls t, i.e. pairs 2t and 2t+1 (words 0,1
+// int8 layout: one code per byte, row-major, any side.  Rows of the grid update
+// the lattices; a thread owns Philox calls t, i.e. pairs 2t and 2t+1 (words 0,1
 // and 2,3 of the call).  As in k_phase_words, what bounds a launch at medium
 // sides is its chain: the arguments, the descriptor with the tables behind
 // it, and the sites of both pairs, all loaded at once (L = 1000 5.8 -> 5.5 us a
@@ -146,10 +146,11 @@ __global__ void __launch_bounds__(kWordsPhaseMaxThreads) k_phase_bytes(WordsArgs
     __shared__ uint2 s_tab[kDevTabEntries];
     __shared__ __align__(16) uint2 s_slots[kSlotEntries];
     uint8_t *scr = a.scratch[blockIdx.y];
-    const uint32_t sweeps = a.sweeps[blockIdx.y], blocks = a.blocks[blockIdx.y];
+    const uint32_t sweeps = a.sweeps[blockIdx.y], run = a.run[blockIdx.y];
+    const uint32_t blocks = run >> 16, block = (run & 0xFFFFu) + blockIdx.x;
     // the whole block: no barrier is skipped by part of it (one condition of all
     // three arguments, for one wait)
-    if ((scr == nullptr) | (a.iter >= sweeps) | (blockIdx.x >= blocks)) return;
+    if ((scr == nullptr) | (a.iter >= sweeps) | (block >= blocks)) return;
     const uint32_t threads = a.threads;  // (the launch's own count is in a further line of arguments)
     TableLoads tables;
     tables.load((const uint2 *)(scr + kScrDevTab), threads);
@@ -162,7 +163,7 @@ __global__ void __launch_bounds__(kWordsPhaseMaxThreads) k_phase_bytes(WordsArgs
     device_schedule(d.L, d.key0, d.key1, s, r, mm, kk);
     const BytePhase f = byte_phase(d.L, (uint32_t)a.p, r, mm[a.p], kk[a.p]);
     const uint32_t calls = f.L * f.L / 16u, step = blocks * threads;
-    uint32_t t = blockIdx.x * threads + threadIdx.x;
+    uint32_t t = block * threads + threadIdx.x;
     ByteRefs at[2];
     ByteVals v[2];
     u32x4 w;
@@ -185,7 +186,7 @@ __global__ void __launch_bounds__(kWordsPhaseMaxThreads) k_phase_bytes(WordsArgs
         t += step;
         if (t < calls) fetch(t);
     }
-    wave_reduce_add3(tr, (unsigned long long *)(scr + kScrSlots) + 3 * (size_t)(blockIdx.x % kMaxSlots));
+    wave_reduce_add3(tr, (unsigned long long *)(scr + kScrSlots) + 3 * (size_t)(block % kMaxSlots));
 }
 
 // Persistent form, as k_words_series without records: all sweeps of a call in one

@@ -24,7 +24,7 @@
 namespace lat {
 namespace {
 
-// One phase of every lattice of a batch, row i of the grid for lattice i.  What
+// One phase of every lattice of a batch, a row or more of the grid for each.  What
 // bounds it: its chain, since a launch waits for the one before and memory that
 // another kernel wrote is beyond the caches.  The rounds of that chain are the
 // arguments (one wait), the lattice's descriptor with the tables behind it, and
@@ -43,10 +43,11 @@ __global__ void __launch_bounds__(kWordsPhaseMaxThreads) k_phase_words(WordsArgs
     __shared__ uint2 s_tab[kDevTabEntries];
     __shared__ __align__(16) uint2 s_slots[kSlotEntries];
     uint8_t *scr = a.scratch[blockIdx.y];
-    const uint32_t sweeps = a.sweeps[blockIdx.y], blocks = a.blocks[blockIdx.y];
+    const uint32_t sweeps = a.sweeps[blockIdx.y], run = a.run[blockIdx.y];
+    const uint32_t blocks = run >> 16, block = (run & 0xFFFFu) + blockIdx.x;
     // the whole block: no barrier is skipped by part of it (one condition of all
     // three arguments, for one wait)
-    if ((scr == nullptr) | (a.iter >= sweeps) | (blockIdx.x >= blocks)) return;
+    if ((scr == nullptr) | (a.iter >= sweeps) | (block >= blocks)) return;
     const uint32_t threads = a.threads;  // (the launch's own count is in a further line of arguments)
     TableLoads tables;
     tables.load((const uint2 *)(scr + kScrDevTab), threads);
@@ -60,7 +61,7 @@ __global__ void __launch_bounds__(kWordsPhaseMaxThreads) k_phase_words(WordsArgs
     WordPhase f;
     word_phase_setup(f, d.L, d.key0, d.key1, s, a.p, r, mm, kk);
     const uint32_t csz = (uint32_t)f.H * (uint32_t)f.W;
-    const uint32_t task = blockIdx.x * threads + threadIdx.x;
+    const uint32_t task = block * threads + threadIdx.x;
     // tasks = Q * csz is a multiple of Q, so a word's lanes are all in or all
     // out; those that are out load the first word's lanes again
     const int q = (int)(task & (uint32_t)(Q - 1));
@@ -75,7 +76,7 @@ __global__ void __launch_bounds__(kWordsPhaseMaxThreads) k_phase_words(WordsArgs
 
     int tr[3] = {0, 0, 0};
     if (mine) unpack_tracker(word_apply<Q, false, false>(st, f, refs, v, q, draws, s_tab, (const uint8_t *)s_slots, nullptr), tr);
-    wave_reduce_add3(tr, (unsigned long long *)(scr + kScrSlots) + 3 * (size_t)blockIdx.x);
+    wave_reduce_add3(tr, (unsigned long long *)(scr + kScrSlots) + 3 * (size_t)block);
 }
 
 // Block sums of m (per thread: tracker moves 0-2, spin, staggered spin and
