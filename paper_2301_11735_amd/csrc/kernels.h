@@ -144,16 +144,44 @@ constexpr long long kBarrierTimeoutTicks = 20000000;
 constexpr int kWordsBatch = 64;
 constexpr int kWordsThreads = 256;
 constexpr int kWordsSeriesMaxThreads = 512;  // of the persistent form with at least 4 lanes per a-word
-struct WordsArgs {
+// The arguments hold N rows: the host writes them for every launch, and a sweep of a
+// lattice and its record are seven short launches.  100 such intervals of L = 600
+// with room for 4, 16 and 64 rows 2.92, 2.92 to 3.29 and 3.57 ms (2.97 to 3.18 with one
+// lattice's arguments).  The launchers take the smallest form that holds a.
+template <int N>
+struct WordsArgsOf {
     int count;
     int p;
     uint32_t iter;
     uint32_t threads;  // of a block
     uint32_t max_blocks;
-    uint8_t *scratch[kWordsBatch];
-    uint32_t sweeps[kWordsBatch];
-    uint32_t run[kWordsBatch];  // first | blocks << 16
+    uint8_t *scratch[N];
+    uint32_t sweeps[N];
+    uint32_t run[N];  // first | blocks << 16
 };
+using WordsArgs = WordsArgsOf<kWordsBatch>;
+constexpr int kWordsOne = 4, kWordsFew = 16;
+template <int N>
+WordsArgsOf<N> few_rows(const WordsArgs &a)
+{
+    WordsArgsOf<N> b{a.count, a.p, a.iter, a.threads, a.max_blocks, {}, {}, {}};
+    for (int i = 0; i < a.count; ++i) {
+        b.scratch[i] = a.scratch[i];
+        b.sweeps[i] = a.sweeps[i];
+        b.run[i] = a.run[i];
+    }
+    return b;
+}
+template <typename F>
+void with_rows(const WordsArgs &a, F launch)
+{
+    if (a.count <= kWordsOne)
+        launch(few_rows<kWordsOne>(a));
+    else if (a.count <= kWordsFew)
+        launch(few_rows<kWordsFew>(a));
+    else
+        launch(a);
+}
 // Lanes per a-word for side L (fewer for larger lattices, whose words fill
 // the chip anyway), and the blocks one lattice takes.
 int words_lanes(int L);

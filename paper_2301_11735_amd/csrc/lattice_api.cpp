@@ -467,7 +467,7 @@ int words_phase_threads()
 }
 
 // The rows of a per-phase launch over the a.count lattices of a, lattice i with nb[i]
-// blocks: runs as short as kWordsBatch rows allow, so that lattices of unequal
+// blocks: runs as short as the arguments' room for rows allows, so that lattices of unequal
 // sides leave few blocks without work.  (L = 2048 with seven of L = 320, one sweep: 63 us
 // with a row a lattice, 39 us so; L = 1024 with forty of 320 59 and 44.)
 void rows_of_runs(WordsArgs &a, const uint32_t *nb)
@@ -481,8 +481,9 @@ void rows_of_runs(WordsArgs &a, const uint32_t *nb)
     };
     uint32_t least = nb[0], most = nb[0];
     for (int i = 1; i < count; ++i) least = std::min(least, nb[i]), most = std::max(most, nb[i]);
+    const uint32_t room = (uint32_t)(count <= kWordsFew ? kWordsFew : kWordsBatch);
     uint32_t run = least;
-    while (run < most && rows(run) > (uint32_t)kWordsBatch) run = std::min(most, run + (run + 3) / 4);
+    while (run < most && rows(run) > room) run = std::min(most, run + (run + 3) / 4);
     a.max_blocks = run;
     a.count = 0;
     for (int i = 0; i < count; ++i)

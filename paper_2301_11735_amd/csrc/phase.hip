@@ -141,7 +141,8 @@ __device__ __forceinline__ void byte_apply(LAT_GLOBAL uint8_t *st, const BytePha
     }
 }
 
-__global__ void __launch_bounds__(kWordsPhaseMaxThreads) k_phase_bytes(WordsArgs a)
+template <int N>
+__global__ void __launch_bounds__(kWordsPhaseMaxThreads) k_phase_bytes(WordsArgsOf<N> a)
 {
     __shared__ uint2 s_tab[kDevTabEntries];
     __shared__ __align__(16) uint2 s_slots[kSlotEntries];
@@ -548,9 +549,17 @@ int num_cus()
 // ---------------------------------------------------------------------------
 const void *bytes_series_kernel() { return (const void *)k_bytes_series; }
 
+namespace {
+template <int N>
+void phase_bytes(const WordsArgsOf<N> &a, int threads, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_phase_bytes<N>, dim3(a.max_blocks, (unsigned)a.count), dim3((unsigned)threads), 0, s, a);
+}
+}  // namespace
+
 hipError_t launch_phase_bytes(const WordsArgs &a, int threads, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_phase_bytes, dim3(a.max_blocks, (unsigned)a.count), dim3((unsigned)threads), 0, s, a);
+    with_rows(a, [&](const auto &rows) { phase_bytes(rows, threads, s); });
     return hipGetLastError();
 }
 

@@ -37,8 +37,8 @@ namespace {
 // other kernels (the server runs batches of small lattices beside them): the
 // last block of a launch is waited for (served burst of 40 requests 173 ms
 // without and 147 with priority; all of it 180 -> 126).
-template <int Q>
-__global__ void __launch_bounds__(kWordsPhaseMaxThreads) k_phase_words(WordsArgs a)
+template <int Q, int N>
+__global__ void __launch_bounds__(kWordsPhaseMaxThreads) k_phase_words(WordsArgsOf<N> a)
 {
     __shared__ uint2 s_tab[kDevTabEntries];
     __shared__ __align__(16) uint2 s_slots[kSlotEntries];
@@ -281,7 +281,8 @@ __global__ void __launch_bounds__(kBeginThreads) k_series_begin(WordsSeriesArgs 
         a.records[i] = a.records[i % kFields];
 }
 
-__global__ void k_advance_words(WordsArgs a)
+template <int N>
+__global__ void k_advance_words(WordsArgsOf<N> a)
 {
     if (blockIdx.x == 0 && (int)threadIdx.x < a.count)
         ((LatDesc *)(a.scratch[threadIdx.x] + kScrDesc))->next_sweep += a.sweeps[threadIdx.x];
@@ -357,16 +358,24 @@ int words_lanes(int L)
     return 1;
 }
 
+namespace {
+template <int N>
+void phase_words(const WordsArgsOf<N> &a, int Q, int threads, hipStream_t s)
+{
+    const dim3 grid(a.max_blocks, (unsigned)a.count), block((unsigned)threads);
+    switch (Q) {
+    case 1: hipLaunchKernelGGL((k_phase_words<1, N>), grid, block, 0, s, a); break;
+    case 2: hipLaunchKernelGGL((k_phase_words<2, N>), grid, block, 0, s, a); break;
+    case 4: hipLaunchKernelGGL((k_phase_words<4, N>), grid, block, 0, s, a); break;
+    default: hipLaunchKernelGGL((k_phase_words<8, N>), grid, block, 0, s, a); break;
+    }
+}
+}  // namespace
+
 hipError_t launch_phase_words(const WordsArgs &a, int Q, int threads, hipStream_t s)
 {
     if (Q == 0) return launch_phase_bytes(a, threads, s);
-    const dim3 grid(a.max_blocks, (unsigned)a.count), block((unsigned)threads);
-    switch (Q) {
-    case 1: hipLaunchKernelGGL(k_phase_words<1>, grid, block, 0, s, a); break;
-    case 2: hipLaunchKernelGGL(k_phase_words<2>, grid, block, 0, s, a); break;
-    case 4: hipLaunchKernelGGL(k_phase_words<4>, grid, block, 0, s, a); break;
-    default: hipLaunchKernelGGL(k_phase_words<8>, grid, block, 0, s, a); break;
-    }
+    with_rows(a, [&](const auto &rows) { phase_words(rows, Q, threads, s); });
     return hipGetLastError();
 }
 
@@ -424,9 +433,17 @@ hipError_t launch_words_series(const WordsSeriesArgs &a, int Q, hipStream_t s)
     return hipLaunchKernel(fn, dim3((unsigned)a.count), dim3((unsigned)a.threads), kargs, 0, s);
 }
 
+namespace {
+template <int N>
+void advance_words(const WordsArgsOf<N> &a, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_advance_words<N>, dim3(1), dim3(kWordsBatch), 0, s, a);
+}
+}  // namespace
+
 hipError_t launch_advance_words(const WordsArgs &a, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_advance_words, dim3(1), dim3(kWordsBatch), 0, s, a);
+    with_rows(a, [&](const auto &rows) { advance_words(rows, s); });
     return hipGetLastError();
 }
 
