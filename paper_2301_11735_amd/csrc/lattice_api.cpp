@@ -1402,15 +1402,19 @@ int lattice_read_state(lattice *h, int8_t *host_codes)
     return guarded("lattice_read_state", [&]() -> int {
         if (!live(h)) return fail(LAT_ESTATE, "null or destroyed handle");
         if (!host_codes) return fail(LAT_EINVAL, "null output");
-        // int8 codes go to the caller's memory as they are; packed ones through
-        // pinned memory, or ordinary memory that is not cleared first
+        // Through pinned memory where the state fits; else int8 codes go to the
+        // caller's memory as they are, and packed ones through ordinary memory that
+        // is not cleared first.  (Int8 codes to an array of the caller's, staged and
+        // at once: L = 64 13 and 23 us, L = 1400 101 and 107; into memory that is new on
+        // every call L = 320 33 and 74.)
         const size_t bytes = lattice_state_bytes(h->L, h->enc);
-        const bool packed = h->enc == LAT_ENC_2BIT, pinned = packed && bytes <= kPinnedLarge;
+        const bool packed = h->enc == LAT_ENC_2BIT;
         std::unique_ptr<PinnedBlock> stage;
-        if (pinned) stage = std::make_unique<PinnedBlock>(/*large=*/bytes > kPinnedBytes);
+        if (bytes <= kPinnedLarge) stage = std::make_unique<PinnedBlock>(/*large=*/bytes > kPinnedBytes);
         std::unique_ptr<uint8_t[]> own;
-        if (packed && !(stage && stage->p)) own.reset(new uint8_t[bytes]);
-        uint8_t *dev = !packed ? (uint8_t *)host_codes : own ? own.get() : (uint8_t *)stage->p;
+        uint8_t *dev = stage ? (uint8_t *)stage->p : nullptr;
+        if (!dev && packed) own.reset(dev = new uint8_t[bytes]);
+        if (!dev) dev = (uint8_t *)host_codes;
         uint32_t err = 0;
         hipError_t e = hipMemcpyAsync(dev, h->d_state, bytes, hipMemcpyDeviceToHost, h->stream);
         if (e == hipSuccess && barrier_may_time_out(h))
@@ -1420,7 +1424,10 @@ int lattice_read_state(lattice *h, int8_t *host_codes)
         if (e == hipSuccess) e = waited;
         if (e != hipSuccess) return hip_fail(e, "lattice_read_state");
         if (err & 1u) return barrier_timed_out();
-        if (packed) codes_from_words(h->L, (const uint32_t *)dev, host_codes);
+        if (packed)
+            codes_from_words(h->L, (const uint32_t *)dev, host_codes);
+        else if (dev != (uint8_t *)host_codes)
+            std::memcpy(host_codes, dev, bytes);
         return LAT_OK;
     });
 }
