@@ -790,9 +790,10 @@ int enqueue_words_persistent(lattice *const *hs, int32_t count, const uint32_t *
 // Whether few on-chip lattices of large sides are faster spread over many blocks
 // in the persistent kernels than with a compute unit each, for calls of
 // `sweeps` sweeps that cost `extra` ns more that way.  ns a sweep: on the chip
-// 0.229 L^2 in the four-pair form and 0.34 L^2 per site (L = 256 15.0 us, L = 340
-// 39.5); spread 9.7 us with two bits a site and 12 as bytes, and 4.6 more when
-// every compute unit has a block (L = 256 9.7, L = 340 12.0, 16 of L = 260 17).
+// 0.229 L^2 in the four-pair form and 0.34 L^2 per site (L = 256 14.9 us, L = 340
+// 38.5); spread 9.9 us with two bits a site (also 16 lattices of L = 256), and as bytes
+// 10.5 and up to 3 more when every compute unit has a block (L = 200 10.6, L = 340
+// 10.5, L = 384 with 63 of L = 100 13.5).
 // Lattices whose path was asked for stay on it, and so do those on a stream of
 // their own: side by side with others, a compute unit each is the better use.
 bool spreads(lattice *const *hs, int32_t count, uint64_t sweeps, double extra, hipStream_t stream)
@@ -808,10 +809,12 @@ bool spreads(lattice *const *hs, int32_t count, uint64_t sweeps, double extra, h
     const uint32_t blocks = blocks_of_all(hs, count, kWordsThreads);
     if (blocks > 256u) return false;
     const double on_chip = (quad ? 0.229 : 0.34) * max_L * max_L;
-    const double spread = (hs[0]->enc == LAT_ENC_INT8 ? 12000.0 : 9700.0) + 18.0 * blocks;
+    const double spread = hs[0]->enc == LAT_ENC_INT8 ? 10500.0 + 13.0 * blocks : 9900.0;
     return (double)sweeps * (on_chip - spread) > extra && !captured(stream);
 }
-constexpr double kSpreadCall = 25000.0;  // two launches, one of them cooperative, against one
+// Three launches against one (two sweeps of one lattice of L = 256 on the chip and
+// spread 48.5 and 40.2 us; of 16 53.6 and 47.9).
+constexpr double kSpreadCall = 4000.0;
 
 // Lattices that the whole chip does together in the time of one on its compute unit.
 constexpr double kUnitsWorth = 75.0;
@@ -1323,10 +1326,13 @@ int lattice_sweep_series(lattice *h, uint32_t intervals, uint32_t every, void *d
         // the whole series in persistent launches where they can run
         bool ran = false;
         const bool small = h->path == kPathLds, bytes = h->enc == LAT_ENC_INT8;
-        // records of the persistent kernel cost 2.5 us more than on the chip; int8
-        // lattices as they are take two launches and a reduction an interval
-        const bool wide = small && (bytes ? spreads(one, 1, every, 45000.0, st)
-                                          : spreads(one, 1, (uint64_t)intervals * every, kSpreadCall + 2500.0 * intervals, st));
+        // A series spread over the chip has a reduction more, but each of its records
+        // costs less (L = 256, 20 intervals of one sweep 257 us and 500 on the chip, 1 of two
+        // 50 and 60; L = 192, 4 of five 241 and 234).  Int8 lattices as they are take three
+        // launches and a reduction an interval (L = 260, 4 of two 161 and 227; L = 208,
+        // 4 of five 287 and 268), or launches per phase where that is one sweep.
+        const bool wide = small && (bytes ? every > 1 && spreads(one, 1, every, 13000.0, st)
+                                          : spreads(one, 1, (uint64_t)intervals * every, 10000.0 - 5000.0 * intervals, st));
         if (h->path == kPathWords || (wide && !bytes)) {
             const int rc = enqueue_words_persistent(one, 1, nullptr, intervals, every, (long long *)d_series, st,
                                                     /*bytes=*/false, &ran);
