@@ -84,14 +84,19 @@ __device__ __forceinline__ void stage_sites(uint32_t *lat, const LatDesc &d)
                 ((uint8_t *)lat)[i] = (uint8_t)(kSiteBytes >> (8u * (src[i] & 3u)));
         }
     } else {
-        // word (c, Y, j) of the class layout: sites x = 4 (16 j + t) + (c & 3) of row 2 Y + (c >> 2)
+        // words j of the four classes of row y are its sites 64 j .. 64 j + 63: a task
+        // takes a quarter of them, 16 bytes a store
         const LAT_GLOBAL uint32_t *src = (const LAT_GLOBAL uint32_t *)d.state;
         const uint32_t W = L >> 6, csz = (L >> 1) * W;
-        for (uint32_t i = threadIdx.x; i < 8u * csz; i += blockDim.x) {
-            const uint32_t c = i / csz, rem = i - c * csz, Y = rem / W, j = rem - Y * W, w = src[i];
-            uint8_t *row = (uint8_t *)lat + (2u * Y + (c >> 2)) * L + 64u * j + (c & 3u);
+        for (uint32_t i = threadIdx.x; i < 4u * L * W; i += blockDim.x) {
+            const uint32_t y = (i >> 2) / W, j = (i >> 2) - y * W, at = 4u * (y & 1u) * csz + (y >> 1) * W + j, q = 8u * (i & 3u);
+            const uint32_t w0 = src[at] >> q, w1 = src[at + csz] >> q, w2 = src[at + 2u * csz] >> q, w3 = src[at + 3u * csz] >> q;
+            uint32_t v[4];
 #pragma unroll
-            for (uint32_t t = 0; t < 16u; ++t) row[4u * t] = (uint8_t)(kSiteBytes >> (8u * ((w >> (2u * t)) & 3u)));
+            for (uint32_t t = 0; t < 4u; ++t)
+                v[t] = site_from_codes(((w0 >> 2u * t) & 3u) | ((w1 >> 2u * t) & 3u) << 8 | ((w2 >> 2u * t) & 3u) << 16 |
+                                       ((w3 >> 2u * t) & 3u) << 24);
+            ((uint4 *)lat)[i] = make_uint4(v[0], v[1], v[2], v[3]);
         }
     }
 }
@@ -360,7 +365,7 @@ __global__ void __launch_bounds__(1024) k_sweep_site(BatchArgs args)
     __shared__ __align__(16) uint32_t s_trans[2 * 256];
     __shared__ uint32_t sched[2 * 12 * kSchedSweeps];
     __shared__ ObsStage obs;
-    extern __shared__ uint32_t lat[];
+    extern __shared__ __align__(16) uint32_t lat[];
     uint8_t *scr = args.scratch[blockIdx.x];
     const LatDesc d = *(const LatDesc *)(scr + kScrDesc);
     {
