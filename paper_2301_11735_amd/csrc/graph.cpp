@@ -151,10 +151,12 @@ int lattice_batch_graph_read(lat_batch_graph *g, lat_obs *out)
         size_t i = 0;
         uint32_t k = 0;
         return read_records("lattice_batch_graph_read", g->d_out, 10, n * g->intervals, g->hs.data(), n, false, g->stream,
-                            [&](size_t at, const int64_t *v) {
-                                fill_obs(g->hs[i], v, &out[at]);
-                                out[at].sweep -= (uint64_t)g->sweeps * (g->intervals - 1u - k);
-                                if (++i == n) i = 0, ++k;
+                            [&](size_t at, const int64_t *v, size_t m) {
+                                for (const size_t end = at + m; at < end; ++at, v += 10) {
+                                    fill_obs(g->hs[i], v, &out[at]);
+                                    out[at].sweep -= (uint64_t)g->sweeps * (g->intervals - 1u - k);
+                                    if (++i == n) i = 0, ++k;
+                                }
                             });
     });
 }

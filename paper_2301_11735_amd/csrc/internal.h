@@ -143,11 +143,11 @@ int validate_params(const lat_params *p, int64_t *Q, int64_t *Nc);
 // flags a time-out in its error word.
 bool barrier_may_time_out(const lattice *h);
 // Waits for the stream and hands the n records (`words` int64 each) at dev to
-// fill(k, record) in order.  Also reads the error
+// fill(first, records, m) in order, m at once.  Also reads the error
 // flags of those of the `count` lattices hs that ran a device-wide barrier
 // (always: of all of them): a time-out is an error.  what: the entry point's name.
 int read_records(const char *what, const void *dev, uint32_t words, size_t n, lattice *const *hs, size_t count,
-                 bool always, hipStream_t stream, const std::function<void(size_t, const int64_t *)> &fill);
+                 bool always, hipStream_t stream, const std::function<void(size_t, const int64_t *, size_t)> &fill);
 // v = (tracker nD, nV, nJ, sum S, sum S^2, bonds SS, bonds ss, M, M_st, C_st).
 void fill_obs(const lattice *h, const int64_t *v, lat_obs *out);
 

@@ -981,7 +981,7 @@ bool barrier_may_time_out(const lattice *h)
 // pages, 70 us into pinned memory and 95 in pieces of 1 MiB.)  Without pinned
 // memory, an ordinary buffer holds them all.
 int read_records(const char *what, const void *dev, uint32_t words, size_t n, lattice *const *hs, size_t count,
-                 bool always, hipStream_t stream, const std::function<void(size_t, const int64_t *)> &fill)
+                 bool always, hipStream_t stream, const std::function<void(size_t, const int64_t *, size_t)> &fill)
 {
     const size_t size = 8 * (size_t)words;
     std::vector<uint8_t *> swept;  // scratch of the lattices whose flags are read
@@ -1036,7 +1036,7 @@ int read_records(const char *what, const void *dev, uint32_t words, size_t n, la
         const int64_t *v = (const int64_t *)(ring + half * piece * size);
         const size_t m = std::min(piece, n - k);
         if (k + m < n) e = copy(k + m, half ^= 1u);
-        for (size_t i = 0; i < m; ++i) fill(k + i, v + i * words);
+        fill(k, v, m);
         k += m;
     } while (k < n);
     return LAT_OK;
@@ -1303,7 +1303,9 @@ int lattice_observables_batch(lattice *const *hs, int32_t count, void *d_out, si
         const int rc = enqueue_observables_batch(hs, count, (unsigned long long *)d_out, stream);
         if (rc) return rc;
         return read_records("lattice_observables_batch", d_out, 10, (size_t)count, hs, (size_t)count, false, stream,
-                            [&](size_t i, const int64_t *v) { fill_obs(hs[i], v, &out[i]); });
+                            [&](size_t at, const int64_t *v, size_t m) {
+                                for (size_t i = 0; i < m; ++i) fill_obs(hs[at + i], v + 10 * i, &out[at + i]);
+                            });
     });
 }
 
@@ -1369,9 +1371,11 @@ int lattice_series_read(lattice *h, const void *d_series, uint32_t intervals, la
         if (intervals == 0) return LAT_OK;
         lattice *one[1] = {h};
         return read_records("lattice_series_read", d_series, kSeriesRecord / 8, intervals, one, 1, true, h->stream,
-                            [&](size_t k, const int64_t *v) {
-                                fill_obs(h, v, &out[k]);
-                                out[k].sweep = (uint64_t)v[10] - h->start_sweep;
+                            [&](size_t at, const int64_t *v, size_t m) {
+                                for (size_t k = at; k < at + m; ++k, v += kSeriesRecord / 8) {
+                                    fill_obs(h, v, &out[k]);
+                                    out[k].sweep = (uint64_t)v[10] - h->start_sweep;
+                                }
                             });
     });
 }
