@@ -167,9 +167,9 @@ int lattice_read_state(lattice *h, int8_t *host_codes);
  * 3.2: several lattice copies processed together).  Lattices may differ in
  * L, encoding, parameters and seed; results are identical to calling
  * lattice_sweep on each.  Lattices on the on-chip path (L <= 256 with
- * L % 64 == 0, L <= 384 otherwise) advance together in one launch per 256 of
- * them, each resident in on-chip memory for all the sweeps, or spread over the
- * device where that is faster; those with L % 64 == 0 up to 2048 and int8 ones
+ * L % 64 == 0, L <= 384 otherwise, and up to 512 where there are many of those)
+ * advance together in one launch per 256 of them, each resident in on-chip memory
+ * for all the sweeps, or spread over the device where that is faster; those with L % 64 == 0 up to 2048 and int8 ones
  * of other sides advance together on the multi-block kernels (one
  * launch per 64 of them, as lattice_sweep, or one per phase);
  * larger ones one after another.  The caller orders hip_stream

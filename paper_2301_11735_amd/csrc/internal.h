@@ -15,12 +15,13 @@
 
 // How a lattice is swept (chosen at create from L and the encoding):
 //   kPathLds    one block holds the whole lattice in LDS for all the sweeps of
-//               a launch (batch.hip, quad.hip); by default L <= 256 when
+//               a launch, or it is spread over many blocks where that is
+//               faster (batch.hip, quad.hip); by default L <= 256 when
 //               L % 64 == 0, else L <= 384;
 //   kPathWords  many blocks per lattice, Q lanes per a-word, schedule
 //               computed on the device (words.hip): one persistent launch
-//               per call, or one launch per phase in graphs and in the
-//               server; L % 64 == 0, L <= 2048;
+//               per call, or one launch per phase in graphs, in the server and
+//               on other streams than the default one; L % 64 == 0, L <= 2048;
 //   kPathPhase  one launch per phase (phase.hip): one thread per a-word, or two
 //               pairs a thread for int8 lattices that are not packed;
 //   kPathBytes  the latter for 384 < L <= 512, L % 64 != 0: batch graphs take

@@ -1,5 +1,5 @@
 // Launch interface between the host API (lattice_api.cpp) and the gfx950
-// kernels (phase.hip, obs.hip, batch.hip).  C++ linkage, library-internal.
+// kernels (the .hip sources).  C++ linkage, library-internal.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -109,8 +109,8 @@ struct BatchArgs {
     unsigned long long *obs_out;
     uint32_t intervals, obs_words, obs_stride;
 };
-// Sweeps of one launch of the per-site or quad form over several intervals: bounds
-// how long a launch runs (about half a second at L = 384).
+// Sweeps of one launch of an on-chip form over several intervals: bounds how long a
+// launch runs (0.8 s at L = 384, 2 s at L = 512).
 constexpr uint32_t kFusedSweeps = 16384;
 
 // One phase of one sweep: phase p, displacement D = (r + 4m, 1 + 2k).

@@ -676,14 +676,14 @@ int enqueue_words_persistent(lattice *const *hs, int32_t count, const uint32_t *
     }
     // default: on for every lattice of this path, against one launch per phase
     // (us a sweep, plain / with observables after every sweep): L = 512
-    // 9.6 / 12.0 against 21.7 / 34.4, L = 1024 12.3 / 14.7 against 22.0 /
-    // 34.8, L = 2048 14.2 / 18.3 against 23.6 / 36.5.
+    // 9.5 / 11.8 against 15.5 / 25.6, L = 1024 12.0 / 14.5 against 15.8 /
+    // 26.0, L = 2048 14.6 / 17.8 against 17.9 / 28.2.
     // A call of one sweep is the other way round (from an idle stream to its end
-    // 50 us against 31 at L = 256, 55 against 36 at L = 1000; one sweep and its record
-    // at L = 1088 64 against 50).  Of int8 lattices
+    // 30.2 us against 28.3 at L = 512, 35.7 against 31.2 at L = 2048; with its record
+    // 41.9 against 38.3 and 48.3 against 41.5).  Of int8 lattices
     // as they are: as long as a block a compute unit holds a call a thread (us a
-    // sweep, persistent / launches: L = 388 12.5 / 18.0, L = 1000 16.3 / 19.9, 8 of
-    // L = 500 24.5 / 25.5; but L = 2000 33.8 / 35.4, L = 4000 99 / 75).
+    // sweep, persistent / launches: L = 388 10.7 / 17.5, L = 1000 15.0 / 19.3, 8 of
+    // L = 500 22.6 / 24.9; but L = 2000 32.8 / 34.2, 48 of L = 500 75 / 69, L = 4000 97 / 72).
     // Never on a stream of the caller's own, whatever is asked for: launches of
     // several streams would take places that the blocks of the others wait for, and a
     // program that ran them (as cooperative launches) from six threads with a
@@ -1105,7 +1105,7 @@ int enqueue_sweeps(lattice *h, uint32_t sweeps, hipStream_t stream)
 // kLdsRouteMaxL, whose single compute unit is then still faster than a
 // multi-block launch series; the multi-block word kernel up to kWordsMaxL;
 // the one-thread-per-word phase kernel above.  LATTICE_PATH=lds|words|phase
-// forces a path where it applies (tests run every path at small sizes);
+// forces a path where it applies (lds: up to kLdsMaxL) (tests run every path at small sizes);
 // LATTICE_FORCE_PHASE_KERNELS=1 is the same as LATTICE_PATH=phase.
 constexpr int kLdsRouteMaxL = 256;
 constexpr int kWordsMaxL = 2048;

@@ -6,8 +6,9 @@
 //   2. one wave a map builds it with the paper's sequential algorithm -- draw
 //      a site until an unmarked one comes up, mark it; the same for the
 //      partner; record the pair; mark the neighbours of both -- taking 64
-//      draws at a time (build_map); the block's waves build the next maps of
-//      the launch side by side;
+//      draws at a time (build_map), or one after another for the smallest
+//      lattices (walk_map); the block's waves build the next maps of the launch
+//      side by side;
 //   3. all threads apply one coupled-pair Metropolis step (section 3.1) to the
 //      map's pairs in parallel.  No two pairs of a map interact, so this equals
 //      applying them one after another; a pair's own sites may be neighbours,
@@ -83,7 +84,7 @@ __device__ __forceinline__ uint32_t rank_in(uint64_t mask)  // set bits of the m
 //
 // The build is bound by the chain of dependent LDS operations of a window
 // (about five) and by the draws decided in order, not by bandwidth; a walk one draw at a time took a chain of LDS round trips per
-// candidate.  A call on 256 lattices of L = 128, 10 maps each: 2098 -> 231 us.
+// candidate.  A call on 256 lattices of L = 128, 10 maps each: 2098 -> 213 us.
 //
 // NN (nearest-neighbour partners): a draw on an unmarked site takes the
 // next draw as its direction.  Runs of unmarked draws are independent (the

@@ -191,10 +191,11 @@ __global__ void __launch_bounds__(kWordsPhaseMaxThreads) k_phase_bytes(WordsArgs
 }
 
 // Persistent form, as k_words_series without records: all sweeps of a call in one
-// launch of blocks that are all resident at once, a barrier of a lattice's blocks after every
-// phase.  Against one launch per phase (us a sweep): L = 388 18.0 -> 12.2, L = 500
-// 20.7 -> 14.2, L = 1000 22.2 -> 14.6; for larger lattices, whose threads take
-// several calls a phase, the loads past the caches cost more than the launches.
+// launch of blocks that are all resident at once, a barrier of a lattice's
+// blocks after every phase.  Against one launch per phase (us a sweep): L = 388 17.5 -> 10.7, L = 500
+// 17.4 -> 12.4, L = 1000 19.3 -> 15.0; for larger lattices, whose threads take
+// several calls a phase, the loads past the caches cost more than the launches
+// (L = 4000 72 -> 97).
 __global__ void __launch_bounds__(kBytesSeriesMaxThreads) k_bytes_series(WordsSeriesArgs a)
 {
     __shared__ uint2 s_tab[kDevTabEntries];

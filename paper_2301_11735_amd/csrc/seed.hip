@@ -15,7 +15,7 @@
 // for large ones.  A lattice made, tables and copies included, with the host's
 // keys and selection and with these passes (ms): L = 16 0.15 and 0.10, L = 128
 // 0.40 and 0.09, L = 512 2.8 and 0.09, L = 2048 50 and 0.12, L = 8192 825 and 0.46; a
-// served burst of 40 requests 126 and 89.
+// served burst of 40 requests 126 and 89 in one run.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

@@ -50,9 +50,9 @@ namespace {
 
 constexpr size_t kAlign = 256;
 constexpr uint64_t kSweepCostSites = 11000;
-// A multi-block sweep of a lattice of L = 512 takes about 22 us on MI355X
-// (four dependent phase launches), the time the on-chip kernel needs for
-// about 100,000 site updates on its compute unit.  Chunks are sized as if it
+// A multi-block sweep of a lattice of L = 512 took about 22 us on MI355X when
+// this was set (four dependent phase launches; 16 to 19 us now), the time the
+// on-chip kernel needs for about 100,000 site updates on its compute unit.  Chunks are sized as if it
 // cost half that (twice the sweeps, about 83 a chunk at the default
 // quantum), and three are kept in flight: the second stream then depends
 // less on how promptly its thread is scheduled.  In alternating 60 s served
@@ -263,7 +263,7 @@ void side_worker(lat_server *s)
             continue;
         }
         lk.unlock();
-        // one launch per phase: a cooperative launch beside the on-chip
+        // one launch per phase: a persistent launch beside the on-chip
         // kernels of the first stream could wait for compute units
         int rc = enqueue_offchip_sweeps(big.data(), (int32_t)big.size(), big_sw.data(), 0, s->side,
                                         /*convert=*/true, /*persistent=*/false);

@@ -1,9 +1,8 @@
 // One a-word of a phase of the coupled-pair sweep (arXiv:2301.11735, section
 // 3.1 update, section 3.2 parallel form), 16 pairs computed by Q cooperating
-// lanes, on a lattice in the 2-bit class layout held in LDS or in global
-// memory.  Shared by the batched kernels (lattice in LDS) and the
-// multi-block phase kernels (lattice in global memory).  Included by the
-// .hip sources only.
+// lanes, on a lattice in the 2-bit class layout in global memory, for the
+// multi-block kernels; their device-wide barrier; and the observable sums of a
+// class word.  Included by the .hip sources only.
 #pragma once
 
 #include "device_common.h"
@@ -13,17 +12,16 @@ namespace {
 
 // Word-parallel form, for lattices with L % 64 == 0 in the 2-bit class
 // layout (W = L/64 words per class row): a phase is computed 16 sites at a
-// time as in the single-lattice phase kernel.  The 16 pairs of an a-word are split among Q threads (Q = 1, 2, 4
-// or 8, chosen per lattice so that the block is filled): thread q of a word
-// takes the Philox calls c with c % Q == q, i.e. sites 2c and 2c+1.
+// time as in the single-lattice phase kernel.  The 16 pairs of an a-word are
+// split among Q threads (Q = 1, 2, 4 or 8, chosen per launch by its lattices):
+// thread q of a word takes the Philox calls that call_of_task lists, i.e. sites
+// 2c and 2c+1 of each.
 //
 // Within a phase no updated site neighbours another updated site, so every
-// neighbour word read is constant during the phase; the a-word and the two
-// b-words a thread updates are shared with other threads only in bit fields
-// that those threads neither read nor write (a reader of such a word
-// extracts only its own fields), and the updates are applied as xor atomics
-// of the changed bits (a plain store when Q = 1 for the a-word).  The same
-// holds in LDS and in global memory, where the atomics act at the L2.
+// neighbour word read is constant during the phase.  The a-word belongs to the
+// lanes of one word, whose first lane stores it; the two b-words are shared with
+// another word's lanes in bit fields that each of them neither reads nor writes
+// of the other, and their changes are applied as xor atomics.
 
 struct WordPhase {
     uint32_t oA0, oAL, oAR, oAV, oB0, oBL, oBR, oBV;  // class offsets (words)

@@ -114,8 +114,8 @@ __device__ __forceinline__ void add_to_record(unsigned long long *rec, int i, lo
 }
 
 // Persistent form: the sweeps of a whole call of up to kWordsBatch lattices,
-// or a whole observation series of one lattice, in one launch of
-// blocks that are all resident at once (GridBarrier: assemble); blocks first_block[i] ..
+// or a whole observation series of one lattice, in one launch of blocks that
+// are all resident at once (GridBarrier: assemble); blocks first_block[i] ..
 // first_block[i+1]-1 update lattice i.  Tables are staged once; every phase
 // is one grid-stride pass over each lattice's a-word tasks by its own blocks,
 // followed by a device-wide barrier of those blocks (the lattices do not
