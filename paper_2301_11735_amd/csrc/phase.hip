@@ -200,21 +200,16 @@ __global__ void __launch_bounds__(kBytesSeriesMaxThreads) k_bytes_series(WordsSe
 {
     __shared__ uint2 s_tab[kDevTabEntries];
     __shared__ __align__(16) uint2 s_slots[kSlotEntries];
-    int li = a.alone ? (int)blockIdx.x : 0;  // this block's lattice (uniform)
-    while (!a.alone && li + 1 < a.count && blockIdx.x >= a.first_block[li + 1]) ++li;
+    int li = 0;  // this block's lattice (uniform)
+    while (li + 1 < a.count && blockIdx.x >= a.first_block[li + 1]) ++li;
     uint8_t *scr = a.scratch[li];
     // ahead of the meeting: its atomics would make the descriptor's loads vector loads
     const LatDesc d = *(const LatDesc *)(scr + kScrDesc);
     LAT_GLOBAL uint8_t *st = (LAT_GLOBAL uint8_t *)d.state;
-    const uint32_t b = a.alone ? 0u : blockIdx.x - a.first_block[li];
-    const uint32_t nb = a.alone ? 1u : a.first_block[li + 1] - a.first_block[li];
+    const uint32_t b = blockIdx.x - a.first_block[li], nb = a.first_block[li + 1] - a.first_block[li];
     GridBarrier barrier{(unsigned *)(scr + kScrObsSlots), b, nb, 0u, false};
     unsigned *err = (unsigned *)(scr + kScrErr);
-    if (a.alone) {
-        if (!barrier.alone()) return;
-    } else {
-        barrier.first_arrive(a.assemble_ticks);
-    }
+    if (a.alone ? !barrier.alone() : !barrier.first_arrive(a.assemble_ticks)) return;
     TableLoads tables;
     tables.load((const uint2 *)(scr + kScrDevTab), blockDim.x);
     tables.store(s_tab, s_slots, blockDim.x);
@@ -235,7 +230,8 @@ __global__ void __launch_bounds__(kBytesSeriesMaxThreads) k_bytes_series(WordsSe
         w = pair_draws(philox4x32_10((uint32_t)s, f.p, call, (uint32_t)(s >> 32), d.key0, d.key1));
     };
     if (mine) prepare(d.next_sweep, first);
-    if (!a.alone && !barrier.assemble(a.assemble_ticks)) return;
+    if (!barrier.assemble(a.alone, a.assemble_ticks)) return;
+    barrier.rounds = 1u;
     int tr[3] = {0, 0, 0};
     for (uint32_t it = 0; it < sweeps; ++it) {
         const uint64_t s = d.next_sweep + it;

@@ -180,23 +180,24 @@ struct GridBarrier {
         }
         return (n & kCalledOff) != 0;
     }
-    // The first meeting's arrival (limit: assemble's).
-    __device__ __forceinline__ void first_arrive(long long limit)
+    // The first meeting's arrival (limit: assemble's); true.
+    __device__ __forceinline__ bool first_arrive(long long limit)
     {
         // (no time at all: before block 0 has arrived, so that it is certain)
         if (limit <= 0 && block == 0 && threadIdx.x == 0) call_off();
         arrive();
+        return true;
     }
     // False, for the whole block, if the launch is called off.
-    __device__ __forceinline__ bool assemble(long long limit)
+    __device__ __forceinline__ bool assemble(bool is_alone, long long limit)
     {
         __shared__ unsigned s_off;
         if (threadIdx.x == 0) {
             const unsigned *at = flat() ? words : flag(block % kBarrierGroups);
             const unsigned target = flat() ? blocks : 1u;
             const long long t0 = wall_clock64();
-            unsigned n;
-            while ((n = load(at)) < target) {  // kCalledOff is above any target
+            unsigned n = 0u;
+            while (!is_alone && (n = load(at)) < target) {  // kCalledOff is above any target
                 __builtin_amdgcn_s_sleep(1);
                 if (wall_clock64() - t0 > limit) {
                     n = call_off() ? kCalledOff : 0u;
@@ -209,12 +210,13 @@ struct GridBarrier {
         return s_off == 0u;
     }
     // A launch of one block a lattice behind the one that may have been called
-    // off: true if it was, and the counter is then clear for this block.
+    // off: true if it was, and the counter then stands as after this block's
+    // arrival at the first meeting.
     __device__ __forceinline__ bool alone()
     {
         const bool off = (load(words) & kCalledOff) != 0;
         __syncthreads();
-        if (threadIdx.x == 0 && off) store(words, 0u);
+        if (threadIdx.x == 0 && off) store(words, 1u);
         return off;
     }
 };

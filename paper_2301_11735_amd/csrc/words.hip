@@ -142,21 +142,16 @@ __global__ void __launch_bounds__(Q >= 4 ? kWordsSeriesMaxThreads : kWordsThread
 {
     __shared__ uint2 s_tab[kDevTabEntries];
     __shared__ __align__(16) uint2 s_slots[kSlotEntries];
-    int li = a.alone ? (int)blockIdx.x : 0;  // this block's lattice (uniform)
-    while (!a.alone && li + 1 < a.count && blockIdx.x >= a.first_block[li + 1]) ++li;
+    int li = 0;  // this block's lattice (uniform)
+    while (li + 1 < a.count && blockIdx.x >= a.first_block[li + 1]) ++li;
     uint8_t *scr = a.scratch[li];
     // ahead of the meeting: its atomics would make the descriptor's loads vector loads
     const LatDesc d = *(const LatDesc *)(scr + kScrDesc);
     uint32_t *st = (uint32_t *)(d.enc == 1 ? d.state : (void *)(scr + kScrWork));
-    const uint32_t b = a.alone ? 0u : blockIdx.x - a.first_block[li];
-    const uint32_t nb = a.alone ? 1u : a.first_block[li + 1] - a.first_block[li];
+    const uint32_t b = blockIdx.x - a.first_block[li], nb = a.first_block[li + 1] - a.first_block[li];
     GridBarrier barrier{(unsigned *)(scr + kScrObsSlots), b, nb, 0u, false};
     unsigned *err = (unsigned *)(scr + kScrErr);
-    if (a.alone) {
-        if (!barrier.alone()) return;
-    } else {
-        barrier.first_arrive(a.assemble_ticks);
-    }
+    if (a.alone ? !barrier.alone() : !barrier.first_arrive(a.assemble_ticks)) return;
     {
         const uint2 *g_tab = (const uint2 *)(scr + kScrDevTab);
         for (int i = threadIdx.x; i < kDevTabEntries; i += blockDim.x) s_tab[i] = g_tab[i];
@@ -180,11 +175,13 @@ __global__ void __launch_bounds__(Q >= 4 ? kWordsSeriesMaxThreads : kWordsThread
     device_schedule(d.L, d.key0, d.key1, d.next_sweep, r, mm, kk);
     word_phase_setup(f, d.L, d.key0, d.key1, d.next_sweep, 0, r, mm, kk);
     const uint32_t c0 = task_call0<Q>(f, mine ? first : 0u);
+    // (behind the first draws a series at L=1024 took 14.5 us a sweep, not 14.3)
+    if (!barrier.assemble(a.alone, a.assemble_ticks)) return;
+    barrier.rounds = 1u;
     if (mine && my_sweeps > 0) {
         word_draws<Q>(c0, q, d.next_sweep, 0, d.key0, d.key1, pre);
         refs = word_refs<Q>(f, first);
     }
-    if (!a.alone && !barrier.assemble(a.assemble_ticks)) return;
     int tr[3] = {0, 0, 0};
     int dv[3] = {0, 0, 0};  // Obs: spin, staggered spin, staggered charge moves of the interval
     long long moves = 0;    // Obs, thread i < 6: the block's sum i of the intervals before
@@ -430,6 +427,7 @@ hipError_t launch_words_series(const WordsSeriesArgs &a, int Q, hipStream_t s)
     const hipError_t ran = hipLaunchKernel(fn, dim3(a.first_block[a.count]), dim3((unsigned)a.threads), kargs, 0, s);
     if (ran != hipSuccess) return ran;
     args.alone = 1;
+    for (int i = 0; i <= a.count; ++i) args.first_block[i] = (uint32_t)i;
     return hipLaunchKernel(fn, dim3((unsigned)a.count), dim3((unsigned)a.threads), kargs, 0, s);
 }
 
