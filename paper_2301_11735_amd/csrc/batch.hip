@@ -569,14 +569,6 @@ __global__ void __launch_bounds__(1024) k_sweep_half(BatchArgs args)
     block_reduce_add<3>(tr, (unsigned long long *)(scr + kScrTrackBase));
 }
 
-// This thread's share of the 7 observable sums of a 2-bit lattice in the
-// class layout, read from st (global memory or the LDS copy).
-__device__ __forceinline__ void obs_sums_2bit(const uint32_t *st, int L, long long (&v)[7])
-{
-    const uint32_t n = 8u * (uint32_t)(L >> 1) * (uint32_t)(L >> 6);
-    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) obs_word_2bit(st, L, i, v);
-}
-
 __global__ void k_advance(LatDesc *desc, uint32_t sweeps)
 {
     if (threadIdx.x == 0 && blockIdx.x == 0) desc->next_sweep += sweeps;
@@ -601,7 +593,8 @@ __global__ void __launch_bounds__(256) k_obs_batch(BatchArgs args, unsigned long
                 obs_group_int8<1>(st, (uint32_t)L, t, sums);
         sums.get(v);
     } else {
-        obs_sums_2bit((const uint32_t *)d.state, L, v);
+        for (uint32_t i = threadIdx.x; i < (uint32_t)L * L / 16u; i += blockDim.x)
+            obs_word_2bit((const uint32_t *)d.state, (uint32_t)L, i, v);
     }
     unsigned long long *o = out + 10 * (size_t)blockIdx.x;
     if (threadIdx.x < 10) o[threadIdx.x] = 0ull;

@@ -7,6 +7,8 @@
 #include <algorithm>
 
 #include "device_common.h"
+#include "onchip.h"
+#include "word_task.h"
 
 namespace lat {
 namespace {
@@ -32,58 +34,13 @@ __global__ void __launch_bounds__(1024) k_obs_int8(const uint8_t *__restrict__ s
     block_reduce_store<7>(v, slots + 7 * (size_t)blockIdx.x);
 }
 
-// Adds class word i (16 sites): its right neighbours are the same word of the
-// next class (or class 0 one site on), its lower neighbours the same word of
-// the paired row class.  Popcounts over the bit planes.
-__device__ __forceinline__ void obs_add_2bit(const uint32_t *__restrict__ st, uint32_t L, uint32_t i, long long (&v)[7])
-{
-    const uint32_t W = L >> 6, H = L >> 1, Lq = L >> 2, csz = H * W;
-    const uint32_t c = i / csz, rem = i - c * csz;
-    const uint32_t Y = rem / W, j = rem - Y * W;
-    const uint32_t cx = c & 3u, cy = c >> 2;
-    const uint32_t w = st[i];
-    const uint32_t wr = cx < 3 ? st[i + csz] : load16(st, 4u * cy * csz + Y * W, (int)W, 16 * j + 1 == Lq ? 0 : (int)(16 * j + 1));
-    const uint32_t wd = cy == 0 ? st[i + 4 * csz] : st[cx * csz + (Y + 1 == H ? 0 : Y + 1) * W + j];
-    const uint32_t h = (w >> 1) & kM5, l = w & kM5;
-    const int sumS = __popc(h & ~l) - __popc(h & l);
-    const int sumG = __popc((h | l) ^ kM5) - __popc(l & ~h);
-    int bSS = 0, bss = 0;
-    bond_sums(h, l, (wr >> 1) & kM5, wr & kM5, bSS, bss);
-    bond_sums(h, l, (wd >> 1) & kM5, wd & kM5, bSS, bss);
-    const int sg = ((cx + cy) & 1) ? -1 : 1;
-    v[0] += sumS;
-    v[1] += __popc(h);
-    v[2] += bSS;
-    v[3] += bss;
-    v[4] += sumG;
-    v[5] += sg * sumG;
-    v[6] += sg * sumS;
-}
-
 __global__ void __launch_bounds__(1024) k_obs_2bit(const uint32_t *__restrict__ st, int L, long long *slots)
 {
     long long v[7] = {0, 0, 0, 0, 0, 0, 0};
     const uint32_t nwords = (uint32_t)L * (uint32_t)L / 16u;
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < nwords; i += gridDim.x * blockDim.x)
-        obs_add_2bit(st, (uint32_t)L, i, v);
+        obs_word_2bit(st, (uint32_t)L, i, v);
     block_reduce_store<7>(v, slots + 7 * (size_t)blockIdx.x);
-}
-
-// This thread's share of the tracker slots and, for thread 0, the base.
-__device__ __forceinline__ void add_tracker(const uint8_t *scr, long long *t)
-{
-    const long long *slots = (const long long *)(scr + kScrSlots);
-    for (int i = threadIdx.x; i < kMaxSlots; i += blockDim.x) {
-        t[0] += slots[3 * i];
-        t[1] += slots[3 * i + 1];
-        t[2] += slots[3 * i + 2];
-    }
-    if (threadIdx.x == 0) {
-        const long long *base = (const long long *)(scr + kScrTrackBase);
-        t[0] += base[0];
-        t[1] += base[1];
-        t[2] += base[2];
-    }
 }
 
 // Totals of one lattice: tracker = base triple + every tracker slot;
@@ -94,7 +51,10 @@ constexpr int kFoldThreads = 256;
 __global__ void __launch_bounds__(kFoldThreads) k_fold_sums(uint8_t *scr, int n_obs, long long *dst, int stamp)
 {
     long long t[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-    add_tracker(scr, t);
+    long long t3[3] = {0, 0, 0};
+    tracker_partial(scr, t3);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) t[k] = t3[k];
     const long long *os = (const long long *)(scr + kScrObsSlots);
     for (int i = threadIdx.x; i < n_obs; i += blockDim.x)
 #pragma unroll
@@ -115,9 +75,12 @@ __global__ void __launch_bounds__(1024) k_obs_one(uint8_t *scr, const uint8_t *s
     long long t[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
     long long v[7] = {0, 0, 0, 0, 0, 0, 0};
     const uint32_t N = (uint32_t)L * (uint32_t)L;
-    add_tracker(scr, t);
+    long long t3[3] = {0, 0, 0};
+    tracker_partial(scr, t3);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) t[k] = t3[k];
     if (enc != 0) {
-        for (uint32_t i = threadIdx.x; i < N / 16u; i += blockDim.x) obs_add_2bit((const uint32_t *)st, (uint32_t)L, i, v);
+        for (uint32_t i = threadIdx.x; i < N / 16u; i += blockDim.x) obs_word_2bit((const uint32_t *)st, (uint32_t)L, i, v);
     } else {
         SiteSums sums;
         if (wide)

@@ -62,16 +62,6 @@ __device__ __forceinline__ void xorw(uint32_t *p, uint32_t i, uint32_t v)
     (void)__hip_atomic_fetch_xor((LAT_GLOBAL uint32_t *)((LAT_GLOBAL uint8_t *)p + (i << 2)), v, __ATOMIC_RELAXED,
                                  __HIP_MEMORY_SCOPE_AGENT);
 }
-// 16 sites of the class row at word offset `row` of a lattice in LDS (or
-// plain global memory), starting at class position xs (periodic).
-__device__ __forceinline__ uint32_t ld16(const uint32_t *st, uint32_t row, int W, int xs)
-{
-    const int jw = xs >> 4, sh = xs & 15;
-    const uint32_t w0 = st[row + (uint32_t)jw];
-    const uint32_t w1 = st[row + (uint32_t)(jw + 1 == W ? 0 : jw + 1)];
-    return sh ? __builtin_amdgcn_alignbit(w1, w0, 2u * (uint32_t)sh) : w0;
-}
-
 // Device-wide barrier for kernels whose lattice words are all accessed at
 // device coherence (ldw/stw<true> and device-scope atomics), in two halves.
 // Arrive: every wave waits for its own memory operations to complete, the
@@ -268,18 +258,15 @@ __device__ __forceinline__ int spin_sum16(uint32_t w)
 // right and lower neighbours, sum sigma, and the staggered sums.  The right
 // neighbours are the same word of the next class (or class 0 of the row,
 // one site on), the lower ones the same word of the paired row class.
-__device__ __forceinline__ void obs_word_2bit(const uint32_t *st, int L, uint32_t i, long long (&v)[7])
+__device__ __forceinline__ void obs_word_2bit(const uint32_t *__restrict__ st, uint32_t L, uint32_t i, long long (&v)[7])
 {
-    const int W = L >> 6, H = L >> 1, Lq = L >> 2;
-    const uint32_t csz = (uint32_t)H * W;
-    const int c = (int)(i / csz);
-    const uint32_t rem = i - (uint32_t)c * csz;
-    const int Y = (int)(rem / W), j = (int)(rem - (uint32_t)Y * W);
-    const int cx = c & 3, cy = c >> 2;
+    const uint32_t W = L >> 6, H = L >> 1, Lq = L >> 2, csz = H * W;
+    const uint32_t c = i / csz, rem = i - c * csz;
+    const uint32_t Y = rem / W, j = rem - Y * W;
+    const uint32_t cx = c & 3u, cy = c >> 2;
     const uint32_t w = st[i];
-    const uint32_t wr = cx < 3 ? st[i + csz]
-                               : ld16(st, (uint32_t)(4 * cy) * csz + (uint32_t)Y * W, W, 16 * j + 1 == Lq ? 0 : 16 * j + 1);
-    const uint32_t wd = cy == 0 ? st[i + 4 * csz] : st[(uint32_t)cx * csz + (uint32_t)(Y + 1 == H ? 0 : Y + 1) * W + j];
+    const uint32_t wr = cx < 3 ? st[i + csz] : load16(st, 4u * cy * csz + Y * W, (int)W, 16 * j + 1 == Lq ? 0 : (int)(16 * j + 1));
+    const uint32_t wd = cy == 0 ? st[i + 4 * csz] : st[cx * csz + (Y + 1 == H ? 0 : Y + 1) * W + j];
     const uint32_t h = (w >> 1) & kM5, l = w & kM5;
     const int sumS = charge_sum16(w);
     const int sumG = spin_sum16(w);
