@@ -12,6 +12,7 @@
 #include <map>
 #include <memory>
 #include <tuple>
+#include <type_traits>
 #include <mutex>
 #include <cmath>
 #include <cstdint>
@@ -70,10 +71,13 @@ int barrier_timed_out() { return fail(LAT_EHIP, "a device-wide phase barrier tim
 bool live(const lattice *h) { return h != nullptr && h->magic == kMagic; }
 
 namespace {
+// (no destructor: threads that outlive main may still be in a call)
 struct PinnedPool {
     size_t bytes, keep;
-    std::vector<void *> free{};
+    size_t n = 0;
+    void *free[kPinnedKeep] = {};
 };
+static_assert(std::is_trivially_destructible_v<PinnedPool> && kPinnedLargeKeep <= kPinnedKeep);
 std::mutex g_pinned_mu;
 PinnedPool g_pinned[2] = {{kPinnedBytes, kPinnedKeep}, {kPinnedLarge, kPinnedLargeKeep}};
 }  // namespace
@@ -83,11 +87,7 @@ PinnedBlock::PinnedBlock(bool large) : large_(large)
     PinnedPool &pool = g_pinned[large_];
     {
         std::lock_guard<std::mutex> lock(g_pinned_mu);
-        pool.free.reserve(pool.keep);  // the destructor's push_back never allocates
-        if (!pool.free.empty()) {
-            p = pool.free.back();
-            pool.free.pop_back();
-        }
+        if (pool.n > 0) p = pool.free[--pool.n];
     }
     // portable: usable with every device of the process
     if (!p && hipHostMalloc(&p, pool.bytes, hipHostMallocPortable) != hipSuccess) {
@@ -102,8 +102,8 @@ PinnedBlock::~PinnedBlock()
     PinnedPool &pool = g_pinned[large_];
     {
         std::lock_guard<std::mutex> lock(g_pinned_mu);
-        if (pool.free.size() < pool.keep) {
-            pool.free.push_back(p);
+        if (pool.n < pool.keep) {
+            pool.free[pool.n++] = p;
             return;
         }
     }
@@ -554,7 +554,7 @@ namespace {
 int words_capacity(int Q, int threads)
 {
     static std::mutex mu;
-    static std::map<std::tuple<int, int, int>, int> cache;
+    static auto &cache = *new std::map<std::tuple<int, int, int>, int>;  // never destroyed, as the pinned pool
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     std::lock_guard<std::mutex> lock(mu);
