@@ -1,6 +1,6 @@
 // gfx950 phase kernels of the coupled-pair Metropolis sweep on one lattice
-// (arXiv:2301.11735, section 3.1 update, section 3.2 parallel form): one
-// launch per phase, or all phases of a call in one cooperative launch.
+// (arXiv:2301.11735, section 3.1 update, section 3.2 parallel form): one launch
+// per phase, or all phases of a call in one launch with device-wide barriers.
 // Integer-only: no floating point, no matrix cores.
 //
 // One phase updates the N/8 pairs a = (x, y), x = p (mod 4), y even, with
